@@ -143,7 +143,7 @@ qarvd_status qarvd_quantize_weight(const float *W, int32_t N, int32_t K, int64_t
  * qarvd_quantize_weight for callers that cannot allocate device memory or hand over a workspace:
  * code under HIP graph capture set-up, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments minus the workspace, same results bit for bit.  The detector's workspace lives in a fixed
- * device array inside the library (528 KB on every GPU the library is used on, held until the
+ * device array inside the library (2.2 MB on every GPU the library is used on, held until the
  * process ends), which limits K to qarvd_quantize_weight_static_max_k() = 16384: a larger K returns
  * QARVD_ERR_WORKSPACE before anything is launched.  The call allocates nothing (no hipMalloc/hipFree,
  * no allocating library routine).  All calls on one GPU share that array: two calls that overlap on
@@ -208,8 +208,7 @@ qarvd_status qarvd_w8a8_dual_gemm(const int8_t *Xq, int64_t ldxq, const float *s
  * position 16g+i in its low nibble and 16g+4+i in its high nibble, byte 4+i positions 16g+8+i and
  * 16g+12+i (two's-complement nibbles).  Row extent qarvd_packed_k(K, K_o) / 2 bytes.
  *   Wq4   out  u8 [N, ldwq4]; ldwq4 in BYTES, >= qarvd_packed_k(K, -1) / 2, multiple of 16
- *   workspace  >= qarvd_quantize_weight_w4_workspace(N, K) bytes (it also holds one byte per code
- *              of the whole matrix until they are packed), 256-byte aligned
+ *   workspace  >= qarvd_quantize_weight_w4_workspace(N, K) bytes, 256-byte aligned
  * Everything else as qarvd_quantize_weight.  Synchronises `stream`.
  */
 size_t qarvd_quantize_weight_w4_workspace(int32_t N, int32_t K);

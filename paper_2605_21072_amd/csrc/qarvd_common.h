@@ -122,3 +122,53 @@ __device__ __forceinline__ float wave_max(float v)
     for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
     return v;
 }
+
+// Reductions over a wave by data-parallel-primitive moves: the values pass between lanes inside vector-ALU
+// instructions (sixteen lanes of a row, then the last lane of a row to the next), a few cycles a step, where a shuffle
+// goes through the LDS crossbar at its latency, six times in a row.  The result is in lane 63 and is read
+// from there, so every lane gets it in a scalar register.  `idle` is what a lane without a source receives.
+template <int CTRL> __device__ __forceinline__ int dpp_move(int idle, int v)
+{
+    return __builtin_amdgcn_update_dpp(idle, v, CTRL, 0xF, 0xF, false);
+}
+template <typename Step> __device__ __forceinline__ int wave_reduce_bits(int v, Step step)      // step(v, moved copy of v)
+{
+    v = step(v, [](int idle, int x) { return dpp_move<0x111>(idle, x); });      // row_shr:1, 2, 4, 8
+    v = step(v, [](int idle, int x) { return dpp_move<0x112>(idle, x); });
+    v = step(v, [](int idle, int x) { return dpp_move<0x114>(idle, x); });
+    v = step(v, [](int idle, int x) { return dpp_move<0x118>(idle, x); });
+    v = step(v, [](int idle, int x) { return dpp_move<0x142>(idle, x); });      // row_bcast:15, 31
+    v = step(v, [](int idle, int x) { return dpp_move<0x143>(idle, x); });
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ int wave_sum_all(int v)
+{
+    return wave_reduce_bits(v, [](int x, auto move) { return x + move(0, x); });
+}
+__device__ __forceinline__ unsigned wave_min_all(unsigned v)
+{
+    return (unsigned)wave_reduce_bits((int)v, [](int x, auto move) { return (int)min((unsigned)x, (unsigned)move(x, x)); });
+}
+__device__ __forceinline__ float wave_max_all(float v)
+{
+    return __int_as_float(wave_reduce_bits(__float_as_int(v), [](int x, auto move) {
+        return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(move(x, x))));
+    }));
+}
+__device__ __forceinline__ double wave_sum_all(double v)
+{
+    auto add = [](double x, auto move) {
+        const long long b = __double_as_longlong(x);
+        const unsigned lo = (unsigned)move(0, (int)b), hi = (unsigned)move(0, (int)(b >> 32));
+        return x + __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    };
+    v = add(v, [](int idle, int x) { return dpp_move<0x111>(idle, x); });
+    v = add(v, [](int idle, int x) { return dpp_move<0x112>(idle, x); });
+    v = add(v, [](int idle, int x) { return dpp_move<0x114>(idle, x); });
+    v = add(v, [](int idle, int x) { return dpp_move<0x118>(idle, x); });
+    v = add(v, [](int idle, int x) { return dpp_move<0x142>(idle, x); });
+    v = add(v, [](int idle, int x) { return dpp_move<0x143>(idle, x); });
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63), hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}

@@ -1,173 +1,637 @@
 // Offline weight step for gfx950 (Sec. 3.2): input-channel L2 norms, Modified-Z-score +
 // minimum-magnitude outlier detection (Eqs. (mad), (new_threshold)), alignment of the outlier
 // count (Fig. "outlier patterns" caption), [outlier | normal] permutation and dual per-row scales
-// with INT8 rounding (Eq. (dual_scale), Eq. (quantization)).
+// with INT8 / INT4 rounding (Eq. (dual_scale), Eq. (quantization)).
 //
-// Runs once per layer and is not on the timed path; the kernels favour exact, order-defined
-// arithmetic over speed:
-//   - a column norm is accumulated by ONE thread in ascending row order in fp64, so the sum has
-//     the same rounding sequence as a sequential loop (loads are coalesced across columns);
-//   - medians come from exact ranks: rank_i = #{j : x_j > x_i or (x_j == x_i and j < i)} is a
-//     bijection onto 0..K-1, scattering by rank sorts the vector, and the detector's flagged set
-//     plus its largest-norm fillers is simply {i : rank_i < K_o};
-//   - every floating-point expression of the detector is evaluated in fp64 with separate
-//     multiply and add (the library is built with -ffp-contract=off).
+// Every result is defined bit for bit, some of them through sums taken in a fixed order.  The kernels take
+// those sums in parallel and PROVE that the order cannot matter: a sum of n non-negative doubles lies within
+// n 2^-53 (relative) of the exact sum in any order, so when the whole interval around the parallel sum leads to the
+// same fp32 norm (or the same comparison), the ordered sum does too.  The rare sums that fail the test (about
+// 3 columns in 10^5 at 8960 rows) are redone in order.  W is streamed twice: once for the norms, once by
+// the row quantizer; detection between them is one workgroup working from registers.
+//   kernel times, us        norms       detection    scales and codes
+//   8960 x 1536, INT8       15 (397)    22 (258)     19 (32)
+//   1536 x 8960, INT4, clip 15 (70)     30 (1316)    50 (4697: search, codes, packing)
+// In brackets one thread per column, O(K^2) rankings, one thread per (row, block) for the search and byte stores.
 #include "qarvd_common.h"
 
 namespace {
 
 struct DetectScalars {   // lives in the workspace
-    double med, mad, T;
     int32_t n_det, K_o;
 };
 
 // ---- norms -------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void column_norm_kernel(const float *__restrict__ W, int N, int K, int64_t ldw,
-                                                         float *__restrict__ v)
+// v[k] = (float) sqrt(sum_j W[j,k]^2), the sum in fp64 in ascending j.  A product of two floats is exact in fp64, so
+// fma(d, d, S) rounds exactly as S + d * d does.
+//
+// Pass 1, bound by the 4 N K bytes it reads: a workgroup sums a chunk of rows for a slab of 256 columns (four waves
+// take every fourth row, 1 KB of a row per load).  At most NORM_BLOCKS workgroups (four per CU), so the partial
+// sums never exceed NORM_BLOCKS x 256 doubles whatever N and K are.
+constexpr int NORM_BLOCKS = 1024;
+
+template <bool VEC>
+__global__ __launch_bounds__(256) void norm_partial_kernel(const float *__restrict__ W, int N, int K, int64_t ldw,
+                                                           int rows_per_chunk, double *__restrict__ partial)
 {
-    const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k >= K) return;
-    const float *w = W + k;
-    double S = 0.0;
-    int j = 0;
-    for (; j + 8 <= N; j += 8) {
-        float t[8];
+    __shared__ double part[4][256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col0 = blockIdx.x * 256;
+    const int r0 = blockIdx.y * rows_per_chunk, r1 = min(N, r0 + rows_per_chunk);
+    double S[4] = {0.0, 0.0, 0.0, 0.0};
+    // VEC: columns col0 + 4 lane + u by one 16-byte load; else columns col0 + lane + 64 u
+    int col[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = w[(size_t)(j + u) * ldw];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double d = (double)t[u];
-            S = S + d * d;
-        }
-    }
-    for (; j < N; ++j) {
-        const double d = (double)w[(size_t)j * ldw];
-        S = S + d * d;
-    }
-    v[k] = (float)sqrt(S);
-}
-
-// ---- ranks (descending, ties by smaller index first) and sort-by-rank --------------------
-template <typename T>
-__global__ __launch_bounds__(256) void rank_desc_kernel(const T *__restrict__ x, int K, int32_t *__restrict__ rank,
-                                                        T *__restrict__ sorted_desc)
-{
-    __shared__ T tile[256];
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    const T xi = i < K ? x[i] : (T)0;
-    int r = 0;
-    for (int j0 = 0; j0 < K; j0 += 256) {
-        const int j = j0 + threadIdx.x;
-        tile[threadIdx.x] = j < K ? x[j] : (T)0;
-        __syncthreads();
-        const int lim = min(256, K - j0);
-        for (int t = 0; t < lim; ++t) {
-            const T xj = tile[t];
-            r += (xj > xi || (xj == xi && (j0 + t) < i)) ? 1 : 0;
-        }
-        __syncthreads();
-    }
-    if (i < K) {
-        if (rank) rank[i] = r;
-        sorted_desc[r] = xi;
-    }
-}
-
-// med = median(v) (even K: mean of the two middle values), d = |v - med| in fp64.
-__global__ void median_dev_kernel(const float *__restrict__ v, const float *__restrict__ sorted_desc, int K,
-                                  DetectScalars *sc, double *__restrict__ d)
-{
-    // the two middle order statistics are the same pair counted from either end
-    const double med = (K & 1) ? (double)sorted_desc[K / 2]
-                               : ((double)sorted_desc[K / 2] + (double)sorted_desc[K / 2 - 1]) / 2.0;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < K) d[i] = fabs((double)v[i] - med);
-    if (i == 0) sc->med = med;
-}
-
-// MAD, threshold, flagged count, aligned K_o.  One workgroup.
-__global__ __launch_bounds__(256) void threshold_kernel(const float *__restrict__ v, const double *__restrict__ sorted_d,
-                                                        int K, double c, double alpha, int align, DetectScalars *sc)
-{
-    __shared__ int cnt[256];
-    const double mad = (K & 1) ? sorted_d[K / 2] : (sorted_d[K / 2] + sorted_d[K / 2 - 1]) / 2.0;
-    const double med = sc->med;
-    double T1 = c * mad;
-    T1 = med + T1;
-    const double T2 = alpha * med;
-    const double T = T1 > T2 ? T1 : T2;
-    int n = 0;
-    for (int i = threadIdx.x; i < K; i += 256) n += ((double)v[i] > T) ? 1 : 0;
-    cnt[threadIdx.x] = n;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) cnt[threadIdx.x] += cnt[threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const int n_det = cnt[0];
-        int K_o = 0;
-        if (n_det > 0) {
-            K_o = (n_det + align - 1) / align * align;
-            if (K_o > K) K_o = K;
-        }
-        sc->mad = mad;
-        sc->T = T;
-        sc->n_det = n_det;
-        sc->K_o = K_o;
-    }
-}
-
-__global__ void select_by_rank_kernel(const int32_t *__restrict__ rank, int K, const DetectScalars *sc,
-                                      uint8_t *__restrict__ sel)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < K) sel[i] = rank[i] < sc->K_o ? 1 : 0;
-}
-
-// Stable partition: perm = [selected ascending | rest ascending]; pos = packed position of each
-// channel.  One workgroup of 1024 threads, each owning a contiguous run of channels.
-__global__ __launch_bounds__(1024) void build_perm_kernel(const uint8_t *__restrict__ sel, int K, DetectScalars *sc,
-                                                          int forced, int32_t *__restrict__ perm,
-                                                          int32_t *__restrict__ pos)
-{
-    __shared__ int part[1024];
-    __shared__ int total;
-    const int t = threadIdx.x;
-    const int per = (K + 1023) / 1024;
-    const int b = min(K, t * per), e = min(K, b + per);
-    int n = 0;
-    for (int k = b; k < e; ++k) n += sel[k] ? 1 : 0;
-    part[t] = n;
-    __syncthreads();
-    if (t == 0) {
-        int run = 0;
-        for (int i = 0; i < 1024; ++i) {
-            const int c = part[i];
-            part[i] = run;
-            run += c;
-        }
-        total = run;
-        if (forced) sc->K_o = run;
-    }
-    __syncthreads();
-    const int K_o = total;
-    const int n_off = (K_o + 31) / 32 * 32;
-    int so = part[t];          // selected channels before k
-    for (int k = b; k < e; ++k) {
-        if (sel[k]) {
-            perm[so] = k;
-            pos[k] = so;
-            ++so;
+    for (int u = 0; u < 4; ++u) col[u] = min(col0 + (VEC ? 4 * lane + u : lane + 64 * u), K - 1);
+    auto row4 = [&](int r, float (&t)[4]) {
+        const float *w = W + (size_t)r * ldw;
+        if constexpr (VEC) {      // K % 4 == 0: the four columns are inside the matrix or the whole chunk is clamped
+            const float4 f = *reinterpret_cast<const float4 *>(w + min(col0 + 4 * lane, K - 4));
+            t[0] = f.x; t[1] = f.y; t[2] = f.z; t[3] = f.w;
         } else {
-            const int p = K_o + (k - so);
-            perm[p] = k;
-            pos[k] = n_off + (k - so);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = w[col[u]];
+        }
+    };
+    auto add = [&](const float (&t)[4]) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double d = (double)t[u];
+            S[u] = fma(d, d, S[u]);
+        }
+    };
+    int r = r0 + wave;
+    for (; r + 28 < r1; r += 32) {        // eight rows of this wave in flight
+        float t[8][4];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) row4(r + 4 * i, t[i]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) add(t[i]);
+    }
+    for (; r < r1; r += 4) {
+        float t[4];
+        row4(r, t);
+        add(t);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) part[wave][VEC ? 4 * lane + u : lane + 64 * u] = S[u];
+    __syncthreads();
+    const int k = col0 + threadIdx.x;
+    if (k < K)
+        partial[(size_t)blockIdx.y * K + k] =
+            (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
+}
+
+// Pass 2: 64 columns per workgroup, four threads per column.  With S the parallel sum and n = N terms, both S and the
+// ordered sum are within n u / (1 - n u) of the exact one (u = 2^-53), so the ordered sum lies in
+// S (1 -+ 2.5 (n + 2) u), which leaves room for the roundings of the bounds themselves.  sqrt and the conversion
+// to float are monotone: equal ends mean that the ordered sum gives this float.  (NaN fails the test.)
+__global__ __launch_bounds__(256) void norm_final_kernel(const double *__restrict__ partial, int chunks,
+                                                         const float *__restrict__ W, int N, int K, int64_t ldw,
+                                                         float *__restrict__ v, float *__restrict__ v_out)
+{
+    __shared__ double part[4][64];
+    __shared__ unsigned long long redo;
+    __shared__ float stage[256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane;
+    const double *p = partial + min(k, K - 1);
+    double S = 0.0;
+    int c = wave;
+    for (; c + 28 < chunks; c += 32) {
+        double t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = p[(size_t)(c + 4 * i) * K];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) S += t[i];
+    }
+    for (; c < chunks; c += 4) S += p[(size_t)c * K];
+    part[wave][lane] = S;
+    __syncthreads();
+    if (wave == 0) {
+        S = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+        const double e = 2.5 * ((double)N + 2.0) * 0x1p-53;
+        const float lo = (float)sqrt(S * (1.0 - e)), hi = (float)sqrt(S * (1.0 + e));
+        const unsigned long long bad = __ballot(k < K && !(lo == hi));
+        if (k < K && lo == hi) {
+            v[k] = lo;
+            if (v_out) v_out[k] = lo;
+        }
+        if (lane == 0) redo = bad;
+    }
+    __syncthreads();
+    for (unsigned long long m = redo; m; m &= m - 1) {       // in order, 256 rows at a time through LDS
+        const int kr = blockIdx.x * 64 + __builtin_ctzll(m);
+        double T = 0.0;
+        for (int r0 = 0; r0 < N; r0 += 256) {
+            if (r0 + (int)threadIdx.x < N) stage[threadIdx.x] = W[(size_t)(r0 + threadIdx.x) * ldw + kr];
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const int lim = min(256, N - r0);
+                for (int i = 0; i < lim; ++i) {
+                    const double d = (double)stage[i];
+                    T = fma(d, d, T);
+                }
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            const float f = (float)sqrt(T);
+            v[kr] = f;
+            if (v_out) v_out[kr] = f;
         }
     }
 }
 
-// ---- dual scales + INT8 rows -------------------------------------------------------------
+// ---- detection and permutation: one workgroup ------------------------------------------------
+// Norms are non-negative floats, so their bit patterns order as they do, and any order statistic is found by
+// bisecting the pattern range with counts (one compare and one add per value, keys in registers), and once at most 64
+// values are left in the range they are ranked directly.  Three selections (median, MAD, the K_o-th largest norm) of
+// about ten counts each replace two O(K^2) rankings of all the values (K = 1536: 112 us each; 8960: 640 us).
+// The MAD's doubles are bisected by their upper 32 bits first.
+// One workgroup on an otherwise idle chip is bound by latency: a count ends at a barrier, so the workgroup has few waves, and
+// code that runs once is fetched from memory at about a microsecond per kilobyte, so every loop but the count itself is rolled
+// (everything unrolled over register-resident values: 10 KB and 25 us at K = 1536, 26 KB and 39 us at K = 8960; as it is 22 and 30).
+// KPT: keys per thread; 0 (K > 16384): keys are recomputed from memory.
+template <int KPT, int NT>
+__global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v, int K, double c, double alpha, int align,
+                                                    const uint8_t *__restrict__ forced, DetectScalars *sc,
+                                                    int32_t *__restrict__ perm)
+{
+    constexpr int R = KPT > 0 ? KPT : 1, NW = NT / 64;
+    __shared__ int red[2][NW];
+    __shared__ __align__(16) unsigned long long cand[64];
+    __shared__ int n_cand, rank[64];
+    extern __shared__ float vl[];              // K norms (KPT > 0)
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    int buf = 0;
+
+    if constexpr (KPT > 0) {
+        float x[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) x[u] = u * NT + t < K ? v[u * NT + t] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * NT + t < K) vl[u * NT + t] = x[u];
+    }
+    double med = 0.0;
+    bool devs = false;                         // keys: deviations from the median (upper halves) instead of norms
+    auto value = [&](int i) { return KPT > 0 ? vl[i] : v[i]; };
+    auto dev = [&](float f) { return (unsigned long long)__double_as_longlong(fabs((double)f - med)); };
+    auto key_of = [&](float f) { return devs ? (unsigned)(dev(f) >> 32) : __float_as_uint(f); };
+    unsigned key[R];                           // keys of the selection at hand, ~0 past the end
+    // workgroup sum / minimum: one barrier each, two alternating LDS buffers
+    auto all_sum = [&](int n) {
+        n = wave_sum_all(n);
+        if (lane == 0) red[buf][wave] = n;
+        __syncthreads();
+        n = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) n += red[buf][w];
+        buf ^= 1;
+        return __builtin_amdgcn_readfirstlane(n);      // (keeps the bisection in scalar registers)
+    };
+    auto all_min = [&](unsigned m) {
+        m = wave_min_all(m);
+        if (lane == 0) red[buf][wave] = (int)m;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m = min(m, (unsigned)red[buf][w]);
+        buf ^= 1;
+        return (unsigned)__builtin_amdgcn_readfirstlane((int)m);
+    };
+    auto count = [&](auto pred) __attribute__((always_inline)) {              // number of values with pred(index, value)
+        int n = 0;
+#pragma unroll 4
+        for (int i = t; i < K; i += NT) n += pred(i, value(i)) ? 1 : 0;
+        return all_sum(n);
+    };
+
+    int K_o = 0;
+    unsigned sel_min = ~0u;                    // selected: channels with a pattern above this one,
+    int cut = K - 1;                           // and those equal to it up to this index
+    // selections: 0 the median of the norms, 1 the median of the deviations, 2 the smallest of the K_o largest norms
+#pragma unroll 1
+    for (int stage = forced ? 3 : 0; stage < 3; ++stage) {
+        devs = stage == 1;
+        unsigned min_key = ~0u, max_inv = ~0u;
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int i = u * NT + t;
+                key[u] = i < K ? key_of(vl[i]) : ~0u;
+                min_key = min(min_key, key[u]);
+                max_inv = i < K ? min(max_inv, ~key[u]) : max_inv;
+            }
+        } else {
+            for (int i = t; i < K; i += NT) {
+                const unsigned q = key_of(v[i]);
+                min_key = min(min_key, q);
+                max_inv = min(max_inv, ~q);
+            }
+        }
+        min_key = all_min(min_key);
+        const unsigned max_key = ~all_min(max_inv);
+        // k-th smallest (from 0) of the 32- or (deviations) 64-bit patterns; `second` is the next order statistic
+        int k = stage < 2 ? (K - 1) / 2 : K - K_o;
+        unsigned long long first = 0, second = 0;
+#pragma unroll 1
+        for (int rep = 0; rep < 2; ++rep) {
+            unsigned lo = min_key, hi = max_key;
+            int below = 0, upto = K;           // values below the range, and up to its end
+            while (lo < hi && upto - below > 64) {
+                const unsigned mid = lo + ((hi - lo) >> 1);       // < hi: never the key past the end
+                int n = 0;
+                if constexpr (KPT > 0) {
+#pragma unroll
+                    for (int u = 0; u < R; ++u) n += key[u] <= mid ? 1 : 0;
+                } else {
+                    for (int i = t; i < K; i += NT) n += key_of(v[i]) <= mid ? 1 : 0;
+                }
+                n = all_sum(n);
+                if (n > k) {
+                    hi = mid;
+                    upto = n;
+                } else {
+                    lo = mid + 1;
+                    below = n;
+                }
+            }
+            unsigned long long lo2 = devs ? (unsigned long long)lo << 32 : lo;
+            unsigned long long hi2 = devs ? ((unsigned long long)hi << 32) | 0xFFFFFFFFull : hi;
+            while (lo2 < hi2 && upto - below > 64) {              // more than 64 deviations share the upper half
+                const unsigned long long mid = lo2 + ((hi2 - lo2) >> 1);
+                const int n = count([&](int, float f) { return dev(f) <= mid; });
+                if (n > k) {
+                    hi2 = mid;
+                    upto = n;
+                } else {
+                    lo2 = mid + 1;
+                    below = n;
+                }
+            }
+            unsigned long long kth = lo2;      // lo2 == hi2: every value left is this one
+            bool have_next = false;
+            if (lo2 < hi2) {
+                if (t == 0) n_cand = 0;
+                if (t < 64) rank[t] = 0;
+                __syncthreads();
+#pragma unroll 4
+                for (int i = t; i < K; i += NT) {
+                    const float f = value(i);
+                    const unsigned long long q = devs ? dev(f) : (unsigned long long)__float_as_uint(f);
+                    if (q >= lo2 && q <= hi2) {
+                        const int slot = atomicAdd(&n_cand, 1);
+                        if (slot < 64) cand[slot] = q;
+                    }
+                }
+                __syncthreads();
+                const int m = min(n_cand, 64);
+                const unsigned long long mine = lane < m ? cand[lane] : ~0ull;
+                int r = 0;                     // every wave compares with its share of the candidates
+#pragma unroll
+                for (int u = 0; u < 64 / NW; ++u) {
+                    const int j = wave * (64 / NW) + u;
+                    const unsigned long long o = cand[j];
+                    r += j < m && (o < mine || (o == mine && j < lane)) ? 1 : 0;
+                }
+                if (r) atomicAdd(&rank[lane], r);
+                __syncthreads();
+                r = rank[lane];
+                const unsigned long long who = __ballot(lane < m && r == k - below);
+                const unsigned long long next = __ballot(lane < m && r == k + 1 - below);
+                if (who) kth = cand[__builtin_ctzll(who)];
+                if (next) {
+                    have_next = true;
+                    second = cand[__builtin_ctzll(next)];
+                }
+                __syncthreads();               // cand and n_cand may be rewritten
+            } else if (k + 1 < upto) {
+                have_next = true;
+                second = kth;
+            }
+            if (rep == 0) first = kth;
+            else second = kth;
+            if (stage == 2 || (K & 1) || have_next) break;
+            ++k;                               // even K and the upper middle lies beyond the range: select it too
+        }
+        if (stage < 2) {                       // median: mean of the two middle order statistics (odd K: the middle one)
+            const double a = devs ? __longlong_as_double((long long)first) : (double)__uint_as_float((unsigned)first);
+            const double b = devs ? __longlong_as_double((long long)second) : (double)__uint_as_float((unsigned)second);
+            const double middle = (K & 1) ? a : (b + a) / 2.0;
+            if (stage == 0) {
+                med = middle;
+            } else {
+                double T1 = c * middle;        // middle = MAD
+                T1 = med + T1;
+                const double T2 = alpha * med;
+                const double T = T1 > T2 ? T1 : T2;
+                const int n_det = count([&](int, float f) { return (double)f > T; });
+                if (t == 0) sc->n_det = n_det;
+                if (n_det == 0) break;
+                const long long up = ((long long)n_det + align - 1) / align * align;
+                K_o = up > K ? K : (int)up;
+            }
+        } else {
+            sel_min = (unsigned)first;
+            const int need = K_o - count([&](int, float f) { return __float_as_uint(f) > sel_min; });
+            const int equal = count([&](int, float f) { return __float_as_uint(f) == sel_min; });
+            for (int lo = 0; need < equal && lo < cut;) {         // ties: the smaller indices
+                const int mid = (lo + cut) / 2;
+                if (count([&](int i, float f) { return __float_as_uint(f) == sel_min && i <= mid; }) >= need) cut = mid;
+                else lo = mid + 1;
+            }
+        }
+    }
+    // Stable partition: perm = [selected ascending | rest ascending].  A thread takes P consecutive channels (P odd: no
+    // bank conflicts); the selected channels before them are counted over the lanes below it, bit by bit of their
+    // counts, and over the waves before.
+    auto selected = [&](int i) {
+        if (i >= K) return false;
+        if (forced) return forced[i] != 0;
+        const unsigned q = __float_as_uint(value(i));
+        return K_o > 0 && (q > sel_min || (q == sel_min && i <= cut));
+    };
+    const int P = ((K + NT - 1) / NT) | 1, i0 = t * P;
+    if constexpr (KPT > 0) __syncthreads();    // norms written by other threads
+    int n = 0;
+#pragma unroll 4
+    for (int j = 0; j < P; ++j) n += selected(i0 + j) ? 1 : 0;
+    int so = 0, wave_n = 0;
+#pragma unroll
+    for (int b = 0; b < (KPT > 0 ? 6 : 9); ++b) {        // P <= 33 (K <= 16384), 131 (K <= QARVD_MAX_K)
+        const unsigned long long bits = __ballot((n >> b) & 1);
+        so += __popcll(bits & ((1ull << lane) - 1)) << b;
+        wave_n += __popcll(bits) << b;
+    }
+    if (lane == 0) red[buf][wave] = wave_n;
+    __syncthreads();
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        so += w < wave ? red[buf][w] : 0;
+        all += red[buf][w];
+    }
+    if (forced) K_o = all;
+#pragma unroll 4
+    for (int j = 0; j < P; ++j) {
+        const int i = i0 + j;
+        const bool s = selected(i);
+        if (i < K) perm[s ? so : K_o + (i - so)] = i;
+        so += s ? 1 : 0;
+    }
+    if (t == 0) sc->K_o = K_o;
+}
+
+// ---- dual scales + codes -------------------------------------------------------------------
+// A row of W in PACKED order in the registers of a workgroup (NT = 64: of one wave).  Wave w holds the chunks of 256 packed
+// positions w, w + NT / 64, ...: in chunk c its lane l holds the positions 256 chunk + 64 e + l, e < 4.  The
+// permutation is applied by the loads themselves: the channel offsets of a lane's positions are the same for every row
+// and stay in registers, and since [outlier | normal] keeps both blocks in ascending order, the 64 addresses of a
+// load are consecutive but for the outliers left out.  So there is no LDS image, no position table and no byte
+// scatter, and rows of any length and alignment take the same path.  (Four consecutive positions per lane instead,
+// which need no transpose before the store, spread each load over 1 KB: 26 us against 21 for 8960 x 1536.)
+template <int CH, int NT>
+struct PackedRow {
+    uint32_t off[CH][4];     // byte offset in the row of every position (pads: some channel of the same block)
+    int n_off, end_o, end_n; // outlier block [0, end_o), normal block [n_off, end_n)
+    int kp;                  // packed extent
+    int base[CH];            // first position of the chunk (wave-uniform)
+
+    // wave: index of the wave among those that share the row
+    __device__ __forceinline__ void init(const int32_t *__restrict__ perm, int K, int K_o, int wave, int lane)
+    {
+        n_off = (K_o + 31) / 32 * 32;
+        end_o = K_o;
+        end_n = n_off + (K - K_o);
+        kp = (end_n + 127) / 128 * 128;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            base[c] = 256 * (wave + c * (NT / 64));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int p = base[c] + 64 * e + lane;
+                const int q = p < n_off ? min(p, K_o - 1) : min(K_o + (p - n_off), K - 1);
+                off[c][e] = 4u * (uint32_t)perm[max(q, 0)];
+            }
+        }
+    }
+    // w wave-uniform.  Raw buffer loads: the row's base sits in scalar registers and a position costs one 32-bit offset
+    // (the compiler keeps 64-bit addresses per position for global loads: twice the registers).
+    __device__ __forceinline__ void load(const float *w, int K, float (&x)[CH][4]) const
+    {
+#if defined(__HIP_DEVICE_COMPILE__)
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(w), 0, 4 * K, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (base[c] < kp) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    x[c][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off[c][e], 0, 0));
+            }
+#endif
+    }
+};
+
+// Quotients x / s for one scale.  RN(1 / s) times x, corrected twice with fused multiply-adds, IS the correctly rounded
+// quotient for 1e-30 <= s <= 1e30 and |x| <= 127.5 s (Markstein's theorem; the argument stands at quantize4_static in
+// gemm_dma_common.h): five instructions and no branch, where a product with a redo of the IEEE division near rounding
+// boundaries takes as many and 500 bytes of code per value (8960 x 1536: 21 -> 19 us).  s == 0 (a block of zeros, or none): every quotient is 0.
+struct Quotient {
+    float s, rs, bound;      // bound = RN(qmax s): beyond it the code is +-qmax whatever the quotient
+    __device__ __forceinline__ Quotient(float scale, float qmax) : s(scale), rs(scale == 0.0f ? 0.0f : 1.0f / scale), bound(qmax * scale) {}
+    __device__ __forceinline__ bool exact() const { return s == 0.0f || (s >= 1e-30f && s <= 1e30f); }
+    __device__ __forceinline__ float operator()(float x) const
+    {
+        const float q0 = x * rs;
+        const float q1 = fmaf(fmaf(-q0, s, x), rs, q0);
+        return fmaf(fmaf(-q1, s, x), rs, q1);
+    }
+};
+
+struct RowsArgs {
+    const float *W;
+    int64_t ldw;
+    const int32_t *perm;
+    const DetectScalars *sc;
+    uint8_t *out;            // INT8: one byte per position; INT4: two positions per byte
+    int64_t ldo;             // bytes
+    float *s_normal, *s_outlier;
+    float qmax;              // 127 or 7
+    int32_t N, K;
+};
+
+// Codes of a row and their store.  A lane's four codes of a chunk lie 64 positions apart; two exchanges inside each group of
+// four lanes (bytes i of lanes 4a .. 4a+3 belong together) turn them into the dword of positions 64 (l & 3) + 4 (l >> 2) ..+3
+// of the chunk, so that one store writes the 256 bytes.
+//
+// INT4 packing: the codes of each aligned group of 16 packed positions g go into 8 bytes; byte i < 4
+// holds positions 16g+i (low nibble) and 16g+4+i (high nibble), byte 4+i positions 16g+8+i and
+// 16g+12+i.  (Shifting a packed dword left by 4 and masking 0xF0F0F0F0 then yields four consecutive
+// codes, each times 16, in byte order; masking the dword itself the next four.)  So an even dword of codes and
+// the odd one after it, four lanes up, make one packed dword.
+template <int CH, int NT>
+__device__ __forceinline__ void store_codes(const RowsArgs &a, const PackedRow<CH, NT> &pr, const float (&x)[CH][4], int row, int lane,
+                                            const Quotient &qo, const Quotient &qn)
+{
+    constexpr float MAGIC = 12582912.0f;       // 1.5 * 2^23: the sum rounds half-to-even, the code is its low byte
+    uint8_t *out = a.out + (size_t)row * a.ldo;
+    const bool w4 = a.qmax < 8.0f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (pr.base[c] >= pr.kp) continue;
+        uint32_t b[4];
+        if (pr.base[c] >= pr.n_off && pr.base[c] + 256 <= pr.end_n) {        // normal channels only
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                b[e] = __float_as_uint(qn(__builtin_amdgcn_fmed3f(x[c][e], -qn.bound, qn.bound)) + MAGIC);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int p = pr.base[c] + 64 * e + lane;
+                const bool is_o = p < pr.n_off;
+                Quotient q = qn;
+                q.s = is_o ? qo.s : qn.s;
+                q.rs = is_o ? qo.rs : qn.rs;
+                q.bound = is_o ? qo.bound : qn.bound;
+                const float f = p < (is_o ? pr.end_o : pr.end_n) ? x[c][e] : 0.0f;      // pads
+                b[e] = __float_as_uint(q(__builtin_amdgcn_fmed3f(f, -q.bound, q.bound)) + MAGIC);
+            }
+        }
+        uint32_t w = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u),
+                                           0x05040100u);
+        // 4 x 4 byte transpose over lanes 4a .. 4a+3: bytes of odd / even pairs with lane ^ 1, then halves with lane ^ 2
+        const uint32_t w1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);
+        w = __builtin_amdgcn_perm(w1, w, (lane & 1) ? 0x03070105u : 0x06020400u);
+        const uint32_t w2 = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true);
+        w = __builtin_amdgcn_perm(w2, w, (lane & 2) ? 0x03020706u : 0x05040100u);
+        const int p0 = pr.base[c] + 64 * (lane & 3) + 4 * (lane >> 2);
+        if (!w4) {
+            if (p0 < pr.kp) *reinterpret_cast<uint32_t *>(out + p0) = w;
+        } else {
+            const uint32_t up = (uint32_t)__builtin_amdgcn_ds_swizzle((int)w, 0x101F);     // lane ^ 4
+            if (!(lane & 4) && p0 < pr.kp)
+                *reinterpret_cast<uint32_t *>(out + p0 / 2) = (w & 0x0F0F0F0Fu) | ((up & 0x0F0F0F0Fu) << 4);
+        }
+    }
+}
+
+// The same for scales outside the range of the exact quotient above (rows of magnitudes around 1e-30 and below, or 1e30 and
+// above): IEEE divisions, one position per thread, the row gathered again.
+template <int NT>
+__device__ __forceinline__ void store_codes_far(const RowsArgs &a, int row, int t, int K_o, float so, float sn)
+{
+    const float *w = a.W + (size_t)row * a.ldw;
+    uint8_t *out = a.out + (size_t)row * a.ldo;
+    const int n_off = (K_o + 31) / 32 * 32, end_n = n_off + (a.K - K_o), kp = (end_n + 127) / 128 * 128;
+    auto code = [&](int p) {
+        if (p < n_off) return p < K_o ? quantize_sym(w[a.perm[p]], so, a.qmax) : 0;
+        return p < end_n ? quantize_sym(w[a.perm[K_o + (p - n_off)]], sn, a.qmax) : 0;
+    };
+    if (a.qmax > 8.0f)
+        for (int p = t; p < kp; p += NT) out[p] = (uint8_t)code(p);
+    else
+        for (int b = t; b < kp / 2; b += NT) {
+            const int p = 16 * (b >> 3) + (b & 3) + 8 * ((b >> 2) & 1);
+            out[b] = (uint8_t)((code(p) & 15) | ((code(p + 4) & 15) << 4));
+        }
+}
+
+// Absmax scales.  NT = 64: four independent rows per workgroup, one per wave, no barrier; else one row per workgroup.
+// Bound by the 4 N K bytes read and N K written (3.6 TB/s at 8960 x 1536, of which 4 us are the first row's latency).
+template <int CH, int NT>
+__global__ __launch_bounds__(NT == 64 ? 256 : NT) void weight_rows_kernel(RowsArgs a)
+{
+    constexpr int RW = NT == 64 ? 4 : 1, NWAVE = NT / 64;
+    __shared__ float red[2][2][NWAVE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int K_o = a.sc->K_o;
+    PackedRow<CH, NT> pr;
+    pr.init(a.perm, a.K, K_o, NT == 64 ? 0 : wave, lane);
+    const int stride = gridDim.x * RW;
+    int row = blockIdx.x * RW + (NT == 64 ? wave : 0);
+    float x[CH][4], xn[CH][4];
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[c][e] = xn[c][e] = 0.0f;
+    if (row < a.N) pr.load(a.W + (size_t)row * a.ldw, a.K, x);
+    for (int buf = 0; row < a.N; row += stride, buf ^= 1) {
+        if (row + stride < a.N) pr.load(a.W + (size_t)(row + stride) * a.ldw, a.K, xn);      // in flight under this row's work
+        float m_o = 0.0f, m_n = 0.0f;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (pr.base[c] >= pr.n_off) {
+                m_n = fmaxf(m_n, fmaxf(fmaxf(fabsf(x[c][0]), fabsf(x[c][1])), fmaxf(fabsf(x[c][2]), fabsf(x[c][3]))));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool is_o = pr.base[c] + 64 * e + lane < pr.n_off;
+                    m_o = fmaxf(m_o, is_o ? fabsf(x[c][e]) : 0.0f);
+                    m_n = fmaxf(m_n, is_o ? 0.0f : fabsf(x[c][e]));
+                }
+            }
+        }
+        m_o = wave_max_all(m_o);
+        m_n = wave_max_all(m_n);
+        if constexpr (NT > 64) {
+            if (lane == 0) {
+                red[buf][0][wave] = m_o;
+                red[buf][1][wave] = m_n;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < NWAVE; ++w) {
+                m_o = fmaxf(m_o, red[buf][0][w]);
+                m_n = fmaxf(m_n, red[buf][1][w]);
+            }
+        }
+        // a block without channels holds only pads (which load some channel of the row): its scale is zero
+        const float so = K_o > 0 ? m_o / a.qmax : 0.0f, sn = K_o < a.K ? m_n / a.qmax : 0.0f;
+        if (lane == 0 && (NT == 64 || wave == 0)) {
+            a.s_outlier[row] = so;
+            a.s_normal[row] = sn;
+        }
+        const Quotient qo(so, a.qmax), qn(sn, a.qmax);
+        if (qo.exact() && qn.exact()) store_codes<CH, NT>(a, pr, x, row, lane, qo, qn);
+        else store_codes_far<NT>(a, row, NT == 64 ? lane : (int)threadIdx.x, K_o, so, sn);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[c][e] = xn[c][e];
+    }
+}
+
+// Rows of more than 16384 channels: two passes over the row, gathered through perm from memory.
+__global__ __launch_bounds__(256) void weight_rows_long_kernel(RowsArgs a)
+{
+    __shared__ float red[2][4];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, row = blockIdx.x;
+    const int K_o = a.sc->K_o;
+    const float *w = a.W + (size_t)row * a.ldw;
+    float m_o = 0.0f, m_n = 0.0f;
+    for (int q = t; q < a.K; q += 256) {
+        const float m = fabsf(w[a.perm[q]]);
+        if (q < K_o) m_o = fmaxf(m_o, m);
+        else m_n = fmaxf(m_n, m);
+    }
+    m_o = wave_max_all(m_o);
+    m_n = wave_max_all(m_n);
+    if (lane == 0) {
+        red[0][wave] = m_o;
+        red[1][wave] = m_n;
+    }
+    __syncthreads();
+    const float so = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])) / a.qmax;
+    const float sn = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3])) / a.qmax;
+    if (t == 0) {
+        a.s_outlier[row] = so;
+        a.s_normal[row] = sn;
+    }
+    store_codes_far<256>(a, row, t, K_o, so, sn);
+}
+
+// ---- percentile-clip scales ----------------------------------------------------------------
 // Percentile-clip initialisation of the two scales of every output row (Sec. 4.1 "Quantization
 // Implementation": the clipping percentile is searched over {0.999, 0.9999, 0.99999}).  Per row and block,
 // with the block's n values taken in packed order:
@@ -175,156 +639,242 @@ __global__ __launch_bounds__(1024) void build_perm_kernel(const uint8_t *__restr
 //              in double, rounded to float),  s_p = clip_p / qmax,
 //     SSE_p  = sum (double) e^2,  e = fmaf(-s_p, q(w, s_p), w),  summed in packed order in double;
 //     the smallest SSE wins, the larger percentile on a tie.
-// The sums are order-dependent in their last bits and decide an integer, so one thread owns one block of one
-// row and walks it serially (this is the offline step).  Only the CLIP_TOP largest magnitudes are ever needed:
-// n - 1 - floor(0.999 (n-1)) < CLIP_TOP for n <= 16384.
-constexpr int CLIP_TOP = 20;
-__global__ __launch_bounds__(64) void clip_search_kernel(const float *__restrict__ W, int N, int K, int64_t ldw,
-                                                         const int32_t *__restrict__ perm, const DetectScalars *sc,
-                                                         float qmax, float *__restrict__ s_normal,
-                                                         float *__restrict__ s_outlier)
-{
-    const int t = blockIdx.x * 64 + threadIdx.x;
-    if (t >= 2 * N) return;
-    const int blk = t / N, j = t - blk * N;            // the first N threads take the outlier blocks
-    const int K_o = sc->K_o;
-    const int p0 = blk ? K_o : 0, n = blk ? K - K_o : K_o;
-    float *dst = blk ? s_normal : s_outlier;
-    if (n == 0) {
-        dst[j] = 0.0f;
-        return;
-    }
-    const float *w = W + (size_t)j * ldw;
-    float top[CLIP_TOP];                               // ascending; -1 marks an empty slot (magnitudes are >= 0)
-#pragma unroll
-    for (int i = 0; i < CLIP_TOP; ++i) top[i] = -1.0f;
-    for (int p = p0; p < p0 + n; ++p) {
-        const float a = fabsf(w[perm[p]]);
-        if (a > top[0]) {
-            top[0] = a;
-#pragma unroll
-            for (int i = 0; i + 1 < CLIP_TOP; ++i) {
-                const float lo = fminf(top[i], top[i + 1]), hi = fmaxf(top[i], top[i + 1]);
-                top[i] = lo;
-                top[i + 1] = hi;
-            }
-        }
-    }
-    auto order_stat = [&](int i) {                     // a_(i) of the ascending order, i >= n - CLIP_TOP
-        const int slot = CLIP_TOP - n + i;
-        float r = top[0];
-#pragma unroll
-        for (int u = 1; u < CLIP_TOP; ++u) r = u == slot ? top[u] : r;
-        return r;
-    };
-    const double P[3] = {0.999, 0.9999, 0.99999};
-    float s[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double h = (double)(n - 1) * P[c];
-        const int lo = (int)floor(h);
-        const int hi = lo + 1 < n ? lo + 1 : n - 1;
-        const double frac = h - (double)lo;
-        const double alo = (double)order_stat(lo), ahi = (double)order_stat(hi);
-        const float clip = (float)(alo + frac * (ahi - alo));
-        s[c] = clip / qmax;
-    }
-    double sse[3] = {0.0, 0.0, 0.0};
-    for (int p = p0; p < p0 + n; ++p) {
-        const float x = w[perm[p]];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const float q = (float)quantize_sym(x, s[c], qmax);
-            const float e = fmaf(-s[c], q, x);
-            sse[c] += (double)e * (double)e;
-        }
-    }
-    int best = 2;
-    if (sse[1] < sse[best]) best = 1;
-    if (sse[0] < sse[best]) best = 0;
-    dst[j] = best == 2 ? s[2] : best == 1 ? s[1] : s[0];
-}
+// One workgroup per row, values in registers in packed order (PackedRow), both blocks in each phase.  The quantiles need
+// the T = n - floor(0.999 (n-1)) largest magnitudes only (T <= 18 for n <= 16384).  The T-th largest of the NT / 16 maxima
+// of groups of sixteen lanes is a lower bound of the T-th largest value; the few dozen values that reach it go to
+// LDS and are ranked there.
+// The three sums are taken in parallel.  They decide an integer, so a comparison counts only where it holds for every order of
+// summation: serial and parallel sums are both within n u / (1 - n u) of the exact one (u = 2^-53; e^2 is exact).
+// Candidates with equal scales have equal sums term by term.  Anything else (intervals that overlap, NaN) is summed
+// in order by one thread.  Bound by the latency of its phases (14 us a row) and by vector-ALU issue (about 35
+// instructions per value), so one row per workgroup and registers held low enough for three workgroups per CU (1536 x 8960:
+// 50 us; with the offsets kept for three rows 79, one workgroup per CU).
+constexpr int CLIP_MAX_T = 20, CLIP_CAND = 512;
 
-// One workgroup per output row.  Pass 1: absmax of each block; pass 2: quantize and store each
-// byte at its packed position (the row is re-read from cache).  K_o is read from the workspace
-// scalars so that no host round trip sits between detection and quantization.
-__global__ __launch_bounds__(256) void quantize_rows_kernel(const float *__restrict__ W, int N, int K, int64_t ldw,
-                                                            const int32_t *__restrict__ pos, const DetectScalars *sc,
-                                                            int8_t *__restrict__ Wq, int64_t ldwq,
-                                                            float *__restrict__ s_normal, float *__restrict__ s_outlier,
-                                                            float qmax, bool scales_given)
+template <int CH, int NT>
+__global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(RowsArgs a)
 {
-    __shared__ float red[8];
-    const int j = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int K_o = sc->K_o;
-    const int n_off = (K_o + 31) / 32 * 32;
-    const int kp = (n_off + (K - K_o) + 127) / 128 * 128;
-    const float *w = W + (size_t)j * ldw;
-    float so, sn;
-    if (scales_given) {              // (uniform) the clip search has written this row's scales
-        so = s_outlier[j];
-        sn = s_normal[j];
-    } else {
-        float a_o = 0.0f, a_n = 0.0f;
-        for (int k = tid; k < K; k += 256) {
-            const float a = fabsf(w[k]);
-            if (pos[k] < K_o) a_o = fmaxf(a_o, a);
-            else a_n = fmaxf(a_n, a);
-        }
-        a_o = wave_max(a_o);
-        a_n = wave_max(a_n);
-        if ((tid & 63) == 0) {
-            red[tid >> 6] = a_o;
-            red[4 + (tid >> 6)] = a_n;
+    constexpr int NWAVE = NT / 64, G = NT / 16;
+    static_assert(G <= 64, "one group maximum per lane");
+    __shared__ float gmax[2][G], top[2][CLIP_MAX_T], redf[NWAVE], scale[2][3], chosen[2];
+    __shared__ __align__(16) float cand[2][CLIP_CAND];
+    __shared__ double sums[2][NWAVE][3];
+    __shared__ int n_cand[2], redi[NWAVE];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int K_o = a.sc->K_o;
+    PackedRow<CH, NT> pr;
+    pr.init(a.perm, a.K, K_o, wave, lane);
+    auto block_n = [&](int blk) { return blk ? a.K - K_o : K_o; };
+    auto block_T = [&](int blk) { return block_n(blk) - (int)floor((double)(block_n(blk) - 1) * 0.999); };
+    {
+        const int row = blockIdx.x;
+        const float *w = a.W + (size_t)row * a.ldw;
+        float x[CH][4];
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[c][e] = 0.0f;
+        pr.load(w, a.K, x);
+        // f(value, real) over the chunks that hold positions of block blk (whole waves)
+        auto for_each = [&](int blk, auto f) {
+            const int b0 = blk ? pr.n_off : 0, b1 = blk ? pr.end_n : pr.end_o;
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+                if (pr.base[c] < b1 && pr.base[c] + 256 > b0) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int p = pr.base[c] + 64 * e + lane;
+                        f(x[c][e], p >= b0 && p < b1);
+                    }
+                }
+        };
+        // ---- the T largest magnitudes of each block, descending, in top[] ----
+#pragma unroll 1
+        for (int blk = 0; blk < 2; ++blk) {
+            float m = -1.0f;
+            for_each(blk, [&](float f, bool real) { m = fmaxf(m, real ? fabsf(f) : -1.0f); });
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+            if ((lane & 15) == 0) gmax[blk][t >> 4] = m;
+            if (t == 0) n_cand[blk] = 0;
+            if (t < CLIP_MAX_T) top[blk][t] = -1.0f;
         }
         __syncthreads();
-        a_o = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        a_n = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
-        so = a_o / qmax;     // qmax = 127 (INT8 codes) or 7 (INT4 codes)
-        sn = a_n / qmax;
-        if (tid == 0) {
-            s_outlier[j] = so;
-            s_normal[j] = sn;
+#pragma unroll 1
+        for (int blk = 0; blk < 2; ++blk) {
+            const int T = block_T(blk);
+            float L = -1.0f;                   // at least T values reach the T-th largest group maximum
+            const float mine = lane < G ? gmax[blk][lane] : -2.0f;
+            int r = 0;
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
+                r += (o > mine || (o == mine && j < lane)) ? 1 : 0;
+            }
+            const unsigned long long who = __ballot(lane < G && r == T - 1);
+            if (who) L = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), __builtin_ctzll(who)));
+            for_each(blk, [&](float f, bool real) {
+                if (real && fabsf(f) >= L) {
+                    const int slot = atomicAdd(&n_cand[blk], 1);
+                    if (slot < CLIP_CAND) cand[blk][slot] = fabsf(f);
+                }
+            });
         }
+        __syncthreads();
+        {
+            const int blk = t < NT / 2 ? 1 : 0;        // half of the workgroup ranks each block's candidates
+            const int nc = n_cand[blk], T = block_T(blk);
+            if (nc <= CLIP_CAND)
+                for (int i = t & (NT / 2 - 1); i < nc; i += NT / 2) {
+                    const float mine = cand[blk][i];
+                    int r = 0;
+#pragma unroll 4
+                    for (int j = 0; j < nc; j += 4) {
+                        const float4 o = *reinterpret_cast<const float4 *>(&cand[blk][j]);
+                        r += (o.x > mine || (o.x == mine && j < i)) ? 1 : 0;
+                        r += j + 1 < nc && (o.y > mine || (o.y == mine && j + 1 < i)) ? 1 : 0;
+                        r += j + 2 < nc && (o.z > mine || (o.z == mine && j + 2 < i)) ? 1 : 0;
+                        r += j + 3 < nc && (o.w > mine || (o.w == mine && j + 3 < i)) ? 1 : 0;
+                    }
+                    if (r < T) top[blk][r] = mine;
+                }
+        }
+#pragma unroll 1
+        for (int blk = 0; blk < 2; ++blk) {
+            if (n_cand[blk] <= CLIP_CAND) continue;
+            // many ties or a crowded group: one distinct magnitude per round
+            const int T = block_T(blk);
+            float prev = __builtin_inff();
+            bool first = true;
+            for (int have = 0; have < T;) {
+                float mx = -1.0f;
+                for_each(blk, [&](float f, bool real) {
+                    const float v = fabsf(f);
+                    if (real && (first || v < prev)) mx = fmaxf(mx, v);
+                });
+                mx = wave_max_all(mx);
+                if (lane == 0) redf[wave] = mx;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < NWAVE; ++i) mx = fmaxf(mx, redf[i]);
+                int eq = 0;
+                for_each(blk, [&](float f, bool real) { eq += (real && fabsf(f) == mx) ? 1 : 0; });
+                eq = wave_sum_all(eq);
+                if (lane == 0) redi[wave] = eq;
+                __syncthreads();
+                eq = 0;
+#pragma unroll
+                for (int i = 0; i < NWAVE; ++i) eq += redi[i];
+                if (eq == 0) mx = -1.0f;       // nothing left to find (NaN in the row): no further rounds
+                const int upto = eq == 0 ? T : min(T, have + eq);
+                if (t >= have && t < upto) top[blk][t] = mx;
+                have = upto;
+                prev = mx;
+                first = false;
+                __syncthreads();
+            }
+        }
+        __syncthreads();
+        // ---- candidate scales: thread 3 blk + c ----
+        if (t < 6) {
+            const int blk = t / 3, c = t - 3 * blk, n = block_n(blk);
+            const double h = (double)(n - 1) * (c == 0 ? 0.999 : c == 1 ? 0.9999 : 0.99999);
+            const int lo = (int)floor(h);
+            const int hi = lo + 1 < n ? lo + 1 : n - 1;
+            const double frac = h - (double)lo;
+            const double alo = n > 0 ? (double)top[blk][n - 1 - lo] : 0.0, ahi = n > 0 ? (double)top[blk][n - 1 - hi] : 0.0;
+            const float clip = (float)(alo + frac * (ahi - alo));
+            scale[blk][c] = clip / a.qmax;
+        }
+        __syncthreads();
+        // ---- squared errors ----
+#pragma unroll 1
+        for (int blk = 0; blk < 2; ++blk) {
+            const Quotient qt[3] = {Quotient(scale[blk][0], a.qmax), Quotient(scale[blk][1], a.qmax), Quotient(scale[blk][2], a.qmax)};
+            double sse[3] = {0.0, 0.0, 0.0};
+            for_each(blk, [&](float f0, bool real) {
+                const float f = real ? f0 : 0.0f;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const float q = rintf(qt[c](__builtin_amdgcn_fmed3f(f, -qt[c].bound, qt[c].bound)));
+                    const double e = (double)fmaf(-qt[c].s, q, f);
+                    sse[c] = fma(e, e, sse[c]);
+                }
+            });
+            // scales outside the exact quotient's range: the sums prove nothing
+            if (!(qt[0].exact() && qt[1].exact() && qt[2].exact())) sse[0] = sse[1] = sse[2] = __builtin_nan("");
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                sse[c] = wave_sum_all(sse[c]);
+                if (lane == 0) sums[blk][wave][c] = sse[c];
+            }
+        }
+        __syncthreads();
+        if (t < 2) {                           // thread blk decides
+            const int blk = t, n = block_n(blk);
+            const float s0 = scale[blk][0], s1 = scale[blk][1], s2 = scale[blk][2];
+            double q0 = 0.0, q1 = 0.0, q2 = 0.0;
+#pragma unroll
+            for (int i = 0; i < NWAVE; ++i) {
+                q0 += sums[blk][i][0];
+                q1 += sums[blk][i][1];
+                q2 += sums[blk][i][2];
+            }
+            const double e = 2.5 * ((double)n + 2.0) * 0x1p-53;
+            bool proven = true;
+            auto less = [&](float sp, double p, float sq, double q) {        // ordered sum p < ordered sum q
+                if (sp == sq) return false;
+                if (p * (1.0 + e) < q * (1.0 - e)) return true;
+                if (!(p * (1.0 - e) >= q * (1.0 + e))) proven = false;
+                return false;
+            };
+            const bool one = less(s1, q1, s2, q2);
+            float best = one ? s1 : s2;
+            if (less(s0, q0, best, one ? q1 : q2)) best = s0;
+            if (!proven) {
+                q0 = q1 = q2 = 0.0;
+                for (int p = blk ? K_o : 0, end = p + n; p < end; ++p) {
+                    const float f = w[a.perm[p]];
+                    const double d0 = (double)fmaf(-s0, (float)quantize_sym(f, s0, a.qmax), f);
+                    const double d1 = (double)fmaf(-s1, (float)quantize_sym(f, s1, a.qmax), f);
+                    const double d2 = (double)fmaf(-s2, (float)quantize_sym(f, s2, a.qmax), f);
+                    q0 = fma(d0, d0, q0);
+                    q1 = fma(d1, d1, q1);
+                    q2 = fma(d2, d2, q2);
+                }
+                best = q1 < q2 ? s1 : s2;
+                if (q0 < (q1 < q2 ? q1 : q2)) best = s0;
+            }
+            if (n == 0) best = 0.0f;
+            chosen[blk] = best;
+            (blk ? a.s_normal : a.s_outlier)[row] = best;
+        }
+        __syncthreads();
+        const Quotient qo(chosen[0], a.qmax), qn(chosen[1], a.qmax);
+        if (qo.exact() && qn.exact()) store_codes<CH, NT>(a, pr, x, row, lane, qo, qn);
+        else store_codes_far<NT>(a, row, t, K_o, chosen[0], chosen[1]);
     }
-    int8_t *out = Wq + (size_t)j * ldwq;
-    for (int k = tid; k < K; k += 256) {
-        const int p = pos[k];
-        out[p] = (int8_t)quantize_sym(w[k], p < K_o ? so : sn, qmax);
-    }
-    // zero padding: [K_o, n_off) and [n_off + K_n, kp)
-    for (int p = K_o + tid; p < n_off; p += 256) out[p] = 0;
-    for (int p = n_off + (K - K_o) + tid; p < kp; p += 256) out[p] = 0;
 }
 
-// INT4 packing: the codes of each aligned group of 16 packed positions g go into 8 bytes; byte i < 4
-// holds positions 16g+i (low nibble) and 16g+4+i (high nibble), byte 4+i positions 16g+8+i and
-// 16g+12+i.  (Shifting a packed dword left by 4 and masking 0xF0F0F0F0 then yields four consecutive
-// codes, each times 16, in byte order; masking the dword itself the next four.)
-__global__ __launch_bounds__(256) void pack_w4_kernel(const int8_t *__restrict__ codes, int64_t ldc, int N, int kp,
-                                                      uint8_t *__restrict__ Wq4, int64_t ldwq4)
-{
-    const int j = blockIdx.x;
-    const int b = blockIdx.y * 256 + threadIdx.x;      // output byte of the row
-    if (b >= kp / 2) return;
-    const int g = b >> 3, i = b & 7;
-    const int lo = 16 * g + (i < 4 ? i : 8 + (i - 4));
-    const int8_t *c = codes + (size_t)j * ldc;
-    Wq4[(size_t)j * ldwq4 + b] = (uint8_t)((c[lo] & 0xF) | ((c[lo + 4] & 0xF) << 4));
-}
-
+// ---- host ------------------------------------------------------------------------------------
 struct Workspace {
-    float *v, *sorted_v;
-    int32_t *rank, *pos;
-    double *d, *sorted_d;
-    uint8_t *sel;
     DetectScalars *sc;
+    float *v;
+    double *partial;
+    uint8_t *forced;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t carve(void *base, int32_t K, Workspace *ws)
+int norm_chunks(int32_t N, int32_t K)
+{
+    const int slabs = (K + 255) / 256;
+    const int most = NORM_BLOCKS / slabs > 0 ? NORM_BLOCKS / slabs : 1;
+    const int want = (N + 15) / 16;              // at least four rows per wave
+    return want < most ? want : most;
+}
+
+size_t carve(void *base, int32_t N, int32_t K, Workspace *ws)
 {
     unsigned char *p = reinterpret_cast<unsigned char *>(base);
     size_t off = 0;
@@ -333,20 +883,53 @@ size_t carve(void *base, int32_t K, Workspace *ws)
         off += align256(bytes);
         return r;
     };
-    void *sc = take(sizeof(DetectScalars));
-    void *v = take((size_t)K * 4), *sv = take((size_t)K * 4), *rk = take((size_t)K * 4), *ps = take((size_t)K * 4);
-    void *d = take((size_t)K * 8), *sd = take((size_t)K * 8), *sel = take((size_t)K);
+    void *sc = take(sizeof(DetectScalars)), *v = take((size_t)K * 4), *forced = take((size_t)K);
+    const int chunks = norm_chunks(N, K);
+    void *partial = take((size_t)(chunks > 4 ? chunks : 4) * K * 8);      // (short layers ask for no less than 37 K bytes in all)
     if (ws) {
         ws->sc = reinterpret_cast<DetectScalars *>(sc);
         ws->v = reinterpret_cast<float *>(v);
-        ws->sorted_v = reinterpret_cast<float *>(sv);
-        ws->rank = reinterpret_cast<int32_t *>(rk);
-        ws->pos = reinterpret_cast<int32_t *>(ps);
-        ws->d = reinterpret_cast<double *>(d);
-        ws->sorted_d = reinterpret_cast<double *>(sd);
-        ws->sel = reinterpret_cast<uint8_t *>(sel);
+        ws->forced = reinterpret_cast<uint8_t *>(forced);
+        ws->partial = reinterpret_cast<double *>(partial);
     }
     return off;
+}
+
+qarvd_status launch_detect(const Workspace &ws, int32_t K, const qarvd_detect_cfg &c, int32_t *perm, hipStream_t st)
+{
+    const uint8_t *forced = c.forced_mask ? ws.forced : nullptr;
+    const double f = c.tau / 0.6745;
+    auto go = [&](auto kern, int nt, bool keep) {
+        const size_t lds = keep ? (size_t)K * sizeof(float) : 0;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), lds, st, ws.v, K, f, c.alpha, c.align, forced, ws.sc, perm);
+    };
+    if (K <= 6 * 256) go(detect_kernel<6, 256>, 256, true);
+    else if (K <= 10 * 512) go(detect_kernel<10, 512>, 512, true);
+    else if (K <= 9 * 1024) go(detect_kernel<9, 1024>, 1024, true);
+    else if (K <= 16 * 1024) {
+        static unsigned long long raised = 0;  // K = 16384 takes 66 KB of LDS
+        if (qarvd_status s_a = qarvd_raise_lds_limit_once(detect_kernel<16, 1024>, 80 * 1024, raised); s_a != QARVD_OK) return s_a;
+        go(detect_kernel<16, 1024>, 1024, true);
+    } else go(detect_kernel<0, 1024>, 1024, false);
+    return qarvd_launch_status();
+}
+
+template <int CH, int NT>
+void launch_rows(const RowsArgs &a, int cus, hipStream_t st)
+{
+    constexpr int RW = NT == 64 ? 4 : 1, TH = NT == 64 ? 256 : NT;
+    // as many workgroups as the registers let run at once (sixteen waves per CU), so that the offsets are set up once
+    // for several rows, trimmed to whole rounds
+    const int slots = cus * 1024 / TH;
+    const int groups = (a.N + RW - 1) / RW;
+    const int rounds = (groups + slots - 1) / slots;
+    hipLaunchKernelGGL((weight_rows_kernel<CH, NT>), dim3((groups + rounds - 1) / rounds), dim3(TH), 0, st, a);
+}
+
+template <int CH, int NT>
+void launch_rows_clip(const RowsArgs &a, hipStream_t st)
+{
+    hipLaunchKernelGGL((weight_rows_clip_kernel<CH, NT>), dim3(a.N), dim3(NT), 0, st, a);
 }
 
 }  // namespace
@@ -394,13 +977,12 @@ extern "C" int32_t qarvd_packed_ld(int32_t K, int32_t K_o)
 extern "C" size_t qarvd_quantize_weight_workspace(int32_t N, int32_t K)
 {
     if (N <= 0 || K <= 0 || K > QARVD_MAX_K) return 0;
-    return carve(nullptr, K, nullptr);
+    return carve(nullptr, N, K, nullptr);
 }
 
 namespace {
 
-// bits = 8: Wq is the INT8 output [N, ldwq].  bits = 4: Wq is the packed INT4 output [N, ldwq bytes]; the
-// one-byte codes go to a temporary behind the detector's workspace and are packed by a second kernel.
+// bits = 8: Wq is the INT8 output [N, ldwq].  bits = 4: Wq is the packed INT4 output [N, ldwq bytes].
 qarvd_status quantize_weight_impl(int bits, const float *W, int32_t N, int32_t K, int64_t ldw,
                                   const qarvd_detect_cfg *cfg, void *Wq, int64_t ldwq, float *s_normal,
                                   float *s_outlier, int32_t *perm, int32_t *K_o_host, float *v_out,
@@ -422,51 +1004,47 @@ qarvd_status quantize_weight_impl(int bits, const float *W, int32_t N, int32_t K
     if (ldwq < (bits == 8 ? kp_max : kp_max / 2)) return QARVD_ERR_INVALID_ARG;
     if (!qarvd_aligned16(Wq) || (ldwq % 16) != 0 || (reinterpret_cast<uintptr_t>(W) & 3u)) return QARVD_ERR_UNSUPPORTED;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return QARVD_ERR_WORKSPACE;
-    const size_t ws_detect = carve(nullptr, K, nullptr);
-    const int64_t ld_codes = qarvd_packed_k(K, -1);
-    if (workspace_bytes < ws_detect + (bits == 4 ? (size_t)N * ld_codes : 0)) return QARVD_ERR_WORKSPACE;
+    if (workspace_bytes < carve(nullptr, N, K, nullptr)) return QARVD_ERR_WORKSPACE;
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     Workspace ws;
-    carve(workspace, K, &ws);
-    int8_t *codes = bits == 8 ? reinterpret_cast<int8_t *>(Wq) : reinterpret_cast<int8_t *>(workspace) + ws_detect;
-    const int64_t ldc = bits == 8 ? ldwq : ld_codes;
-    const int gK256 = (K + 255) / 256;
+    carve(workspace, N, K, &ws);
+    int cus = 0;
+    if (qarvd_status s_d = qarvd_current_device(nullptr, &cus); s_d != QARVD_OK) return s_d;
+    if (c.forced_mask) QARVD_HIP_TRY(hipMemcpyAsync(ws.forced, c.forced_mask, (size_t)K, hipMemcpyHostToDevice, st));
 
-    hipLaunchKernelGGL(column_norm_kernel, dim3((K + 63) / 64), dim3(64), 0, st, W, N, K, ldw, ws.v);
-    if (c.forced_mask) {
-        QARVD_HIP_TRY(hipMemcpyAsync(ws.sel, c.forced_mask, (size_t)K, hipMemcpyHostToDevice, st));
-        // normalise to 0/1 is unnecessary: the kernels test for non-zero
+    const int chunks = norm_chunks(N, K), per_chunk = (N + chunks - 1) / chunks;
+    const bool vec = (K % 4) == 0 && (ldw % 4) == 0 && qarvd_aligned16(W);
+    const dim3 ng((K + 255) / 256, chunks);
+    if (vec) hipLaunchKernelGGL((norm_partial_kernel<true>), ng, dim3(256), 0, st, W, N, K, ldw, per_chunk, ws.partial);
+    else hipLaunchKernelGGL((norm_partial_kernel<false>), ng, dim3(256), 0, st, W, N, K, ldw, per_chunk, ws.partial);
+    hipLaunchKernelGGL(norm_final_kernel, dim3((K + 63) / 64), dim3(256), 0, st, ws.partial, chunks, W, N, K, ldw, ws.v, v_out);
+    if (qarvd_status s_l = launch_detect(ws, K, c, perm, st); s_l != QARVD_OK) return s_l;
+
+    RowsArgs a;
+    a.W = W; a.ldw = ldw; a.perm = perm; a.sc = ws.sc;
+    a.out = reinterpret_cast<uint8_t *>(Wq); a.ldo = ldwq;
+    a.s_normal = s_normal; a.s_outlier = s_outlier;
+    a.qmax = bits == 8 ? 127.0f : 7.0f; a.N = N; a.K = K;
+    // threads per row and dwords per thread by the longest packed row the call can produce
+    if (c.clip_search) {
+        if (kp_max <= 2 * 1024) launch_rows_clip<2, 256>(a, st);
+        else if (kp_max <= 5 * 1024) launch_rows_clip<5, 256>(a, st);
+        else if (kp_max <= 5 * 2048) launch_rows_clip<5, 512>(a, st);
+        else launch_rows_clip<9, 512>(a, st);
     } else {
-        hipLaunchKernelGGL((rank_desc_kernel<float>), dim3(gK256), dim3(256), 0, st, ws.v, K, ws.rank, ws.sorted_v);
-        hipLaunchKernelGGL(median_dev_kernel, dim3(gK256), dim3(256), 0, st, ws.v, ws.sorted_v, K, ws.sc, ws.d);
-        hipLaunchKernelGGL((rank_desc_kernel<double>), dim3(gK256), dim3(256), 0, st, ws.d, K, (int32_t *)nullptr, ws.sorted_d);
-        hipLaunchKernelGGL(threshold_kernel, dim3(1), dim3(256), 0, st, ws.v, ws.sorted_d, K, c.tau / 0.6745, c.alpha,
-                           c.align, ws.sc);
-        hipLaunchKernelGGL(select_by_rank_kernel, dim3(gK256), dim3(256), 0, st, ws.rank, K, ws.sc, ws.sel);
+        if (kp_max <= 6 * 256) launch_rows<6, 64>(a, cus, st);
+        else if (kp_max <= 5 * 512) launch_rows<5, 128>(a, cus, st);
+        else if (kp_max <= 5 * 1024) launch_rows<5, 256>(a, cus, st);
+        else if (kp_max <= 9 * 1024) launch_rows<9, 256>(a, cus, st);
+        else if (kp_max <= 9 * 2048) launch_rows<9, 512>(a, cus, st);
+        else hipLaunchKernelGGL(weight_rows_long_kernel, dim3(N), dim3(256), 0, st, a);
     }
-    hipLaunchKernelGGL(build_perm_kernel, dim3(1), dim3(1024), 0, st, ws.sel, K, ws.sc, c.forced_mask ? 1 : 0, perm, ws.pos);
-    const float qmax = bits == 8 ? 127.0f : 7.0f;
-    if (c.clip_search)
-        hipLaunchKernelGGL(clip_search_kernel, dim3((2 * N + 63) / 64), dim3(64), 0, st, W, N, K, ldw, perm, ws.sc, qmax,
-                           s_normal, s_outlier);
-    hipLaunchKernelGGL(quantize_rows_kernel, dim3(N), dim3(256), 0, st, W, N, K, ldw, ws.pos, ws.sc, codes, ldc, s_normal,
-                       s_outlier, qmax, c.clip_search != 0);
-    if (v_out) QARVD_HIP_TRY(hipMemcpyAsync(v_out, ws.v, (size_t)K * 4, hipMemcpyDeviceToDevice, st));
-    qarvd_status ls = qarvd_launch_status();
-    if (ls != QARVD_OK) return ls;
+    if (qarvd_status s_l = qarvd_launch_status(); s_l != QARVD_OK) return s_l;
     DetectScalars host_sc;
     QARVD_HIP_TRY(hipMemcpyAsync(&host_sc, ws.sc, sizeof(host_sc), hipMemcpyDeviceToHost, st));
     QARVD_HIP_TRY(hipStreamSynchronize(st));
     *K_o_host = host_sc.K_o;
-    if (bits == 4) {    // the packed extent depends on K_o, which is known on the host only now
-        const int kp = qarvd_packed(K, host_sc.K_o).kp;
-        hipLaunchKernelGGL(pack_w4_kernel, dim3(N, (kp / 2 + 255) / 256), dim3(256), 0, st, codes, ldc, N, kp,
-                           reinterpret_cast<uint8_t *>(Wq), ldwq);
-        ls = qarvd_launch_status();
-        if (ls != QARVD_OK) return ls;
-        QARVD_HIP_TRY(hipStreamSynchronize(st));   // the temporary lives in the caller's workspace
-    }
     return QARVD_OK;
 }
 
@@ -483,14 +1061,14 @@ extern "C" qarvd_status qarvd_quantize_weight(const float *W, int32_t N, int32_t
 }
 
 // ---- the same offline step for callers that cannot allocate ----------------------------------------------
-// The detector's workspace (norms, ranks, sorted copies, deviations, selection flags, the scalars) lives in a
-// file-scope device array instead of a caller buffer: 528 KB per GPU the library runs on, held until the
-// process ends.  In host code the array's name is only a stand-in; its device address is looked up once per
+// The workspace (partial norm sums, norms, mask, the scalars) lives in a file-scope device array instead of a caller
+// buffer: 2.1 MB per GPU the library runs on, held until the process ends.  In host code the array's name is only a stand-in; its device address is looked up once per
 // device with hipGetSymbolAddress and that pointer is what the kernels get.
 namespace {
 constexpr int32_t STATIC_SCRATCH_MAX_K = 16384;
-// carve() for K = 16384: 256 (scalars) + 4 x 65536 (v, sorted v, rank, pos) + 2 x 131072 (d, sorted d) + 16384 (flags)
-constexpr size_t STATIC_SCRATCH_BYTES = 256 + 4 * 65536 + 2 * 131072 + 16384;
+// carve() for K <= 16384: 256 (scalars) + 65536 (norms) + 16384 (mask) + partial sums (at most NORM_BLOCKS slabs of 256 columns)
+constexpr size_t STATIC_SCRATCH_BYTES = 256 + 65536 + 16384 + (size_t)NORM_BLOCKS * 256 * 8;
+static_assert(4 * STATIC_SCRATCH_MAX_K <= NORM_BLOCKS * 256, "the least a layer asks for fits too");
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 // device address of `scratch` on the current device (each GPU holds its own copy at its own address)
@@ -519,7 +1097,7 @@ extern "C" qarvd_status qarvd_quantize_weight_static(const float *W, int32_t N, 
                                                      int32_t *K_o_host, float *v_out, void *stream)
 {
     if (K > STATIC_SCRATCH_MAX_K) return QARVD_ERR_WORKSPACE;      // the fixed array holds the workspace of K <= 16384
-    if (K > 0 && carve(nullptr, K, nullptr) > STATIC_SCRATCH_BYTES) return QARVD_ERR_WORKSPACE;
+    if (N > 0 && K > 0 && carve(nullptr, N, K, nullptr) > STATIC_SCRATCH_BYTES) return QARVD_ERR_WORKSPACE;
     void *ws = nullptr;
     if (qarvd_status st = static_scratch_ptr(&ws); st != QARVD_OK) return st;
     // Every kernel of the step writes the part of the workspace it owns before anything reads it (the existing
@@ -531,7 +1109,7 @@ extern "C" qarvd_status qarvd_quantize_weight_static(const float *W, int32_t N, 
 extern "C" size_t qarvd_quantize_weight_w4_workspace(int32_t N, int32_t K)
 {
     if (N <= 0 || K <= 0 || K > QARVD_MAX_K) return 0;
-    return carve(nullptr, K, nullptr) + (size_t)N * qarvd_packed_k(K, -1);
+    return carve(nullptr, N, K, nullptr);
 }
 
 extern "C" qarvd_status qarvd_quantize_weight_w4(const float *W, int32_t N, int32_t K, int64_t ldw,
