@@ -91,20 +91,22 @@ __device__ __forceinline__ int quantize_sym(float x, float s, float qmax)
     return (int)r;
 }
 
-// Same result as quantize_i8, without the ~10-instruction IEEE division on the common path.
-//   y' = x * rcp(s) is within |x/s| * 2^-22 <= 127 * 2^-22 < 4e-5 of the true quotient (|x/s| <= 127
-//   under an absmax scale; larger quotients only occur with a static scale and are far from any
-//   boundary that matters or land in the slow path), and the oracle's RN(x/s) is within 8e-6 of it,
-//   so rint(y') == rint(RN(x/s)) whenever y' is at least 1e-4 away from a half-integer.  The few
-//   lanes closer than that (about 2 in 10^4) redo the exact division.  `r` must be rcp(s), s > 0.
-__device__ __forceinline__ int quantize_i8_fast(float x, float s, float r)
-{
-    const float y = x * r;
-    float q = rintf(y);
-    if (!(fabsf(y - q) < 0.4999f)) q = rintf(x / s);   // also taken for NaN / inf intermediates
-    q = fminf(fmaxf(q, -127.0f), 127.0f);
-    return (int)q;
-}
+// ExactQuotients x / s for one scale.  RN(1 / s) times x, corrected twice with fused multiply-adds, IS the correctly rounded
+// quotient for 1e-30 <= s <= 1e30 and |x| <= 127.5 s (Markstein's theorem; the argument stands at quantize4_static in
+// gemm_dma_common.h): five instructions and no branch, where a product with a redo of the IEEE division near rounding
+// boundaries takes as many and 500 bytes of code per value (8960 x 1536: 21 -> 19 us).  s == 0 (a block of zeros, or none): every quotient is 0.
+struct ExactQuotient {
+    float s, rs, bound;      // bound = RN(qmax s): beyond it the code is +-qmax whatever the quotient
+    __device__ __forceinline__ ExactQuotient(float scale, float qmax) : s(scale), rs(scale == 0.0f ? 0.0f : 1.0f / scale), bound(qmax * scale) {}
+    __device__ __forceinline__ bool exact() const { return s == 0.0f || (s >= 1e-30f && s <= 1e30f); }
+    __device__ __forceinline__ float clamped(float x) const        // quotient of x clamped to [-bound, bound]
+    {
+        x = __builtin_amdgcn_fmed3f(x, -bound, bound);
+        const float q0 = x * rs;
+        const float q1 = fmaf(fmaf(-q0, s, x), rs, q0);
+        return fmaf(fmaf(-q1, s, x), rs, q1);
+    }
+};
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
@@ -114,13 +116,6 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
     uint32_t u = __float_as_uint(f);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return u >> 16;
-}
-
-__device__ __forceinline__ float wave_max(float v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
 }
 
 // Reductions over a wave by data-parallel-primitive moves: the values pass between lanes inside vector-ALU

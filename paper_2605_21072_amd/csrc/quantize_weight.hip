@@ -433,22 +433,6 @@ struct PackedRow {
     }
 };
 
-// Quotients x / s for one scale.  RN(1 / s) times x, corrected twice with fused multiply-adds, IS the correctly rounded
-// quotient for 1e-30 <= s <= 1e30 and |x| <= 127.5 s (Markstein's theorem; the argument stands at quantize4_static in
-// gemm_dma_common.h): five instructions and no branch, where a product with a redo of the IEEE division near rounding
-// boundaries takes as many and 500 bytes of code per value (8960 x 1536: 21 -> 19 us).  s == 0 (a block of zeros, or none): every quotient is 0.
-struct Quotient {
-    float s, rs, bound;      // bound = RN(qmax s): beyond it the code is +-qmax whatever the quotient
-    __device__ __forceinline__ Quotient(float scale, float qmax) : s(scale), rs(scale == 0.0f ? 0.0f : 1.0f / scale), bound(qmax * scale) {}
-    __device__ __forceinline__ bool exact() const { return s == 0.0f || (s >= 1e-30f && s <= 1e30f); }
-    __device__ __forceinline__ float operator()(float x) const
-    {
-        const float q0 = x * rs;
-        const float q1 = fmaf(fmaf(-q0, s, x), rs, q0);
-        return fmaf(fmaf(-q1, s, x), rs, q1);
-    }
-};
-
 struct RowsArgs {
     const float *W;
     int64_t ldw;
@@ -472,7 +456,7 @@ struct RowsArgs {
 // the odd one after it, four lanes up, make one packed dword.
 template <int CH, int NT>
 __device__ __forceinline__ void store_codes(const RowsArgs &a, const PackedRow<CH, NT> &pr, const float (&x)[CH][4], int row, int lane,
-                                            const Quotient &qo, const Quotient &qn)
+                                            const ExactQuotient &qo, const ExactQuotient &qn)
 {
     constexpr float MAGIC = 12582912.0f;       // 1.5 * 2^23: the sum rounds half-to-even, the code is its low byte
     uint8_t *out = a.out + (size_t)row * a.ldo;
@@ -484,18 +468,18 @@ __device__ __forceinline__ void store_codes(const RowsArgs &a, const PackedRow<C
         if (pr.base[c] >= pr.n_off && pr.base[c] + 256 <= pr.end_n) {        // normal channels only
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                b[e] = __float_as_uint(qn(__builtin_amdgcn_fmed3f(x[c][e], -qn.bound, qn.bound)) + MAGIC);
+                b[e] = __float_as_uint(qn.clamped(x[c][e]) + MAGIC);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int p = pr.base[c] + 64 * e + lane;
                 const bool is_o = p < pr.n_off;
-                Quotient q = qn;
+                ExactQuotient q = qn;
                 q.s = is_o ? qo.s : qn.s;
                 q.rs = is_o ? qo.rs : qn.rs;
                 q.bound = is_o ? qo.bound : qn.bound;
                 const float f = p < (is_o ? pr.end_o : pr.end_n) ? x[c][e] : 0.0f;      // pads
-                b[e] = __float_as_uint(q(__builtin_amdgcn_fmed3f(f, -q.bound, q.bound)) + MAGIC);
+                b[e] = __float_as_uint(q.clamped(f) + MAGIC);
             }
         }
         uint32_t w = __builtin_amdgcn_perm(__builtin_amdgcn_perm(b[3], b[2], 0x0c0c0400u), __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u),
@@ -592,7 +576,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void weight_rows_kernel(RowsAr
             a.s_outlier[row] = so;
             a.s_normal[row] = sn;
         }
-        const Quotient qo(so, a.qmax), qn(sn, a.qmax);
+        const ExactQuotient qo(so, a.qmax), qn(sn, a.qmax);
         if (qo.exact() && qn.exact()) store_codes<CH, NT>(a, pr, x, row, lane, qo, qn);
         else store_codes_far<NT>(a, row, NT == 64 ? lane : (int)threadIdx.x, K_o, so, sn);
 #pragma unroll
@@ -790,13 +774,13 @@ __global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(Ro
         // ---- squared errors ----
 #pragma unroll 1
         for (int blk = 0; blk < 2; ++blk) {
-            const Quotient qt[3] = {Quotient(scale[blk][0], a.qmax), Quotient(scale[blk][1], a.qmax), Quotient(scale[blk][2], a.qmax)};
+            const ExactQuotient qt[3] = {ExactQuotient(scale[blk][0], a.qmax), ExactQuotient(scale[blk][1], a.qmax), ExactQuotient(scale[blk][2], a.qmax)};
             double sse[3] = {0.0, 0.0, 0.0};
             for_each(blk, [&](float f0, bool real) {
                 const float f = real ? f0 : 0.0f;
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    const float q = rintf(qt[c](__builtin_amdgcn_fmed3f(f, -qt[c].bound, qt[c].bound)));
+                    const float q = rintf(qt[c].clamped(f));
                     const double e = (double)fmaf(-qt[c].s, q, f);
                     sse[c] = fma(e, e, sse[c]);
                 }
@@ -850,7 +834,7 @@ __global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(Ro
             (blk ? a.s_normal : a.s_outlier)[row] = best;
         }
         __syncthreads();
-        const Quotient qo(chosen[0], a.qmax), qn(chosen[1], a.qmax);
+        const ExactQuotient qo(chosen[0], a.qmax), qn(chosen[1], a.qmax);
         if (qo.exact() && qn.exact()) store_codes<CH, NT>(a, pr, x, row, lane, qo, qn);
         else store_codes_far<NT>(a, row, t, K_o, chosen[0], chosen[1]);
     }

@@ -1,0 +1,73 @@
+"""Activation quantization where its kernels change shape: channel counts on both sides of every row width, with and
+without a permutation, pads inside the packed row, element-wise loads, permutations in no order, more rows than fit at once,
+and rows whose scale the exact quotient does not cover.  Codes and scales against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+q = pytest.importorskip("paper_2605_21072_amd")
+from gpu_util import dev, logical  # noqa: E402
+
+
+def make(M, K, seed, dtype):
+    rng = np.random.default_rng(seed)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    X[:, rng.integers(0, K, 3)] *= np.float32(15)
+    Xd = dev(X).to(dtype)
+    return Xd.float().cpu().numpy(), Xd, rng
+
+
+def check(X, Xd, perm, K_o):
+    K = X.shape[1]
+    pd = None if perm is None else dev(perm)
+    ref, sx = oracle.quant_act(X, perm)
+    Xq, s = q.quant_act(Xd, pd, K_o)
+    assert np.array_equal(s.cpu().numpy().view(np.uint32), sx.view(np.uint32))
+    assert np.array_equal(logical(Xq, K, K_o), ref)
+    scale = np.float32(np.abs(X).max() * 0.4 / 127)                     # clips the largest values
+    if scale > 0:
+        got = q.quant_act_static(Xd, pd, K_o, float(scale))
+        assert np.array_equal(logical(got, K, K_o), oracle.quant_act_static(X, scale, perm))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", [1, 4, 130, 1532, 1536, 1537, 1540, 3072, 3073, 3076, 6144, 6148, 10240, 10244, 16384, 16388])
+def test_row_widths(K, dtype):
+    X, Xd, rng = make(9, K, K, dtype)
+    check(X, Xd, None, 0)
+    for K_o in sorted({min(K, 32), min(K, 7), min(K, K // 2)}):
+        sel = np.sort(rng.choice(K, K_o, replace=False))
+        perm = np.concatenate([sel, np.setdiff1d(np.arange(K), sel)]).astype(np.int32)
+        check(X, Xd, perm, K_o)
+    check(X, Xd, rng.permutation(K).astype(np.int32), min(K, 32))
+
+
+@pytest.mark.parametrize("M,K", [(9001, 1536), (9001, 200), (3100, 2048), (1700, 8960)])
+def test_more_rows_than_fit_at_once(M, K):
+    X, Xd, rng = make(M, K, M + K, torch.float32)
+    check(X, Xd, rng.permutation(K).astype(np.int32), 32)
+    check(X, Xd, None, 0)
+
+
+def test_unaligned_rows_and_odd_strides():
+    X, _, rng = make(33, 1001, 5, torch.float32)
+    big = torch.zeros((33, 1005), device="cuda")
+    big[:, 3:1004] = dev(X)
+    check(X, big[:, 3:1004], rng.permutation(1001).astype(np.int32), 31)
+
+
+@pytest.mark.parametrize("K", [1536, 8960])
+def test_scales_outside_the_exact_quotients_range(K):
+    X, _, rng = make(12, K, 7, torch.float32)
+    X = (X.astype(np.float64) * np.array([1, 1e-29, 1e-36, 1e-42, 1e33, 1] * 2)[:, None]).astype(np.float32)
+    X[5] = 0
+    perm = rng.permutation(K).astype(np.int32)
+    for p, K_o in ((perm, 64), (None, 0)):
+        ref, sx = oracle.quant_act(X, p)
+        Xq, s = q.quant_act(dev(X), None if p is None else dev(p), K_o)
+        assert np.array_equal(s.cpu().numpy().view(np.uint32), sx.view(np.uint32))
+        assert np.array_equal(logical(Xq, K, K_o), ref)
