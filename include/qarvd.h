@@ -239,6 +239,22 @@ qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, const float *s
 int32_t qarvd_w4_gemm_num_variants(void);
 
 /*
+ * The online pair in one call: qarvd_quant_act of X into the workspace, then the GEMM of that and the layer's weights
+ * (w_bits 8: qarvd_w8a8_dual_gemm, 4: qarvd_w4a8_dual_gemm) into Y.  Same kernels, same results; a caller saves the
+ * second crossing into the library and the two intermediate buffers.
+ *   perm       in  i32 [K] or NULL (then K_o must be 0); ignored when K_o is 0
+ *   Wq         in  packed INT8 [N, ldwq] or INT4 [N, ldwq bytes] for (K, K_o)
+ *   workspace  device, >= qarvd_linear_workspace(M, K, K_o) bytes, 128-byte aligned; free for reuse once
+ *              the work queued on `stream` has run
+ * Fully asynchronous on `stream`.
+ */
+size_t qarvd_linear_workspace(int32_t M, int32_t K, int32_t K_o);
+qarvd_status qarvd_linear(const void *X, qarvd_dtype xdt, int64_t ldx, const int32_t *perm, int32_t w_bits, const void *Wq,
+                          int64_t ldwq, const float *s_normal, const float *s_outlier, const float *bias, int32_t M,
+                          int32_t N, int32_t K, int32_t K_o, void *Y, qarvd_dtype ydt, int64_t ldy, void *workspace,
+                          size_t workspace_bytes, void *stream);
+
+/*
  * ONLINE GEMM + de-quantization for CHAINED layers (Sec. 4.1: activations are quantized per tensor
  * with static, calibrated scales, so a layer can hand the next one INT8 codes directly; Eq.
  * (quantization) applied to this layer's output with the next layer's scale):

@@ -279,3 +279,30 @@ extern "C" qarvd_status qarvd_w8a8_dual_gemm_q8(const int8_t *Xq, int64_t ldxq, 
     const Q8Variant &v = kQ8Variants[variant - 1];
     return (g.n_off > 0 ? v.dual : v.single)(g, reinterpret_cast<hipStream_t>(stream));
 }
+
+// ---- the online pair in one call ------------------------------------------------------------------------------
+// Workspace: Xq [M, packed_ld] | s_x [M]; packed_ld is a multiple of 128, so both are aligned.
+extern "C" size_t qarvd_linear_workspace(int32_t M, int32_t K, int32_t K_o)
+{
+    const int32_t ld = K_o < 0 ? 0 : qarvd_packed_ld(K, K_o);
+    return M > 0 && ld > 0 ? (size_t)M * (size_t)ld + (size_t)M * sizeof(float) : 0;
+}
+
+extern "C" qarvd_status qarvd_linear(const void *X, qarvd_dtype xdt, int64_t ldx, const int32_t *perm, int32_t w_bits,
+                                     const void *Wq, int64_t ldwq, const float *s_normal, const float *s_outlier,
+                                     const float *bias, int32_t M, int32_t N, int32_t K, int32_t K_o, void *Y,
+                                     qarvd_dtype ydt, int64_t ldy, void *workspace, size_t workspace_bytes, void *stream)
+{
+    const size_t need = qarvd_linear_workspace(M, K, K_o);
+    if (need == 0 || (w_bits != 8 && w_bits != 4)) return QARVD_ERR_INVALID_ARG;
+    if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 127u) || workspace_bytes < need) return QARVD_ERR_WORKSPACE;
+    const int64_t ld = qarvd_packed_ld(K, K_o);
+    int8_t *const Xq = reinterpret_cast<int8_t *>(workspace);
+    float *const s_x = reinterpret_cast<float *>(Xq + (size_t)M * (size_t)ld);
+    if (qarvd_status st = qarvd_quant_act(X, xdt, M, K, ldx, K_o > 0 ? perm : nullptr, K_o, Xq, ld, s_x, stream); st != QARVD_OK) return st;
+    if (w_bits == 4)
+        return qarvd_w4a8_dual_gemm(Xq, ld, s_x, reinterpret_cast<const uint8_t *>(Wq), ldwq, s_normal, s_outlier, bias, M, N, K, K_o,
+                                    Y, ydt, ldy, nullptr, nullptr, 0, stream);
+    return qarvd_w8a8_dual_gemm_variant(0, Xq, ld, s_x, reinterpret_cast<const int8_t *>(Wq), ldwq, s_normal, s_outlier, bias, M, N, K,
+                                        K_o, Y, ydt, ldy, nullptr, nullptr, stream);
+}
