@@ -6,68 +6,81 @@ using namespace qarvd_gemm;
 namespace {
 
 const Variant kVariants[] = {
-    // name, BM, BN, widest outlier block (packed bytes), needs vector output, launcher
-    {"staged 256x128 dual", 256, 128, 1 << 30, false, launch_staged<256, 128, 2, 2, true>},
-    {"staged 128x128 dual", 128, 128, 1 << 30, false, launch_staged<128, 128, 2, 2, true>},
-    {"staged 256x128 single", 256, 128, 0, false, launch_staged<256, 128, 2, 2, false>},
-    {"staged 128x128 single", 128, 128, 0, false, launch_staged<128, 128, 2, 2, false>},
-    {"lds-direct 256x128 (4 waves, 3 stages) dual", 256, 128, 128, true, launch_dma<256, 128, 2, 2, 3, true>},
-    {"lds-direct 256x128 (4 waves, 3 stages) single", 256, 128, 0, true, launch_dma<256, 128, 2, 2, 3, false>},
-    {"lds-direct 192x128 (4 waves, 3 stages) dual", 192, 128, 128, true, launch_dma<192, 128, 2, 2, 3, true>},
-    {"lds-direct 192x128 (4 waves, 3 stages) single", 192, 128, 0, true, launch_dma<192, 128, 2, 2, 3, false>},
-    {"lds-direct 128x128 (4 waves, 4 stages) dual", 128, 128, 128, true, launch_dma<128, 128, 2, 2, 4, true>},
-    {"lds-direct 128x128 (4 waves, 4 stages) single", 128, 128, 0, true, launch_dma<128, 128, 2, 2, 4, false>},
-    {"lds-direct 256x256 (8 waves, 4 stages) dual", 256, 256, 128, true, launch_dma<256, 256, 2, 4, 4, true>},
-    {"lds-direct 256x256 (8 waves, 4 stages) single", 256, 256, 0, true, launch_dma<256, 256, 2, 4, 4, false>},
-    {"lds-direct 256x128 (8 waves, 4 stages) dual", 256, 128, 128, true, launch_dma<256, 128, 4, 2, 4, true>},
-    {"lds-direct 256x128 (8 waves, 4 stages) single", 256, 128, 0, true, launch_dma<256, 128, 4, 2, 4, false>},
-    {"lds-direct 128x256 (8 waves, 4 stages) dual", 128, 256, 128, true, launch_dma<128, 256, 2, 4, 4, true>},
-    {"lds-direct 128x256 (8 waves, 4 stages) single", 128, 256, 0, true, launch_dma<128, 256, 2, 4, 4, false>},
-    {"16x16x64 256x224 (8 waves, 4 stages) dual", 256, 224, 128, true, launch_mfma16<256, 224, 4, 2, 4, true>},
-    {"16x16x64 256x224 (8 waves, 4 stages) single", 256, 224, 0, true, launch_mfma16<256, 224, 4, 2, 4, false>},
-    {"lds-direct 64x128 (4 waves, 5 stages) dual", 64, 128, 128, true, launch_dma<64, 128, 2, 2, 5, true>},
-    {"lds-direct 64x128 (4 waves, 5 stages) single", 64, 128, 0, true, launch_dma<64, 128, 2, 2, 5, false>},
-    {"lds-direct 64x64 (4 waves, 6 stages) dual", 64, 64, 128, true, launch_dma<64, 64, 2, 2, 6, true>},
-    {"lds-direct 64x64 (4 waves, 6 stages) single", 64, 64, 0, true, launch_dma<64, 64, 2, 2, 6, false>},
-    {"lds-direct 256x128 (8 waves, 6 stages) dual", 256, 128, 128, true, launch_dma<256, 128, 4, 2, 6, true>},
-    {"lds-direct 256x128 (8 waves, 6 stages) single", 256, 128, 0, true, launch_dma<256, 128, 4, 2, 6, false>},
-    {"lds-direct 256x128 (8 waves, 5 stages) dual", 256, 128, 128, true, launch_dma<256, 128, 4, 2, 5, true>},
-    {"lds-direct 256x128 (8 waves, 5 stages) single", 256, 128, 0, true, launch_dma<256, 128, 4, 2, 5, false>},
-    {"128-byte stages 256x256 (8 waves, 2 stages) dual", 256, 256, 128, true, launch_dma128<256, 256, 2, 4, 2, true>},
-    {"128-byte stages 256x256 (8 waves, 2 stages) single", 256, 256, 0, true, launch_dma128<256, 256, 2, 4, 2, false>},
-    {"128-byte stages 256x128 (8 waves, 3 stages) dual", 256, 128, 128, true, launch_dma128<256, 128, 4, 2, 3, true>},
-    {"128-byte stages 256x128 (8 waves, 3 stages) single", 256, 128, 0, true, launch_dma128<256, 128, 4, 2, 3, false>},
-    {"128-byte stages 128x256 (8 waves, 3 stages) dual", 128, 256, 128, true, launch_dma128<128, 256, 2, 4, 3, true>},
-    {"128-byte stages 128x256 (8 waves, 3 stages) single", 128, 256, 0, true, launch_dma128<128, 256, 2, 4, 3, false>},
+    // name, BM, BN, widest outlier block (packed bytes), needs vector output, operand strides up to 2^22, launcher
+    {"staged 256x128 dual", 256, 128, 1 << 30, false, false, launch_staged<256, 128, 2, 2, true>},
+    {"staged 128x128 dual", 128, 128, 1 << 30, false, false, launch_staged<128, 128, 2, 2, true>},
+    {"staged 256x128 single", 256, 128, 0, false, false, launch_staged<256, 128, 2, 2, false>},
+    {"staged 128x128 single", 128, 128, 0, false, false, launch_staged<128, 128, 2, 2, false>},
+    {"lds-direct 256x128 (4 waves, 3 stages) dual", 256, 128, 128, true, true, launch_dma<256, 128, 2, 2, 3, true>},
+    {"lds-direct 256x128 (4 waves, 3 stages) single", 256, 128, 0, true, true, launch_dma<256, 128, 2, 2, 3, false>},
+    {"lds-direct 192x128 (4 waves, 3 stages) dual", 192, 128, 128, true, true, launch_dma<192, 128, 2, 2, 3, true>},
+    {"lds-direct 192x128 (4 waves, 3 stages) single", 192, 128, 0, true, true, launch_dma<192, 128, 2, 2, 3, false>},
+    {"lds-direct 128x128 (4 waves, 4 stages) dual", 128, 128, 128, true, true, launch_dma<128, 128, 2, 2, 4, true>},
+    {"lds-direct 128x128 (4 waves, 4 stages) single", 128, 128, 0, true, true, launch_dma<128, 128, 2, 2, 4, false>},
+    {"lds-direct 256x256 (8 waves, 4 stages) dual", 256, 256, 128, true, true, launch_dma<256, 256, 2, 4, 4, true>},
+    {"lds-direct 256x256 (8 waves, 4 stages) single", 256, 256, 0, true, true, launch_dma<256, 256, 2, 4, 4, false>},
+    {"lds-direct 256x128 (8 waves, 4 stages) dual", 256, 128, 128, true, true, launch_dma<256, 128, 4, 2, 4, true>},
+    {"lds-direct 256x128 (8 waves, 4 stages) single", 256, 128, 0, true, true, launch_dma<256, 128, 4, 2, 4, false>},
+    {"lds-direct 128x256 (8 waves, 4 stages) dual", 128, 256, 128, true, true, launch_dma<128, 256, 2, 4, 4, true>},
+    {"lds-direct 128x256 (8 waves, 4 stages) single", 128, 256, 0, true, true, launch_dma<128, 256, 2, 4, 4, false>},
+    {"16x16x64 256x224 (8 waves, 4 stages) dual", 256, 224, 128, true, true, launch_mfma16<256, 224, 4, 2, 4, true>},
+    {"16x16x64 256x224 (8 waves, 4 stages) single", 256, 224, 0, true, true, launch_mfma16<256, 224, 4, 2, 4, false>},
+    {"lds-direct 64x128 (4 waves, 5 stages) dual", 64, 128, 128, true, true, launch_dma<64, 128, 2, 2, 5, true>},
+    {"lds-direct 64x128 (4 waves, 5 stages) single", 64, 128, 0, true, true, launch_dma<64, 128, 2, 2, 5, false>},
+    {"lds-direct 64x64 (4 waves, 6 stages) dual", 64, 64, 128, true, true, launch_dma<64, 64, 2, 2, 6, true>},
+    {"lds-direct 64x64 (4 waves, 6 stages) single", 64, 64, 0, true, true, launch_dma<64, 64, 2, 2, 6, false>},
+    {"lds-direct 256x128 (8 waves, 6 stages) dual", 256, 128, 128, true, true, launch_dma<256, 128, 4, 2, 6, true>},
+    {"lds-direct 256x128 (8 waves, 6 stages) single", 256, 128, 0, true, true, launch_dma<256, 128, 4, 2, 6, false>},
+    {"lds-direct 256x128 (8 waves, 5 stages) dual", 256, 128, 128, true, true, launch_dma<256, 128, 4, 2, 5, true>},
+    {"lds-direct 256x128 (8 waves, 5 stages) single", 256, 128, 0, true, true, launch_dma<256, 128, 4, 2, 5, false>},
+    {"128-byte stages 256x256 (8 waves, 2 stages) dual", 256, 256, 128, true, true, launch_dma128<256, 256, 2, 4, 2, true>},
+    {"128-byte stages 256x256 (8 waves, 2 stages) single", 256, 256, 0, true, true, launch_dma128<256, 256, 2, 4, 2, false>},
+    {"128-byte stages 256x128 (8 waves, 3 stages) dual", 256, 128, 128, true, true, launch_dma128<256, 128, 4, 2, 3, true>},
+    {"128-byte stages 256x128 (8 waves, 3 stages) single", 256, 128, 0, true, true, launch_dma128<256, 128, 4, 2, 3, false>},
+    {"128-byte stages 128x256 (8 waves, 3 stages) dual", 128, 256, 128, true, true, launch_dma128<128, 256, 2, 4, 3, true>},
+    {"128-byte stages 128x256 (8 waves, 3 stages) single", 128, 256, 0, true, true, launch_dma128<128, 256, 2, 4, 3, false>},
+    {"128-byte stages 128x128 (8 waves, 4 stages) dual", 128, 128, 128, true, true, launch_dma128<128, 128, 2, 4, 4, true>},
+    {"128-byte stages 128x128 (8 waves, 4 stages) single", 128, 128, 0, true, true, launch_dma128<128, 128, 2, 4, 4, false>},
+    {"128-byte stages 64x64 (4 waves, 4 stages) dual", 64, 64, 128, true, true, launch_dma128<64, 64, 2, 2, 4, true>},
+    {"128-byte stages 64x64 (4 waves, 4 stages) single", 64, 64, 0, true, true, launch_dma128<64, 64, 2, 2, 4, false>},
+    {"128-byte stages 128x128 (8 waves, 4 stages) any width", 128, 128, 1 << 30, false, true, launch_dma128<128, 128, 2, 4, 4, true, true>},
+    {"128-byte stages 64x64 (4 waves, 4 stages) any width", 64, 64, 1 << 30, false, true, launch_dma128<64, 64, 2, 2, 4, true, true>},
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
+
+bool short_rows_ok(const GemmArgs &g) { return g.ldxq <= (1 << 22) && g.ldwq <= (1 << 22); }
 
 bool vector_out_ok(const GemmArgs &g, qarvd_dtype ydt)
 {
     const size_t esz = ydt == QARVD_F32 ? 4 : 2;
     // the LDS-direct kernels also address a tile's rows with 32-bit byte offsets: 256 rows x stride x 4 < 2^31
     return (g.N % 8) == 0 && qarvd_aligned16(g.Y) && ((g.ldy * esz) % 16) == 0 && qarvd_aligned16(g.s_n) &&
-           qarvd_aligned16(g.s_o) && qarvd_aligned16(g.bias) && g.ldxq <= (1 << 22) && g.ldwq <= (1 << 22) && g.ldy <= (1 << 20);
+           qarvd_aligned16(g.s_o) && qarvd_aligned16(g.bias) && short_rows_ok(g) && g.ldy <= (1 << 20);
 }
 
 bool variant_fits(const Variant &v, const GemmArgs &g, qarvd_dtype ydt)
 {
     if (g.n_off > v.max_n_off) return false;
     if (v.needs_vector_out && !vector_out_ok(g, ydt)) return false;
+    if (v.short_rows && !short_rows_ok(g)) return false;
     return true;
 }
 
 // Heuristic: a three-constant cost model per candidate, fitted to back-to-back timings on MI355X over the
-// DiT shapes (M = 256..4680, N and K in {1536, 4608, 5120, 8960, 13824}, operands at the padded strides of
-// qarvd_packed_ld):
+// DiT shapes (M = 64..4680, N and K in {1536, 4608, 5120, 8960, 13824}, operands at the padded strides of
+// qarvd_packed_ld) and some ragged ones:
 //     time ~ c + ceil(tiles / CUs) * (a + b * T),     T = packed K / 64          (constants in microseconds)
 // c is launch plus the first tile's lead-in, a a tile's epilogue and hand-over, b one 64-byte K step of a tile
 // that has its CU to itself (two four-wave workgroups sharing a CU each run at half speed, which the ceil over
-// the CUs already accounts for).  The three eight-wave tiles run on 128-byte-deep stages (gemm_dma128.hip):
+// the CUs already accounts for).  All but two of the tiles run on 128-byte-deep stages (gemm_dma128.hip):
 // 256x256 has the cheapest K step per MAC and wins when N is wide; the half tiles fill the chip when N = 1536
-// (4680 x 8960 -> 1536: 61 us against 81 us for 256x256) and on M of a few hundred rows with N = 8960.  The
-// four-wave tiles on 64-byte stages serve short M: 128x128 for M around 1500, 64x128 / 64x64 when even those
-// would leave most CUs without a tile (M = 520, N = 1536, K = 8960: 24 us instead of 45 us).
+// (4680 x 8960 -> 1536: 60 us against 78 us for 256x256) and on M of a few hundred rows with N = 8960; 128x128 on eight
+// waves when those leave CUs empty over a long K (1560 x 8960 -> 1536: 31 us, 45 for the four-wave 128x128 tile
+// on 64-byte stages that this one replaces); 64x64 when even those would leave most without a tile (520 x 8960 -> 1536:
+// 20.5 us, 24.2 on 64-byte stages).  Up to K of about 1600 the 64-byte-stage 64x64 tile is the faster
+// one (256 x 1536 -> 1536: 6.5 against 6.6 us, 16 x 256 -> 256: 3.8 against 4.2).
+// What needs the general kernels (outlier block over 128 bytes, N % 8 != 0, unaligned outputs) picks by the same model
+// from the two tiles built for it; operand strides beyond 2^22 go to the register-staged kernel.
 int device_cus()
 {
     int cus = 0;
@@ -78,19 +91,14 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
 {
     const bool dual = g.n_off > 0;
     const int cus = device_cus();      // rounds are counted over the CUs of the device the call runs on
-    if (g.n_off <= 128 && vector_out_ok(g, ydt)) {
-        struct Cand { int variant, bm, bn; double c, a, b; };
-        const Cand cand[6] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
-                              {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
-                              {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
-                              {dual ? 9 : 10, 128, 128, 2.0, 1.5, 0.309},
-                              {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
-                              {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
-        const double T = g.kp / 64;
+    struct Cand { int variant, bm, bn; double c, a, b; };
+    const double T = g.kp / 64;
+    const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    auto cheapest = [&](const Cand *cand, int n) {
         int best = cand[0].variant;
         double best_cost = 1e300;
-        const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
-        for (const Cand &c : cand) {
+        for (int i = 0; i < n; ++i) {
+            const Cand &c = cand[i];
             if (c.bm == 64 && tiles128 > cus) continue;     // the small tiles only pay while 128x128 tiles leave CUs empty
             const long tiles = (long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
             const double cost = c.c + (double)((tiles + cus - 1) / cus) * (c.a + c.b * T);
@@ -100,6 +108,20 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
             }
         }
         return best;
+    };
+    if (g.n_off <= 128 && vector_out_ok(g, ydt)) {
+        const Cand cand[7] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
+                              {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
+                              {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
+                              {dual ? 33 : 34, 128, 128, 1.6, 3.2, 0.200},
+                              {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
+                              {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120},
+                              {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
+        return cheapest(cand, 7);
+    }
+    if (short_rows_ok(g)) {
+        const Cand cand[2] = {{37, 128, 128, 1.8, 3.6, 0.200}, {38, 64, 64, 3.0, 1.0, 0.125}};
+        return cheapest(cand, 2);
     }
     const long tiles_big = (long)((g.M + 255) / 256) * ((g.N + 127) / 128);
     if (dual) return tiles_big >= cus ? 1 : 2;
@@ -141,7 +163,8 @@ extern "C" qarvd_status qarvd_w8a8_dual_gemm_variant(int32_t variant, const int8
     g.Xq = Xq; g.Wq = Wq; g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
     g.Y = Y; g.dbg_n = dbg_acc_normal; g.dbg_o = dbg_acc_outlier;
     g.ldxq = ldxq; g.ldwq = ldwq; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
-    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.store_wt = 0;
+    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.vec_out = 1; g.store_wt = 0;
+    g.vec_out = vector_out_ok(g, ydt);
     if (variant == 0) variant = pick_variant(g, ydt);
     const Variant &v = kVariants[variant - 1];
     if (!variant_fits(v, g, ydt)) return QARVD_ERR_UNSUPPORTED;
@@ -200,7 +223,7 @@ extern "C" qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, con
     g.Xq = Xq; g.Wq = reinterpret_cast<const int8_t *>(Wq4); g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
     g.Y = Y; g.dbg_n = dbg_acc_normal; g.dbg_o = dbg_acc_outlier;
     g.ldxq = ldxq; g.ldwq = ldwq4; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
-    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.store_wt = 0;
+    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.vec_out = 1; g.store_wt = 0;
     const bool fast_ok = g.n_off <= 128 && vector_out_ok(g, ydt);
     if (!fast_ok) {
         if (variant == 1 || variant == 2) return QARVD_ERR_UNSUPPORTED;     // an LDS-direct tile asked for by name
@@ -263,7 +286,7 @@ extern "C" qarvd_status qarvd_w8a8_dual_gemm_q8(const int8_t *Xq, int64_t ldxq, 
     g.Xq = Xq; g.Wq = Wq; g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
     g.Y = Y8; g.dbg_n = nullptr; g.dbg_o = nullptr;
     g.ldxq = ldxq; g.ldwq = ldwq; g.ldy = ldy8; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
-    g.tiles_m = g.tiles_n = 0; g.act = (int32_t)act; g.out_scale = out_scale; g.store_wt = 0;
+    g.tiles_m = g.tiles_n = 0; g.act = (int32_t)act; g.out_scale = out_scale; g.vec_out = 1; g.store_wt = 0;
     if (g.n_off > 128) return QARVD_ERR_UNSUPPORTED;
     if (variant == 0) {
         const double T = g.kp / 64;

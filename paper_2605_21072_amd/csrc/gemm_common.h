@@ -41,6 +41,7 @@ struct GemmArgs {
     // next layer's static activation scale; unused for fp32 / bf16 outputs
     int32_t act;
     float out_scale;
+    int32_t vec_out;   // every row of Y is whole, 16-byte aligned chunks; set by the launchers that take other outputs too
     int32_t store_wt;  // output stores write through the L2 (small outputs); set by the launchers
 };
 
@@ -81,6 +82,7 @@ struct Variant {
     int BM, BN;
     int max_n_off;
     bool needs_vector_out;   // needs N % 8 == 0 and 16-byte aligned Y rows, scales and bias
+    bool short_rows;         // operand strides up to 2^22 (32-bit byte offsets inside a tile)
     qarvd_status (*launch)(const GemmArgs &, qarvd_dtype, hipStream_t);
 };
 
@@ -93,7 +95,8 @@ template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>   // INT8 outpu
 qarvd_status launch_dma_q8(const GemmArgs &g, hipStream_t st);
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
 qarvd_status launch_dma128_q8(const GemmArgs &g, hipStream_t st);
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>   // 128-byte-deep K stages (gemm_dma128.hip)
+// 128-byte-deep K stages (gemm_dma128.hip); GEN: two accumulator sets, any outlier width, any N and output alignment
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN = false>
 qarvd_status launch_dma128(const GemmArgs &g, qarvd_dtype ydt, hipStream_t st);
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
 qarvd_status launch_mfma16(const GemmArgs &g, qarvd_dtype ydt, hipStream_t st);

@@ -16,6 +16,15 @@
 //     in use and a load has NSTAGE - 1 iterations to land; 256 x 256 tiles run with two 64 KB stages;
 //   * where the LDS has room (256 x 256) the output patches get their own 16 KB behind the stages, so a whole
 //     stage is free for the next tile's first K tile during the epilogue; otherwise they sit in a free stage.
+//
+// GEN = true is the general form: an outlier block of any width, any N, any output alignment.  Tiles of at most 64
+// accumulator registers a wave have room for a second set, so the K loop runs in natural order and the sums move to
+// the outlier set where the range ends; nothing is kept in LDS or multiplied again.  Outputs that are not whole
+// 16-byte chunks leave through unaligned 16-byte stores, the last partial chunk of a row element by element.
+// Against the register-staged kernel that took these shapes before: 2251 x 2360 x 2252, 150 outliers, fp32 out
+// 64.1 -> 25.7 us; 4680 x 5120 x 13825, 200 outliers 1213 -> 369; 20 x 13824 x 700 126 -> 29; 1001 x 1003 x 1005
+// 21.1 -> 6.6.  256 x 128 tiles (two full sets leave too few registers: 60 spilled) were 27 us on the first
+// and 352 on the second and are not built.
 #include <algorithm>
 #include <type_traits>
 
@@ -59,15 +68,19 @@ struct Geo2 {
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "row groups of eight must divide over the waves");
     static_assert(NW % 2 == 0, "the load swizzle takes bit 3 of a row from the wave number");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is TM x TN blocks of 32 x 32");
-    static_assert(TM * TN * 16 <= 128, "two waves per SIMD: at most 128 accumulator registers");
+    static constexpr int WG_PER_CU = NW >= 8 || 2 * LDS_BYTES > 160 * 1024 ? 1 : 8 / NW;     // bounded by LDS, two waves per SIMD
+    static constexpr int WAVES_PER_SIMD = WG_PER_CU * NW >= 8 ? 2 : 1;
+    static_assert(TM * TN * 16 <= 256 / WAVES_PER_SIMD, "accumulators: half of the registers a wave can have");
     static_assert(PATCHES <= STG, "the output patches fit into one stage");
     static_assert(PATCH_EXTRA ? NSTAGE >= 2 : NSTAGE >= 3, "a head tile, the patches and one stage for the next tile");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
     static_assert((NSTAGE - 1) * NLOAD < 64, "vmcnt is a 6-bit counter");
 };
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT>
-__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g)
+typedef v4i v4i_unaligned __attribute__((aligned(2)));   // 16 bytes at an address that is aligned to an output element only
+
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN>
+__global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_PER_SIMD)) void gemm_dma128_kernel(GemmArgs g)
 {
     using G = Geo2<BM, BN, WM, WN, NSTAGE>;
     constexpr int TM = G::TM, TN = G::TN, NA = G::NA, NB = G::NB, NW = G::NW, STG = G::STG, NL = G::NLOAD;
@@ -156,6 +169,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
     for (int ks = 0; ks < KS2; ++ks) coff[ks] = (((2 * ks) | fhalf) ^ fsw) << 4;
 
     v16i acc[TM][TN];
+    v16i acc_o[GEN ? TM : 1][GEN ? TN : 1];     // (GEN) the outlier sum, moved here when the K loop passes its end
+    static_assert(!GEN || TM * TN <= 4, "two accumulator sets");
     v4i xf[2][TM], wf[2][TN];   // fragments of k-steps of even / odd number
     auto load_frags = [&](const unsigned char *sb, int ks) {
 #pragma unroll
@@ -223,7 +238,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
     // order H, .., T-1, 0.  Iteration `it` reads stage (base + it) % NSTAGE and, once read, refills it.
     const int T = g.kp / BK2;
     const int o_steps = DUAL ? g.n_off / 32 : 0;      // 32-byte k-steps of the outlier range (<= 4)
-    const int H = o_steps > 0 ? 1 : 0;
+    const int H = !GEN && o_steps > 0 ? 1 : 0;
     const int Tn = T - H;
     auto seq = [&](int it) { return it < Tn ? it + H : it - Tn; };
     const int NPRO = min(NSTAGE, T);                  // stages filled before a tile's K loop starts
@@ -265,6 +280,79 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
     //                read F0(it+1), refill this stage with K tile it+NSTAGE | MFMA F3
     // Before the barrier a wave waits for its own loads of stage it+1 and for its own LDS reads (the last
     // fragments of this stage), so after the barrier stage it+1 is complete and stage `it` is dead.
+    if constexpr (GEN) {
+        // Natural K order.  The tiles up to the one in which the outlier range ends go through an unscheduled loop; at its
+        // end the sums so far become the outlier accumulators and the normal ones start from zero.  The rest runs
+        // through the scheduled iteration of the kernel above with nothing in it that knows of the split (a
+        // test between the k-steps of one loop for all cost 40 % of the loop's rate).
+        clear_acc();
+        const int o_tile = o_steps >> 2, o_ks = o_steps & 3;
+        auto split = [&]() {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc_o[i][j] = acc[i][j];
+            clear_acc();
+        };
+        int it = 0;
+#pragma unroll 1
+        for (; it <= o_tile && it < T; ++it) {
+            const unsigned char *sb = smem + stage * STG;
+            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
+#pragma unroll
+            for (int ks = 0; ks < KS2; ++ks) {
+                if (ks + 1 < KS2) {
+                    load_frags(sb, ks + 1);
+                } else if (it + 1 < T) {
+                    wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);
+                    wait_lgkmcnt0();
+                    __builtin_amdgcn_s_barrier();
+                }
+                if (it == o_tile && ks == o_ks) split();
+                mma(ks);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (it + 1 < T) load_frags(smem + nstage * STG, 0);
+            if (it + NSTAGE < T) issue(it + NSTAGE, stage);
+            stage = nstage;
+        }
+        auto three_steps = [&](const unsigned char *sb) {
+#pragma unroll
+            for (int ks = 0; ks < KS2 - 1; ++ks) {
+                load_frags(sb, ks + 1);
+                mma(ks);
+                interleave_reads();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        for (; it < T - NSTAGE; ++it) {
+            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
+            three_steps(smem + stage * STG);
+            wait_vmcnt<(NSTAGE - 2) * NL>();
+            wait_lgkmcnt0();
+            __builtin_amdgcn_s_barrier();
+            load_frags(smem + nstage * STG, 0);
+            issue(it + NSTAGE, stage);
+            mma(3);
+            interleave_reads_and_loads();
+            __builtin_amdgcn_sched_barrier(0);
+            stage = nstage;
+        }
+#pragma unroll 1
+        for (; it < T; ++it) {
+            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
+            three_steps(smem + stage * STG);
+            if (it + 1 < T) {
+                wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);
+                wait_lgkmcnt0();
+                __builtin_amdgcn_s_barrier();
+                load_frags(smem + nstage * STG, 0);
+            }
+            mma(3);
+            stage = nstage;
+        }
+        if (o_tile >= T) split();        // every k-step belongs to the outlier range
+    } else {
     if (i_lim < TM) {                            // ragged tile: same steps, unneeded row blocks left out
         clear_acc();
 #pragma unroll 1
@@ -400,6 +488,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
         if (3 >= first) mma_r(3);
         stage = nstage;
     }
+    }
     const long long p_t1 = QARVD_PROF ? clock64() : 0;
     wait_lgkmcnt0();                // this wave's scale writes and fragment reads have landed ...
     __builtin_amdgcn_s_barrier();   // ... and everyone is done with every stage but the head tile's
@@ -445,8 +534,25 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
         auto blk_j = [&](int b) { return ((b / TN) & 1) ? TN - 1 - b % TN : b % TN; };
 
         v4i pend[2];
-        int pend_voff = 0, pend_soff = 0;
+        int pend_voff = 0, pend_soff = 0, pend_row = 0, pend_col = 0;
         bool pending = false, stored = false;       // compile-time after unrolling
+        auto store_unaligned = [&]() {              // (GEN) rows that are not whole, 16-byte aligned chunks
+            const int left = n_left - pend_col;     // columns of the matrix from this lane's chunk on
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int ml = wm * G::WTM + pend_row + p * 16 + (lane >> 2);
+                if (m0 + ml >= g.M) continue;
+                OutT *const y = Y + (size_t)(m0 + ml) * g.ldy + (g.N - left);
+                if (left >= EPC) {
+                    *reinterpret_cast<v4i_unaligned *>(y) = pend[p];
+                } else if (left > 0) {              // the last, partial chunk of a row
+                    using bits_t = std::conditional_t<ESZ == 4, uint32_t, uint16_t>;
+#pragma unroll
+                    for (int k = 0; k < EPC - 1; ++k)
+                        if (k < left) reinterpret_cast<bits_t *>(y)[k] = (bits_t)((unsigned)pend[p][k * ESZ / 4] >> (8 * (k * ESZ % 4)));
+                }
+            }
+        };
         auto flush_commit = [&]() {                 // patch (already in registers) -> global
             if (!pending) return;
             if (!stored) {
@@ -463,8 +569,13 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
                 __builtin_amdgcn_sched_barrier(0);
                 stored = true;
             }
+            if constexpr (GEN) {
+                if (!g.vec_out) store_unaligned();
+            }
+            if (!GEN || g.vec_out) {
 #pragma unroll
-            for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * 16 * ldy_b, pend[p], wt);
+                for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * 16 * ldy_b, pend[p], wt);
+            }
             pending = false;
         };
         auto flush_issue = [&](int i, int col0) {   // col0: first column of the pass inside the wave tile
@@ -475,6 +586,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
             }
             pend_voff = col0 + EPC <= n_left ? y_lane : 0x7ffffff0;
             pend_soff = i * 32 * ldy_b + col0 * ESZ;
+            pend_row = i * 32;
+            pend_col = col0;
             pending = true;
         };
         auto flush = [&](int i, int col0) {
@@ -509,7 +622,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
                 bs[q] = *reinterpret_cast<const v4f *>(bs_lds + nt);
             }
         };
-        constexpr bool AO_AHEAD = HASO && sizeof(OutT) <= 2 && !DBG && TM * TN < 8;   // 16 registers: only where they are to spare
+        constexpr bool AO_AHEAD = HASO && !GEN && sizeof(OutT) <= 2 && !DBG && TM * TN < 8;   // 16 registers: only where they are to spare
         v16i ao_next;
         if constexpr (AO_AHEAD) ao_next = head_mma(blk_i(0), blk_j(0));
 #pragma unroll
@@ -520,6 +633,8 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
             if constexpr (AO_AHEAD) {
                 ao = ao_next;
                 if (b + 1 < NBLK) ao_next = head_mma(blk_i(b + 1), blk_j(b + 1));
+            } else if constexpr (HASO && GEN) {
+                ao = acc_o[i][j];
             } else if constexpr (HASO) {
                 ao = head_mma(i, j);
             }
@@ -546,9 +661,10 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
                 }
                 if constexpr (DBG) {
                     const int n = n0 + nt;
-                    if (m_lane < g.M && n + 4 <= g.N) {
+                    if (m_lane < g.M) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
+                            if (n + e >= g.N) continue;
                             if (g.dbg_n) g.dbg_n[(size_t)m_lane * g.N + n + e] = acc[i][j][4 * q + e];
                             if (g.dbg_o) {
                                 int aov = 0;
@@ -616,24 +732,22 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_dma128_kernel(GemmArgs g
 #endif
 }
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN = false>
 qarvd_status launch128_one(const GemmArgs &g, hipStream_t st)
 {
     using G = Geo2<BM, BN, WM, WN, NSTAGE>;
-    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT>;
+    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN>;
     static unsigned long long lds_limit_raised = 0;      // one mask per instantiation, i.e. per kernel symbol
     if (qarvd_status st_a = qarvd_raise_lds_limit_once(k, G::LDS_BYTES, lds_limit_raised); st_a != QARVD_OK) return st_a;
-    constexpr int LDS_PER_CU = 160 * 1024;
-    const int wg_per_cu = std::max(1, std::min(LDS_PER_CU / G::LDS_BYTES, 8 / G::NW));
     int grid = 0;
-    if (qarvd_status st_g = persistent_grid(g.tiles_m * g.tiles_n, wg_per_cu, &grid); st_g != QARVD_OK) return st_g;
+    if (qarvd_status st_g = persistent_grid(g.tiles_m * g.tiles_n, G::WG_PER_CU, &grid); st_g != QARVD_OK) return st_g;
     hipLaunchKernelGGL(k, dim3(grid), dim3(G::THREADS), G::LDS_BYTES, st, g);
     return qarvd_launch_status();
 }
 
 }  // namespace
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN>
 qarvd_status launch_dma128(const GemmArgs &g0, qarvd_dtype ydt, hipStream_t st)
 {
     GemmArgs g = g0;
@@ -642,10 +756,10 @@ qarvd_status launch_dma128(const GemmArgs &g0, qarvd_dtype ydt, hipStream_t st)
     g.store_wt = store_write_through(g, ydt == QARVD_BF16 ? 2 : 4);
     const bool dbg = g.dbg_n != nullptr || g.dbg_o != nullptr;   // raw-accumulator dumps: separate, slower build
     if (ydt == QARVD_BF16)
-        return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, uint16_t>(g, st)
-                    : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, uint16_t>(g, st);
-    return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, float>(g, st)
-                : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, float>(g, st);
+        return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, uint16_t, GEN>(g, st)
+                    : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, uint16_t, GEN>(g, st);
+    return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, float, GEN>(g, st)
+                : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, float, GEN>(g, st);
 }
 
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
@@ -667,10 +781,17 @@ QARVD_INST128_Q8(256, 128, 4, 2, 3)
 QARVD_INST128_Q8(128, 256, 2, 4, 3)
 
 #define QARVD_INST128(BM, BN, WM, WN, NS)                                                                        \
-    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true>(const GemmArgs &, qarvd_dtype, hipStream_t);   \
-    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, false>(const GemmArgs &, qarvd_dtype, hipStream_t);   \
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, false, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
 QARVD_INST128(256, 256, 2, 4, 2)
 QARVD_INST128(256, 128, 4, 2, 3)
 QARVD_INST128(128, 256, 2, 4, 3)
+QARVD_INST128(128, 128, 2, 4, 4)
+QARVD_INST128(64, 64, 2, 2, 4)
+
+#define QARVD_INST128_GEN(BM, BN, WM, WN, NS)                                                                    \
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, true>(const GemmArgs &, qarvd_dtype, hipStream_t);
+QARVD_INST128_GEN(128, 128, 2, 4, 4)
+QARVD_INST128_GEN(64, 64, 2, 2, 4)
 
 }  // namespace qarvd_gemm
