@@ -87,28 +87,31 @@ int device_cus()
     return (qarvd_current_device(nullptr, &cus) == QARVD_OK && cus > 0) ? cus : 256;
 }
 
+struct Cand { int variant, bm, bn; double c, a, b; };
+
+int cheapest(const Cand *cand, int n, const GemmArgs &g)
+{
+    const int cus = device_cus();      // rounds are counted over the CUs of the device the call runs on
+    const double T = g.kp / 64;
+    const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
+    int best = cand[0].variant;
+    double best_cost = 1e300;
+    for (int i = 0; i < n; ++i) {
+        const Cand &c = cand[i];
+        if (c.bm == 64 && tiles128 > cus) continue;     // the small tiles only pay while 128x128 tiles leave CUs empty
+        const long tiles = (long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
+        const double cost = c.c + (double)((tiles + cus - 1) / cus) * (c.a + c.b * T);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = c.variant;
+        }
+    }
+    return best;
+}
+
 int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
 {
     const bool dual = g.n_off > 0;
-    const int cus = device_cus();      // rounds are counted over the CUs of the device the call runs on
-    struct Cand { int variant, bm, bn; double c, a, b; };
-    const double T = g.kp / 64;
-    const long tiles128 = (long)((g.M + 127) / 128) * ((g.N + 127) / 128);
-    auto cheapest = [&](const Cand *cand, int n) {
-        int best = cand[0].variant;
-        double best_cost = 1e300;
-        for (int i = 0; i < n; ++i) {
-            const Cand &c = cand[i];
-            if (c.bm == 64 && tiles128 > cus) continue;     // the small tiles only pay while 128x128 tiles leave CUs empty
-            const long tiles = (long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
-            const double cost = c.c + (double)((tiles + cus - 1) / cus) * (c.a + c.b * T);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best = c.variant;
-            }
-        }
-        return best;
-    };
     if (g.n_off <= 128 && vector_out_ok(g, ydt)) {
         const Cand cand[7] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
                               {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
@@ -117,12 +120,13 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
                               {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
                               {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120},
                               {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
-        return cheapest(cand, 7);
+        return cheapest(cand, 7, g);
     }
     if (short_rows_ok(g)) {
         const Cand cand[2] = {{37, 128, 128, 1.8, 3.6, 0.200}, {38, 64, 64, 3.0, 1.0, 0.125}};
-        return cheapest(cand, 2);
+        return cheapest(cand, 2, g);
     }
+    const int cus = device_cus();
     const long tiles_big = (long)((g.M + 255) / 256) * ((g.N + 127) / 128);
     if (dual) return tiles_big >= cus ? 1 : 2;
     return tiles_big >= cus ? 3 : 4;
@@ -186,14 +190,21 @@ namespace {
 using namespace qarvd_gemm;
 struct W4Variant {
     int BM, BN;
+    int form;     // 0: N % 8 == 0, aligned outputs, outlier block up to 128 bytes; 1: any of these, strides up to 2^22; 2: any
     qarvd_status (*dual)(const GemmArgs &, qarvd_dtype, hipStream_t);
     qarvd_status (*single)(const GemmArgs &, qarvd_dtype, hipStream_t);
 };
 const W4Variant kW4Variants[] = {
-    {256, 256, launch_dma<256, 256, 2, 4, 4, true, true>, launch_dma<256, 256, 2, 4, 4, false, true>},
-    {128, 128, launch_dma<128, 128, 2, 2, 4, true, true>, launch_dma<128, 128, 2, 2, 4, false, true>},
-    // register-staged: any N, any outlier-block width, any output alignment
-    {128, 128, launch_staged<128, 128, 2, 2, true, true>, launch_staged<128, 128, 2, 2, false, true>},
+    {256, 256, 0, launch_dma<256, 256, 2, 4, 4, true, true>, launch_dma<256, 256, 2, 4, 4, false, true>},
+    {128, 128, 0, launch_dma<128, 128, 2, 2, 4, true, true>, launch_dma<128, 128, 2, 2, 4, false, true>},
+    // register-staged: any N, any outlier-block width, any output alignment, any stride
+    {128, 128, 2, launch_staged<128, 128, 2, 2, true, true>, launch_staged<128, 128, 2, 2, false, true>},
+    // 128-byte stages; one build serves layers with and without outliers
+    {256, 256, 0, launch_dma128<256, 256, 2, 4, 3, true, false, true>, launch_dma128<256, 256, 2, 4, 3, true, false, true>},
+    {256, 128, 0, launch_dma128<256, 128, 4, 2, 3, true, false, true>, launch_dma128<256, 128, 4, 2, 3, true, false, true>},
+    {128, 256, 0, launch_dma128<128, 256, 2, 4, 3, true, false, true>, launch_dma128<128, 256, 2, 4, 3, true, false, true>},
+    {128, 128, 1, launch_dma128<128, 128, 2, 4, 4, true, true, true>, launch_dma128<128, 128, 2, 4, 4, true, true, true>},
+    {64, 64, 1, launch_dma128<64, 64, 2, 2, 4, true, true, true>, launch_dma128<64, 64, 2, 2, 4, true, true, true>},
 };
 constexpr int kNumW4Variants = sizeof(kW4Variants) / sizeof(kW4Variants[0]);
 }  // namespace
@@ -225,18 +236,18 @@ extern "C" qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, con
     g.ldxq = ldxq; g.ldwq = ldwq4; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
     g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.vec_out = 1; g.store_wt = 0;
     const bool fast_ok = g.n_off <= 128 && vector_out_ok(g, ydt);
-    if (!fast_ok) {
-        if (variant == 1 || variant == 2) return QARVD_ERR_UNSUPPORTED;     // an LDS-direct tile asked for by name
-        variant = kNumW4Variants;                                           // the register-staged kernel takes the rest
+    g.vec_out = vector_out_ok(g, ydt);
+    if (variant == 0) {
+        // the cost model of the INT8 path on the 128-byte-stage tiles.  An INT4 weight stage is half as wide, so 256x256 has room
+        // for three stages and less LDS traffic a K step: 4680 x 5120 -> 13824 279 us (64-byte stages 309, INT8 weights
+        // 303); 4680 x 1536 -> 1536 15.8 (19.3), 520 x 8960 -> 1536 23.6 (41.7), 64 x 5120 -> 5120 15.1 (24.6);
+        // 2251 x 2360 -> 2252 with 150 outliers 27.0 against 65.6 register-staged, which keeps strides beyond 2^22
+        const Cand cand[5] = {{7, 128, 128, 1.8, 3.6, 0.205}, {8, 64, 64, 3.4, 1.1, 0.135},
+                              {4, 256, 256, 7.2, 9.2, 0.443}, {5, 256, 128, 4.5, 3.6, 0.379}, {6, 128, 256, 3.9, 3.9, 0.381}};
+        variant = short_rows_ok(g) ? cheapest(cand, fast_ok ? 5 : 2, g) : 3;
     }
-    if (variant == 0) {     // same cost model as the INT8 path, restricted to the two tiles built for INT4
-        const double T = g.kp / 64;
-        const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256), t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-        const int cus = device_cus();
-        const double c256 = 2.2 + (double)((t256 + cus - 1) / cus) * (8.9 + 0.688 * T);
-        const double c128 = 2.0 + (double)((t128 + cus - 1) / cus) * (1.5 + 0.309 * T);
-        variant = c256 <= c128 ? 1 : 2;
-    }
+    const int form = kW4Variants[variant - 1].form;
+    if ((form == 0 && !fast_ok) || (form == 1 && !short_rows_ok(g))) return QARVD_ERR_UNSUPPORTED;     // a tile asked for by name
     const W4Variant &v = kW4Variants[variant - 1];
     return (g.n_off > 0 ? v.dual : v.single)(g, ydt, reinterpret_cast<hipStream_t>(stream));
 }

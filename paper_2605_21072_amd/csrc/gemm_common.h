@@ -96,7 +96,7 @@ qarvd_status launch_dma_q8(const GemmArgs &g, hipStream_t st);
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
 qarvd_status launch_dma128_q8(const GemmArgs &g, hipStream_t st);
 // 128-byte-deep K stages (gemm_dma128.hip); GEN: two accumulator sets, any outlier width, any N and output alignment
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN = false>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN = false, bool W4 = false>
 qarvd_status launch_dma128(const GemmArgs &g, qarvd_dtype ydt, hipStream_t st);
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
 qarvd_status launch_mfma16(const GemmArgs &g, qarvd_dtype ydt, hipStream_t st);

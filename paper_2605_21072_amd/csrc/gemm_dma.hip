@@ -84,14 +84,6 @@ struct Geo {
     static_assert(NSTAGE >= 3, "two head tiles plus one free stage");
 };
 
-// widen eight packed INT4 codes (two dwords) to sixteen INT8 lanes, each code times 16: with the nibble
-// order of the packed layout, (p << 4) & 0xF0F0F0F0 are four consecutive codes and p & 0xF0F0F0F0 the next four
-__device__ __forceinline__ v4i unpack_w4(v2i p)
-{
-    const int m = (int)0xF0F0F0F0u;
-    return v4i{(p.x << 4) & m, p.x & m, (p.y << 4) & m, p.y & m};
-}
-
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool W4>
 __global__ __launch_bounds__(64 * WM * WN, (Geo<BM, BN, WM, WN, NSTAGE, W4>::WAVES_PER_EU)) void gemm_dma_kernel(GemmArgs g)
 {

@@ -48,15 +48,22 @@ constexpr int PATCH2_BYTES = 32 * PATCH2_RS;
 // target-shape kernel read ten times what the 64-byte-stage kernel's does.)
 __device__ __forceinline__ int swz128(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
 
-template <int BM, int BN, int WM, int WN, int NSTAGE>
+// 64-byte rows of packed INT4 (four chunks, an 8-byte read per lane): four rows cover the banks once, so rows r,
+// r + 4, r + 8, r + 12 put a k-step's chunk into different slots.
+__device__ __forceinline__ int swz_w4(int r) { return (r >> 2) & 3; }
+
+// W4: the W operand is packed INT4, 64 bytes per row and stage.
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool W4>
 struct Geo2 {
     static constexpr int NW = WM * WN;
     static constexpr int THREADS = 64 * NW;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
     static constexpr int TM = WTM / 32, TN = WTN / 32;
-    static constexpr int NA = BM / 8 / NW, NB = BN / 8 / NW;      // LDS-direct loads (8 rows x 128 B) per wave per stage
+    static constexpr int WROW = W4 ? 64 : BK2;                     // bytes of a W row in a stage
+    static constexpr int WGRP = W4 ? 16 : 8;                       // W rows an LDS-direct load (1 KB) covers
+    static constexpr int NA = BM / 8 / NW, NB = BN / WGRP / NW;    // LDS-direct loads per wave per stage
     static constexpr int NLOAD = NA + NB;
-    static constexpr int STG = (BM + BN) * BK2;
+    static constexpr int STG = BM * BK2 + BN * WROW;
     static constexpr int PATCHES = NW * PATCH2_BYTES;
     static constexpr int NSCALE = BM + 3 * BN;
     static constexpr int SCALE_BYTES = 2 * NSCALE * (int)sizeof(float);
@@ -65,7 +72,7 @@ struct Geo2 {
     static constexpr int SCALES_OFF = NSTAGE * STG + (PATCH_EXTRA ? PATCHES : 0);
     static constexpr int LDS_BYTES = SCALES_OFF + SCALE_BYTES;
     static constexpr int SPT = (NSCALE + THREADS - 1) / THREADS;
-    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "row groups of eight must divide over the waves");
+    static_assert(BM % (8 * NW) == 0 && BN % (WGRP * NW) == 0, "row groups must divide over the waves");
     static_assert(NW % 2 == 0, "the load swizzle takes bit 3 of a row from the wave number");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is TM x TN blocks of 32 x 32");
     static constexpr int WG_PER_CU = NW >= 8 || 2 * LDS_BYTES > 160 * 1024 ? 1 : 8 / NW;     // bounded by LDS, two waves per SIMD
@@ -79,10 +86,10 @@ struct Geo2 {
 
 typedef v4i v4i_unaligned __attribute__((aligned(2)));   // 16 bytes at an address that is aligned to an output element only
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN>
-__global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_PER_SIMD)) void gemm_dma128_kernel(GemmArgs g)
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN, bool W4>
+__global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WAVES_PER_SIMD)) void gemm_dma128_kernel(GemmArgs g)
 {
-    using G = Geo2<BM, BN, WM, WN, NSTAGE>;
+    using G = Geo2<BM, BN, WM, WN, NSTAGE, W4>;
     constexpr int TM = G::TM, TN = G::TN, NA = G::NA, NB = G::NB, NW = G::NW, STG = G::STG, NL = G::NLOAD;
     extern __shared__ __align__(16) unsigned char smem[];
     float *const sc_both = reinterpret_cast<float *>(smem + G::SCALES_OFF);   // 2 x { s_x[BM] | s_n[BN] | s_o[BN] | bias[BN] }
@@ -116,8 +123,12 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
         for (int i = 0; i < NA; ++i)
             va[i] = (min(lm0 + (NW * i + wave) * 8 + drow, g.M - 1) - lm0) * (int)g.ldxq + dchunk;
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-            vb[i] = (min(ln0 + (NW * i + wave) * 8 + drow, g.N - 1) - ln0) * (int)g.ldwq + dchunk;
+        for (int i = 0; i < NB; ++i) {
+            if constexpr (W4)     // 16 rows x 64 bytes per load, chunk (l & 3) ^ swz_w4(row) of row l >> 2
+                vb[i] = (min(ln0 + (NW * i + wave) * 16 + (lane >> 2), g.N - 1) - ln0) * (int)g.ldwq + (((lane & 3) ^ swz_w4(lane >> 2)) << 4);
+            else
+                vb[i] = (min(ln0 + (NW * i + wave) * 8 + drow, g.N - 1) - ln0) * (int)g.ldwq + dchunk;
+        }
     };
     auto issue = [&](int ktile, int stage) {
         unsigned char *sb = smem + stage * STG;
@@ -127,7 +138,7 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
             buffer_load_lds16(base_a, va[i], koff, sb + (NW * i + wave) * 1024);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
-            buffer_load_lds16(base_b, vb[i], koff, sb + BM * BK2 + (NW * i + wave) * 1024);
+            buffer_load_lds16(base_b, vb[i], W4 ? koff / 2 : koff, sb + BM * BK2 + (NW * i + wave) * 1024);
     };
 
     // ---- scales and bias: registers during the previous tile's K loop, then the other LDS buffer ----
@@ -138,8 +149,8 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
             const int e = tid + u * G::THREADS;
             float v = 0.f;
             if (e < BM) v = g.s_x[min(sm0 + e, g.M - 1)];
-            else if (e < BM + BN) v = g.s_n[min(sn0 + e - BM, g.N - 1)];
-            else if (e < BM + 2 * BN) v = g.s_o[min(sn0 + e - BM - BN, g.N - 1)];
+            else if (e < BM + BN) v = g.s_n[min(sn0 + e - BM, g.N - 1)] * (W4 ? 0.0625f : 1.0f);             // INT4 codes enter the
+            else if (e < BM + 2 * BN) v = g.s_o[min(sn0 + e - BM - BN, g.N - 1)] * (W4 ? 0.0625f : 1.0f);    // MFMA times 16 (exact)
             else if (e < BM + 3 * BN && g.bias) v = g.bias[min(sn0 + e - BM - 2 * BN, g.N - 1)];
             r_s[u] = v;
         }
@@ -163,10 +174,17 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
     // ---- fragment addressing: lane l reads row (l & 31), chunk 2*ks + (l >> 5) of a k-step ----
     const int frow = lane & 31, fhalf = lane >> 5, fsw = swz128(frow);
     const int x_base = (wm * G::WTM + frow) * BK2;               // X rows: MFMA B operand
-    const int w_base = BM * BK2 + (wn * G::WTN + frow) * BK2;    // W rows: MFMA A operand
-    int coff[KS2];
+    const int w_base = BM * BK2 + (wn * G::WTN + frow) * G::WROW + (W4 ? 8 * fhalf : 0);    // W rows: MFMA A operand
+    int coff[KS2], wcoff[KS2];
 #pragma unroll
-    for (int ks = 0; ks < KS2; ++ks) coff[ks] = (((2 * ks) | fhalf) ^ fsw) << 4;
+    for (int ks = 0; ks < KS2; ++ks) {
+        coff[ks] = (((2 * ks) | fhalf) ^ fsw) << 4;
+        wcoff[ks] = W4 ? (ks ^ swz_w4(frow)) << 4 : coff[ks];     // packed INT4: k-step ks is one chunk, this lane's half of it 8 bytes
+    }
+    auto read_w = [&](const unsigned char *sb, int j, int c) -> v4i {   // W fragment of block j, k-step offset c
+        if constexpr (W4) return unpack_w4(*reinterpret_cast<const v2i *>(sb + w_base + j * 32 * G::WROW + c));
+        else return *reinterpret_cast<const v4i *>(sb + w_base + j * 32 * BK2 + c);
+    };
 
     v16i acc[TM][TN];
     v16i acc_o[GEN ? TM : 1][GEN ? TN : 1];     // (GEN) the outlier sum, moved here when the K loop passes its end
@@ -174,7 +192,7 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
     v4i xf[2][TM], wf[2][TN];   // fragments of k-steps of even / odd number
     auto load_frags = [&](const unsigned char *sb, int ks) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) wf[ks & 1][j] = *reinterpret_cast<const v4i *>(sb + w_base + j * 32 * BK2 + coff[ks]);
+        for (int j = 0; j < TN; ++j) wf[ks & 1][j] = read_w(sb, j, wcoff[ks]);
 #pragma unroll
         for (int i = 0; i < TM; ++i) xf[ks & 1][i] = *reinterpret_cast<const v4i *>(sb + x_base + i * 32 * BK2 + coff[ks]);
     };
@@ -598,11 +616,11 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
             const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             const unsigned char *hb = smem + hstage0 * STG;
             v16i ao = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                *reinterpret_cast<const v4i *>(hb + w_base + j * 32 * BK2 + coff[0]),
+                read_w(hb, j, wcoff[0]),
                 *reinterpret_cast<const v4i *>(hb + x_base + i * 32 * BK2 + coff[0]), zero, 0, 0, 0);
             for (int s = 1; s < o_steps; ++s) {
                 const int c = s == 1 ? coff[1] : s == 2 ? coff[2] : coff[3];
-                const v4i wo = *reinterpret_cast<const v4i *>(hb + w_base + j * 32 * BK2 + c);
+                const v4i wo = read_w(hb, j, s == 1 ? wcoff[1] : s == 2 ? wcoff[2] : wcoff[3]);
                 const v4i xo = *reinterpret_cast<const v4i *>(hb + x_base + i * 32 * BK2 + c);
                 ao = __builtin_amdgcn_mfma_i32_32x32x32_i8(wo, xo, ao, 0, 0, 0);
             }
@@ -665,10 +683,10 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             if (n + e >= g.N) continue;
-                            if (g.dbg_n) g.dbg_n[(size_t)m_lane * g.N + n + e] = acc[i][j][4 * q + e];
+                            if (g.dbg_n) g.dbg_n[(size_t)m_lane * g.N + n + e] = acc[i][j][4 * q + e] >> (W4 ? 4 : 0);
                             if (g.dbg_o) {
                                 int aov = 0;
-                                if constexpr (HASO) aov = ao[4 * q + e];
+                                if constexpr (HASO) aov = ao[4 * q + e] >> (W4 ? 4 : 0);
                                 g.dbg_o[(size_t)m_lane * g.N + n + e] = aov;
                             }
                         }
@@ -732,11 +750,11 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE>::WAVES_
 #endif
 }
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN = false>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN = false, bool W4 = false>
 qarvd_status launch128_one(const GemmArgs &g, hipStream_t st)
 {
-    using G = Geo2<BM, BN, WM, WN, NSTAGE>;
-    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN>;
+    using G = Geo2<BM, BN, WM, WN, NSTAGE, W4>;
+    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN, W4>;
     static unsigned long long lds_limit_raised = 0;      // one mask per instantiation, i.e. per kernel symbol
     if (qarvd_status st_a = qarvd_raise_lds_limit_once(k, G::LDS_BYTES, lds_limit_raised); st_a != QARVD_OK) return st_a;
     int grid = 0;
@@ -747,7 +765,7 @@ qarvd_status launch128_one(const GemmArgs &g, hipStream_t st)
 
 }  // namespace
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN>
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool GEN, bool W4>
 qarvd_status launch_dma128(const GemmArgs &g0, qarvd_dtype ydt, hipStream_t st)
 {
     GemmArgs g = g0;
@@ -756,10 +774,10 @@ qarvd_status launch_dma128(const GemmArgs &g0, qarvd_dtype ydt, hipStream_t st)
     g.store_wt = store_write_through(g, ydt == QARVD_BF16 ? 2 : 4);
     const bool dbg = g.dbg_n != nullptr || g.dbg_o != nullptr;   // raw-accumulator dumps: separate, slower build
     if (ydt == QARVD_BF16)
-        return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, uint16_t, GEN>(g, st)
-                    : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, uint16_t, GEN>(g, st);
-    return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, float, GEN>(g, st)
-                : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, float, GEN>(g, st);
+        return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, uint16_t, GEN, W4>(g, st)
+                    : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, uint16_t, GEN, W4>(g, st);
+    return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, float, GEN, W4>(g, st)
+                : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, true, float, GEN, W4>(g, st);
 }
 
 template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL>
@@ -781,8 +799,8 @@ QARVD_INST128_Q8(256, 128, 4, 2, 3)
 QARVD_INST128_Q8(128, 256, 2, 4, 3)
 
 #define QARVD_INST128(BM, BN, WM, WN, NS)                                                                        \
-    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, false>(const GemmArgs &, qarvd_dtype, hipStream_t);   \
-    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, false, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, false, false>(const GemmArgs &, qarvd_dtype, hipStream_t);   \
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, false, false, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
 QARVD_INST128(256, 256, 2, 4, 2)
 QARVD_INST128(256, 128, 4, 2, 3)
 QARVD_INST128(128, 256, 2, 4, 3)
@@ -790,8 +808,16 @@ QARVD_INST128(128, 128, 2, 4, 4)
 QARVD_INST128(64, 64, 2, 2, 4)
 
 #define QARVD_INST128_GEN(BM, BN, WM, WN, NS)                                                                    \
-    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, true>(const GemmArgs &, qarvd_dtype, hipStream_t);
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, true, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
 QARVD_INST128_GEN(128, 128, 2, 4, 4)
 QARVD_INST128_GEN(64, 64, 2, 2, 4)
+
+#define QARVD_INST128_W4(BM, BN, WM, WN, NS, GEN)                                                                    \
+    template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, GEN, true>(const GemmArgs &, qarvd_dtype, hipStream_t);
+QARVD_INST128_W4(256, 256, 2, 4, 3, false)
+QARVD_INST128_W4(256, 128, 4, 2, 3, false)
+QARVD_INST128_W4(128, 256, 2, 4, 3, false)
+QARVD_INST128_W4(128, 128, 2, 4, 4, true)
+QARVD_INST128_W4(64, 64, 2, 2, 4, true)
 
 }  // namespace qarvd_gemm

@@ -29,6 +29,14 @@ typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 // (row parity, slot) pairs and any 16 consecutive rows over all (row mod 4, slot) pairs.
 __device__ __forceinline__ int swz64(int r) { return (((r >> 1) ^ (r >> 3)) & 1) | (((r >> 2) & 1) << 1); }
 
+// widen eight packed INT4 codes (two dwords) to sixteen INT8 lanes, each code times 16: with the nibble
+// order of the packed layout, (p << 4) & 0xF0F0F0F0 are four consecutive codes and p & 0xF0F0F0F0 the next four
+__device__ __forceinline__ v4i unpack_w4(v2i p)
+{
+    const int m = (int)0xF0F0F0F0u;
+    return v4i{(p.x << 4) & m, p.x & m, (p.y << 4) & m, p.y & m};
+}
+
 // s_waitcnt with only vmcnt set (gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[15:14]).
 template <int N> __device__ __forceinline__ void wait_vmcnt()
 {

@@ -66,3 +66,26 @@ def test_small_tiles_on_whole_lines(M, N, K, K_o):
         want = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=_named("any width")[0])
         for v in _named("128-byte stages 128x128 (8 waves, 4 stages) " + kind) + _named("128-byte stages 64x64 (4 waves, 4 stages) " + kind):
             assert torch.equal(q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=v), want), q.gemm_variant_name(v)
+
+
+@pytest.mark.parametrize("M,N,K,K_o", [(1, 1, 1, 0), (1, 8, 100, 32), (65, 129, 130, 1), (127, 255, 640, 161), (129, 264, 1280, 96), (300, 1003, 1000, 129),
+                                       (520, 1536, 2048, 32), (40, 64, 2048, 1900), (4400, 4352, 256, 0)])
+def test_packed_int4_tiles(M, N, K, K_o):
+    """Every INT4 tile that takes a shape, and the heuristic, against the register-staged one (pinned to the oracle elsewhere)."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    kp = q.packed_k(K, K_o)
+    Xq = torch.randint(-127, 128, (M, kp), generator=gen, device="cuda", dtype=torch.int8)
+    lo, hi = (torch.randint(-7, 8, (N, kp // 2), generator=gen, device="cuda") for _ in range(2))
+    Wq4 = ((hi & 15) << 4 | (lo & 15)).to(torch.uint8)
+    sx, sn, so, b = (torch.rand(n, generator=gen, device="cuda") * 0.1 for n in (M, N, N, N))
+    w = q.DualScaleWeight(Wq4, sn, so, None, K_o, N, K, bits=4)
+    for dt in (torch.float32, torch.bfloat16):
+        want, an, ao = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, debug_acc=True, variant=3)
+        for v in [0] + list(range(4, q.load_library().qarvd_w4_gemm_num_variants() + 1)):
+            try:
+                got = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, debug_acc=True, variant=v)
+            except q.QarvdError as e:
+                assert e.status == -2 and 4 <= v <= 6 and (N % 8 or q.packed_normal_offset(K_o) > 128)
+                continue
+            assert torch.equal(got[0], want) and torch.equal(got[1], an) and torch.equal(got[2], ao), v
+            assert torch.equal(q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=v), want), v
