@@ -78,7 +78,9 @@ bool variant_fits(const Variant &v, const GemmArgs &g, qarvd_dtype ydt)
 // waves when those leave CUs empty over a long K (1560 x 8960 -> 1536: 31 us, 45 for the four-wave 128x128 tile
 // on 64-byte stages that this one replaces); 64x64 when even those would leave most without a tile (520 x 8960 -> 1536:
 // 20.5 us, 24.2 on 64-byte stages).  Up to K of about 1600 the 64-byte-stage 64x64 tile is the faster
-// one (256 x 1536 -> 1536: 6.5 against 6.6 us, 16 x 256 -> 256: 3.8 against 4.2).
+// one (256 x 1536 -> 1536: 6.5 against 6.6 us, 16 x 256 -> 256: 3.8 against 4.2), and at any K while a quarter of the CUs or
+// fewer have a tile: the loads then wait for latency, not for lines, and six stages reach further than four (64 x 8960 ->
+// 1536, 24 tiles: 17.6 against 19.8 us; 64 x 5120 -> 5120, 80 tiles: 13.2 both; 64 x 13824 -> 5120: 34.8 against 28.8).
 // What needs the general kernels (outlier block over 128 bytes, N % 8 != 0, unaligned outputs) picks by the same model
 // from the two tiles built for it; operand strides beyond 2^22 go to the register-staged kernel.
 int device_cus()
@@ -118,9 +120,10 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
                               {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
                               {dual ? 33 : 34, 128, 128, 1.6, 3.2, 0.200},
                               {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
-                              {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120},
-                              {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
-        return cheapest(cand, 7, g);
+                              {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152},
+                              {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120}};
+        const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+        return cheapest(cand, tiles64 * 4 > device_cus() ? 7 : 6, g);
     }
     if (short_rows_ok(g)) {
         const Cand cand[2] = {{37, 128, 128, 1.8, 3.6, 0.200}, {38, 64, 64, 3.0, 1.0, 0.125}};
