@@ -1,6 +1,6 @@
 // Register-staged variant of the dual-scale W8A8 GEMM: global -> VGPR -> swizzled LDS, two LDS
-// stages of 128 K-bytes, both accumulator sets live in registers.  Handles every shape and any
-// outlier-block width; the general fallback behind the faster LDS-direct kernels.
+// stages of 128 K-bytes, both accumulator sets live in registers.  Handles every shape, any
+// outlier-block width and any stride; the fallback for operand strides beyond the 2^22 bytes that the LDS-direct kernels address.
 // W4: the W operand is packed INT4 (two codes per byte, the nibble order of qarvd_quantize_weight_w4); a thread
 // loads 8 bytes where the INT8 build loads 16 and widens them to sixteen INT8 lanes holding 16 * code on the
 // way into LDS.  Both sums are then 16 times the INT8 ones and the weight scales are multiplied by 1/16 (exact
