@@ -135,6 +135,34 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
     return tiles_big >= cus ? 3 : 4;
 }
 
+// Host-only checks of a GEMM call's arguments (all but the variant number), and the kernel arguments they give.  Wq: bits = 8 one
+// byte per code, bits = 4 two codes per byte.
+qarvd_status check_and_fill(int bits, const int8_t *Xq, int64_t ldxq, const float *s_x, const void *Wq, int64_t ldwq, const float *s_normal,
+                            const float *s_outlier, const float *bias, int32_t M, int32_t N, int32_t K, int32_t K_o, void *Y,
+                            qarvd_dtype ydt, int64_t ldy, int32_t *dbg_acc_normal, int32_t *dbg_acc_outlier, GemmArgs *out)
+{
+    if (!Xq || !Wq || !s_x || !s_normal || !s_outlier || !Y) return QARVD_ERR_INVALID_ARG;
+    if (M <= 0 || N <= 0 || K <= 0 || K > QARVD_MAX_K || K_o < 0 || K_o > K) return QARVD_ERR_INVALID_ARG;
+    const PackedK pk = qarvd_packed(K, K_o);
+    if (ldxq < pk.kp || ldwq < pk.kp * bits / 8 || ldy < N) return QARVD_ERR_INVALID_ARG;
+    if (ydt != QARVD_F32 && ydt != QARVD_BF16) return QARVD_ERR_UNSUPPORTED;
+    if (!qarvd_aligned16(Xq) || !qarvd_aligned16(Wq) || (ldxq % 16) || (ldwq % 16)) return QARVD_ERR_UNSUPPORTED;
+    const size_t esz = ydt == QARVD_F32 ? 4 : 2;
+    if (reinterpret_cast<uintptr_t>(Y) % esz) return QARVD_ERR_UNSUPPORTED;
+    if ((reinterpret_cast<uintptr_t>(s_x) | reinterpret_cast<uintptr_t>(s_normal) | reinterpret_cast<uintptr_t>(s_outlier) |
+         reinterpret_cast<uintptr_t>(bias) | reinterpret_cast<uintptr_t>(dbg_acc_normal) |
+         reinterpret_cast<uintptr_t>(dbg_acc_outlier)) & 3u)
+        return QARVD_ERR_UNSUPPORTED;
+    GemmArgs g;
+    g.Xq = Xq; g.Wq = reinterpret_cast<const int8_t *>(Wq); g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
+    g.Y = Y; g.dbg_n = dbg_acc_normal; g.dbg_o = dbg_acc_outlier;
+    g.ldxq = ldxq; g.ldwq = ldwq; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
+    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.store_wt = 0;
+    g.vec_out = vector_out_ok(g, ydt);
+    *out = g;
+    return QARVD_OK;
+}
+
 }  // namespace
 
 extern "C" int32_t qarvd_gemm_num_variants(void) { return kNumVariants; }
@@ -153,25 +181,12 @@ extern "C" qarvd_status qarvd_w8a8_dual_gemm_variant(int32_t variant, const int8
                                                      int32_t *dbg_acc_normal, int32_t *dbg_acc_outlier,
                                                      void *stream)
 {
-    if (!Xq || !Wq || !s_x || !s_normal || !s_outlier || !Y) return QARVD_ERR_INVALID_ARG;
-    if (M <= 0 || N <= 0 || K <= 0 || K > QARVD_MAX_K || K_o < 0 || K_o > K) return QARVD_ERR_INVALID_ARG;
     if (variant < 0 || variant > kNumVariants) return QARVD_ERR_INVALID_ARG;
-    const PackedK pk = qarvd_packed(K, K_o);
-    if (ldxq < pk.kp || ldwq < pk.kp || ldy < N) return QARVD_ERR_INVALID_ARG;
-    if (ydt != QARVD_F32 && ydt != QARVD_BF16) return QARVD_ERR_UNSUPPORTED;
-    if (!qarvd_aligned16(Xq) || !qarvd_aligned16(Wq) || (ldxq % 16) || (ldwq % 16)) return QARVD_ERR_UNSUPPORTED;
-    const size_t esz = ydt == QARVD_F32 ? 4 : 2;
-    if (reinterpret_cast<uintptr_t>(Y) % esz) return QARVD_ERR_UNSUPPORTED;
-    if ((reinterpret_cast<uintptr_t>(s_x) | reinterpret_cast<uintptr_t>(s_normal) | reinterpret_cast<uintptr_t>(s_outlier) |
-         reinterpret_cast<uintptr_t>(bias) | reinterpret_cast<uintptr_t>(dbg_acc_normal) |
-         reinterpret_cast<uintptr_t>(dbg_acc_outlier)) & 3u)
-        return QARVD_ERR_UNSUPPORTED;
     GemmArgs g;
-    g.Xq = Xq; g.Wq = Wq; g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
-    g.Y = Y; g.dbg_n = dbg_acc_normal; g.dbg_o = dbg_acc_outlier;
-    g.ldxq = ldxq; g.ldwq = ldwq; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
-    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.vec_out = 1; g.store_wt = 0;
-    g.vec_out = vector_out_ok(g, ydt);
+    if (qarvd_status s_c = check_and_fill(8, Xq, ldxq, s_x, Wq, ldwq, s_normal, s_outlier, bias, M, N, K, K_o, Y, ydt, ldy, dbg_acc_normal,
+                                          dbg_acc_outlier, &g);
+        s_c != QARVD_OK)
+        return s_c;
     if (variant == 0) variant = pick_variant(g, ydt);
     const Variant &v = kVariants[variant - 1];
     if (!variant_fits(v, g, ydt)) return QARVD_ERR_UNSUPPORTED;
@@ -220,26 +235,13 @@ extern "C" qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, con
                                              qarvd_dtype ydt, int64_t ldy, int32_t *dbg_acc_normal,
                                              int32_t *dbg_acc_outlier, int32_t variant, void *stream)
 {
-    if (!Xq || !Wq4 || !s_x || !s_normal || !s_outlier || !Y) return QARVD_ERR_INVALID_ARG;
-    if (M <= 0 || N <= 0 || K <= 0 || K > QARVD_MAX_K || K_o < 0 || K_o > K) return QARVD_ERR_INVALID_ARG;
     if (variant < 0 || variant > kNumW4Variants) return QARVD_ERR_INVALID_ARG;
-    const PackedK pk = qarvd_packed(K, K_o);
-    if (ldxq < pk.kp || ldwq4 < pk.kp / 2 || ldy < N) return QARVD_ERR_INVALID_ARG;
-    if (ydt != QARVD_F32 && ydt != QARVD_BF16) return QARVD_ERR_UNSUPPORTED;
-    if (!qarvd_aligned16(Xq) || !qarvd_aligned16(Wq4) || (ldxq % 16) || (ldwq4 % 16)) return QARVD_ERR_UNSUPPORTED;
-    const size_t esz = ydt == QARVD_F32 ? 4 : 2;
-    if (reinterpret_cast<uintptr_t>(Y) % esz) return QARVD_ERR_UNSUPPORTED;
-    if ((reinterpret_cast<uintptr_t>(s_x) | reinterpret_cast<uintptr_t>(s_normal) | reinterpret_cast<uintptr_t>(s_outlier) |
-         reinterpret_cast<uintptr_t>(bias) | reinterpret_cast<uintptr_t>(dbg_acc_normal) |
-         reinterpret_cast<uintptr_t>(dbg_acc_outlier)) & 3u)
-        return QARVD_ERR_UNSUPPORTED;
     GemmArgs g;
-    g.Xq = Xq; g.Wq = reinterpret_cast<const int8_t *>(Wq4); g.s_x = s_x; g.s_n = s_normal; g.s_o = s_outlier; g.bias = bias;
-    g.Y = Y; g.dbg_n = dbg_acc_normal; g.dbg_o = dbg_acc_outlier;
-    g.ldxq = ldxq; g.ldwq = ldwq4; g.ldy = ldy; g.M = M; g.N = N; g.n_off = pk.n_off; g.kp = pk.kp;
-    g.tiles_m = g.tiles_n = 0; g.act = 0; g.out_scale = 0.0f; g.vec_out = 1; g.store_wt = 0;
-    const bool fast_ok = g.n_off <= 128 && vector_out_ok(g, ydt);
-    g.vec_out = vector_out_ok(g, ydt);
+    if (qarvd_status s_c = check_and_fill(4, Xq, ldxq, s_x, Wq4, ldwq4, s_normal, s_outlier, bias, M, N, K, K_o, Y, ydt, ldy, dbg_acc_normal,
+                                          dbg_acc_outlier, &g);
+        s_c != QARVD_OK)
+        return s_c;
+    const bool fast_ok = g.n_off <= 128 && g.vec_out;
     if (variant == 0) {
         // the cost model of the INT8 path on the 128-byte-stage tiles.  An INT4 weight stage is half as wide, so 256x256 has room
         // for three stages and less LDS traffic a K step: 4680 x 5120 -> 13824 279 us (64-byte stages 309, INT8 weights
@@ -336,6 +338,12 @@ extern "C" qarvd_status qarvd_linear(const void *X, qarvd_dtype xdt, int64_t ldx
     const int64_t ld = qarvd_packed_ld(K, K_o);
     int8_t *const Xq = reinterpret_cast<int8_t *>(workspace);
     float *const s_x = reinterpret_cast<float *>(Xq + (size_t)M * (size_t)ld);
+    // Both halves' arguments are checked before the first of them is launched: the GEMM's here, quant_act's by itself.
+    GemmArgs g;
+    if (qarvd_status s_c = check_and_fill(w_bits, Xq, ld, s_x, Wq, ldwq, s_normal, s_outlier, bias, M, N, K, K_o, Y, ydt, ldy, nullptr,
+                                          nullptr, &g);
+        s_c != QARVD_OK)
+        return s_c;
     if (qarvd_status st = qarvd_quant_act(X, xdt, M, K, ldx, K_o > 0 ? perm : nullptr, K_o, Xq, ld, s_x, stream); st != QARVD_OK) return st;
     if (w_bits == 4)
         return qarvd_w4a8_dual_gemm(Xq, ld, s_x, reinterpret_cast<const uint8_t *>(Wq), ldwq, s_normal, s_outlier, bias, M, N, K, K_o,

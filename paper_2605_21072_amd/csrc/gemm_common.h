@@ -41,7 +41,7 @@ struct GemmArgs {
     // next layer's static activation scale; unused for fp32 / bf16 outputs
     int32_t act;
     float out_scale;
-    int32_t vec_out;   // every row of Y is whole, 16-byte aligned chunks; set by the launchers that take other outputs too
+    int32_t vec_out;   // every row of Y is whole, 16-byte aligned chunks; set by the entry points
     int32_t store_wt;  // output stores write through the L2 (small outputs); set by the launchers
 };
 
