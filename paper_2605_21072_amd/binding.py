@@ -122,6 +122,23 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+def _empty(size, dtype, device, stream, scratch: bool = False) -> torch.Tensor:
+    """Memory that the call's kernels write.  An explicit `stream` may run ahead of the current one or behind it, so the block
+    comes from that stream's own pool (a block of the current stream's could still be read there by work queued before it was
+    freed) and, if the caller gets it (not `scratch`), is marked as used by the current stream too: after it is dropped it
+    is not handed out again before what reads it there has run."""
+    if stream is None:
+        return torch.empty(size, dtype=dtype, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    current = torch.cuda.current_stream(device)
+    with torch.cuda.stream(stream):
+        t = torch.empty(size, dtype=dtype, device=device)
+    if not scratch:
+        t.record_stream(current)
+    return t
+
+
 _DTYPES = {torch.float32: QARVD_F32, torch.bfloat16: QARVD_BF16}
 
 
@@ -165,7 +182,7 @@ def gemm_variant_name(i: int) -> str:
 def probe_mfma_peak(iters: int = 20000, stream=None) -> float:
     """qarvd_probe_mfma_peak: measured issue-bound INT8 MFMA rate of the current device in TOPS."""
     lib = load_library()
-    ws = torch.empty(8192, dtype=torch.uint8, device="cuda")
+    ws = _empty(8192, torch.uint8, "cuda", stream, scratch=True)
     tops = C.c_double(0.0)
     _check(lib.qarvd_probe_mfma_peak(int(iters), _ptr(ws), ws.numel(), C.byref(tops), _stream(stream)), "qarvd_probe_mfma_peak")
     return float(tops.value)
@@ -226,13 +243,13 @@ def quantize_weight(W: torch.Tensor, tau: float = 3.5, alpha: float = 1.2, align
         ldwq = packed_ld(K, -1) if (forced_mask is not None or align % 32) else (K + 127) // 128 * 128 + 128
         if bits == 4:
             ldwq //= 2
-    Wq = torch.empty((N, ldwq), dtype=torch.int8 if bits == 8 else torch.uint8, device=dev)
-    sn = torch.empty(N, dtype=torch.float32, device=dev)
-    so = torch.empty(N, dtype=torch.float32, device=dev)
-    perm = torch.empty(K, dtype=torch.int32, device=dev)
-    v = torch.empty(K, dtype=torch.float32, device=dev) if want_norms else None
+    Wq = _empty((N, ldwq), torch.int8 if bits == 8 else torch.uint8, dev, stream)
+    sn = _empty(N, torch.float32, dev, stream)
+    so = _empty(N, torch.float32, dev, stream)
+    perm = _empty(K, torch.int32, dev, stream)
+    v = _empty(K, torch.float32, dev, stream) if want_norms else None
     ws_bytes = quantize_weight_workspace(N, K) if bits == 8 else int(lib.qarvd_quantize_weight_w4_workspace(N, K))
-    ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=dev)
+    ws = _empty(ws_bytes + 256, torch.uint8, dev, stream, scratch=True)
     ws_ptr = (ws.data_ptr() + 255) // 256 * 256
     cfg = _DetectCfg(float(tau), float(alpha), int(align), int(bool(clip_search)), None)
     keep = None
@@ -282,9 +299,9 @@ def quant_act(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, Xq: Optio
     _dev2d(X, "X")
     M, K = X.shape
     if Xq is None:
-        Xq = torch.empty((M, packed_ld(K, K_o)), dtype=torch.int8, device=X.device)   # row stride: see qarvd_packed_ld
+        Xq = _empty((M, packed_ld(K, K_o)), torch.int8, X.device, stream)   # row stride: see qarvd_packed_ld
     if s_x is None:
-        s_x = torch.empty(M, dtype=torch.float32, device=X.device)
+        s_x = _empty(M, torch.float32, X.device, stream)
     st = lib.qarvd_quant_act(_ptr(X), _dt(X), M, K, X.stride(0), _ptr(perm), K_o, _ptr(Xq), Xq.stride(0), _ptr(s_x),
                              _stream(stream))
     _check(st, "qarvd_quant_act")
@@ -298,7 +315,7 @@ def quant_act_static(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, sc
     _dev2d(X, "X")
     M, K = X.shape
     if Xq is None:
-        Xq = torch.empty((M, packed_ld(K, K_o)), dtype=torch.int8, device=X.device)
+        Xq = _empty((M, packed_ld(K, K_o)), torch.int8, X.device, stream)
     st = lib.qarvd_quant_act_static(_ptr(X), _dt(X), M, K, X.stride(0), _ptr(perm), K_o, C.c_float(scale), _ptr(Xq),
                                     Xq.stride(0), _stream(stream))
     _check(st, "qarvd_quant_act_static")
@@ -312,11 +329,11 @@ def w8a8_dual_gemm(Xq: torch.Tensor, s_x: torch.Tensor, w: DualScaleWeight, bias
     (Y, acc_normal, acc_outlier) with debug_acc."""
     lib = load_library()
     if Y is None:
-        Y = torch.empty((M, w.N), dtype=out_dtype, device=Xq.device)
+        Y = _empty((M, w.N), out_dtype, Xq.device, stream)
     an = ao = None
     if debug_acc:
-        an = torch.empty((M, w.N), dtype=torch.int32, device=Xq.device)
-        ao = torch.empty((M, w.N), dtype=torch.int32, device=Xq.device)
+        an = _empty((M, w.N), torch.int32, Xq.device, stream)
+        ao = _empty((M, w.N), torch.int32, Xq.device, stream)
     if w.bits == 4:
         st = lib.qarvd_w4a8_dual_gemm(_ptr(Xq), Xq.stride(0), _ptr(s_x), _ptr(w.Wq), w.Wq.stride(0),
                                       _ptr(w.s_normal), _ptr(w.s_outlier), _ptr(bias), M, w.N, w.K, w.K_o,
@@ -346,7 +363,7 @@ def w8a8_dual_gemm_q8(Xq: torch.Tensor, s_x: torch.Tensor, w: DualScaleWeight, b
     if w.bits != 8:
         raise ValueError("the chained epilogue takes INT8 weights")
     if Y8 is None:
-        Y8 = torch.empty((M, w.N), dtype=torch.int8, device=Xq.device)
+        Y8 = _empty((M, w.N), torch.int8, Xq.device, stream)
     st = lib.qarvd_w8a8_dual_gemm_q8(_ptr(Xq), Xq.stride(0), _ptr(s_x), _ptr(w.Wq), w.Wq.stride(0), _ptr(w.s_normal),
                                      _ptr(w.s_outlier), _ptr(bias), M, w.N, w.K, w.K_o, int(act), C.c_float(out_scale),
                                      _ptr(Y8), Y8.stride(0), variant, _stream(stream))
@@ -374,8 +391,8 @@ def w8a8_linear(X: torch.Tensor, w: DualScaleWeight, bias: Optional[torch.Tensor
     if K != w.K:
         raise ValueError("X has %d channels, the layer %d" % (K, w.K))
     need = lib.qarvd_linear_workspace(M, K, K_o)
-    ws = torch.empty(need, dtype=torch.uint8, device=dev)
-    Y = torch.empty((M, w.N), dtype=out_dtype, device=dev)
+    ws = _empty(need, torch.uint8, dev, stream, scratch=True)
+    Y = _empty((M, w.N), out_dtype, dev, stream)
     st = lib.qarvd_linear(X.data_ptr(), _dt(X), X.stride(0), _ptr(w.perm), w.bits, w.Wq.data_ptr(), w.Wq.stride(0),
                           w.s_normal.data_ptr(), w.s_outlier.data_ptr(), _ptr(bias), M, w.N, K, K_o, Y.data_ptr(), _dt(Y),
                           w.N, ws.data_ptr(), need, _stream(stream))
