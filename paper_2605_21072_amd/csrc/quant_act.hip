@@ -15,27 +15,36 @@ namespace {
 
 constexpr int TPB = 256;
 
-// Four consecutive elements of X as loaded, and widened (exactly) to fp32.
+// Four consecutive elements of X as loaded, at any element's address (one instruction whatever the alignment), and widened
+// (exactly) to fp32.
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     typedef float4 raw;
+    typedef float raw_any __attribute__((ext_vector_type(4), aligned(4)));
     static __device__ __forceinline__ raw zero() { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
+    static __device__ __forceinline__ raw of(raw_any r) { return make_float4(r.x, r.y, r.z, r.w); }
     static __device__ __forceinline__ float4 widen(raw r) { return r; }
     static __device__ __forceinline__ float load1(const float *p) { return *p; }
-    static __device__ __forceinline__ raw pack(float a, float b, float c, float d) { return make_float4(a, b, c, d); }
+    static __device__ __forceinline__ raw drop(raw r, int n)        // the first n elements, 0 < n < 4, moved out, zeros behind
+    {
+        return n == 1 ? make_float4(r.y, r.z, r.w, 0.0f) : n == 2 ? make_float4(r.z, r.w, 0.0f, 0.0f) : make_float4(r.w, 0.0f, 0.0f, 0.0f);
+    }
 };
 template <> struct Elem<uint16_t> {   // bf16 bit patterns
     typedef uint2 raw;
+    typedef uint32_t raw_any __attribute__((ext_vector_type(2), aligned(2)));
     static __device__ __forceinline__ raw zero() { return make_uint2(0u, 0u); }
+    static __device__ __forceinline__ raw of(raw_any r) { return make_uint2(r.x, r.y); }
     static __device__ __forceinline__ float4 widen(raw u)
     {
         return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
                            __uint_as_float(u.y & 0xFFFF0000u));
     }
     static __device__ __forceinline__ float load1(const uint16_t *p) { return bf16_bits_to_f32(*p); }
-    static __device__ __forceinline__ raw pack(float a, float b, float c, float d)
+    static __device__ __forceinline__ raw drop(raw r, int n)
     {
-        return make_uint2((__float_as_uint(a) >> 16) | __float_as_uint(b), (__float_as_uint(c) >> 16) | __float_as_uint(d));
+        const uint64_t w = (((uint64_t)r.y << 32) | r.x) >> (16 * n);
+        return make_uint2((uint32_t)w, (uint32_t)(w >> 32));
     }
 };
 
@@ -49,7 +58,6 @@ struct ActArgs {
     float static_scale;
     int32_t M, K, K_o, n_off, kp;
     int32_t is_static;     // 1: static_scale for every row, no absmax
-    int32_t vec;           // 1: four elements of X and of perm at a time (see quant_act_kernel)
     int32_t store_wt;      // 1: Xq leaves through write-through stores (see store_q)
 };
 
@@ -98,10 +106,17 @@ __device__ __forceinline__ void quant_row_far(const ActArgs &a, const T *x, int8
     }
 }
 
-// Register-resident rows.  NT threads own a token row at a time, CH chunks of 4 channels per thread (K <= CH * NT * 4);
-// NT = 64: four independent rows per workgroup, no barrier.  PERM = false: the codes go straight from registers to
-// memory and no LDS image exists.  VEC: rows of X can be read four channels at a time and, where there is a permutation, perm
-// four entries at a time in packed order (no pads inside); else element by element.
+// How the packed row is put together.
+enum Order {
+    NATURAL,       // no permutation: the codes go straight from registers to memory and no LDS image exists
+    WHOLE_WORDS,   // four entries of perm at a time are four neighbours of the packed row: no pads before the end, perm 16-byte aligned
+    ANY_ORDER,     // pads anywhere (an outlier block that is no multiple of 32), perm at any address
+};
+
+// Register-resident rows.  NT threads own a token row at a time, CH chunks of 4 channels per thread (K <= 4 CH NT); NT = 64: four
+// independent rows per workgroup, no barrier.  X may have any width from 4 on, any stride and any alignment: a chunk is one load at
+// its element's address.  TAIL: K is no multiple of 4; a row's last chunk is loaded from its last four channels and moved down
+// when it is used, so that the loads stay free of branches that would wait for them.
 //
 // Bound by memory at large M (4680 x 8960 fp32, 210 MB from and to memory: 48 -> 42 us, the rate of a device copy; bf16
 // 57 -> 30), by latency at small M (256 x 1536: 5.6 -> 3.6 us; 4680 x 1536 bf16 11.0 -> 7.5): perm and the first row are
@@ -109,13 +124,16 @@ __device__ __forceinline__ void quant_row_far(const ActArgs &a, const T *x, int8
 // on.  (Before: codes scattered byte by byte through a channel -> position table built in LDS by every workgroup, a
 // branch to an IEEE division beside every quotient.  Fetching the four bytes with one v_perm_b32 under a selector
 // per dword instead of four byte reads costs more setting up than it saves: 15.5 us for the last case.)
-template <typename T, int CH, int NT, bool PERM, bool VEC>
+template <typename T, int CH, int NT, Order ORD, bool TAIL>
 __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act_kernel(ActArgs a)
 {
     typedef typename Elem<T>::raw raw;
+    constexpr bool PERM = ORD != NATURAL;
     constexpr int RW = NT == 64 ? 4 : 1, NWAVE = NT / 64;
+    constexpr int CP = ORD == ANY_ORDER ? CH + 1 : CH;       // chunks of the packed row: up to 31 + 127 pads
+    constexpr int ZERO = 4 * CH * NT;                        // (ANY_ORDER) image address of a zero, for the pads
     constexpr float MAGIC = 12582912.0f;       // 1.5 * 2^23: the sum rounds half-to-even, the code is its low byte
-    __shared__ __align__(16) uint32_t image[PERM ? (NT == 64 ? 4 : 2) : 1][PERM ? CH * NT : 1];
+    __shared__ uint32_t image[PERM ? (NT == 64 ? 4 : 2) : 1][PERM ? CH * NT + 1 : 1];      // codes in natural order
     __shared__ float red[2][NWAVE];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = NT == 64 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
@@ -129,38 +147,31 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int k = 4 * (t + c * NT);
-            if (k < K) {
-                if constexpr (VEC) {
-                    v[c] = *reinterpret_cast<const raw *>(reinterpret_cast<const char *>(x) + (uint32_t)k * (uint32_t)sizeof(T));
-                } else {
-                    v[c] = Elem<T>::pack(Elem<T>::load1(x + k), k + 1 < K ? Elem<T>::load1(x + k + 1) : 0.0f,
-                                         k + 2 < K ? Elem<T>::load1(x + k + 2) : 0.0f, k + 3 < K ? Elem<T>::load1(x + k + 3) : 0.0f);
-                }
-            }
+            if (k < K)
+                v[c] = Elem<T>::of(*reinterpret_cast<const typename Elem<T>::raw_any *>(
+                    reinterpret_cast<const char *>(x) + (uint32_t)(TAIL ? min(k, K - 4) : k) * (uint32_t)sizeof(T)));
         }
     };
 
-    // Channels of the four packed positions of this thread's dword t + c NT.  (An entry of perm outside [0, K), which makes the
-    // bytes undefined, is moved inside.)
-    int4 ch[PERM ? CH : 1];
+    // Channels of the four packed positions of this thread's dword t + c NT, which are their byte addresses in the image.  (An entry
+    // of perm outside [0, K), which makes the bytes undefined, is moved inside.)
+    int4 ch[PERM ? CP : 1];
     raw v[CH], vn[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) v[c] = vn[c] = Elem<T>::zero();
-    auto logical = [&](int p) {                    // packed position -> index into perm, -1 at pads
-        if (p < a.n_off) return p < a.K_o ? p : -1;
-        const int q = a.K_o + (p - a.n_off);
-        return q < K ? q : -1;
-    };
+    typedef int entries __attribute__((ext_vector_type(4), aligned(4)));
+    // (ANY_ORDER) index in perm of a dword's first position; its block (n_off is a multiple of 32) ends at index `end`
+    auto first_entry = [&](int p) { return p < a.n_off ? p : a.K_o + (p - a.n_off); };
     if constexpr (PERM) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
+        for (int c = 0; c < CP; ++c) {
             const int p = 4 * (t + c * NT);
-            if constexpr (VEC) {
+            if constexpr (ORD == WHOLE_WORDS) {
                 ch[c] = make_int4(0, 0, 0, 0);
                 if (p < K) ch[c] = *reinterpret_cast<const int4 *>(a.perm + p);
-            } else {
-                ch[c] = make_int4(a.perm[max(logical(p), 0)], a.perm[max(logical(p + 1), 0)], a.perm[max(logical(p + 2), 0)],
-                                  a.perm[max(logical(p + 3), 0)]);
+            } else {                               // four neighbours of perm, from the last four on where they would pass its end
+                const entries e = *reinterpret_cast<const entries *>(a.perm + min(first_entry(p), K - 4));
+                ch[c] = make_int4(e.x, e.y, e.z, e.w);
             }
         }
     }
@@ -168,11 +179,31 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
     if constexpr (PERM) {
         auto inside = [&](int k) { return (int)min((unsigned)k, (unsigned)(K - 1)); };
 #pragma unroll
-        for (int c = 0; c < CH; ++c) ch[c] = make_int4(inside(ch[c].x), inside(ch[c].y), inside(ch[c].z), inside(ch[c].w));
+        for (int c = 0; c < CP; ++c) {
+            if constexpr (ORD == ANY_ORDER) {
+                const int p = 4 * (t + c * NT), i = first_entry(p), end = p < a.n_off ? a.K_o : K;
+                const int by = i - (K - 4);        // > 0: the entries lie that much later in what was loaded
+                int4 e = ch[c];
+                if (by > 0) e = by == 1 ? make_int4(e.y, e.z, e.w, 0) : by == 2 ? make_int4(e.z, e.w, 0, 0) : make_int4(e.w, 0, 0, 0);
+                ch[c] = make_int4(i < end ? inside(e.x) : ZERO, i + 1 < end ? inside(e.y) : ZERO, i + 2 < end ? inside(e.z) : ZERO,
+                                  i + 3 < end ? inside(e.w) : ZERO);
+            } else {
+                ch[c] = make_int4(inside(ch[c].x), inside(ch[c].y), inside(ch[c].z), inside(ch[c].w));
+            }
+        }
+        // (read behind a barrier, or by the wave itself)
+        if (ORD == ANY_ORDER && t < (NT == 64 ? 1 : 2)) image[NT == 64 ? wave : t][CH * NT] = 0u;
     }
 
     for (int buf = 0; m < a.M; m += stride, buf ^= 1) {
         if (m + stride < a.M) load_row(m + stride, vn);        // flies under this row's work
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int k = 4 * (t + c * NT);
+                if (k < K && k > K - 4) v[c] = Elem<T>::drop(v[c], k - (K - 4));
+            }
+        }
         float s;
         if (a.is_static) {
             s = a.static_scale;
@@ -219,19 +250,12 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
                 if constexpr (NT > 64) __syncthreads();            // (one wave's LDS accesses complete in order)
                 const uint8_t *bytes = reinterpret_cast<const uint8_t *>(img);
 #pragma unroll
-                for (int c = 0; c < CH; ++c) {
+                for (int c = 0; c < CP; ++c) {
                     const int p = 4 * (t + c * NT);
                     if (p >= kp) continue;
-                    uint32_t w = (uint32_t)bytes[ch[c].x] | ((uint32_t)bytes[ch[c].y] << 8) | ((uint32_t)bytes[ch[c].z] << 16) |
+                    const uint32_t w = (uint32_t)bytes[ch[c].x] | ((uint32_t)bytes[ch[c].y] << 8) | ((uint32_t)bytes[ch[c].z] << 16) |
                                  ((uint32_t)bytes[ch[c].w] << 24);
-                    if constexpr (VEC) {
-                        w = p < K ? w : 0u;                        // (whole dwords of padding)
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (logical(p + e) < 0) w &= ~(0xFFu << (8 * e));
-                    }
-                    store_q(a, out + p, w);
+                    store_q(a, out + p, ORD == ANY_ORDER || p < K ? w : 0u);       // (whole dwords of padding)
                 }
             }
         }
@@ -240,7 +264,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
     }
 }
 
-// Rows of more than 16384 channels: one workgroup per row, two passes over it (the second is served by the cache), gather
+// Rows longer than the register kernels take, or shorter than one chunk: one workgroup per row, two passes over it (the second is served by the cache), gather
 // through perm from global memory.
 template <typename T>
 __global__ __launch_bounds__(TPB) void quant_act_generic_kernel(ActArgs a)
@@ -288,37 +312,56 @@ template <auto kern> int blocks_per_cu(int threads)
     return n;
 }
 
-template <typename T, int CH, int NT, bool PERM, bool VEC>
+template <typename T, int CH, int NT, Order ORD, bool TAIL>
 qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
 {
     constexpr int RW = NT == 64 ? 4 : 1, TH = NT == 64 ? 256 : NT;
     // as many workgroups as the chip holds, trimmed so that all of them walk the same number of rows
     // (4680 rows on 1024 slots: 936 workgroups of exactly 5 rows instead of 1024 of 4 or 5)
-    const int slots = num_cu() * blocks_per_cu<quant_act_kernel<T, CH, NT, PERM, VEC>>(TH);
+    const int slots = num_cu() * blocks_per_cu<quant_act_kernel<T, CH, NT, ORD, TAIL>>(TH);
     const int groups = (a.M + RW - 1) / RW;
     const int rounds = (groups + slots - 1) / slots;
-    hipLaunchKernelGGL((quant_act_kernel<T, CH, NT, PERM, VEC>), dim3((groups + rounds - 1) / rounds), dim3(TH), 0, st, a);
+    hipLaunchKernelGGL((quant_act_kernel<T, CH, NT, ORD, TAIL>), dim3((groups + rounds - 1) / rounds), dim3(TH), 0, st, a);
     return qarvd_launch_status();
 }
 
-template <typename T>
-qarvd_status dispatch(const ActArgs &a, hipStream_t st)
+// Threads and chunks for a row of `width` channels (ANY_ORDER) or packed bytes; no launch beyond the last width.
+template <typename T, Order ORD, bool TAIL>
+bool launch_by_width(const ActArgs &a, int width, hipStream_t st, qarvd_status *out)
 {
-    const int ext = a.kp;      // (without outliers up to 127 more than K: the threads of a row write its padding too)
-    if (a.perm && a.vec) {
-        // one wave per row while a row fits its registers, then the least threads that hold it at about 24 values each
-        if (ext <= 6 * 256) return launch_rows<T, 6, 64, true, true>(a, st);
-        if (ext <= 6 * 512) return launch_rows<T, 6, 128, true, true>(a, st);
-        if (ext <= 6 * 1024) return launch_rows<T, 6, 256, true, true>(a, st);
-        if (ext <= 5 * 2048) return launch_rows<T, 5, 512, true, true>(a, st);
-        if (ext <= 9 * 2048) return launch_rows<T, 9, 512, true, true>(a, st);
+    auto go = [&](qarvd_status s) {
+        *out = s;
+        return true;
+    };
+    if constexpr (ORD == NATURAL) {
+        // no image to share, little to set up: twice the threads for a row
+        if (width <= 3 * 512) return go(launch_rows<T, 3, 128, ORD, TAIL>(a, st));
+        if (width <= 3 * 1024) return go(launch_rows<T, 3, 256, ORD, TAIL>(a, st));
+        if (width <= 3 * 2048) return go(launch_rows<T, 3, 512, ORD, TAIL>(a, st));
     } else {
-        // no image to share, or element-wise loads that take many threads to keep in flight: twice the threads for a row
-        if (ext <= 3 * 512) return a.perm ? launch_rows<T, 3, 128, true, false>(a, st) : a.vec ? launch_rows<T, 3, 128, false, true>(a, st) : launch_rows<T, 3, 128, false, false>(a, st);
-        if (ext <= 3 * 1024) return a.perm ? launch_rows<T, 3, 256, true, false>(a, st) : a.vec ? launch_rows<T, 3, 256, false, true>(a, st) : launch_rows<T, 3, 256, false, false>(a, st);
-        if (ext <= 3 * 2048) return a.perm ? launch_rows<T, 3, 512, true, false>(a, st) : a.vec ? launch_rows<T, 3, 512, false, true>(a, st) : launch_rows<T, 3, 512, false, false>(a, st);
-        if (ext <= 5 * 2048) return a.perm ? launch_rows<T, 5, 512, true, false>(a, st) : a.vec ? launch_rows<T, 5, 512, false, true>(a, st) : launch_rows<T, 5, 512, false, false>(a, st);
-        if (ext <= 9 * 2048) return a.perm ? launch_rows<T, 9, 512, true, false>(a, st) : a.vec ? launch_rows<T, 9, 512, false, true>(a, st) : launch_rows<T, 9, 512, false, false>(a, st);
+        // one wave per row while a row fits its registers, then the least threads that hold it at about 24 values each
+        if (width <= 6 * 256) return go(launch_rows<T, 6, 64, ORD, TAIL>(a, st));
+        if (width <= 6 * 512) return go(launch_rows<T, 6, 128, ORD, TAIL>(a, st));
+        if (width <= 6 * 1024) return go(launch_rows<T, 6, 256, ORD, TAIL>(a, st));
+    }
+    if (width <= 5 * 2048) return go(launch_rows<T, 5, 512, ORD, TAIL>(a, st));
+    if (width <= 9 * 2048) return go(launch_rows<T, 9, 512, ORD, TAIL>(a, st));
+    return false;
+}
+
+template <typename T>
+qarvd_status dispatch(const ActArgs &a, bool whole_words, hipStream_t st)
+{
+    qarvd_status s = QARVD_OK;
+    const bool tail = a.K % 4 != 0;
+    if (a.K >= 4) {
+        if (!a.perm) {
+            if (tail ? launch_by_width<T, NATURAL, true>(a, a.kp, st, &s) : launch_by_width<T, NATURAL, false>(a, a.kp, st, &s)) return s;
+        } else if (whole_words) {
+            if (launch_by_width<T, WHOLE_WORDS, false>(a, a.kp, st, &s)) return s;
+        } else {
+            if (tail ? launch_by_width<T, ANY_ORDER, true>(a, a.K, st, &s) : launch_by_width<T, ANY_ORDER, false>(a, a.K, st, &s)) return s;
+        }
     }
     int grid = a.M < num_cu() * 8 ? a.M : num_cu() * 8;
     hipLaunchKernelGGL((quant_act_generic_kernel<T>), dim3(grid), dim3(TPB), 0, st, a);
@@ -344,10 +387,9 @@ qarvd_status quant_act_common(const void *X, qarvd_dtype xdt, int32_t M, int32_t
     a.M = M; a.K = K; a.K_o = K_o; a.n_off = g.n_off; a.kp = g.kp;
     a.store_wt = ((size_t)M * (size_t)g.kp <= ((size_t)40 << 20) && (size_t)M * (size_t)ldxq < ((size_t)1 << 31)) ? 1 : 0;
     a.is_static = is_static ? 1 : 0;
-    a.vec = (K % 4 == 0) && (ldx % 4 == 0) && (reinterpret_cast<uintptr_t>(X) % (4 * esz)) == 0 &&
-            (!perm || (g.n_off == K_o && qarvd_aligned16(perm))) ? 1 : 0;
+    const bool whole_words = K % 4 == 0 && g.n_off == K_o && qarvd_aligned16(perm);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    return xdt == QARVD_F32 ? dispatch<float>(a, st) : dispatch<uint16_t>(a, st);
+    return xdt == QARVD_F32 ? dispatch<float>(a, whole_words, st) : dispatch<uint16_t>(a, whole_words, st);
 }
 
 }  // namespace

@@ -35,7 +35,9 @@ def check(X, Xd, perm, K_o):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("K", [1, 4, 130, 1532, 1536, 1537, 1540, 3072, 3073, 3076, 6144, 6148, 10240, 10244, 16384, 16388])
+@pytest.mark.parametrize("K", [1, 3, 4, 5, 130, 256, 257, 512, 513, 1024, 1025, 1532, 1536, 1537, 1540, 2048, 2049, 3072, 3073, 3076,
+                               5120, 5121, 6144, 6148, 10240, 10244, 12288, 12290, 14336, 14339, 16384, 16388, 18400, 18432,
+                               18433, 18436, 20480, 20481, 20484])
 def test_row_widths(K, dtype):
     X, Xd, rng = make(9, K, K, dtype)
     check(X, Xd, None, 0)
@@ -58,6 +60,27 @@ def test_unaligned_rows_and_odd_strides():
     big = torch.zeros((33, 1005), device="cuda")
     big[:, 3:1004] = dev(X)
     check(X, big[:, 3:1004], rng.permutation(1001).astype(np.int32), 31)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", [4, 259, 1000, 1536, 2362, 8960, 13825])
+def test_rows_and_permutations_at_any_address(K, dtype):
+    """X one to three elements off its alignment, strides that move it from row to row, perm off its own."""
+    X, Xd, rng = make(11, K, 3 * K, dtype)
+    for K_o in sorted({0, min(K, 32), min(K, 37), K}):
+        sel = np.sort(rng.choice(K, K_o, replace=False))
+        perm = np.concatenate([sel, np.setdiff1d(np.arange(K), sel)]).astype(np.int32)
+        ref, sx = oracle.quant_act(X, perm)
+        for off, pad in ((0, 1), (1, 0), (2, 3), (3, 2)):
+            big = torch.full((11, K + off + pad), 1e6, dtype=dtype, device="cuda")
+            big[:, off:off + K] = Xd
+            pd = torch.zeros(K + 4, dtype=torch.int32, device="cuda")[off:off + K]
+            pd.copy_(dev(perm))
+            Xq, s = q.quant_act(big[:, off:off + K], pd, K_o)
+            assert np.array_equal(s.cpu().numpy().view(np.uint32), sx.view(np.uint32))
+            assert np.array_equal(logical(Xq, K, K_o), ref)
+            if K_o == 0:                       # (the permutation is the identity)
+                assert torch.equal(q.quant_act(big[:, off:off + K], None, 0)[0][:, :K], Xq[:, :K])
 
 
 @pytest.mark.parametrize("K", [1536, 8960])
