@@ -165,8 +165,8 @@ qarvd_status qarvd_quantize_weight_static(const float *W, int32_t N, int32_t K, 
  *   X     in   [M, ldx] of `xdt` (QARVD_F32 or QARVD_BF16; bf16 is widened exactly first)
  *   perm  in   i32 [K] or NULL (identity; K_o must then be 0)
  *   Xq    out  i8 [M, ldxq] packed for (K, K_o);  s_x out f32 [M]
- * Fully asynchronous on `stream`.  Up to K = 16384 a row stays in registers, whatever its width and alignment
- * (rows that are not 16-byte (fp32) / 8-byte (bf16) aligned load element by element); longer rows are read twice.
+ * Fully asynchronous on `stream`.  A row of up to 20480 channels (and packed bytes) stays in registers, whatever its
+ * width and alignment; longer rows are read twice.
  */
 qarvd_status qarvd_quant_act(const void *X, qarvd_dtype xdt, int32_t M, int32_t K, int64_t ldx,
                              const int32_t *perm, int32_t K_o, int8_t *Xq, int64_t ldxq,

@@ -121,11 +121,17 @@ enum Order {
 // Bound by memory at large M (4680 x 8960 fp32, 210 MB from and to memory: 48 -> 42 us, the rate of a device copy; bf16
 // 57 -> 30), by latency at small M (256 x 1536: 5.6 -> 3.6 us; 4680 x 1536 bf16 11.0 -> 7.5): perm and the first row are
 // requested together and perm is used as it arrives, and the next row of a wave is requested before the current one is worked
-// on.  (Before: codes scattered byte by byte through a channel -> position table built in LDS by every workgroup, a
+// on (NATURAL: once its maximum is known; with eight waves on a SIMD the other rows cover the wait, and that order needs
+// fewer registers: 4680 x 5120 bf16 24.4 -> 18.2 us).  (Before: codes scattered byte by byte through a channel -> position table built in LDS by every workgroup, a
 // branch to an IEEE division beside every quotient.  Fetching the four bytes with one v_perm_b32 under a selector
 // per dword instead of four byte reads costs more setting up than it saves: 15.5 us for the last case.)
+// Waves on a SIMD that the registers have to leave room for: as many as run without spilling more than a few.
+template <typename T, int CH, int NT, Order ORD> constexpr int waves_per_simd()
+{
+    return ORD != NATURAL || CH * NT > 4096 ? (CH > 6 ? 3 : 4) : sizeof(T) == 2 || CH <= 3 ? 8 : 6;
+}
 template <typename T, int CH, int NT, Order ORD, bool TAIL>
-__global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act_kernel(ActArgs a)
+__global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD>())) void quant_act_kernel(ActArgs a)
 {
     typedef typename Elem<T>::raw raw;
     constexpr bool PERM = ORD != NATURAL;
@@ -196,7 +202,10 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
     }
 
     for (int buf = 0; m < a.M; m += stride, buf ^= 1) {
-        if (m + stride < a.M) load_row(m + stride, vn);        // flies under this row's work
+        auto request_next = [&]() {                            // flies under this row's work
+            if (m + stride < a.M) load_row(m + stride, vn);
+        };
+        if constexpr (PERM) request_next();
         if constexpr (TAIL) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
@@ -204,16 +213,16 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
                 if (k < K && k > K - 4) v[c] = Elem<T>::drop(v[c], k - (K - 4));
             }
         }
-        float s;
-        if (a.is_static) {
-            s = a.static_scale;
-        } else {
-            float amax = 0.0f;
+        float s = a.static_scale, amax = 0.0f;
+        if (!a.is_static) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) {                     // (zeros past the end of the row)
                 const float4 f = Elem<T>::widen(v[c]);
                 amax = fmaxf(amax, fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w))));
             }
+        }
+        if constexpr (!PERM) request_next();
+        if (!a.is_static) {
             amax = wave_max_all(amax);
             if constexpr (NT > 64) {
                 if ((threadIdx.x & 63) == 0) red[buf][wave] = amax;
@@ -264,8 +273,8 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, CH > 6 ? 3 : 4) void quant_act
     }
 }
 
-// Rows longer than the register kernels take, or shorter than one chunk: one workgroup per row, two passes over it (the second is served by the cache), gather
-// through perm from global memory.
+// Rows of more than 20480 channels or packed bytes, or of less than one chunk: one workgroup per row, two passes over it (the
+// second is served by the cache), gather through perm from global memory.
 template <typename T>
 __global__ __launch_bounds__(TPB) void quant_act_generic_kernel(ActArgs a)
 {
@@ -325,7 +334,11 @@ qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
     return qarvd_launch_status();
 }
 
-// Threads and chunks for a row of `width` channels (ANY_ORDER) or packed bytes; no launch beyond the last width.
+// Threads and chunks for a row of `width` channels (ANY_ORDER) or packed bytes; no launch beyond the last width.  A row that
+// fits one wave runs without barriers, and work on chunks that hold no channel costs as much as on those that do, so the steps are
+// the narrowest of those that pay: time for 4680 rows of 256, fp32, against six chunks for all rows of one wave 6.4 -> 4.1 us
+// (NATURAL 5.9 -> 4.2), bf16 13824 wide on 7 x 512 or 4 x 1024 against 9 x 512 45.8 -> 42.2 (NATURAL 45.2 -> 40.0), 20000 wide
+// against two passes over the row 237 -> 62.  NATURAL takes more threads a row: nothing is set up per thread there.
 template <typename T, Order ORD, bool TAIL>
 bool launch_by_width(const ActArgs &a, int width, hipStream_t st, qarvd_status *out)
 {
@@ -333,19 +346,32 @@ bool launch_by_width(const ActArgs &a, int width, hipStream_t st, qarvd_status *
         *out = s;
         return true;
     };
+    if (width <= 1 * 256) return go(launch_rows<T, 1, 64, ORD, TAIL>(a, st));
+    if (width <= 2 * 256) return go(launch_rows<T, 2, 64, ORD, TAIL>(a, st));
     if constexpr (ORD == NATURAL) {
-        // no image to share, little to set up: twice the threads for a row
-        if (width <= 3 * 512) return go(launch_rows<T, 3, 128, ORD, TAIL>(a, st));
+        if (width <= 2 * 512) return go(launch_rows<T, 2, 128, ORD, TAIL>(a, st));
+        if (width <= 2 * 1024) return go(launch_rows<T, 2, 256, ORD, TAIL>(a, st));
         if (width <= 3 * 1024) return go(launch_rows<T, 3, 256, ORD, TAIL>(a, st));
         if (width <= 3 * 2048) return go(launch_rows<T, 3, 512, ORD, TAIL>(a, st));
+        if constexpr (sizeof(T) == 4) {
+            if (width <= 3 * 4096) return go(launch_rows<T, 3, 1024, ORD, TAIL>(a, st));
+        } else {
+            if (width <= 5 * 2048) return go(launch_rows<T, 5, 512, ORD, TAIL>(a, st));
+        }
     } else {
-        // one wave per row while a row fits its registers, then the least threads that hold it at about 24 values each
+        if (width <= 4 * 256) return go(launch_rows<T, 4, 64, ORD, TAIL>(a, st));
         if (width <= 6 * 256) return go(launch_rows<T, 6, 64, ORD, TAIL>(a, st));
-        if (width <= 6 * 512) return go(launch_rows<T, 6, 128, ORD, TAIL>(a, st));
+        if (width <= 3 * 1024) return go(launch_rows<T, 3, 256, ORD, TAIL>(a, st));
+        if (width <= 5 * 1024) return go(launch_rows<T, 5, 256, ORD, TAIL>(a, st));
         if (width <= 6 * 1024) return go(launch_rows<T, 6, 256, ORD, TAIL>(a, st));
+        if (width <= 5 * 2048) return go(launch_rows<T, 5, 512, ORD, TAIL>(a, st));
+        if (width <= 7 * 2048) return go(launch_rows<T, 7, 512, ORD, TAIL>(a, st));
     }
-    if (width <= 5 * 2048) return go(launch_rows<T, 5, 512, ORD, TAIL>(a, st));
-    if (width <= 9 * 2048) return go(launch_rows<T, 9, 512, ORD, TAIL>(a, st));
+    if (width <= 4 * 4096) return go(launch_rows<T, 4, 1024, ORD, TAIL>(a, st));
+    if constexpr (ORD != NATURAL && sizeof(T) == 2) {
+        if (width <= 9 * 2048) return go(launch_rows<T, 9, 512, ORD, TAIL>(a, st));
+    }
+    if (width <= 5 * 4096) return go(launch_rows<T, 5, 1024, ORD, TAIL>(a, st));
     return false;
 }
 
