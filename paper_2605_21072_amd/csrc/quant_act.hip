@@ -23,6 +23,7 @@ template <> struct Elem<float> {
     typedef float raw_any __attribute__((ext_vector_type(4), aligned(4)));
     static __device__ __forceinline__ raw zero() { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
     static __device__ __forceinline__ raw of(raw_any r) { return make_float4(r.x, r.y, r.z, r.w); }
+    static __device__ __forceinline__ raw scale(raw r, float f) { return make_float4(r.x * f, r.y * f, r.z * f, r.w * f); }
     static __device__ __forceinline__ float4 widen(raw r) { return r; }
     static __device__ __forceinline__ float load1(const float *p) { return *p; }
     static __device__ __forceinline__ raw drop(raw r, int n)        // the first n elements, 0 < n < 4, moved out, zeros behind
@@ -39,6 +40,12 @@ template <> struct Elem<uint16_t> {   // bf16 bit patterns
     {
         return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
                            __uint_as_float(u.y & 0xFFFF0000u));
+    }
+    static __device__ __forceinline__ raw scale(raw u, float f)      // f a power of two: eight significant bits stay eight
+    {
+        const float4 w = widen(u);
+        return make_uint2((__float_as_uint(w.x * f) >> 16) | (__float_as_uint(w.y * f) & 0xFFFF0000u),
+                          (__float_as_uint(w.z * f) >> 16) | (__float_as_uint(w.w * f) & 0xFFFF0000u));
     }
     static __device__ __forceinline__ float load1(const uint16_t *p) { return bf16_bits_to_f32(*p); }
     static __device__ __forceinline__ raw drop(raw r, int n)
@@ -88,8 +95,7 @@ __device__ __forceinline__ float block_max(float v, float *red)
     return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// One row with IEEE divisions and channels gathered from memory: scales outside the range of the exact quotient (rows of
-// magnitudes around 1e-28 and below, or with infinities), and the rows of the general kernel below.
+// One row with IEEE divisions and channels gathered from memory: rows with infinities, and the rows of the general kernel below.
 template <typename T>
 __device__ __forceinline__ void quant_row_far(const ActArgs &a, const T *x, int8_t *out, float s, int t, int nt)
 {
@@ -234,8 +240,16 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD
             if (t == 0) a.s_x[m] = s;
         }
         const size_t out = (size_t)m * a.ldxq;         // byte offset of the row in Xq
-        const ExactQuotient q(s, 127.0f);
-        if (!q.exact()) {                              // (uniform over the row)
+        ExactQuotient q(s, 127.0f);
+        if (!q.exact() && s < __builtin_inff()) {      // (uniform over the row)
+            // Row and scale times the same power of two: no quotient changes.  Up: exact, or infinite and clipped as before.  Down
+            // (s > 1e30): values that lose bits lie below 1e-9 and have the code 0 either way.
+            const float f = s < 1.0f ? 0x1p96f : 0x1p-96f;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) v[c] = Elem<T>::scale(v[c], f);
+            q = ExactQuotient(s * f, 127.0f);
+        }
+        if (!q.exact()) {                              // an infinity in the row
             quant_row_far<T>(a, X + (size_t)m * a.ldx, a.Xq + out, s, t, NT);
             if constexpr (PERM && NT > 64) __syncthreads();        // as many barriers as the other path
         } else {

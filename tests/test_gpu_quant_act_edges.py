@@ -83,14 +83,30 @@ def test_rows_and_permutations_at_any_address(K, dtype):
                 assert torch.equal(q.quant_act(big[:, off:off + K], None, 0)[0][:, :K], Xq[:, :K])
 
 
-@pytest.mark.parametrize("K", [1536, 8960])
-def test_scales_outside_the_exact_quotients_range(K):
-    X, _, rng = make(12, K, 7, torch.float32)
-    X = (X.astype(np.float64) * np.array([1, 1e-29, 1e-36, 1e-42, 1e33, 1] * 2)[:, None]).astype(np.float32)
-    X[5] = 0
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", [261, 1536, 8960])
+def test_scales_outside_the_exact_quotients_range(K, dtype):
+    """Rows of every magnitude a type holds, down to its denormals, and static scales that such a row has next to one of
+    ordinary size; rows with infinities."""
+    X, _, rng = make(18, K, 7, torch.float32)
+    powers = np.array([1, 1e-29, 1e-30, 1e-33, 1e-36, 1e-38, 1e-40, 1e-42, 1e-44, 1e29, 1e31, 1e33, 1e36, 1, 1, 1, 1, 1])
+    X = (X.astype(np.float64) * powers[:, None]).astype(np.float32)
+    X[13] = 0
+    X[14, ::2] *= np.float32(1e-36)
+    X[15, ::2] *= np.float32(1e34)
+    X[16, 5] = np.inf
+    X[17, 7], X[17, 9] = -np.inf, 1e-40
+    Xd = dev(X).to(dtype)
+    X = Xd.float().cpu().numpy()
     perm = rng.permutation(K).astype(np.int32)
-    for p, K_o in ((perm, 64), (None, 0)):
-        ref, sx = oracle.quant_act(X, p)
-        Xq, s = q.quant_act(dev(X), None if p is None else dev(p), K_o)
+    for p, K_o in ((perm, 64), (perm, 37), (None, 0)):
+        pd = None if p is None else dev(p)
+        with np.errstate(invalid="ignore"):
+            ref, sx = oracle.quant_act(X, p)
+        Xq, s = q.quant_act(Xd, pd, K_o)
         assert np.array_equal(s.cpu().numpy().view(np.uint32), sx.view(np.uint32))
-        assert np.array_equal(logical(Xq, K, K_o), ref)
+        defined = np.isfinite(X if p is None else X[:, p])            # (an infinity over an infinite scale has no code)
+        assert np.array_equal(logical(Xq, K, K_o)[defined], ref[defined])
+        for scale in (np.float32(1e-45), np.float32(3e-39), np.float32(2e-31), np.float32(1e-30), np.float32(3e30), np.float32(3e38)):
+            got = q.quant_act_static(Xd, pd, K_o, float(scale))
+            assert np.array_equal(logical(got, K, K_o), oracle.quant_act_static(X, scale, p)), scale
