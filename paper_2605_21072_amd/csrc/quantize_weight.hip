@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void norm_partial_kernel(const float *__restri
 // Pass 2: 64 columns per workgroup, four threads per column.  With S the parallel sum and n = N terms, both S and the
 // ordered sum are within n u / (1 - n u) of the exact one (u = 2^-53), so the ordered sum lies in
 // S (1 -+ 2.5 (n + 2) u), which leaves room for the roundings of the bounds themselves.  sqrt and the conversion
-// to float are monotone: equal ends mean that the ordered sum gives this float.  (NaN fails the test.)
+// to float are monotone: equal ends mean that the ordered sum gives this float.  A sum is NaN if a term is, in any order.
 __global__ __launch_bounds__(256) void norm_final_kernel(const double *__restrict__ partial, int chunks,
                                                          const float *__restrict__ W, int N, int K, int64_t ldw,
                                                          float *__restrict__ v, float *__restrict__ v_out)
@@ -112,8 +112,9 @@ __global__ __launch_bounds__(256) void norm_final_kernel(const double *__restric
         S = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
         const double e = 2.5 * ((double)N + 2.0) * 0x1p-53;
         const float lo = (float)sqrt(S * (1.0 - e)), hi = (float)sqrt(S * (1.0 + e));
-        const unsigned long long bad = __ballot(k < K && !(lo == hi));
-        if (k < K && lo == hi) {
+        const bool settled = lo == hi || S != S;
+        const unsigned long long bad = __ballot(k < K && !settled);
+        if (k < K && settled) {
             v[k] = lo;
             if (v_out) v_out[k] = lo;
         }

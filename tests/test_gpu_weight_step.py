@@ -67,6 +67,19 @@ def test_norm_half_way_between_two_floats():
     check(rows)
 
 
+def test_a_column_with_a_nan_has_a_nan_norm_and_leaves_the_others_alone():
+    L = wl.small_random_case(5350, 1, 700, 1536, 9)
+    v = oracle.quantize_weight(L["W"])["v"]
+    W = L["W"].copy()
+    cols = [0, 63, 64, 700, 1535]
+    W[np.arange(5) * 99, cols] = np.nan
+    for clip in (False, True):
+        got = q.quantize_weight(dev(W), clip_search=clip).v.cpu().numpy()
+        assert np.all(np.isnan(got[cols]))
+        rest = np.setdiff1d(np.arange(1536), cols)
+        assert np.array_equal(got[rest].view(np.uint32), v[rest].view(np.uint32))
+
+
 @pytest.mark.parametrize("scale", [1e-34, 3e-31, 1e31])
 def test_scales_outside_the_exact_quotients_range(scale):
     L = wl.small_random_case(5400, 1, 40, 1536, 9)
