@@ -630,8 +630,9 @@ __global__ __launch_bounds__(256) void weight_rows_long_kernel(RowsArgs a)
 // LDS and are ranked there.
 // The three sums are taken in parallel.  They decide an integer, so a comparison counts only where it holds for every order of
 // summation: serial and parallel sums are both within n u / (1 - n u) of the exact one (u = 2^-53; e^2 is exact).
-// Candidates with equal scales have equal sums term by term.  Anything else (intervals that overlap, NaN) is summed
-// in order by one thread.  Bound by the latency of its phases (14 us a row) and by vector-ALU issue (about 35
+// Candidates with equal scales have equal sums term by term.  Anything else (intervals that overlap, scales outside the exact
+// quotient's range, NaN) is summed in order: the errors taken by the whole workgroup, then one thread per candidate (1536 x 8960 with
+// every row so: 0.35 ms a call; with the gather and the quotients in that thread too 8.2).  Bound by the latency of its phases (14 us a row) and by vector-ALU issue (about 35
 // instructions per value), so one row per workgroup and registers held low enough for three workgroups per CU (1536 x 8960:
 // 50 us; with the offsets kept for three rows 79, one workgroup per CU).
 constexpr int CLIP_MAX_T = 20, CLIP_CAND = 512;
@@ -644,7 +645,8 @@ __global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(Ro
     __shared__ float gmax[2][G], top[2][CLIP_MAX_T], redf[NWAVE], scale[2][3], chosen[2];
     __shared__ __align__(16) float cand[2][CLIP_CAND];
     __shared__ double sums[2][NWAVE][3];
-    __shared__ int n_cand[2], redi[NWAVE];
+    __shared__ float err[3][NT];
+    __shared__ int n_cand[2], redi[NWAVE], open[2];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int K_o = a.sc->K_o;
     PackedRow<CH, NT> pr;
@@ -816,25 +818,45 @@ __global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(Ro
             const bool one = less(s1, q1, s2, q2);
             float best = one ? s1 : s2;
             if (less(s0, q0, best, one ? q1 : q2)) best = s0;
-            if (!proven) {
-                q0 = q1 = q2 = 0.0;
-                for (int p = blk ? K_o : 0, end = p + n; p < end; ++p) {
-                    const float f = w[a.perm[p]];
-                    const double d0 = (double)fmaf(-s0, (float)quantize_sym(f, s0, a.qmax), f);
-                    const double d1 = (double)fmaf(-s1, (float)quantize_sym(f, s1, a.qmax), f);
-                    const double d2 = (double)fmaf(-s2, (float)quantize_sym(f, s2, a.qmax), f);
-                    q0 = fma(d0, d0, q0);
-                    q1 = fma(d1, d1, q1);
-                    q2 = fma(d2, d2, q2);
-                }
-                best = q1 < q2 ? s1 : s2;
-                if (q0 < (q1 < q2 ? q1 : q2)) best = s0;
-            }
+            open[blk] = proven ? 0 : 1;
             if (n == 0) best = 0.0f;
             chosen[blk] = best;
-            (blk ? a.s_normal : a.s_outlier)[row] = best;
         }
         __syncthreads();
+#pragma unroll 1
+        for (int blk = 0; blk < 2; ++blk) {
+            if (!open[blk]) continue;
+            // in order: all threads take errors, NT values at a time, and thread c sums those of candidate c
+            const int n = block_n(blk);
+            double T = 0.0;
+            for (int p0 = 0; p0 < n; p0 += NT) {
+                if (p0 + t < n) {
+                    const float f = w[a.perm[(blk ? K_o : 0) + p0 + t]];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) err[c][t] = fmaf(-scale[blk][c], (float)quantize_sym(f, scale[blk][c], a.qmax), f);
+                }
+                __syncthreads();
+                if (t < 3) {
+                    const int lim = min(NT, n - p0);
+#pragma unroll 8
+                    for (int i = 0; i < lim; ++i) {
+                        const double d = (double)err[t][i];
+                        T = fma(d, d, T);
+                    }
+                }
+                __syncthreads();
+            }
+            if (t < 3) sums[blk][0][t] = T;
+            __syncthreads();
+            if (t == 0) {
+                const double q0 = sums[blk][0][0], q1 = sums[blk][0][1], q2 = sums[blk][0][2];
+                float best = q1 < q2 ? scale[blk][1] : scale[blk][2];
+                if (q0 < (q1 < q2 ? q1 : q2)) best = scale[blk][0];
+                chosen[blk] = best;
+            }
+            __syncthreads();
+        }
+        if (t < 2) (t ? a.s_normal : a.s_outlier)[row] = chosen[t];
         const ExactQuotient qo(chosen[0], a.qmax), qn(chosen[1], a.qmax);
         if (qo.exact() && qn.exact()) store_codes<CH, NT>(a, pr, x, row, lane, qo, qn);
         else store_codes_far<NT>(a, row, t, K_o, chosen[0], chosen[1]);

@@ -29,7 +29,7 @@ def check(W, **kw):
     return o
 
 
-@pytest.mark.parametrize("K", [1, 3, 255, 1536, 1537, 2560, 2561, 5120, 5121, 9216, 9217, 16384, 16385, 20001])
+@pytest.mark.parametrize("K", [1, 3, 255, 1536, 1537, 2560, 2561, 5120, 5121, 9216, 9217, 16384, 16385, 18400, 18432, 18433, 20001])
 def test_channel_counts_at_the_kernels_edges(K):
     L = wl.small_random_case(5000 + K, 1, 21, K, min(K // 50, 40))
     check(L["W"])
@@ -80,13 +80,15 @@ def test_a_column_with_a_nan_has_a_nan_norm_and_leaves_the_others_alone():
         assert np.array_equal(got[rest].view(np.uint32), v[rest].view(np.uint32))
 
 
-@pytest.mark.parametrize("scale", [1e-34, 3e-31, 1e31])
-def test_scales_outside_the_exact_quotients_range(scale):
-    L = wl.small_random_case(5400, 1, 40, 1536, 9)
+@pytest.mark.parametrize("K", [1536, 8960, 12000])
+@pytest.mark.parametrize("scale", [1e-38, 1e-34, 3e-31, 1e31, 1e35])
+def test_scales_outside_the_exact_quotients_range(scale, K):
+    L = wl.small_random_case(5400, 1, 40, K, 9)
     W = (L["W"].astype(np.float64) * scale).astype(np.float32)
     W[3] = L["W"][3]                                                     # one ordinary row among them
     check(W)
     check(W, clip_search=True)
+    check(W, forced_mask=(np.arange(K) % 13 == 0).astype(np.uint8), clip_search=True)
 
 
 @pytest.mark.parametrize("K", [700, 8960])
