@@ -5,6 +5,8 @@ using namespace qarvd_gemm;
 
 namespace {
 
+// Kernels that a call can ask for by number.  pick_variant chooses among 9, 10, 19 to 22 and 27 to 38, with 1 to 4 for
+// strides beyond 2^22; the others stay selectable for comparison.
 const Variant kVariants[] = {
     // name, BM, BN, widest outlier block (packed bytes), needs vector output, operand strides up to 2^22, launcher
     {"staged 256x128 dual", 256, 128, 1 << 30, false, false, launch_staged<256, 128, 2, 2, true>},
@@ -75,8 +77,10 @@ bool variant_fits(const Variant &v, const GemmArgs &g, qarvd_dtype ydt)
 // the CUs already accounts for).  All but two of the tiles run on 128-byte-deep stages (gemm_dma128.hip):
 // 256x256 has the cheapest K step per MAC and wins when N is wide; the half tiles fill the chip when N = 1536
 // (4680 x 8960 -> 1536: 60 us against 78 us for 256x256) and on M of a few hundred rows with N = 8960; 128x128 on eight
-// waves when those leave CUs empty over a long K (1560 x 8960 -> 1536: 31 us, 45 for the four-wave 128x128 tile
-// on 64-byte stages that this one replaces); 64x64 when even those would leave most without a tile (520 x 8960 -> 1536:
+// waves when those leave CUs empty over a long K (1560 x 8960 -> 1536: 31 us, 45 for the four-wave 128x128 tile on 64-byte
+// stages), the four-wave one while a packed row is at most 512 bytes: little loop to speed up, and two of its workgroups on a CU
+// cover each other's lead-in and epilogue (1634 x 352 -> 5088: 11.3 against 13.8, 4070 x 120 -> 1728: 6.7 against 7.3; but 3403 x
+// 678 -> 2624: 23.8 against 20.9); 64x64 when even those would leave most without a tile (520 x 8960 -> 1536:
 // 20.5 us, 24.2 on 64-byte stages).  Up to K of about 1600 the 64-byte-stage 64x64 tile is the faster
 // one (256 x 1536 -> 1536: 6.5 against 6.6 us, 16 x 256 -> 256: 3.8 against 4.2), and at any K while a quarter of the CUs or
 // fewer have a tile: the loads then wait for latency, not for lines, and six stages reach further than four (64 x 8960 ->
@@ -115,15 +119,17 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
 {
     const bool dual = g.n_off > 0;
     if (g.n_off <= 128 && vector_out_ok(g, ydt)) {
-        const Cand cand[7] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
-                              {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
-                              {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
-                              {dual ? 33 : 34, 128, 128, 1.6, 3.2, 0.200},
-                              {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
-                              {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152},
-                              {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120}};
         const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-        return cheapest(cand, tiles64 * 4 > device_cus() ? 7 : 6, g);
+        Cand cand[8] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
+                        {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
+                        {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
+                        {dual ? 33 : 34, 128, 128, 1.6, 3.2, 0.200},
+                        {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
+                        {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
+        int n = 6;
+        if (tiles64 * 4 > device_cus()) cand[n++] = {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120};
+        if (g.kp <= 512) cand[n++] = {dual ? 9 : 10, 128, 128, 2.0, 1.9, 0.309};
+        return cheapest(cand, n, g);
     }
     if (short_rows_ok(g)) {
         const Cand cand[2] = {{37, 128, 128, 1.8, 3.6, 0.200}, {38, 64, 64, 3.0, 1.0, 0.125}};
@@ -213,6 +219,7 @@ struct W4Variant {
     qarvd_status (*single)(const GemmArgs &, qarvd_dtype, hipStream_t);
 };
 const W4Variant kW4Variants[] = {
+    // 64-byte stages; the first is chosen by number only
     {256, 256, 0, launch_dma<256, 256, 2, 4, 4, true, true>, launch_dma<256, 256, 2, 4, 4, false, true>},
     {128, 128, 0, launch_dma<128, 128, 2, 2, 4, true, true>, launch_dma<128, 128, 2, 2, 4, false, true>},
     // register-staged: any N, any outlier-block width, any output alignment, any stride
@@ -243,13 +250,16 @@ extern "C" qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, con
         return s_c;
     const bool fast_ok = g.n_off <= 128 && g.vec_out;
     if (variant == 0) {
-        // the cost model of the INT8 path on the 128-byte-stage tiles.  An INT4 weight stage is half as wide, so 256x256 has room
-        // for three stages and less LDS traffic a K step: 4680 x 5120 -> 13824 279 us (64-byte stages 309, INT8 weights
-        // 303); 4680 x 1536 -> 1536 15.8 (19.3), 520 x 8960 -> 1536 23.6 (41.7), 64 x 5120 -> 5120 15.1 (24.6);
-        // 2251 x 2360 -> 2252 with 150 outliers 27.0 against 65.6 register-staged, which keeps strides beyond 2^22
-        const Cand cand[5] = {{7, 128, 128, 1.8, 3.6, 0.205}, {8, 64, 64, 3.4, 1.1, 0.135},
-                              {4, 256, 256, 7.2, 9.2, 0.443}, {5, 256, 128, 4.5, 3.6, 0.379}, {6, 128, 256, 3.9, 3.9, 0.381}};
-        variant = short_rows_ok(g) ? cheapest(cand, fast_ok ? 5 : 2, g) : 3;
+        // The cost model of the INT8 path; the three aligned tiles on 128-byte stages carry its constants, which were not fitted
+        // again for INT4.  An INT4 weight stage is half as wide, so 256x256 has room for three stages and less LDS traffic a K step:
+        // 4680 x 5120 -> 13824 279 us (64-byte stages 309, INT8 weights 303); 4680 x 1536 -> 1536 15.8 (19.3), 520 x 8960 -> 1536
+        // 23.6 (41.7), 64 x 5120 -> 5120 15.1 (24.6); 2251 x 2360 -> 2252 with 150 outliers 27.0 against 65.6 register-staged,
+        // which keeps strides beyond 2^22.  Up to packed rows of 768 bytes the four-wave 128x128 tile on 64-byte stages is a
+        // candidate too, for the reason it is one there (1560 x 128 -> 5120: 9.5 against 12.1, 1780 x 640 -> 1160: 8.3 against 8.6).
+        const Cand cand[6] = {{7, 128, 128, 1.8, 3.6, 0.205}, {8, 64, 64, 3.4, 1.1, 0.135},
+                              {4, 256, 256, 7.2, 9.2, 0.443}, {5, 256, 128, 4.5, 3.6, 0.379}, {6, 128, 256, 3.9, 3.9, 0.381},
+                              {2, 128, 128, 3.4, 1.5, 0.309}};
+        variant = !short_rows_ok(g) ? 3 : cheapest(cand, !fast_ok ? 2 : g.kp <= 768 ? 6 : 5, g);
     }
     const int form = kW4Variants[variant - 1].form;
     if ((form == 0 && !fast_ok) || (form == 1 && !short_rows_ok(g))) return QARVD_ERR_UNSUPPORTED;     // a tile asked for by name
