@@ -106,7 +106,8 @@ int32_t qarvd_packed_k(int32_t K, int32_t K_o);
  */
 int32_t qarvd_packed_ld(int32_t K, int32_t K_o);
 
-/* Bytes of device workspace qarvd_quantize_weight needs for an [N,K] layer. */
+/* Bytes of device workspace qarvd_quantize_weight needs for an [N,K] layer: about 2.1 MB + 5 K, whatever N, and never less for
+ * more channels, so that one workspace serves all layers up to the widest. */
 size_t qarvd_quantize_weight_workspace(int32_t N, int32_t K);
 
 /*

@@ -587,7 +587,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT) void weight_rows_kernel(RowsAr
     }
 }
 
-// Rows of more than 16384 channels: two passes over the row, gathered through perm from memory.
+// Packed rows of more than 18432 positions: two passes over the row, gathered through perm from memory.
 __global__ __launch_bounds__(256) void weight_rows_long_kernel(RowsArgs a)
 {
     __shared__ float red[2][4];
@@ -881,7 +881,9 @@ int norm_chunks(int32_t N, int32_t K)
     return want < most ? want : most;
 }
 
-size_t carve(void *base, int32_t N, int32_t K, Workspace *ws)
+// The partial sums get what they need at most, whatever N and K: a workspace that is large enough for a layer is large enough for
+// every layer of no more channels, as callers that allocate one for several layers expect.
+size_t carve(void *base, int32_t K, Workspace *ws)
 {
     unsigned char *p = reinterpret_cast<unsigned char *>(base);
     size_t off = 0;
@@ -891,8 +893,7 @@ size_t carve(void *base, int32_t N, int32_t K, Workspace *ws)
         return r;
     };
     void *sc = take(sizeof(DetectScalars)), *v = take((size_t)K * 4), *forced = take((size_t)K);
-    const int chunks = norm_chunks(N, K);
-    void *partial = take((size_t)(chunks > 4 ? chunks : 4) * K * 8);      // (short layers ask for no less than 37 K bytes in all)
+    void *partial = take((size_t)NORM_BLOCKS * 256 * 8);
     if (ws) {
         ws->sc = reinterpret_cast<DetectScalars *>(sc);
         ws->v = reinterpret_cast<float *>(v);
@@ -984,7 +985,7 @@ extern "C" int32_t qarvd_packed_ld(int32_t K, int32_t K_o)
 extern "C" size_t qarvd_quantize_weight_workspace(int32_t N, int32_t K)
 {
     if (N <= 0 || K <= 0 || K > QARVD_MAX_K) return 0;
-    return carve(nullptr, N, K, nullptr);
+    return carve(nullptr, K, nullptr);
 }
 
 namespace {
@@ -1011,11 +1012,11 @@ qarvd_status quantize_weight_impl(int bits, const float *W, int32_t N, int32_t K
     if (ldwq < (bits == 8 ? kp_max : kp_max / 2)) return QARVD_ERR_INVALID_ARG;
     if (!qarvd_aligned16(Wq) || (ldwq % 16) != 0 || (reinterpret_cast<uintptr_t>(W) & 3u)) return QARVD_ERR_UNSUPPORTED;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u)) return QARVD_ERR_WORKSPACE;
-    if (workspace_bytes < carve(nullptr, N, K, nullptr)) return QARVD_ERR_WORKSPACE;
+    if (workspace_bytes < carve(nullptr, K, nullptr)) return QARVD_ERR_WORKSPACE;
 
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     Workspace ws;
-    carve(workspace, N, K, &ws);
+    carve(workspace, K, &ws);
     int cus = 0;
     if (qarvd_status s_d = qarvd_current_device(nullptr, &cus); s_d != QARVD_OK) return s_d;
     if (c.forced_mask) QARVD_HIP_TRY(hipMemcpyAsync(ws.forced, c.forced_mask, (size_t)K, hipMemcpyHostToDevice, st));
@@ -1069,13 +1070,12 @@ extern "C" qarvd_status qarvd_quantize_weight(const float *W, int32_t N, int32_t
 
 // ---- the same offline step for callers that cannot allocate ----------------------------------------------
 // The workspace (partial norm sums, norms, mask, the scalars) lives in a file-scope device array instead of a caller
-// buffer: 2.1 MB per GPU the library runs on, held until the process ends.  In host code the array's name is only a stand-in; its device address is looked up once per
-// device with hipGetSymbolAddress and that pointer is what the kernels get.
+// buffer: 2.2 MB per GPU the library runs on, held until the process ends.  In host code the array's name is only a stand-in;
+// its device address is looked up once per device with hipGetSymbolAddress and that pointer is what the kernels get.
 namespace {
 constexpr int32_t STATIC_SCRATCH_MAX_K = 16384;
 // carve() for K <= 16384: 256 (scalars) + 65536 (norms) + 16384 (mask) + partial sums (at most NORM_BLOCKS slabs of 256 columns)
-constexpr size_t STATIC_SCRATCH_BYTES = 256 + 65536 + 16384 + (size_t)NORM_BLOCKS * 256 * 8;
-static_assert(4 * STATIC_SCRATCH_MAX_K <= NORM_BLOCKS * 256, "the least a layer asks for fits too");
+constexpr size_t STATIC_SCRATCH_BYTES = 256 + 65536 + 16384 + (size_t)NORM_BLOCKS * 256 * 8;      // 2179328
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 // device address of `scratch` on the current device (each GPU holds its own copy at its own address)
@@ -1104,7 +1104,7 @@ extern "C" qarvd_status qarvd_quantize_weight_static(const float *W, int32_t N, 
                                                      int32_t *K_o_host, float *v_out, void *stream)
 {
     if (K > STATIC_SCRATCH_MAX_K) return QARVD_ERR_WORKSPACE;      // the fixed array holds the workspace of K <= 16384
-    if (N > 0 && K > 0 && carve(nullptr, N, K, nullptr) > STATIC_SCRATCH_BYTES) return QARVD_ERR_WORKSPACE;
+    if (K > 0 && carve(nullptr, K, nullptr) > STATIC_SCRATCH_BYTES) return QARVD_ERR_WORKSPACE;
     void *ws = nullptr;
     if (qarvd_status st = static_scratch_ptr(&ws); st != QARVD_OK) return st;
     // Every kernel of the step writes the part of the workspace it owns before anything reads it (the existing
@@ -1116,7 +1116,7 @@ extern "C" qarvd_status qarvd_quantize_weight_static(const float *W, int32_t N, 
 extern "C" size_t qarvd_quantize_weight_w4_workspace(int32_t N, int32_t K)
 {
     if (N <= 0 || K <= 0 || K > QARVD_MAX_K) return 0;
-    return carve(nullptr, N, K, nullptr);
+    return carve(nullptr, K, nullptr);
 }
 
 extern "C" qarvd_status qarvd_quantize_weight_w4(const float *W, int32_t N, int32_t K, int64_t ldw,

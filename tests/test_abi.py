@@ -49,6 +49,12 @@ def test_packed_geometry(lib):
         assert worst <= q.packed_k(K, -1)
     assert q.quantize_weight_workspace(16, 1536) >= 33 * 1536
     assert q.quantize_weight_workspace(0, 5) == 0
+    for query in (q.quantize_weight_workspace, lib.qarvd_quantize_weight_w4_workspace):
+        # a workspace for the widest of several layers serves them all, and none asks for more than it did before the norms
+        # were summed in parallel plus the 2 MB that takes
+        sizes = [query(n, K) for K in range(1, 20000, 61) for n in (1, 64, 13824)]
+        assert sizes == sorted(sizes)
+        assert all(query(n, K) <= 37 * K + 4096 + (1 << 21) for K in (1, 256, 2048, 133143) for n in (1, 100000))
 
 
 def test_defaults_and_status_strings(lib):
