@@ -8,8 +8,10 @@ workload is config 2: the six linears of a Wan-1.3B-style DiT block for one 3-la
 launches on one stream.  The offline weight step (detection, permutation, dual scales) runs once
 before the timed region.  All inputs are resident in HBM when timing starts.
 
-Prints ONE JSON line.  `value` = sum over layers of 2*M*N*K divided by the step time (INT8 TOPS of
-the whole linear, quantization included) on config 2.  Also in the line:
+Prints ONE JSON line on stdout, short enough to survive in the tail of a log.  `value` = sum over layers of
+2*M*N*K divided by the step time (INT8 TOPS of the whole linear, quantization included) on config 2; beside it the two
+rooflines, the target layer, the CPU baseline and the value of each other workload.  The full record goes to stderr,
+one JSON line too (--full: to stdout in place of the short one):
   roofline / quant_act_roofline   the GEMM at the target shape (M=4680, 1536 -> 8960) against the dense
                                   INT8 MFMA peak and the activation kernel against the HBM peak, both from
                                   per-launch HIP events inside the step ("in-step": operands evicted by the
@@ -46,6 +48,7 @@ def parse():
     ap.add_argument("--other-configs", type=str, default="1,3,4,5",
                     help="configs reported compactly beside the headline ('' = none)")
     ap.add_argument("--variant", type=int, default=0, help="GEMM kernel variant (0 = heuristic)")
+    ap.add_argument("--full", action="store_true", help="the full record on stdout in place of the short line")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a 256 MiB device-to-device copy (reference dispatch for scaling the HBM traffic counters)")
     return ap.parse_args()
@@ -394,7 +397,25 @@ def main():
         torch.cuda.empty_cache()
     if cfgs:
         out["configs"] = cfgs
-    print(json.dumps(out))
+    print(json.dumps(out), file=sys.stdout if args.full else sys.stderr, flush=True)
+    if not args.full:
+        print(json.dumps(short_line(out)), flush=True)
+
+
+def short_line(out):
+    """What the one line on stdout carries of the full record."""
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config", "frac_int8_peak", "event_overhead_us_per_launch")
+    left_out = ("note", "traffic_source", "one_thread", "gemm_tops", "gemm_frac_peak", "gemm_back_to_back_tops", "launches_averaged",
+                "slowest_launch_us", "algorithmic_bytes")
+    line = {k: out[k] for k in keep if k in out}
+    for k in ("roofline", "quant_act_roofline", "target_layer", "cpu_baseline"):
+        if k in out:
+            line[k] = {f: v for f, v in out[k].items() if f not in left_out}
+    if "configs" in out:
+        line["configs"] = [{f: c[f] for f in ("config", "ms_per_step", "value", "error") if f in c} for c in out["configs"]]
+    line["full_record"] = "stderr"
+    return line
 
 
 def compact_config(cfg, args, wl, torch, np, build_layers, timed_steps, instrumented, back_to_back,
@@ -490,8 +511,7 @@ def side_measurements(out, args, layers, tgt, q, wl, torch, np, dev, run_quant, 
                                             gemm_tops=round(2.0 * lt["spec"].macs / us4 / 1e6, 1),
                                             weight_bytes=int(w4.N * w4.kp // 2), int8_weight_bytes=int(w4.N * w4.kp),
                                             note="back-to-back launches of qarvd_w4a8_dual_gemm and of qarvd_w8a8_dual_gemm on "
-                                                 "the target shape (compute-bound: halving the weight bytes cannot pay here, "
-                                                 "and the INT4 path runs on the 64-byte-stage tiles only)")
+                                                 "the target shape (compute-bound: halving the weight bytes hardly pays here)")
             del w4, Xq4, sx4
         except Exception as e:  # diagnostic only
             out["w4a8_target_layer"] = dict(error=str(e))
