@@ -145,7 +145,7 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD
     constexpr int CP = ORD == ANY_ORDER ? CH + 1 : CH;       // chunks of the packed row: up to 31 + 127 pads
     constexpr int ZERO = 4 * CH * NT;                        // (ANY_ORDER) image address of a zero, for the pads
     constexpr float MAGIC = 12582912.0f;       // 1.5 * 2^23: the sum rounds half-to-even, the code is its low byte
-    __shared__ uint32_t image[PERM ? (NT == 64 ? 4 : 2) : 1][PERM ? CH * NT + 1 : 1];      // codes in natural order
+    __shared__ __align__(16) uint32_t image[PERM ? (NT == 64 ? 4 : 2) : 1][PERM ? CH * NT + (ORD == ANY_ORDER ? 4 : 0) : 1];      // natural order
     __shared__ float red[2][NWAVE];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t = NT == 64 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
@@ -241,15 +241,17 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD
         }
         const size_t out = (size_t)m * a.ldxq;         // byte offset of the row in Xq
         ExactQuotient q(s, 127.0f);
-        if (!q.exact() && s < __builtin_inff()) {      // (uniform over the row)
+        bool far = false;
+        if (!q.exact()) {                              // (uniform over the row)
             // Row and scale times the same power of two: no quotient changes.  Up: exact, or infinite and clipped as before.  Down
             // (s > 1e30): values that lose bits lie below 1e-9 and have the code 0 either way.
             const float f = s < 1.0f ? 0x1p96f : 0x1p-96f;
+            far = !(s < __builtin_inff());             // an infinity in the row
 #pragma unroll
             for (int c = 0; c < CH; ++c) v[c] = Elem<T>::scale(v[c], f);
             q = ExactQuotient(s * f, 127.0f);
         }
-        if (!q.exact()) {                              // an infinity in the row
+        if (far) {
             quant_row_far<T>(a, X + (size_t)m * a.ldx, a.Xq + out, s, t, NT);
             if constexpr (PERM && NT > 64) __syncthreads();        // as many barriers as the other path
         } else {

@@ -824,7 +824,7 @@ __global__ __launch_bounds__(NT, CH > 5 ? 4 : 6) void weight_rows_clip_kernel(Ro
         }
         __syncthreads();
 #pragma unroll 1
-        for (int blk = 0; blk < 2; ++blk) {
+        for (int blk = __builtin_expect(open[0] + open[1], 0) ? 0 : 2; blk < 2; ++blk) {
             if (!open[blk]) continue;
             // in order: all threads take errors, NT values at a time, and thread c sums those of candidate c
             const int n = block_n(blk);
