@@ -189,7 +189,8 @@ qarvd_status qarvd_quant_act_static(const void *X, qarvd_dtype xdt, int32_t M, i
  *     Y[m,j] = fmaf(r, s_x[m], bias[j])   stored as fp32, or rounded to bf16 (nearest-even)
  *   Xq, Wq  in  packed i8 for the same (K, K_o); 16-byte aligned, strides multiples of 16
  *   s_x     in  f32 [M];  s_normal, s_outlier in f32 [N];  bias in f32 [N] or NULL (+0.0f)
- *   Y       out [M, ldy] of `ydt`; 16-byte aligned, ldy*sizeof(elem) % 16 == 0
+ *   Y       out [M, ldy] of `ydt`, aligned to its elements; the fastest kernels need it 16-byte aligned,
+ *               ldy*sizeof(elem) % 16 == 0 and N % 8 == 0, anything else runs on general tiles
  *   dbg_acc_normal, dbg_acc_outlier   out i32 [M,N] (dense, ld = N) or NULL: raw accumulators
  *                                     for parity checks; pass NULL when timing.
  * Fully asynchronous on `stream`.
@@ -225,10 +226,10 @@ qarvd_status qarvd_quantize_weight_w4(const float *W, int32_t N, int32_t K, int6
  * which the scales undo exactly), so both INT32 sums and every output are those of the INT8 path on
  * the same codes.
  *   Wq4  in  packed u8 [N, ldwq4] for the same (K, K_o) as Xq; 16-byte aligned, ldwq4 % 16 == 0
- * Shapes outside the fast-path preconditions (N % 8 != 0, Y rows, scales or bias not 16-byte aligned,
- * an outlier block of more than 128 packed bytes) run on a slower register-staged kernel (the last
- * variant); asking for one of the fast variants by number on such a shape returns
- * QARVD_ERR_UNSUPPORTED.  variant: 0 = heuristic, 1..qarvd_w4_gemm_num_variants() pick a kernel.
+ * variant: 0 = heuristic, 1..qarvd_w4_gemm_num_variants() pick a kernel.  Kernels 1, 2, 4, 5 and 6 need N % 8 == 0,
+ * 16-byte aligned Y rows, scales and bias, ldy <= 2^20, an outlier block of at most 128 packed bytes and strides of at
+ * most 2^22; 7 and 8 strides of at most 2^22 and nothing else; 3 (register-staged, the slowest) takes every shape.
+ * A kernel asked for by number that cannot run the shape returns QARVD_ERR_UNSUPPORTED.
  * Fully asynchronous on `stream`.
  */
 qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, const float *s_x,
