@@ -354,7 +354,9 @@ qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
 // fits one wave runs without barriers, and work on chunks that hold no channel costs as much as on those that do, so the steps are
 // the narrowest of those that pay: time for 4680 rows of 256, fp32, against six chunks for all rows of one wave 6.4 -> 4.1 us
 // (NATURAL 5.9 -> 4.2), bf16 13824 wide on 7 x 512 or 4 x 1024 against 9 x 512 45.8 -> 42.2 (NATURAL 45.2 -> 40.0), 20000 wide
-// against two passes over the row 237 -> 62.  NATURAL takes more threads a row: nothing is set up per thread there.
+// against two passes over the row 237 -> 62.  From inputs that no cache holds, WHOLE_WORDS: bf16 2048 wide on 2 x 256 against
+// 3 x 256 10.6 -> 9.4, 4096 wide on 4 x 256 against 5 x 256 16.8 -> 15.4 (fp32 20.2 -> 19.6).  NATURAL takes more threads a row:
+// nothing is set up per thread there.
 template <typename T, Order ORD, bool TAIL>
 bool launch_by_width(const ActArgs &a, int width, hipStream_t st, qarvd_status *out)
 {
@@ -377,7 +379,11 @@ bool launch_by_width(const ActArgs &a, int width, hipStream_t st, qarvd_status *
     } else {
         if (width <= 4 * 256) return go(launch_rows<T, 4, 64, ORD, TAIL>(a, st));
         if (width <= 6 * 256) return go(launch_rows<T, 6, 64, ORD, TAIL>(a, st));
+        if constexpr (sizeof(T) == 2) {
+            if (width <= 2 * 1024) return go(launch_rows<T, 2, 256, ORD, TAIL>(a, st));
+        }
         if (width <= 3 * 1024) return go(launch_rows<T, 3, 256, ORD, TAIL>(a, st));
+        if (width <= 4 * 1024) return go(launch_rows<T, 4, 256, ORD, TAIL>(a, st));
         if (width <= 5 * 1024) return go(launch_rows<T, 5, 256, ORD, TAIL>(a, st));
         if (width <= 6 * 1024) return go(launch_rows<T, 6, 256, ORD, TAIL>(a, st));
         if (width <= 5 * 2048) return go(launch_rows<T, 5, 512, ORD, TAIL>(a, st));

@@ -36,7 +36,7 @@ def check(X, Xd, perm, K_o):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("K", [1, 3, 4, 5, 130, 256, 257, 512, 513, 1024, 1025, 1532, 1536, 1537, 1540, 2048, 2049, 3072, 3073, 3076,
-                               5120, 5121, 6144, 6148, 10240, 10244, 12288, 12290, 14336, 14339, 16384, 16388, 18400, 18432,
+                               4096, 4097, 4100, 5120, 5121, 6144, 6148, 10240, 10244, 12288, 12290, 14336, 14339, 16384, 16388, 18400, 18432,
                                18433, 18436, 20480, 20481, 20484])
 def test_row_widths(K, dtype):
     X, Xd, rng = make(9, K, K, dtype)
