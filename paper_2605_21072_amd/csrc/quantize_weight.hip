@@ -632,9 +632,10 @@ __global__ __launch_bounds__(256) void weight_rows_long_kernel(RowsArgs a)
 // summation: serial and parallel sums are both within n u / (1 - n u) of the exact one (u = 2^-53; e^2 is exact).
 // Candidates with equal scales have equal sums term by term.  Anything else (intervals that overlap, scales outside the exact
 // quotient's range, NaN) is summed in order: the errors taken by the whole workgroup, then one thread per candidate (1536 x 8960 with
-// every row so: 0.35 ms a call; with the gather and the quotients in that thread too 8.2).  Bound by the latency of its phases (14 us a row) and by vector-ALU issue (about 35
-// instructions per value), so one row per workgroup and registers held low enough for three workgroups per CU (1536 x 8960:
-// 50 us; with the offsets kept for three rows 79, one workgroup per CU).
+// every row so: 0.35 ms a call; with the gather and the quotients in that thread too 8.2).  Bound by the latency of its phases
+// (14 us a row) and by vector-ALU issue (about 35 instructions per value), so one row per workgroup and registers held low enough
+// for three workgroups per CU, at the price of a few spilled ones (28 bytes of scratch a lane at <5, 512>) (1536 x 8960: 50 us;
+// with the offsets kept for three rows 79, one workgroup per CU).
 constexpr int CLIP_MAX_T = 20, CLIP_CAND = 512;
 
 template <int CH, int NT>
