@@ -1,10 +1,10 @@
 // Dual-scale W8A8 GEMM + de-quantization for gfx950 (appendix "Quantization Kernels", kernel
-// (ii); Eq. (dual_scale)): INT8 x INT8 -> INT32 on v_mfma_i32_32x32x32_i8, the outlier and the
+// (ii); Eq. (dual_scale)): INT8 x INT8 -> INT32 on the matrix cores, the outlier and the
 // normal K range summed in separate INT32 accumulators and merged by the fp32 epilogue
 //     r = (float)acc_o * s_o[n];  r = fmaf((float)acc_n, s_n[n], r);  y = fmaf(r, s_x[m], bias[n]).
 //
 // Operand geometry.  Both operands are K-contiguous ("NT"): Xq[M, ldxq], Wq[N, ldwq], packed K
-// axis [outlier | pad to 32 | normal | pad to 128].  One MFMA consumes a 32-row x 32-byte slab
+// axis [outlier | pad to 32 | normal | pad to 128].  One v_mfma_i32_32x32x32_i8 consumes a 32-row x 32-byte slab
 // of each operand: lane l supplies 16 consecutive K bytes of row (l & 31) starting at byte
 // 16*(l >> 5).  A and B use the same lane -> K mapping, so the product is a plain dot product
 // over those 32 bytes whatever order the hardware assigns to them.  The 32x32 INT32 result has

@@ -1,28 +1,42 @@
 // LDS-direct dual-scale W8A8 GEMM for gfx950 with 128-byte-deep K stages (appendix "Quantization Kernels",
-// kernel (ii); Eq. (dual_scale)): INT8 x INT8 -> INT32 on v_mfma_i32_32x32x32_i8, fp32 dequant epilogue.
+// kernel (ii); Eq. (dual_scale)): INT8 x INT8 -> INT32 on v_mfma_i32_16x16x64_i8, fp32 dequant epilogue.
 //
 // Same design as the 64-byte-stage kernel (persistent workgroups, a ring of LDS stages filled by
 // buffer_load ... lds, the outlier head tile visited last and re-multiplied from LDS in the epilogue, scales
-// double-buffered in LDS, swizzled output patches), with one difference that matters on MI355X: a stage row is
-// a whole 128-byte cache line.  One LDS-direct load moves 8 rows x 128 bytes, so every line that leaves the L2
+// double-buffered in LDS, swizzled output patches), with two differences that matter on MI355X.
+//
+// A stage row is a whole 128-byte cache line.  One LDS-direct load moves 8 rows x 128 bytes, so every line that leaves the L2
 // is used completely by the instruction that asked for it; with 64-byte rows each line is requested twice, one
 // iteration apart, and under load (all CUs streaming) the vector L1 fill path then delivers half as many useful
 // bytes (measured with a K-loop skeleton on 256 CUs: 2500 against 1220 cycles per 256 x 256 x 64 step).
+//
+// The instruction is 16x16x64.  The chip is power-limited on real data, and a MAC costs less energy there than in 32x32x32 (half
+// the accumulator traffic per MAC): a 256 x 256 K loop without epilogue runs at 3.08 POPS with 16x16x64 and at 2.69 with
+// 32x32x32 on Gaussian codes, although it takes more cycles (zeros as operands, where the clock stays up: 3.6 and 4.1).  Same
+// tiles on 32x32x32 against now, us: 4680 x 8960 -> 1536 62.2 -> 58.3, 4680 x 5120 -> 13824 302 -> 290 (128 x 256: 308 -> 284),
+// 4680 x 1536 -> 8960 76.9 -> 75.0, 4680 x 1536 -> 1536 15.8 -> 15.0, 520 x 8960 -> 1536 on 64 x 64 21.1 -> 17.0 (two k-steps a
+// stage instead of four, each with twice the MFMAs to hide its reads behind).
 // Consequences:
-//   * four MFMA k-steps of 32 bytes per stage and one barrier per 128 K-bytes (half as many as before);
-//   * the outlier range (at most 128 packed bytes) is exactly the first K tile: one head tile, H <= 1;
+//   * two MFMA k-steps of 64 bytes per stage, all fragments of the next in flight under this one's MFMAs, one barrier per stage;
+//   * the outlier range (at most 128 packed bytes, in units of 32) is exactly the first K tile: one head tile, H <= 1.  Where it
+//     ends in the middle of a k-step, that step is multiplied twice, with the other half's lanes zeroed;
+//   * a lane owns 4 consecutive columns of every 16x16 block and the same columns in every row block, so the epilogue reads
+//     its scales and biases once a tile, and an output patch is whole 128-byte lines;
 //   * a stage is refilled by the iteration that consumed it (its last fragments are in registers before the
 //     iteration's barrier, and each wave waits for its own LDS reads before arriving), so all NSTAGE stages are
 //     in use and a load has NSTAGE - 1 iterations to land; 256 x 256 tiles run with two 64 KB stages;
 //   * where the LDS has room (256 x 256) the output patches get their own 16 KB behind the stages, so a whole
-//     stage is free for the next tile's first K tile during the epilogue; otherwise they sit in a free stage.
+//     stage is free for the next tile's first K tile during the epilogue; otherwise they sit in a free stage;
+//   * 256 x 256 tiles need all 256 registers of a wave: no second copy of the K loop (rows below the matrix are multiplied as the
+//     zeros they load as, which costs issue slots but hardly power), and the accumulators are cleared, not started from an inline
+//     zero in a first iteration of its own (which the compiler no longer keeps in place: 140 registers spilled).
 //
 // GEN = true is the general form: an outlier block of any width, any N, any output alignment.  Tiles of at most 64
 // accumulator registers a wave have room for a second set, so the K loop runs in natural order and the sums move to
 // the outlier set where the range ends; nothing is kept in LDS or multiplied again.  Outputs that are not whole
 // 16-byte chunks leave through unaligned 16-byte stores, the last partial chunk of a row element by element.
 // Against the register-staged kernel that took these shapes before: 2251 x 2360 x 2252, 150 outliers, fp32 out
-// 64.1 -> 25.7 us; 4680 x 5120 x 13825, 200 outliers 1213 -> 369; 20 x 13824 x 700 126 -> 29; 1001 x 1003 x 1005
+// 64.1 -> 26 us; 4680 x 5120 x 13825, 200 outliers 1213 -> 369; 20 x 13824 x 700 126 -> 29; 1001 x 1003 x 1005
 // 21.1 -> 6.6.  256 x 128 tiles (two full sets leave too few registers: 60 spilled) were 27 us on the first
 // and 352 on the second and are not built.
 #include <algorithm>
@@ -35,21 +49,18 @@ namespace qarvd_gemm {
 namespace {
 
 constexpr int BK2 = 128;                  // K bytes per stage row
-constexpr int KS2 = BK2 / 32;             // MFMA k-steps per stage
-constexpr int PATCH2_RS = 64;
-constexpr int PATCH2_BYTES = 32 * PATCH2_RS;
+constexpr int KS2 = BK2 / 64;             // MFMA k-steps per stage
+constexpr int PATCH2_BYTES = 2048;        // output patch of a wave: 16 rows of 128 bytes, or 32 of 64
 
 // Swizzle for 128-byte LDS rows (eight 16-byte slots).  A row covers half of the 64 banks, so rows of equal
-// parity share their banks.  A fragment read (ds_read_b128, lane l -> row l & 31, half l >> 5 of a k-step)
+// parity share their banks.  A fragment read (ds_read_b128, lane l -> row l & 15, chunk l >> 4 of a k-step's four)
 // must spread over all banks both when the hardware groups lanes {8p..8p+7, 32+8p..32+8p+7} (eight consecutive
-// rows times the two halves of a k-step) and when it groups sixteen consecutive lanes (sixteen consecutive
-// rows, one half): rows r, r+2, r+4, r+6 take their chunk pair {2s, 2s+1} at four different slot pairs, and
-// rows r and r+8 swap the two slots of a pair.  (With the first rule alone the bank-conflict counter of the
-// target-shape kernel read ten times what the 64-byte-stage kernel's does.)
-__device__ __forceinline__ int swz128(int r) { return (((r >> 1) & 3) << 1) | ((r >> 3) & 1); }
+// rows times the chunks c and c ^ 2) and when it groups sixteen consecutive lanes (sixteen consecutive rows, one
+// chunk): rows r, r+2, r+4, r+6 take slots that differ in bits 0 and 2, rows r and r+8 in bit 1.
+__device__ __forceinline__ int swz128(int r) { return ((r >> 1) & 1) | (((r >> 3) & 1) << 1) | (((r >> 2) & 1) << 2); }
 
-// 64-byte rows of packed INT4 (four chunks, an 8-byte read per lane): four rows cover the banks once, so rows r,
-// r + 4, r + 8, r + 12 put a k-step's chunk into different slots.
+// 64-byte rows of packed INT4 (four chunks, two a k-step, an 8-byte read per lane): four rows cover the banks once, so rows r,
+// r + 4, r + 8, r + 12 put a chunk into different slots.
 __device__ __forceinline__ int swz_w4(int r) { return (r >> 2) & 3; }
 
 // W4: the W operand is packed INT4, 64 bytes per row and stage.
@@ -58,7 +69,7 @@ struct Geo2 {
     static constexpr int NW = WM * WN;
     static constexpr int THREADS = 64 * NW;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
-    static constexpr int TM = WTM / 32, TN = WTN / 32;
+    static constexpr int TM = WTM / 16, TN = WTN / 16;
     static constexpr int WROW = W4 ? 64 : BK2;                     // bytes of a W row in a stage
     static constexpr int WGRP = W4 ? 16 : 8;                       // W rows an LDS-direct load (1 KB) covers
     static constexpr int NA = BM / 8 / NW, NB = BN / WGRP / NW;    // LDS-direct loads per wave per stage
@@ -74,10 +85,10 @@ struct Geo2 {
     static constexpr int SPT = (NSCALE + THREADS - 1) / THREADS;
     static_assert(BM % (8 * NW) == 0 && BN % (WGRP * NW) == 0, "row groups must divide over the waves");
     static_assert(NW % 2 == 0, "the load swizzle takes bit 3 of a row from the wave number");
-    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is TM x TN blocks of 32 x 32");
+    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is TM x TN blocks of 16 x 16, stored in pairs");
     static constexpr int WG_PER_CU = NW >= 8 || 2 * LDS_BYTES > 160 * 1024 ? 1 : 8 / NW;     // bounded by LDS, two waves per SIMD
     static constexpr int WAVES_PER_SIMD = WG_PER_CU * NW >= 8 ? 2 : 1;
-    static_assert(TM * TN * 16 <= 256 / WAVES_PER_SIMD, "accumulators: half of the registers a wave can have");
+    static_assert(TM * TN * 4 <= 256 / WAVES_PER_SIMD, "accumulators: half of the registers a wave can have");
     static_assert(PATCHES <= STG, "the output patches fit into one stage");
     static_assert(PATCH_EXTRA ? NSTAGE >= 2 : NSTAGE >= 3, "a head tile, the patches and one stage for the next tile");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
@@ -104,13 +115,18 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
     int m0, n0;                                    // tile being computed
 
     // ---- LDS-direct load addressing: load i of this wave fills rows (NW*i + wave)*8 .. +8 of the operand tile;
-    // lane l fills slot (l & 7) of row (l >> 3) of those with global chunk (l & 7) ^ swz128(row in the tile).  Tile base in SGPRs, one
-    // byte offset per lane and load, the K position as scalar offset.  Rows past the matrix are clamped to its
-    // last row (their products land in rows / columns that are never stored).
+    // lane l fills slot (l & 7) of row (l >> 3) of those with global chunk (l & 7) ^ swz128(row in the tile).  Tile base in the
+    // descriptor, one byte offset per lane and operand, the load's rows and the K position as scalar offset.  The descriptor
+    // covers the rows of the tile that exist, so rows past the matrix read as zeros and cost no traffic (their products land
+    // in rows / columns that are never stored).
     const int drow = lane >> 3;
     const int dchunk = ((lane & 7) ^ swz128(8 * (wave & 1) + drow)) << 4;      // (NW is even: row bit 3 = wave bit 0)
+    const int ldx = (int)g.ldxq, ldw = (int)g.ldwq;
+    const int va = (wave * 8 + drow) * ldx + dchunk;
+    const int vb = W4 ? (wave * 16 + (lane >> 2)) * ldw + (((lane & 3) ^ swz_w4(lane >> 2)) << 4)      // 16 rows x 64 bytes per load
+                      : (wave * 8 + drow) * ldw + dchunk;
     const int8_t *base_a, *base_b;
-    int va[NA], vb[NB];
+    int bytes_a, bytes_b;
     int lm0, ln0;                                  // tile the load addressing points at
     auto aim_loads = [&](int t) {
         int tm, tn;
@@ -119,26 +135,18 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
         ln0 = tn * BN;
         base_a = g.Xq + (size_t)lm0 * g.ldxq;
         base_b = g.Wq + (size_t)ln0 * g.ldwq;
-#pragma unroll
-        for (int i = 0; i < NA; ++i)
-            va[i] = (min(lm0 + (NW * i + wave) * 8 + drow, g.M - 1) - lm0) * (int)g.ldxq + dchunk;
-#pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            if constexpr (W4)     // 16 rows x 64 bytes per load, chunk (l & 3) ^ swz_w4(row) of row l >> 2
-                vb[i] = (min(ln0 + (NW * i + wave) * 16 + (lane >> 2), g.N - 1) - ln0) * (int)g.ldwq + (((lane & 3) ^ swz_w4(lane >> 2)) << 4);
-            else
-                vb[i] = (min(ln0 + (NW * i + wave) * 8 + drow, g.N - 1) - ln0) * (int)g.ldwq + dchunk;
-        }
+        bytes_a = (min(BM, g.M - lm0) - 1) * ldx + g.kp;
+        bytes_b = (min(BN, g.N - ln0) - 1) * ldw + (W4 ? g.kp / 2 : g.kp);
     };
     auto issue = [&](int ktile, int stage) {
         unsigned char *sb = smem + stage * STG;
         const int koff = ktile * BK2;
 #pragma unroll
         for (int i = 0; i < NA; ++i)
-            buffer_load_lds16(base_a, va[i], koff, sb + (NW * i + wave) * 1024);
+            buffer_load_lds16(base_a, bytes_a, va, koff + i * NW * 8 * ldx, sb + (NW * i + wave) * 1024);
 #pragma unroll
         for (int i = 0; i < NB; ++i)
-            buffer_load_lds16(base_b, vb[i], W4 ? koff / 2 : koff, sb + BM * BK2 + (NW * i + wave) * 1024);
+            buffer_load_lds16(base_b, bytes_b, vb, (W4 ? koff / 2 : koff) + i * NW * G::WGRP * ldw, sb + BM * BK2 + (NW * i + wave) * 1024);
     };
 
     // ---- scales and bias: registers during the previous tile's K loop, then the other LDS buffer ----
@@ -171,91 +179,76 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
         fetch_scales(tm * BM, tn * BN);
     };
 
-    // ---- fragment addressing: lane l reads row (l & 31), chunk 2*ks + (l >> 5) of a k-step ----
-    const int frow = lane & 31, fhalf = lane >> 5, fsw = swz128(frow);
+    // ---- fragment addressing: lane l reads row (l & 15), chunk 4*ks + (l >> 4) of a k-step ----
+    const int frow = lane & 15, fq = lane >> 4, fsw = swz128(frow);
     const int x_base = (wm * G::WTM + frow) * BK2;               // X rows: MFMA B operand
-    const int w_base = BM * BK2 + (wn * G::WTN + frow) * G::WROW + (W4 ? 8 * fhalf : 0);    // W rows: MFMA A operand
+    const int w_base = BM * BK2 + (wn * G::WTN + frow) * G::WROW + (W4 ? 8 * (fq & 1) : 0);    // W rows: MFMA A operand
     int coff[KS2], wcoff[KS2];
 #pragma unroll
     for (int ks = 0; ks < KS2; ++ks) {
-        coff[ks] = (((2 * ks) | fhalf) ^ fsw) << 4;
-        wcoff[ks] = W4 ? (ks ^ swz_w4(frow)) << 4 : coff[ks];     // packed INT4: k-step ks is one chunk, this lane's half of it 8 bytes
+        coff[ks] = (((4 * ks) | fq) ^ fsw) << 4;
+        wcoff[ks] = W4 ? (((2 * ks) | (fq >> 1)) ^ swz_w4(frow)) << 4 : coff[ks];     // packed INT4: k-step ks is two chunks, 8 bytes a lane
     }
     auto read_w = [&](const unsigned char *sb, int j, int c) -> v4i {   // W fragment of block j, k-step offset c
-        if constexpr (W4) return unpack_w4(*reinterpret_cast<const v2i *>(sb + w_base + j * 32 * G::WROW + c));
-        else return *reinterpret_cast<const v4i *>(sb + w_base + j * 32 * BK2 + c);
+        if constexpr (W4) return unpack_w4(*reinterpret_cast<const v2i *>(sb + w_base + j * 16 * G::WROW + c));
+        else return *reinterpret_cast<const v4i *>(sb + w_base + j * 16 * BK2 + c);
+    };
+    auto read_x = [&](const unsigned char *sb, int i, int c) -> v4i {
+        return *reinterpret_cast<const v4i *>(sb + x_base + i * 16 * BK2 + c);
     };
 
-    v16i acc[TM][TN];
-    v16i acc_o[GEN ? TM : 1][GEN ? TN : 1];     // (GEN) the outlier sum, moved here when the K loop passes its end
-    static_assert(!GEN || TM * TN <= 4, "two accumulator sets");
-    v4i xf[2][TM], wf[2][TN];   // fragments of k-steps of even / odd number
+    v4i acc[TM][TN];
+    v4i acc_o[GEN ? TM : 1][GEN ? TN : 1];      // (GEN) the outlier sum, moved here when the K loop passes its end
+    static_assert(!GEN || TM * TN <= 16, "two accumulator sets");
+    v4i xf[KS2][TM], wf[KS2][TN];
+    const v4i zero4 = {0, 0, 0, 0};
     auto load_frags = [&](const unsigned char *sb, int ks) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) wf[ks & 1][j] = read_w(sb, j, wcoff[ks]);
+        for (int j = 0; j < TN; ++j) wf[ks][j] = read_w(sb, j, wcoff[ks]);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) xf[ks & 1][i] = *reinterpret_cast<const v4i *>(sb + x_base + i * 32 * BK2 + coff[ks]);
+        for (int i = 0; i < TM; ++i) xf[ks][i] = read_x(sb, i, coff[ks]);
     };
     auto mma = [&](int ks) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[ks & 1][j], xf[ks & 1][i], acc[i][j], 0, 0, 0);
-    };
-    auto mma_z = [&](int ks) {      // the same from zero accumulators (first k-step of a tile)
-        const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[ks & 1][j], xf[ks & 1][i], zero, 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[ks][j], xf[ks][i], acc[i][j], 0, 0, 0);
     };
     auto clear_acc = [&]() {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+            for (int j = 0; j < TN; ++j) acc[i][j] = zero4;
     };
-    // last row of tiles: 32-row blocks that lie entirely below the matrix are left out
-    int i_lim = TM;
-    auto mma_r = [&](int ks) {
+    auto mask_w = [&](int ks, bool keep) {         // lanes that do not keep their bytes multiply by zero
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-            if (i < i_lim) {
+        for (int j = 0; j < TN; ++j) wf[ks][j] = keep ? wf[ks][j] : zero4;
+    };
+    // Instruction-order hints (masks: 0x008 MFMA, 0x100 LDS read, 0x020 VMEM read).  The fragment reads of the next k-step go
+    // out behind the first MFMAs of this one, one each, the refill's loads behind every second one after them: the reads then
+    // have the rest of the k-step to land (256 x 256: spread evenly over the k-step 3.08, so 3.16 POPS in a K loop without epilogue).
+    auto interleave = [&](auto loads_tag) {
+        constexpr int S = TM * TN, R = TM + TN, L = decltype(loads_tag)::value ? NL : 0;
+        constexpr int FREE = S > R ? S - R : 1;    // MFMAs without a read behind them
+        int loads = 0;
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[ks & 1][j], xf[ks & 1][i], acc[i][j], 0, 0, 0);
+        for (int m = 0; m < S; ++m) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            if (m < R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            while (loads < L && loads * FREE < (m + 1 - R) * L) {
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                ++loads;
             }
-    };
-    // instruction-order hints (masks: 0x008 MFMA, 0x100 LDS read, 0x020 VMEM read)
-    auto interleave_reads = [&]() {
-#pragma unroll
-        for (int i = 0; i < TM * TN; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (i < TM + TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
     };
-    auto interleave_reads_and_loads = [&]() {
-        constexpr int S = TM * TN, R = TM + TN, OPS = R + NL;
-#pragma unroll
-        for (int i = 0; i < S; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-#pragma unroll
-            for (int j = 0; j < OPS; ++j)
-                if (j * S / OPS == i) {
-                    if (j < R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    else __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                }
-        }
-    };
+    auto interleave_reads = [&]() { interleave(std::false_type{}); };
+    auto interleave_reads_and_loads = [&]() { interleave(std::true_type{}); };
 
     // ---- K tiles: T >= 1 of 128 bytes.  Tile 0 holds the outlier range (when there is one) and is visited last:
     // order H, .., T-1, 0.  Iteration `it` reads stage (base + it) % NSTAGE and, once read, refills it.
     const int T = g.kp / BK2;
-    const int o_steps = DUAL ? g.n_off / 32 : 0;      // 32-byte k-steps of the outlier range (<= 4)
+    const int o_steps = DUAL ? g.n_off / 32 : 0;      // the outlier range in units of half a k-step, 32 bytes (!GEN: <= 4)
     const int H = !GEN && o_steps > 0 ? 1 : 0;
     const int Tn = T - H;
     auto seq = [&](int it) { return it < Tn ? it + H : it - Tn; };
@@ -291,20 +284,43 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
     }
     load_frags(smem + base * STG, 0);
     int stage = base;
-    const long long p_t0 = QARVD_PROF ? clock64() : 0;
-    i_lim = min(TM, max(0, (min(BM, g.M - m0) - wm * G::WTM + 31) / 32));
+    [[maybe_unused]] const long long p_t0 = QARVD_PROF ? clock64() : 0;
 
-    // iteration it:  read F1 | MFMA F0 | read F2 | MFMA F1 | read F3 | MFMA F2 | wait, barrier |
-    //                read F0(it+1), refill this stage with K tile it+NSTAGE | MFMA F3
+    // iteration it:  MFMA F0 | read F1 under it;  wait, barrier;  MFMA F1 | read F0(it+1), refill this stage with K tile it+NSTAGE
     // Before the barrier a wave waits for its own loads of stage it+1 and for its own LDS reads (the last
     // fragments of this stage), so after the barrier stage it+1 is complete and stage `it` is dead.
+    auto next_of = [&](int st) { return st + 1 == NSTAGE ? 0 : st + 1; };
+    auto first_half = [&]() {
+        load_frags(smem + stage * STG, 1);
+        mma(0);
+        interleave_reads();
+        __builtin_amdgcn_sched_barrier(0);       // the waits must not float up into the MFMAs
+    };
+    auto refill_half = [&](int ktile) {
+#if QARVD_PROF
+        const long long q1 = clock64();
+#endif
+        wait_vmcnt<(NSTAGE - 2) * NL>();
+        wait_lgkmcnt0();
+        __builtin_amdgcn_s_barrier();
+#if QARVD_PROF
+        p_bar += clock64() - q1;
+#endif
+        load_frags(smem + next_of(stage) * STG, 0);
+        issue(ktile, stage);
+        mma(1);
+        interleave_reads_and_loads();
+        __builtin_amdgcn_sched_barrier(0);
+        stage = next_of(stage);
+    };
     if constexpr (GEN) {
         // Natural K order.  The tiles up to the one in which the outlier range ends go through an unscheduled loop; at its
-        // end the sums so far become the outlier accumulators and the normal ones start from zero.  The rest runs
-        // through the scheduled iteration of the kernel above with nothing in it that knows of the split (a
+        // end the sums so far become the outlier accumulators and the normal ones start from zero (in the middle of a k-step:
+        // its two halves are multiplied one after the other, the other half's lanes zeroed).  The rest runs
+        // through the scheduled iteration with nothing in it that knows of the split (a
         // test between the k-steps of one loop for all cost 40 % of the loop's rate).
         clear_acc();
-        const int o_tile = o_steps >> 2, o_ks = o_steps & 3;
+        const int o_tile = o_steps >> 2, o_sub = o_steps & 3;
         auto split = [&]() {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
@@ -316,7 +332,6 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
 #pragma unroll 1
         for (; it <= o_tile && it < T; ++it) {
             const unsigned char *sb = smem + stage * STG;
-            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
 #pragma unroll
             for (int ks = 0; ks < KS2; ++ks) {
                 if (ks + 1 < KS2) {
@@ -326,194 +341,81 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
                     wait_lgkmcnt0();
                     __builtin_amdgcn_s_barrier();
                 }
-                if (it == o_tile && ks == o_ks) split();
-                mma(ks);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (it + 1 < T) load_frags(smem + nstage * STG, 0);
-            if (it + NSTAGE < T) issue(it + NSTAGE, stage);
-            stage = nstage;
-        }
-        auto three_steps = [&](const unsigned char *sb) {
+                if (it == o_tile && 2 * ks == o_sub) split();
+                if (it == o_tile && 2 * ks + 1 == o_sub) {
+                    v4i whole[TN];
 #pragma unroll
-            for (int ks = 0; ks < KS2 - 1; ++ks) {
-                load_frags(sb, ks + 1);
+                    for (int j = 0; j < TN; ++j) whole[j] = wf[ks][j];
+                    mask_w(ks, fq < 2);
+                    mma(ks);
+                    split();
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) wf[ks][j] = whole[j];
+                    mask_w(ks, fq >= 2);
+                }
                 mma(ks);
-                interleave_reads();
-                __builtin_amdgcn_sched_barrier(0);
             }
-        };
-        for (; it < T - NSTAGE; ++it) {
-            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-            three_steps(smem + stage * STG);
-            wait_vmcnt<(NSTAGE - 2) * NL>();
-            wait_lgkmcnt0();
-            __builtin_amdgcn_s_barrier();
-            load_frags(smem + nstage * STG, 0);
-            issue(it + NSTAGE, stage);
-            mma(3);
-            interleave_reads_and_loads();
             __builtin_amdgcn_sched_barrier(0);
-            stage = nstage;
+            if (it + 1 < T) load_frags(smem + next_of(stage) * STG, 0);
+            if (it + NSTAGE < T) issue(it + NSTAGE, stage);
+            stage = next_of(stage);
+        }
+        for (; it < T - NSTAGE; ++it) {
+            first_half();
+            refill_half(it + NSTAGE);
         }
 #pragma unroll 1
         for (; it < T; ++it) {
-            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-            three_steps(smem + stage * STG);
+            first_half();
             if (it + 1 < T) {
                 wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);
                 wait_lgkmcnt0();
                 __builtin_amdgcn_s_barrier();
-                load_frags(smem + nstage * STG, 0);
+                load_frags(smem + next_of(stage) * STG, 0);
             }
-            mma(3);
-            stage = nstage;
+            mma(1);
+            stage = next_of(stage);
         }
         if (o_tile >= T) split();        // every k-step belongs to the outlier range
     } else {
-    if (i_lim < TM) {                            // ragged tile: same steps, unneeded row blocks left out
         clear_acc();
+        int it = 0;
+        for (; it < T - NSTAGE; ++it) {          // steady state: every tile here is a normal tile
+            first_half();
+            refill_half(seq(it + NSTAGE));
+        }
+        // the last tiles, nothing left to issue
 #pragma unroll 1
-        for (int it = 0; it < T - NSTAGE; ++it) {
-            const unsigned char *sb = smem + stage * STG;
-            const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-            load_frags(sb, 1);
-            mma_r(0);
-            load_frags(sb, 2);
-            mma_r(1);
-            load_frags(sb, 3);
-            mma_r(2);
-            wait_vmcnt<(NSTAGE - 2) * NL>();
+        for (; it < T - 1; ++it) {
+            first_half();
+            wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);       // stage it + 1 has landed
             wait_lgkmcnt0();
             __builtin_amdgcn_s_barrier();
-            load_frags(smem + nstage * STG, 0);
-            issue(seq(it + NSTAGE), stage);
-            mma_r(3);
-            stage = nstage;
+            load_frags(smem + next_of(stage) * STG, 0);
+            mma(1);
+            interleave_reads();
+            __builtin_amdgcn_sched_barrier(0);
+            stage = next_of(stage);
         }
-    } else {
-    // The accumulators start from the MFMA's inline zero in a first iteration of its own (128 register moves less
-    // per tile and wave than clearing them, in a phase that is bound by vector-ALU issue).
-    int it0 = 0;
-    if (T > NSTAGE) {
-        const unsigned char *sb = smem + stage * STG;
-        const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-        load_frags(sb, 1);
-        mma_z(0);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 2);
-        mma(1);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 3);
-        mma(2);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<(NSTAGE - 2) * NL>();
-        wait_lgkmcnt0();
-        __builtin_amdgcn_s_barrier();
-        load_frags(smem + nstage * STG, 0);
-        issue(seq(NSTAGE), stage);
-        mma(3);
-        interleave_reads_and_loads();
-        __builtin_amdgcn_sched_barrier(0);
-        stage = nstage;
-        it0 = 1;
-    } else {
-        clear_acc();
+        // the very last one is the head tile, if there is one: only its normal part, what lies past the outlier range (which may
+        // end in the middle of a k-step), is summed here
+        load_frags(smem + stage * STG, 1);
+        if (o_steps == 1) mask_w(0, fq >= 2);
+        if (o_steps < 2) mma(0);
+        if (o_steps == 3) mask_w(1, fq >= 2);
+        if (o_steps < 4) mma(1);
     }
-    for (int it = it0; it < T - NSTAGE; ++it) {    // steady state: every tile here is a normal tile
-        const unsigned char *sb = smem + stage * STG;
-        const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-        load_frags(sb, 1);
-        mma(0);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 2);
-        mma(1);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 3);
-        mma(2);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);       // the waits below must not float up into the MFMAs
-#if QARVD_PROF
-        const long long q1 = clock64();
-#endif
-        wait_vmcnt<(NSTAGE - 2) * NL>();
-        wait_lgkmcnt0();
-        __builtin_amdgcn_s_barrier();
-#if QARVD_PROF
-        p_bar += clock64() - q1;
-#endif
-        load_frags(smem + nstage * STG, 0);
-        issue(seq(it + NSTAGE), stage);
-        mma(3);
-        interleave_reads_and_loads();
-        __builtin_amdgcn_sched_barrier(0);
-        stage = nstage;
-    }
-    }
-    // Two stages: the second-to-last K tile is always a normal one; it runs through a copy of the scheduled
-    // iteration that has nothing to refill, which leaves only the last tile (the head tile, if any) to the
-    // unscheduled drain loop below.
-    int drain_from = T > NSTAGE ? T - NSTAGE : 0;
-    if (NSTAGE == 2 && i_lim == TM && T >= 2) {
-        const unsigned char *sb = smem + stage * STG;
-        const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-        load_frags(sb, 1);
-        mma(0);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 2);
-        mma(1);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(sb, 3);
-        mma(2);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vmcnt<0>();
-        wait_lgkmcnt0();
-        __builtin_amdgcn_s_barrier();
-        load_frags(smem + nstage * STG, 0);
-        mma(3);
-        interleave_reads();
-        __builtin_amdgcn_sched_barrier(0);
-        stage = nstage;
-        drain_from = T - 1;
-    }
-    // drain: the last tiles, nothing left to issue; the head tile is the last of them and only its
-    // normal k-steps (those past the outlier range) are summed here
-#pragma unroll 1
-    for (int it = drain_from; it < T; ++it) {
-        const unsigned char *sb = smem + stage * STG;
-        const int nstage = stage + 1 == NSTAGE ? 0 : stage + 1;
-        const int first = it < Tn ? 0 : o_steps;    // first k-step of this tile that belongs to the normal range
-        load_frags(sb, 1);
-        if (0 >= first) mma_r(0);
-        load_frags(sb, 2);
-        if (1 >= first) mma_r(1);
-        load_frags(sb, 3);
-        if (2 >= first) mma_r(2);
-        if (it + 1 < T) {
-            wait_stages_in_flight<(NSTAGE >= 2 ? NSTAGE - 2 : 0), NL>(T - 2 - it);   // stage it + 1 has landed
-            wait_lgkmcnt0();
-            __builtin_amdgcn_s_barrier();
-            load_frags(smem + nstage * STG, 0);
-        }
-        if (3 >= first) mma_r(3);
-        stage = nstage;
-    }
-    }
-    const long long p_t1 = QARVD_PROF ? clock64() : 0;
+    [[maybe_unused]] const long long p_t1 = QARVD_PROF ? clock64() : 0;
     wait_lgkmcnt0();                // this wave's scale writes and fragment reads have landed ...
     __builtin_amdgcn_s_barrier();   // ... and everyone is done with every stage but the head tile's
 
     // ---- epilogue -------------------------------------------------------------------------
     // the head tile sits in stage (base + Tn) % NSTAGE; the patches behind the stages, or in the stage read just
     // before the head; the rest of the ring takes the next tile's first PF stages
+    // (the lane number is taken anew: what the epilogue derives from it would otherwise be kept, or spilled, through the K loop)
+    int el = lane;
+    asm volatile("" : "+v"(el));
+    const int er = el & 15, eq = el >> 4;
     const int hstage0 = (base + Tn) % NSTAGE;
     const int pstage = (base + Tn - 1 + 2 * NSTAGE) % NSTAGE;
     const int nbase = (base + T) % NSTAGE;
@@ -526,31 +428,32 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
     const float *sx_lds = sc_lds, *sn_lds = sc_lds + BM, *so_lds = sc_lds + BM + BN, *bs_lds = sc_lds + BM + 2 * BN;
     unsigned char *const patch = (G::PATCH_EXTRA ? smem + G::PATCH_OFF : smem + pstage * STG) + wave * PATCH2_BYTES;
     OutT *Y = reinterpret_cast<OutT *>(g.Y);
-    constexpr int EPC = 16 / sizeof(OutT);          // output elements per 16-byte chunk
-    const int pswz = (frow >> 2) & 3;               // chunk swizzle of this lane's patch row when writing
-    constexpr int ESZ = (int)sizeof(OutT);
+    constexpr int ESZ = (int)sizeof(OutT), EPC = 16 / ESZ;     // output elements per 16-byte chunk
+    // A patch is 16 rows of 128 bytes, whole lines of the output, or 32 rows of 64 where a wave's row is that short.  Block (i, j)
+    // puts this lane's four outputs, columns 16 j + 4 eq .., into row 16 i + er.  Read back, lane l takes chunk l % chunks of a
+    // row; the rows go to the lanes so that the sixteen lanes a pass serves, 8p .. 8p+7 and 32+8p .. 32+8p+7, cover the banks.
+    constexpr int PRS = G::WTN * ESZ >= 128 ? 128 : 64, PROWS = PATCH2_BYTES / PRS, PCH = PRS / 16;
+    constexpr int PCB = PRS / ESZ / 16, PRB = PROWS / 16;      // blocks of a patch: columns, rows
+    static_assert(G::WTN * ESZ % PRS == 0 && (PRB == 1 || PCB == TN), "patches are whole rows of the wave tile, or parts of one row block");
+    auto pswz = [](int row) { return PRS == 128 ? swz128(row) : (row >> 2) & 3; };
+    const int prow = PRS == 128 ? 2 * ((el >> 3) & 3) + (el >> 5) : 4 * ((el >> 3) & 3) + 2 * (el >> 5) + ((el >> 2) & 1);
+    const int pch = el & (PCH - 1);
+    const int pw_addr = er * PRS + ((((4 * eq * ESZ) >> 4) ^ pswz(er)) << 4) + ((4 * eq * ESZ) & 15);     // column block 0 of a patch
     unsigned char *const y_tile = reinterpret_cast<unsigned char *>(Y + (size_t)m0 * g.ldy);
     const int ldy_b = (int)g.ldy * ESZ;
     const int y_bytes = (min(BM, g.M - m0) - 1) * ldy_b + g.N * ESZ;
-    const int y_lane = (wm * G::WTM + (lane >> 2)) * ldy_b + (n0 + wn * G::WTN + (lane & 3) * EPC) * ESZ;
-    const int n_left = g.N - n0 - wn * G::WTN - (lane & 3) * EPC;     // columns from this lane's chunk to the matrix edge
-    const bool has_o = DUAL && o_steps > 0;
+    const int y_lane = (wm * G::WTM + prow) * ldy_b + (n0 + wn * G::WTN + pch * EPC) * ESZ;
+    const int n_left = g.N - n0 - wn * G::WTN - pch * EPC;            // columns from this lane's chunk to the matrix edge
     const bool wt = g.store_wt != 0;
     const StaticQuant sq = make_static_quant(sizeof(OutT) == 1 ? g.out_scale : 1.0f);
 
-    // Software pipeline over 32 x 32 blocks, as in the 64-byte-stage kernel: a patch is read back as soon as it
-    // is complete and stored after the next block's arithmetic; the outlier MFMAs of the next block start before
-    // the current block's arithmetic; the row block is the outer loop so that the two halves of a 128-byte
-    // output line are written back to back.
-    auto epilogue = [&](auto haso_tag) {
-        constexpr bool HASO = decltype(haso_tag)::value;
-        constexpr int NBLK = TM * TN;
-        auto blk_i = [&](int b) { return b / TN; };
-        // column blocks run back and forth (0 .. TN-1, TN-1 .. 0, ...): consecutive row blocks then share a column
-        // block at the turn, and its scales and biases -- twelve broadcast 16-byte LDS reads per lane, the
-        // epilogue's largest LDS traffic -- are loaded once for both (5 loads instead of 8 per 4 x 2 wave tile)
-        auto blk_j = [&](int b) { return ((b / TN) & 1) ? TN - 1 - b % TN : b % TN; };
-
+    // Software pipeline over the 16 x 16 blocks, row blocks outermost: a patch is read back as soon as it is complete and
+    // stored after the next block's arithmetic; the outlier MFMAs of a row of blocks start before its arithmetic.  A lane
+    // serves the same 4 TN columns in every row block, so their scales and biases are read once a tile, and so are the W fragments
+    // of the outlier range's first 64 bytes.
+    auto epilogue = [&](auto steps_tag) {
+        constexpr int OSTEPS = decltype(steps_tag)::value;      // k-steps of the outlier range (GEN: 1 if there is one)
+        constexpr bool HASO = OSTEPS > 0;
         v4i pend[2];
         int pend_voff = 0, pend_soff = 0, pend_row = 0, pend_col = 0;
         bool pending = false, stored = false;       // compile-time after unrolling
@@ -558,7 +461,7 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
             const int left = n_left - pend_col;     // columns of the matrix from this lane's chunk on
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int ml = wm * G::WTM + pend_row + p * 16 + (lane >> 2);
+                const int ml = wm * G::WTM + pend_row + p * (PROWS / 2) + prow;
                 if (m0 + ml >= g.M) continue;
                 OutT *const y = Y + (size_t)(m0 + ml) * g.ldy + (g.N - left);
                 if (left >= EPC) {
@@ -592,137 +495,124 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
             }
             if (!GEN || g.vec_out) {
 #pragma unroll
-                for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * 16 * ldy_b, pend[p], wt);
+                for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * (PROWS / 2) * ldy_b, pend[p], wt);
             }
             pending = false;
         };
-        auto flush_issue = [&](int i, int col0) {   // col0: first column of the pass inside the wave tile
+        auto flush = [&](int row0, int col0) {      // first row and column of the patch inside the wave tile
+            flush_commit();
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int row = p * 16 + (lane >> 2), ch = lane & 3;
-                pend[p] = *reinterpret_cast<const v4i *>(patch + row * PATCH2_RS + ((ch ^ ((row >> 2) & 3)) << 4));
+                const int row = p * (PROWS / 2) + prow;
+                pend[p] = *reinterpret_cast<const v4i *>(patch + row * PRS + ((pch ^ pswz(row)) << 4));
             }
             pend_voff = col0 + EPC <= n_left ? y_lane : 0x7ffffff0;
-            pend_soff = i * 32 * ldy_b + col0 * ESZ;
-            pend_row = i * 32;
+            pend_soff = row0 * ldy_b + col0 * ESZ;
+            pend_row = row0;
             pend_col = col0;
             pending = true;
         };
-        auto flush = [&](int i, int col0) {
-            flush_commit();
-            flush_issue(i, col0);
-        };
-        auto head_mma = [&](int i, int j) -> v16i {   // outlier sum of block (i, j): the first k-step starts from zero
-            const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-            const unsigned char *hb = smem + hstage0 * STG;
-            v16i ao = __builtin_amdgcn_mfma_i32_32x32x32_i8(
-                read_w(hb, j, wcoff[0]),
-                *reinterpret_cast<const v4i *>(hb + x_base + i * 32 * BK2 + coff[0]), zero, 0, 0, 0);
-            for (int s = 1; s < o_steps; ++s) {
-                const int c = s == 1 ? coff[1] : s == 2 ? coff[2] : coff[3];
-                const v4i wo = read_w(hb, j, s == 1 ? wcoff[1] : s == 2 ? wcoff[2] : wcoff[3]);
-                const v4i xo = *reinterpret_cast<const v4i *>(hb + x_base + i * 32 * BK2 + c);
-                ao = __builtin_amdgcn_mfma_i32_32x32x32_i8(wo, xo, ao, 0, 0, 0);
-            }
-            return ao;
-        };
 
-        float sxr[TM];
+        v4f sn[TN], so[TN], bs[TN];
 #pragma unroll
-        for (int i = 0; i < TM; ++i) sxr[i] = sx_lds[wm * G::WTM + i * 32 + frow];
-        v4f sn[4], so[4], bs[4];
-        auto load_cols = [&](int j) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int nt = wn * G::WTN + j * 32 + 8 * q + 4 * fhalf;      // column inside the workgroup tile
-                sn[q] = *reinterpret_cast<const v4f *>(sn_lds + nt);
-                if constexpr (HASO) so[q] = *reinterpret_cast<const v4f *>(so_lds + nt);
-                bs[q] = *reinterpret_cast<const v4f *>(bs_lds + nt);
-            }
+        for (int j = 0; j < TN; ++j) {
+            const int nt = wn * G::WTN + j * 16 + 4 * eq;             // column inside the workgroup tile
+            sn[j] = *reinterpret_cast<const v4f *>(sn_lds + nt);
+            if constexpr (HASO) so[j] = *reinterpret_cast<const v4f *>(so_lds + nt);
+            bs[j] = *reinterpret_cast<const v4f *>(bs_lds + nt);
+        }
+        // The outlier sum of a block is multiplied while the block before it is worked on, from fragments read a row of blocks
+        // ahead.  Half k-steps past the end of the outlier range multiply by zero in the X fragment.
+        constexpr bool HEAD = HASO && !GEN;
+        const unsigned char *hb = smem + hstage0 * STG;
+        const int keep0 = o_steps > (eq >> 1) ? -1 : 0, keep1 = o_steps > 2 + (eq >> 1) ? -1 : 0;
+        constexpr bool HOLD = HEAD && OSTEPS == 1;      // the W fragments stay in registers, where there is room for them
+        v4i wh[HOLD ? TN : 1], xo0, xo1, xn0 = zero4, xn1 = zero4, ao_next = zero4;
+        auto read_head = [&](int i) {
+            if constexpr (HEAD) xn0 = read_x(hb, i, coff[0]) & keep0;
+            if constexpr (HEAD && OSTEPS > 1) xn1 = read_x(hb, i, coff[1]) & keep1;
         };
-        constexpr bool AO_AHEAD = HASO && !GEN && sizeof(OutT) <= 2 && !DBG && TM * TN < 8;   // 16 registers: only where they are to spare
-        v16i ao_next;
-        if constexpr (AO_AHEAD) ao_next = head_mma(blk_i(0), blk_j(0));
+        auto head_mma = [&](int j) {
+            if constexpr (HEAD) ao_next = __builtin_amdgcn_mfma_i32_16x16x64_i8(HOLD ? wh[HOLD ? j : 0] : read_w(hb, j, wcoff[0]), xo0, zero4, 0, 0, 0);
+            if constexpr (HEAD && OSTEPS > 1) ao_next = __builtin_amdgcn_mfma_i32_16x16x64_i8(read_w(hb, j, wcoff[1]), xo1, ao_next, 0, 0, 0);
+        };
+        if constexpr (HOLD) {
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-            const int i = blk_i(b), j = blk_j(b);
-            if (b == 0 || blk_j(b - 1) != j) load_cols(j);
-            v16i ao;
-            if constexpr (AO_AHEAD) {
-                ao = ao_next;
-                if (b + 1 < NBLK) ao_next = head_mma(blk_i(b + 1), blk_j(b + 1));
-            } else if constexpr (HASO && GEN) {
-                ao = acc_o[i][j];
-            } else if constexpr (HASO) {
-                ao = head_mma(i, j);
+            for (int j = 0; j < TN; ++j) wh[j] = read_w(hb, j, wcoff[0]);
+        }
+        read_head(0);
+        xo0 = xn0;
+        xo1 = xn1;
+        head_mma(0);
+        float sx_next = sx_lds[wm * G::WTM + er];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const float sx = sx_next;
+            if (i + 1 < TM) {
+                sx_next = sx_lds[wm * G::WTM + (i + 1) * 16 + er];
+                read_head(i + 1);
             }
-            const int m_lane = m0 + wm * G::WTM + i * 32 + frow;
-            const float sx = sxr[i];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int nt = wn * G::WTN + j * 32 + 8 * q + 4 * fhalf;
+            for (int j = 0; j < TN; ++j) {
+                v4i ao;
+                if constexpr (HASO && GEN) {
+                    ao = acc_o[i][j];
+                } else {
+                    ao = ao_next;
+                    if (j == TN - 1) {
+                        xo0 = xn0;
+                        xo1 = xn1;
+                    }
+                    if (i + 1 < TM || j + 1 < TN) head_mma((j + 1) % TN);
+                }
                 float y[4];
-                const float snv[4] = {sn[q].x, sn[q].y, sn[q].z, sn[q].w}, bsv[4] = {bs[q].x, bs[q].y, bs[q].z, bs[q].w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int r = 4 * q + e;
                     float v;
                     if constexpr (HASO) {
-                        const float sov[4] = {so[q].x, so[q].y, so[q].z, so[q].w};
-                        v = (float)ao[r] * sov[e];
-                        v = fmaf((float)acc[i][j][r], snv[e], v);
+                        v = (float)ao[e] * so[j][e];
+                        v = fmaf((float)acc[i][j][e], sn[j][e], v);
                     } else {
                         // acc_o == 0: (float)0 * s_o is +0 and the first fma reduces to this one
-                        v = fmaf((float)acc[i][j][r], snv[e], 0.0f);
+                        v = fmaf((float)acc[i][j][e], sn[j][e], 0.0f);
                     }
-                    y[e] = fmaf(v, sx, bsv[e]);
+                    y[e] = fmaf(v, sx, bs[j][e]);
                 }
                 if constexpr (DBG) {
-                    const int n = n0 + nt;
-                    if (m_lane < g.M) {
+                    const int m = m0 + wm * G::WTM + i * 16 + er, n = n0 + wn * G::WTN + j * 16 + 4 * eq;
+                    if (m < g.M) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             if (n + e >= g.N) continue;
-                            if (g.dbg_n) g.dbg_n[(size_t)m_lane * g.N + n + e] = acc[i][j][4 * q + e] >> (W4 ? 4 : 0);
+                            if (g.dbg_n) g.dbg_n[(size_t)m * g.N + n + e] = acc[i][j][e] >> (W4 ? 4 : 0);
                             if (g.dbg_o) {
                                 int aov = 0;
-                                if constexpr (HASO) aov = ao[4 * q + e] >> (W4 ? 4 : 0);
-                                g.dbg_o[(size_t)m_lane * g.N + n + e] = aov;
+                                if constexpr (HASO) aov = ao[e] >> (W4 ? 4 : 0);
+                                g.dbg_o[(size_t)m * g.N + n + e] = aov;
                             }
                         }
                     }
                 }
+                unsigned char *const pw = patch + (i % PRB) * 16 * PRS + (pw_addr ^ ((j % PCB) * 16 * ESZ));
                 if constexpr (sizeof(OutT) == 1) {
-                    // chained layer: activation, then the next layer's static scale (Eq. (quantization)); two
-                    // blocks of 32 INT8 columns share a 64-byte patch row
-                    static_assert(sizeof(OutT) != 1 || TN % 2 == 0, "INT8 output pairs the column blocks");
-                    const unsigned pk = quantize4_static<out_is_gelu<OutT>::value>(y, sq);
-                    const int c = 2 * (j & 1) + (q >> 1);
-                    *reinterpret_cast<unsigned *>(patch + frow * PATCH2_RS + ((c ^ pswz) << 4) + 8 * (q & 1) + 4 * fhalf) = pk;
+                    // chained layer: activation, then the next layer's static scale (Eq. (quantization))
+                    *reinterpret_cast<unsigned *>(pw) = quantize4_static<out_is_gelu<OutT>::value>(y, sq);
                 } else if constexpr (sizeof(OutT) == 2) {
                     v2u pk;
                     pk.x = cvt_pk_bf16(y[0], y[1]);
                     pk.y = cvt_pk_bf16(y[2], y[3]);
-                    *reinterpret_cast<v2u *>(patch + frow * PATCH2_RS + ((q ^ pswz) << 4) + 8 * fhalf) = pk;
+                    *reinterpret_cast<v2u *>(pw) = pk;
                 } else {
-                    const int c = 2 * (q & 1) + fhalf;
-                    *reinterpret_cast<v4f *>(patch + frow * PATCH2_RS + ((c ^ pswz) << 4)) = v4f{y[0], y[1], y[2], y[3]};
-                    if (q & 1) flush(i, j * 32 + (q >> 1) * 16);
+                    *reinterpret_cast<v4f *>(pw) = v4f{y[0], y[1], y[2], y[3]};
                 }
-            }
-            if constexpr (sizeof(OutT) == 2) flush(i, j * 32);
-            if constexpr (sizeof(OutT) == 1) {
-                if (b & 1) flush(i, (j & ~1) * 32);        // both blocks of a 64-column pair are in the patch
+                if (i % PRB == PRB - 1 && j % PCB == PCB - 1) flush(i / PRB * PROWS, j / PCB * PCB * 16);
             }
         }
         flush_commit();
     };
-    if constexpr (DUAL) {
-        if (has_o) epilogue(std::true_type{});
-        else epilogue(std::false_type{});
-    } else {
-        epilogue(std::false_type{});
-    }
+    if (!DUAL || o_steps == 0) epilogue(std::integral_constant<int, 0>{});
+    else if (GEN || o_steps <= 2) epilogue(std::integral_constant<int, DUAL ? 1 : 0>{});
+    else epilogue(std::integral_constant<int, DUAL && !GEN ? 2 : 0>{});
 #if QARVD_PROF
     {
         const long long p_t2 = clock64();

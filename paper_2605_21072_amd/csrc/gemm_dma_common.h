@@ -59,14 +59,18 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 
 // soffset wave-uniform).  The buffer descriptor (raw, no stride, no bounds) is rebuilt from `base` at
 // each call; it is wave-uniform, so the compiler keeps it in four SGPRs across the K loop.  The body
 // exists in the device pass only: the host pass has neither the descriptor type nor the builtin.
-__device__ __forceinline__ void buffer_load_lds16(const void *base, int voffset, int soffset, unsigned char *lds)
+__device__ __forceinline__ void buffer_load_lds16(const void *base, int bytes, int voffset, int soffset, unsigned char *lds)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, bytes, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, QARVD_LPTR(lds), 16, voffset, soffset, 0, 0);
 #else
-    (void)base; (void)voffset; (void)soffset; (void)lds;
+    (void)base; (void)bytes; (void)voffset; (void)soffset; (void)lds;
 #endif
+}
+__device__ __forceinline__ void buffer_load_lds16(const void *base, int voffset, int soffset, unsigned char *lds)
+{
+    buffer_load_lds16(base, 0x7fffffff, voffset, soffset, lds);
 }
 
 // One 16-byte store per lane through a raw buffer descriptor over [base, base + bytes): lanes whose

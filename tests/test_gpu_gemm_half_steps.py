@@ -1,0 +1,43 @@
+"""Outlier ranges of one to four 32-byte units beside K loops of every short length, on the 128-byte-stage tiles: the range may end in the
+middle of a 64-byte MFMA step, be the whole K, and the loop may be shorter than the LDS ring."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import bf16_bits, dev
+
+q = pytest.importorskip("paper_2605_21072_amd")
+pytestmark = pytest.mark.gpu
+
+
+def _pack(a, K, K_o):
+    n_off, kp = q.packed_normal_offset(K_o), q.packed_k(K, K_o)
+    out = np.zeros((a.shape[0], kp), np.int8)
+    out[:, :K_o] = a[:, :K_o]
+    out[:, n_off:n_off + K - K_o] = a[:, K_o:]
+    return out
+
+
+@pytest.mark.parametrize("M,N", [(17, 24), (145, 280), (300, 272)])     # a few rows of a tile; ragged tiles of every size
+@pytest.mark.parametrize("K,K_o", [(128, 0), (128, 32), (128, 64), (128, 96), (128, 128), (200, 90), (256, 32), (384, 96), (512, 33), (640, 128), (900, 1)])
+def test_every_tile(M, N, K, K_o):
+    rng = np.random.default_rng(M + N + K + K_o)
+    Xq, Wq = (rng.integers(-127, 128, (r, K)).astype(np.int8) for r in (M, N))
+    sx, sn, so = (rng.uniform(0.001, 0.1, n).astype(np.float32) for n in (M, N, N))
+    b = rng.standard_normal(N).astype(np.float32)
+    ref = oracle.dual_gemm(Xq, sx, Wq, sn, so, b, K_o)
+    w = q.DualScaleWeight(dev(_pack(Wq, K, K_o)), dev(sn), dev(so), None, K_o, N, K)
+    Xd, sxd, bd = dev(_pack(Xq, K, K_o)), dev(sx), dev(b)
+    ran = 0
+    for v in range(1, q.gemm_num_variants() + 1):
+        if "128-byte stages" not in q.gemm_variant_name(v) or ("single" in q.gemm_variant_name(v) and K_o):
+            continue
+        Yf, an, ao = q.w8a8_dual_gemm(Xd, sxd, w, bd, M, torch.float32, debug_acc=True, variant=v)
+        assert np.array_equal(an.cpu().numpy(), ref["acc_n"]) and np.array_equal(ao.cpu().numpy(), ref["acc_o"]), q.gemm_variant_name(v)
+        # the epilogue is defined operation by operation: bit-equal, in the builds without the accumulator dump too
+        assert np.array_equal(Yf.cpu().numpy(), ref["Y_f32"])
+        assert np.array_equal(q.w8a8_dual_gemm(Xd, sxd, w, bd, M, torch.float32, variant=v).cpu().numpy(), ref["Y_f32"])
+        assert np.array_equal(bf16_bits(q.w8a8_dual_gemm(Xd, sxd, w, bd, M, torch.bfloat16, variant=v)), ref["Y_bf16"])
+        ran += 1
+    assert ran >= 7
