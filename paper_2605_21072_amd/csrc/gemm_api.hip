@@ -5,8 +5,8 @@ using namespace qarvd_gemm;
 
 namespace {
 
-// Kernels that a call can ask for by number.  pick_variant chooses among 9, 10, 19 to 22 and 27 to 38, with 1 to 4 for
-// strides beyond 2^22; the others stay selectable for comparison.
+// Kernels that a call can ask for by number.  pick_variant chooses among 27 to 41, with 1 to 4 for strides beyond 2^22; the
+// others stay selectable for comparison.
 const Variant kVariants[] = {
     // name, BM, BN, widest outlier block (packed bytes), needs vector output, operand strides up to 2^22, launcher
     {"staged 256x128 dual", 256, 128, 1 << 30, false, false, launch_staged<256, 128, 2, 2, true>},
@@ -41,12 +41,15 @@ const Variant kVariants[] = {
     {"128-byte stages 256x128 (8 waves, 3 stages) single", 256, 128, 0, true, true, launch_dma128<256, 128, 4, 2, 3, false>},
     {"128-byte stages 128x256 (8 waves, 3 stages) dual", 128, 256, 128, true, true, launch_dma128<128, 256, 2, 4, 3, true>},
     {"128-byte stages 128x256 (8 waves, 3 stages) single", 128, 256, 0, true, true, launch_dma128<128, 256, 2, 4, 3, false>},
-    {"128-byte stages 128x128 (8 waves, 4 stages) dual", 128, 128, 128, true, true, launch_dma128<128, 128, 2, 4, 4, true>},
-    {"128-byte stages 128x128 (8 waves, 4 stages) single", 128, 128, 0, true, true, launch_dma128<128, 128, 2, 4, 4, false>},
+    {"128-byte stages 128x128 (8 waves, 3 stages) dual", 128, 128, 128, true, true, launch_dma128<128, 128, 2, 4, 3, true>},
+    {"128-byte stages 128x128 (8 waves, 3 stages) single", 128, 128, 0, true, true, launch_dma128<128, 128, 2, 4, 3, false>},
     {"128-byte stages 64x64 (4 waves, 4 stages) dual", 64, 64, 128, true, true, launch_dma128<64, 64, 2, 2, 4, true>},
     {"128-byte stages 64x64 (4 waves, 4 stages) single", 64, 64, 0, true, true, launch_dma128<64, 64, 2, 2, 4, false>},
-    {"128-byte stages 128x128 (8 waves, 4 stages) any width", 128, 128, 1 << 30, false, true, launch_dma128<128, 128, 2, 4, 4, true, true>},
+    {"128-byte stages 128x128 (8 waves, 3 stages) any width", 128, 128, 1 << 30, false, true, launch_dma128<128, 128, 2, 4, 3, true, true>},
     {"128-byte stages 64x64 (4 waves, 4 stages) any width", 64, 64, 1 << 30, false, true, launch_dma128<64, 64, 2, 2, 4, true, true>},
+    {"128-byte stages 64x128 (8 waves, 4 stages) dual", 64, 128, 128, true, true, launch_dma128<64, 128, 2, 4, 4, true>},
+    {"128-byte stages 64x128 (8 waves, 4 stages) single", 64, 128, 0, true, true, launch_dma128<64, 128, 2, 4, 4, false>},
+    {"128-byte stages 64x128 (8 waves, 4 stages) any width", 64, 128, 1 << 30, false, true, launch_dma128<64, 128, 2, 4, 4, true, true>},
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -68,25 +71,22 @@ bool variant_fits(const Variant &v, const GemmArgs &g, qarvd_dtype ydt)
     return true;
 }
 
-// Heuristic: a three-constant cost model per candidate, fitted to back-to-back timings on MI355X over the
-// DiT shapes (M = 64..4680, N and K in {1536, 4608, 5120, 8960, 13824}, operands at the padded strides of
-// qarvd_packed_ld) and some ragged ones:
+// Heuristic: a three-constant cost model per candidate, fitted to timings on MI355X (all tiles in turn, operands at the padded
+// strides of qarvd_packed_ld, M = 16..4680, N and K = 256..13824, fixed and drawn):
 //     time ~ c + ceil(tiles / CUs) * (a + b * T),     T = packed K / 64          (constants in microseconds)
 // c is launch plus the first tile's lead-in, a a tile's epilogue and hand-over, b one 64-byte K step of a tile
-// that has its CU to itself (two four-wave workgroups sharing a CU each run at half speed, which the ceil over
-// the CUs already accounts for).  All but two of the tiles run on 128-byte-deep stages (gemm_dma128.hip):
+// that has its CU to itself (two workgroups sharing a CU each run at half speed, which the ceil over
+// the CUs already accounts for).  All tiles run on 128-byte-deep stages (gemm_dma128.hip):
 // 256x256 has the cheapest K step per MAC and wins when N is wide; the half tiles fill the chip when N = 1536
-// (4680 x 8960 -> 1536: 60 us against 78 us for 256x256) and on M of a few hundred rows with N = 8960; 128x128 on eight
-// waves when those leave CUs empty over a long K (1560 x 8960 -> 1536: 31 us, 45 for the four-wave 128x128 tile on 64-byte
-// stages), the four-wave one while a packed row is at most 512 bytes: little loop to speed up, and two of its workgroups on a CU
-// cover each other's lead-in and epilogue (1634 x 352 -> 5088: 11.3 against 13.8, 4070 x 120 -> 1728: 6.7 against 7.3; but 3403 x
-// 678 -> 2624: 23.8 against 20.9); 64x64 when even those would leave most without a tile (520 x 8960 -> 1536:
-// 20.5 us, 24.2 on 64-byte stages).  Up to K of about 1600 the 64-byte-stage 64x64 tile is the faster
-// one (256 x 1536 -> 1536: 6.5 against 6.6 us, 16 x 256 -> 256: 3.8 against 4.2), and at any K while a quarter of the CUs or
-// fewer have a tile: the loads then wait for latency, not for lines, and six stages reach further than four (64 x 8960 ->
-// 1536, 24 tiles: 17.6 against 19.8 us; 64 x 5120 -> 5120, 80 tiles: 13.2 both; 64 x 13824 -> 5120: 34.8 against 28.8).
+// (4680 x 8960 -> 1536: 54 us against 79 us for 256x256) and on M of a few hundred rows with N = 8960; 128x128
+// when those leave CUs empty (1560 x 8960 -> 1536: 29 us against 45, 1560 x 1536 -> 1536 9.4 against 13.0); 64x128 between that and
+// 64x64 (256 x 5120 -> 5120: 15.5 against 18.8 and 17.7), 64x64 when even those would leave most without a tile (520 x 8960 ->
+// 1536: 17.0 against 22.6).  The smallest tiles' 64-byte-stage forms, which were the better ones on 32x32x32, are slower than these at
+// every size now (256 x 1536 -> 1536 6.7 against 5.9 us, 64 x 8960 -> 1536 19.2 against 15.3, 38 x 296 -> 1008 4.3 against 3.9).
+// Depth of the rings: 128x128 on three stages (4 and 3: 1560 x 1536 -> 1536 9.8 and 9.4, 4680 x 5120 -> 5120 even), 64x64 on four
+// (3 and 4: 256 x 8960 -> 1536 19.6 and 16.0; INT4 weights on three, 22.8 and 21.9 on four and three; eight: 22.7).
 // What needs the general kernels (outlier block over 128 bytes, N % 8 != 0, unaligned outputs) picks by the same model
-// from the two tiles built for it; operand strides beyond 2^22 go to the register-staged kernel.
+// from the three tiles built for it; operand strides beyond 2^22 go to the register-staged kernel.
 int device_cus()
 {
     int cus = 0;
@@ -104,7 +104,7 @@ int cheapest(const Cand *cand, int n, const GemmArgs &g)
     double best_cost = 1e300;
     for (int i = 0; i < n; ++i) {
         const Cand &c = cand[i];
-        if (c.bm == 64 && tiles128 > cus) continue;     // the small tiles only pay while 128x128 tiles leave CUs empty
+        if (c.bm == 64 && tiles128 > cus * c.bn / 64) continue;     // the small tiles only pay while 128x128 tiles leave CUs empty, or fill them badly
         const long tiles = (long)((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn);
         const double cost = c.c + (double)((tiles + cus - 1) / cus) * (c.a + c.b * T);
         if (cost < best_cost) {
@@ -119,21 +119,17 @@ int pick_variant(const GemmArgs &g, qarvd_dtype ydt)
 {
     const bool dual = g.n_off > 0;
     if (g.n_off <= 128 && vector_out_ok(g, ydt)) {
-        const long tiles64 = (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
-        Cand cand[8] = {{dual ? 27 : 28, 256, 256, 7.2, 9.2, 0.443},
-                        {dual ? 29 : 30, 256, 128, 4.5, 3.6, 0.379},
-                        {dual ? 31 : 32, 128, 256, 3.9, 3.9, 0.381},
-                        {dual ? 33 : 34, 128, 128, 1.6, 3.2, 0.200},
-                        {dual ? 19 : 20, 64, 128, 2.0, 0.8, 0.187},
-                        {dual ? 21 : 22, 64, 64, 2.0, 0.77, 0.152}};
-        int n = 6;
-        if (tiles64 * 4 > device_cus()) cand[n++] = {dual ? 35 : 36, 64, 64, 2.7, 0.9, 0.120};
-        if (g.kp <= 512) cand[n++] = {dual ? 9 : 10, 128, 128, 2.0, 1.9, 0.309};
-        return cheapest(cand, n, g);
+        const Cand cand[6] = {{dual ? 27 : 28, 256, 256, 0.50, 7.85, 0.539},
+                              {dual ? 29 : 30, 256, 128, 0.60, 5.81, 0.314},
+                              {dual ? 31 : 32, 128, 256, 0.55, 5.40, 0.333},
+                              {dual ? 33 : 34, 128, 128, 1.30, 3.60, 0.183},
+                              {dual ? 39 : 40, 64, 128, 1.91, 2.35, 0.157},
+                              {dual ? 35 : 36, 64, 64, 2.40, 0.77, 0.083}};
+        return cheapest(cand, 6, g);
     }
     if (short_rows_ok(g)) {
-        const Cand cand[2] = {{37, 128, 128, 1.8, 3.6, 0.200}, {38, 64, 64, 3.0, 1.0, 0.125}};
-        return cheapest(cand, 2, g);
+        const Cand cand[3] = {{37, 128, 128, 1.69, 4.01, 0.181}, {41, 64, 128, 1.62, 2.97, 0.131}, {38, 64, 64, 3.13, 0.98, 0.088}};
+        return cheapest(cand, 3, g);
     }
     const int cus = device_cus();
     const long tiles_big = (long)((g.M + 255) / 256) * ((g.N + 127) / 128);
@@ -228,8 +224,8 @@ const W4Variant kW4Variants[] = {
     {256, 256, 0, launch_dma128<256, 256, 2, 4, 3, true, false, true>, launch_dma128<256, 256, 2, 4, 3, true, false, true>},
     {256, 128, 0, launch_dma128<256, 128, 4, 2, 3, true, false, true>, launch_dma128<256, 128, 4, 2, 3, true, false, true>},
     {128, 256, 0, launch_dma128<128, 256, 2, 4, 3, true, false, true>, launch_dma128<128, 256, 2, 4, 3, true, false, true>},
-    {128, 128, 1, launch_dma128<128, 128, 2, 4, 4, true, true, true>, launch_dma128<128, 128, 2, 4, 4, true, true, true>},
-    {64, 64, 1, launch_dma128<64, 64, 2, 2, 4, true, true, true>, launch_dma128<64, 64, 2, 2, 4, true, true, true>},
+    {128, 128, 1, launch_dma128<128, 128, 2, 4, 3, true, true, true>, launch_dma128<128, 128, 2, 4, 3, true, true, true>},
+    {64, 64, 1, launch_dma128<64, 64, 2, 2, 3, true, true, true>, launch_dma128<64, 64, 2, 2, 3, true, true, true>},
 };
 constexpr int kNumW4Variants = sizeof(kW4Variants) / sizeof(kW4Variants[0]);
 }  // namespace
@@ -250,16 +246,14 @@ extern "C" qarvd_status qarvd_w4a8_dual_gemm(const int8_t *Xq, int64_t ldxq, con
         return s_c;
     const bool fast_ok = g.n_off <= 128 && g.vec_out;
     if (variant == 0) {
-        // The cost model of the INT8 path; the three aligned tiles on 128-byte stages carry its constants, which were not fitted
-        // again for INT4.  An INT4 weight stage is half as wide, so 256x256 has room for three stages and less LDS traffic a K step:
-        // 4680 x 5120 -> 13824 279 us (64-byte stages 309, INT8 weights 303); 4680 x 1536 -> 1536 15.8 (19.3), 520 x 8960 -> 1536
-        // 23.6 (41.7), 64 x 5120 -> 5120 15.1 (24.6); 2251 x 2360 -> 2252 with 150 outliers 27.0 against 65.6 register-staged,
-        // which keeps strides beyond 2^22.  Up to packed rows of 768 bytes the four-wave 128x128 tile on 64-byte stages is a
-        // candidate too, for the reason it is one there (1560 x 128 -> 5120: 9.5 against 12.1, 1780 x 640 -> 1160: 8.3 against 8.6).
-        const Cand cand[6] = {{7, 128, 128, 1.8, 3.6, 0.205}, {8, 64, 64, 3.4, 1.1, 0.135},
-                              {4, 256, 256, 7.2, 9.2, 0.443}, {5, 256, 128, 4.5, 3.6, 0.379}, {6, 128, 256, 3.9, 3.9, 0.381},
-                              {2, 128, 128, 3.4, 1.5, 0.309}};
-        variant = !short_rows_ok(g) ? 3 : cheapest(cand, !fast_ok ? 2 : g.kp <= 768 ? 6 : 5, g);
+        // The cost model of the INT8 path, with constants of its own.  An INT4 weight stage is half as wide, so 256x256 has room for
+        // three stages and less LDS traffic a K step: 4680 x 5120 -> 13824 280 us (64-byte stages 309), 4680 x 1536 -> 1536 15.7
+        // (19.3), 520 x 8960 -> 1536 22.5 (41.7), 64 x 5120 -> 5120 14.4 (24.6); 2251 x 2360 -> 2252 with 150 outliers 27.0 against
+        // 65.6 register-staged, which keeps strides beyond 2^22.  (The 64-byte-stage 128x128 tile is no candidate any more: level at
+        // best, 2609 x 277 -> 1400 7.9 both, elsewhere 84 x 732 -> 4008 8.1 against 5.5.)
+        const Cand cand[5] = {{7, 128, 128, 2.74, 3.47, 0.196}, {8, 64, 64, 3.60, 1.00, 0.101},
+                              {4, 256, 256, 2.80, 8.00, 0.517}, {5, 256, 128, 1.59, 4.44, 0.366}, {6, 128, 256, 1.29, 4.79, 0.357}};
+        variant = !short_rows_ok(g) ? 3 : cheapest(cand, fast_ok ? 5 : 2, g);
     }
     const int form = kW4Variants[variant - 1].form;
     if ((form == 0 && !fast_ok) || (form == 1 && !short_rows_ok(g))) return QARVD_ERR_UNSUPPORTED;     // a tile asked for by name
@@ -276,12 +270,14 @@ struct Q8Variant {
     qarvd_status (*single)(const GemmArgs &, hipStream_t);
 };
 const Q8Variant kQ8Variants[] = {
-    {256, 256, 2.2, 8.9, 0.688, launch_dma_q8<256, 256, 2, 4, 4, true>, launch_dma_q8<256, 256, 2, 4, 4, false>},
-    {128, 256, 5.0, 2.75, 0.490, launch_dma_q8<128, 256, 2, 4, 4, true>, launch_dma_q8<128, 256, 2, 4, 4, false>},
-    {128, 128, 2.0, 1.5, 0.309, launch_dma_q8<128, 128, 2, 2, 4, true>, launch_dma_q8<128, 128, 2, 2, 4, false>},
-    {256, 256, 7.2, 9.2, 0.443, launch_dma128_q8<256, 256, 2, 4, 2, true>, launch_dma128_q8<256, 256, 2, 4, 2, false>},
-    {256, 128, 4.5, 3.6, 0.379, launch_dma128_q8<256, 128, 4, 2, 3, true>, launch_dma128_q8<256, 128, 4, 2, 3, false>},
-    {128, 256, 3.9, 3.9, 0.381, launch_dma128_q8<128, 256, 2, 4, 3, true>, launch_dma128_q8<128, 256, 2, 4, 3, false>},
+    // 64-byte stages: chosen by number only (128x128: 256 x 5120 -> 5120 28 us against 20 for the last one)
+    {256, 256, 0, 0, 0, launch_dma_q8<256, 256, 2, 4, 4, true>, launch_dma_q8<256, 256, 2, 4, 4, false>},
+    {128, 256, 0, 0, 0, launch_dma_q8<128, 256, 2, 4, 4, true>, launch_dma_q8<128, 256, 2, 4, 4, false>},
+    {128, 128, 0, 0, 0, launch_dma_q8<128, 128, 2, 2, 4, true>, launch_dma_q8<128, 128, 2, 2, 4, false>},
+    {256, 256, 1.48, 11.37, 0.489, launch_dma128_q8<256, 256, 2, 4, 2, true>, launch_dma128_q8<256, 256, 2, 4, 2, false>},
+    {256, 128, 1.53, 6.29, 0.319, launch_dma128_q8<256, 128, 4, 2, 3, true>, launch_dma128_q8<256, 128, 4, 2, 3, false>},
+    {128, 256, 1.38, 6.22, 0.326, launch_dma128_q8<128, 256, 2, 4, 3, true>, launch_dma128_q8<128, 256, 2, 4, 3, false>},
+    {128, 128, 1.49, 3.83, 0.159, launch_dma128_q8<128, 128, 4, 2, 3, true>, launch_dma128_q8<128, 128, 4, 2, 3, false>},
 };
 constexpr int kNumQ8Variants = sizeof(kQ8Variants) / sizeof(kQ8Variants[0]);
 }  // namespace
@@ -320,6 +316,7 @@ extern "C" qarvd_status qarvd_w8a8_dual_gemm_q8(const int8_t *Xq, int64_t ldxq, 
         const int cus = device_cus();
         for (int i = 0; i < kNumQ8Variants; ++i) {
             const Q8Variant &c = kQ8Variants[i];
+            if (c.a == 0) continue;
             const long tiles = (long)((M + c.BM - 1) / c.BM) * ((N + c.BN - 1) / c.BN);
             const double cost = c.c + (double)((tiles + cus - 1) / cus) * (c.a + c.b * T);
             if (cost < best_cost) { best_cost = cost; variant = i + 1; }

@@ -208,18 +208,19 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
 #pragma unroll
         for (int i = 0; i < TM; ++i) xf[ks][i] = read_x(sb, i, coff[ks]);
     };
-    auto mma = [&](int ks) {
+    auto mma_to = [&](auto &sums, int ks, int keep) {      // keep: -1, or 0 in lanes whose part of the k-step is left out
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[ks][j], xf[ks][i], acc[i][j], 0, 0, 0);
+                sums[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[ks][j] & keep, xf[ks][i], sums[i][j], 0, 0, 0);
     };
-    auto clear_acc = [&]() {
+    auto mma = [&](int ks) { mma_to(acc, ks, -1); };
+    auto clear = [&](auto &sums) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = zero4;
+            for (int j = 0; j < TN; ++j) sums[i][j] = zero4;
     };
     auto mask_w = [&](int ks, bool keep) {         // lanes that do not keep their bytes multiply by zero
 #pragma unroll
@@ -314,51 +315,41 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
         stage = next_of(stage);
     };
     if constexpr (GEN) {
-        // Natural K order.  The tiles up to the one in which the outlier range ends go through an unscheduled loop; at its
-        // end the sums so far become the outlier accumulators and the normal ones start from zero (in the middle of a k-step:
-        // its two halves are multiplied one after the other, the other half's lanes zeroed).  The rest runs
-        // through the scheduled iteration with nothing in it that knows of the split (a
-        // test between the k-steps of one loop for all cost 40 % of the loop's rate).
-        clear_acc();
+        // Natural K order.  The tiles up to the one in which the outlier range ends go through an unscheduled loop, that one is
+        // multiplied twice, each time with the lanes of the other range zeroed, and the rest runs through the scheduled iteration
+        // with nothing in it that knows of the split (a test between the k-steps of one loop for all cost 40 % of its rate).
         const int o_tile = o_steps >> 2, o_sub = o_steps & 3;
-        auto split = [&]() {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) acc_o[i][j] = acc[i][j];
-            clear_acc();
-        };
-        int it = 0;
-#pragma unroll 1
-        for (; it <= o_tile && it < T; ++it) {
-            const unsigned char *sb = smem + stage * STG;
-#pragma unroll
-            for (int ks = 0; ks < KS2; ++ks) {
-                if (ks + 1 < KS2) {
-                    load_frags(sb, ks + 1);
-                } else if (it + 1 < T) {
-                    wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);
-                    wait_lgkmcnt0();
-                    __builtin_amdgcn_s_barrier();
-                }
-                if (it == o_tile && 2 * ks == o_sub) split();
-                if (it == o_tile && 2 * ks + 1 == o_sub) {
-                    v4i whole[TN];
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) whole[j] = wf[ks][j];
-                    mask_w(ks, fq < 2);
-                    mma(ks);
-                    split();
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) wf[ks][j] = whole[j];
-                    mask_w(ks, fq >= 2);
-                }
-                mma(ks);
+        auto other_half = [&](int it, auto mma1) {
+            if (it + 1 < T) {
+                wait_stages_in_flight<NSTAGE - 2, NL>(T - 2 - it);
+                wait_lgkmcnt0();
+                __builtin_amdgcn_s_barrier();
             }
+            mma1();
             __builtin_amdgcn_sched_barrier(0);
             if (it + 1 < T) load_frags(smem + next_of(stage) * STG, 0);
             if (it + NSTAGE < T) issue(it + NSTAGE, stage);
             stage = next_of(stage);
+        };
+        clear(acc_o);
+        int it = 0;
+#pragma unroll 1
+        for (; it < o_tile && it < T; ++it) {
+            load_frags(smem + stage * STG, 1);
+            mma_to(acc_o, 0, -1);
+            other_half(it, [&]() { mma_to(acc_o, 1, -1); });
+        }
+        clear(acc);
+        if (o_sub > 0 && it < T) {
+            const int in0 = o_sub > (fq >> 1) ? -1 : 0, in1 = o_sub > 2 + (fq >> 1) ? -1 : 0;       // this lane's half k-steps of the range
+            load_frags(smem + stage * STG, 1);
+            mma_to(acc_o, 0, in0);
+            mma_to(acc, 0, ~in0);
+            other_half(it, [&]() {
+                mma_to(acc_o, 1, in1);
+                mma_to(acc, 1, ~in1);
+            });
+            ++it;
         }
         for (; it < T - NSTAGE; ++it) {
             first_half();
@@ -376,9 +367,8 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
             mma(1);
             stage = next_of(stage);
         }
-        if (o_tile >= T) split();        // every k-step belongs to the outlier range
     } else {
-        clear_acc();
+        clear(acc);
         int it = 0;
         for (; it < T - NSTAGE; ++it) {          // steady state: every tile here is a normal tile
             first_half();
@@ -687,6 +677,7 @@ qarvd_status launch_dma128_q8(const GemmArgs &g0, hipStream_t st)
 QARVD_INST128_Q8(256, 256, 2, 4, 2)
 QARVD_INST128_Q8(256, 128, 4, 2, 3)
 QARVD_INST128_Q8(128, 256, 2, 4, 3)
+QARVD_INST128_Q8(128, 128, 4, 2, 3)
 
 #define QARVD_INST128(BM, BN, WM, WN, NS)                                                                        \
     template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, false, false>(const GemmArgs &, qarvd_dtype, hipStream_t);   \
@@ -694,12 +685,14 @@ QARVD_INST128_Q8(128, 256, 2, 4, 3)
 QARVD_INST128(256, 256, 2, 4, 2)
 QARVD_INST128(256, 128, 4, 2, 3)
 QARVD_INST128(128, 256, 2, 4, 3)
-QARVD_INST128(128, 128, 2, 4, 4)
+QARVD_INST128(128, 128, 2, 4, 3)
+QARVD_INST128(64, 128, 2, 4, 4)
 QARVD_INST128(64, 64, 2, 2, 4)
 
 #define QARVD_INST128_GEN(BM, BN, WM, WN, NS)                                                                    \
     template qarvd_status launch_dma128<BM, BN, WM, WN, NS, true, true, false>(const GemmArgs &, qarvd_dtype, hipStream_t);
-QARVD_INST128_GEN(128, 128, 2, 4, 4)
+QARVD_INST128_GEN(128, 128, 2, 4, 3)
+QARVD_INST128_GEN(64, 128, 2, 4, 4)
 QARVD_INST128_GEN(64, 64, 2, 2, 4)
 
 #define QARVD_INST128_W4(BM, BN, WM, WN, NS, GEN)                                                                    \
@@ -707,7 +700,7 @@ QARVD_INST128_GEN(64, 64, 2, 2, 4)
 QARVD_INST128_W4(256, 256, 2, 4, 3, false)
 QARVD_INST128_W4(256, 128, 4, 2, 3, false)
 QARVD_INST128_W4(128, 256, 2, 4, 3, false)
-QARVD_INST128_W4(128, 128, 2, 4, 4, true)
-QARVD_INST128_W4(64, 64, 2, 2, 4, true)
+QARVD_INST128_W4(128, 128, 2, 4, 3, true)
+QARVD_INST128_W4(64, 64, 2, 2, 3, true)
 
 }  // namespace qarvd_gemm

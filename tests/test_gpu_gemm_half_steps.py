@@ -41,3 +41,20 @@ def test_every_tile(M, N, K, K_o):
         assert np.array_equal(bf16_bits(q.w8a8_dual_gemm(Xd, sxd, w, bd, M, torch.bfloat16, variant=v)), ref["Y_bf16"])
         ran += 1
     assert ran >= 7
+
+
+@pytest.mark.parametrize("M,N,K,K_o", [(1, 8, 100, 0), (65, 136, 640, 128), (129, 392, 1280, 96), (520, 1536, 8960, 32), (1560, 1536, 2048, 64), (2300, 2312, 200, 33)])
+def test_aligned_tiles_against_the_general_one(M, N, K, K_o):
+    """Every aligned 128-byte-stage tile on longer loops and on more tiles than workgroups, against the general tile (pinned to the oracle)."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N)
+    Xq, Wq = (torch.randint(-127, 128, (r, q.packed_k(K, K_o)), generator=gen, device="cuda", dtype=torch.int8) for r in (M, N))
+    sx, sn, so, b = (torch.rand(n, generator=gen, device="cuda") * 0.1 for n in (M, N, N, N))
+    w = q.DualScaleWeight(Wq, sn, so, None, K_o, N, K)
+    names = {v: q.gemm_variant_name(v) for v in range(1, q.gemm_num_variants() + 1)}
+    general = [v for v in names if "any width" in names[v]]
+    tiles = [v for v in names if "128-byte stages" in names[v] and ("dual" if K_o else "single") in names[v]]
+    assert len(general) == 3 and len(tiles) == 6
+    for dt in (torch.float32, torch.bfloat16):
+        want = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=general[0])
+        for v in general[1:] + tiles:
+            assert torch.equal(q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=v), want), names[v]
