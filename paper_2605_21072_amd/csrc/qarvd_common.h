@@ -140,6 +140,17 @@ __device__ __forceinline__ int wave_sum_all(int v)
 {
     return wave_reduce_bits(v, [](int x, auto move) { return x + move(0, x); });
 }
+// Inclusive running sum over the lanes, by the same moves (the row_bcast steps add to the rows behind their source only).
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += dpp_move<0x111>(0, v);
+    v += dpp_move<0x112>(0, v);
+    v += dpp_move<0x114>(0, v);
+    v += dpp_move<0x118>(0, v);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
 __device__ __forceinline__ unsigned wave_min_all(unsigned v)
 {
     return (unsigned)wave_reduce_bits((int)v, [](int x, auto move) { return (int)min((unsigned)x, (unsigned)move(x, x)); });

@@ -8,10 +8,10 @@
 // n 2^-53 (relative) of the exact sum in any order, so when the whole interval around the parallel sum leads to the
 // same fp32 norm (or the same comparison), the ordered sum does too.  The rare sums that fail the test (about
 // 3 columns in 10^5 at 8960 rows) are redone in order.  W is streamed twice: once for the norms, once by
-// the row quantizer; detection between them is one workgroup working from registers.
+// the row quantizer; detection between them is one workgroup that sorts the norms.
 //   kernel times, us        norms       detection    scales and codes
-//   8960 x 1536, INT8       15 (397)    22 (258)     19 (32)
-//   1536 x 8960, INT4, clip 15 (70)     30 (1316)    50 (4697: search, codes, packing)
+//   8960 x 1536, INT8       15 (397)    9.5 (258)    19 (32)
+//   1536 x 8960, INT4, clip 14 (70)     18 (1316)    50 (4697: search, codes, packing)
 // In brackets one thread per column, O(K^2) rankings, one thread per (row, block) for the search and byte stores.
 #include "qarvd_common.h"
 
@@ -82,34 +82,37 @@ __global__ __launch_bounds__(256) void norm_partial_kernel(const float *__restri
             (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
 }
 
-// Pass 2: 64 columns per workgroup, four threads per column.  With S the parallel sum and n = N terms, both S and the
+// Pass 2: 64 columns per workgroup, sixteen threads per column.  With S the parallel sum and n = N terms, both S and the
 // ordered sum are within n u / (1 - n u) of the exact one (u = 2^-53), so the ordered sum lies in
 // S (1 -+ 2.5 (n + 2) u), which leaves room for the roundings of the bounds themselves.  sqrt and the conversion
 // to float are monotone: equal ends mean that the ordered sum gives this float.  A sum is NaN if a term is, in any order.
-__global__ __launch_bounds__(256) void norm_final_kernel(const double *__restrict__ partial, int chunks,
+__global__ __launch_bounds__(1024) void norm_final_kernel(const double *__restrict__ partial, int chunks,
                                                          const float *__restrict__ W, int N, int K, int64_t ldw,
                                                          float *__restrict__ v, float *__restrict__ v_out)
 {
-    __shared__ double part[4][64];
+    __shared__ double part[16][64];
     __shared__ unsigned long long redo;
-    __shared__ float stage[256];
+    __shared__ float stage[1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int k = blockIdx.x * 64 + lane;
     const double *p = partial + min(k, K - 1);
     double S = 0.0;
     int c = wave;
-    for (; c + 28 < chunks; c += 32) {
+    for (; c + 112 < chunks; c += 128) {
         double t[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = p[(size_t)(c + 4 * i) * K];
+        for (int i = 0; i < 8; ++i) t[i] = p[(size_t)(c + 16 * i) * K];
 #pragma unroll
         for (int i = 0; i < 8; ++i) S += t[i];
     }
-    for (; c < chunks; c += 4) S += p[(size_t)c * K];
+#pragma unroll 4
+    for (; c < chunks; c += 16) S += p[(size_t)c * K];
     part[wave][lane] = S;
     __syncthreads();
     if (wave == 0) {
-        S = (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]);
+        S = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) S += part[w][lane];
         const double e = 2.5 * ((double)N + 2.0) * 0x1p-53;
         const float lo = (float)sqrt(S * (1.0 - e)), hi = (float)sqrt(S * (1.0 + e));
         const bool settled = lo == hi || S != S;
@@ -121,14 +124,14 @@ __global__ __launch_bounds__(256) void norm_final_kernel(const double *__restric
         if (lane == 0) redo = bad;
     }
     __syncthreads();
-    for (unsigned long long m = redo; m; m &= m - 1) {       // in order, 256 rows at a time through LDS
+    for (unsigned long long m = redo; m; m &= m - 1) {       // in order, 1024 rows at a time through LDS
         const int kr = blockIdx.x * 64 + __builtin_ctzll(m);
         double T = 0.0;
-        for (int r0 = 0; r0 < N; r0 += 256) {
+        for (int r0 = 0; r0 < N; r0 += 1024) {
             if (r0 + (int)threadIdx.x < N) stage[threadIdx.x] = W[(size_t)(r0 + threadIdx.x) * ldw + kr];
             __syncthreads();
             if (threadIdx.x == 0) {
-                const int lim = min(256, N - r0);
+                const int lim = min(1024, N - r0);
                 for (int i = 0; i < lim; ++i) {
                     const double d = (double)stage[i];
                     T = fma(d, d, T);
@@ -144,43 +147,28 @@ __global__ __launch_bounds__(256) void norm_final_kernel(const double *__restric
     }
 }
 
-// ---- detection and permutation: one workgroup ------------------------------------------------
-// Norms are non-negative floats, so their bit patterns order as they do, and any order statistic is found by
-// bisecting the pattern range with counts (one compare and one add per value, keys in registers), and once at most 64
-// values are left in the range they are ranked directly.  Three selections (median, MAD, the K_o-th largest norm) of
-// about ten counts each replace two O(K^2) rankings of all the values (K = 1536: 112 us each; 8960: 640 us).
-// The MAD's doubles are bisected by their upper 32 bits first.
-// One workgroup on an otherwise idle chip is bound by latency: a count ends at a barrier, so the workgroup has few waves, and
-// code that runs once is fetched from memory at about a microsecond per kilobyte, so every loop but the count itself is rolled
-// (everything unrolled over register-resident values: 10 KB and 25 us at K = 1536, 26 KB and 39 us at K = 8960; as it is 22 and 30).
-// KPT: keys per thread; 0 (K > 16384): keys are recomputed from memory.
-template <int KPT, int NT>
-__global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v, int K, double c, double alpha, int align,
-                                                    const uint8_t *__restrict__ forced, DetectScalars *sc,
-                                                    int32_t *__restrict__ perm)
+// ---- detection by searches --------------------------------------------------------------------
+// For more than 16384 channels, and for norms that the sort below gives up on.  Norms are non-negative floats, so their
+// bit patterns order as they do, and any order statistic is found by
+// bisecting the pattern range with counts, and once at most 64
+// values are left in the range they are ranked directly: three selections (median, MAD, the K_o-th largest norm) of
+// about ten counts each.  The MAD's doubles are bisected by their upper 32 bits first.  Keys are recomputed from memory.
+template <int NT>
+__device__ __forceinline__ void detect_by_search(const float *v, int K, double c, double alpha, int align, const uint8_t *__restrict__ forced,
+                                                 DetectScalars *sc, int32_t *__restrict__ perm)
 {
-    constexpr int R = KPT > 0 ? KPT : 1, NW = NT / 64;
+    constexpr int NW = NT / 64;
     __shared__ int red[2][NW];
     __shared__ __align__(16) unsigned long long cand[64];
     __shared__ int n_cand, rank[64];
-    extern __shared__ float vl[];              // K norms (KPT > 0)
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     int buf = 0;
 
-    if constexpr (KPT > 0) {
-        float x[R];
-#pragma unroll
-        for (int u = 0; u < R; ++u) x[u] = u * NT + t < K ? v[u * NT + t] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (u * NT + t < K) vl[u * NT + t] = x[u];
-    }
     double med = 0.0;
     bool devs = false;                         // keys: deviations from the median (upper halves) instead of norms
-    auto value = [&](int i) { return KPT > 0 ? vl[i] : v[i]; };
+    auto value = [&](int i) { return v[i]; };
     auto dev = [&](float f) { return (unsigned long long)__double_as_longlong(fabs((double)f - med)); };
     auto key_of = [&](float f) { return devs ? (unsigned)(dev(f) >> 32) : __float_as_uint(f); };
-    unsigned key[R];                           // keys of the selection at hand, ~0 past the end
     // workgroup sum / minimum: one barrier each, two alternating LDS buffers
     auto all_sum = [&](int n) {
         n = wave_sum_all(n);
@@ -216,20 +204,10 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
     for (int stage = forced ? 3 : 0; stage < 3; ++stage) {
         devs = stage == 1;
         unsigned min_key = ~0u, max_inv = ~0u;
-        if constexpr (KPT > 0) {
-#pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const int i = u * NT + t;
-                key[u] = i < K ? key_of(vl[i]) : ~0u;
-                min_key = min(min_key, key[u]);
-                max_inv = i < K ? min(max_inv, ~key[u]) : max_inv;
-            }
-        } else {
-            for (int i = t; i < K; i += NT) {
-                const unsigned q = key_of(v[i]);
-                min_key = min(min_key, q);
-                max_inv = min(max_inv, ~q);
-            }
+        for (int i = t; i < K; i += NT) {
+            const unsigned q = key_of(v[i]);
+            min_key = min(min_key, q);
+            max_inv = min(max_inv, ~q);
         }
         min_key = all_min(min_key);
         const unsigned max_key = ~all_min(max_inv);
@@ -241,14 +219,9 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
             unsigned lo = min_key, hi = max_key;
             int below = 0, upto = K;           // values below the range, and up to its end
             while (lo < hi && upto - below > 64) {
-                const unsigned mid = lo + ((hi - lo) >> 1);       // < hi: never the key past the end
+                const unsigned mid = lo + ((hi - lo) >> 1);
                 int n = 0;
-                if constexpr (KPT > 0) {
-#pragma unroll
-                    for (int u = 0; u < R; ++u) n += key[u] <= mid ? 1 : 0;
-                } else {
-                    for (int i = t; i < K; i += NT) n += key_of(v[i]) <= mid ? 1 : 0;
-                }
+                for (int i = t; i < K; i += NT) n += key_of(v[i]) <= mid ? 1 : 0;
                 n = all_sum(n);
                 if (n > k) {
                     hi = mid;
@@ -354,13 +327,12 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
         return K_o > 0 && (q > sel_min || (q == sel_min && i <= cut));
     };
     const int P = ((K + NT - 1) / NT) | 1, i0 = t * P;
-    if constexpr (KPT > 0) __syncthreads();    // norms written by other threads
     int n = 0;
 #pragma unroll 4
     for (int j = 0; j < P; ++j) n += selected(i0 + j) ? 1 : 0;
     int so = 0, wave_n = 0;
 #pragma unroll
-    for (int b = 0; b < (KPT > 0 ? 6 : 9); ++b) {        // P <= 33 (K <= 16384), 131 (K <= QARVD_MAX_K)
+    for (int b = 0; b < 9; ++b) {              // P <= 131 (K <= QARVD_MAX_K)
         const unsigned long long bits = __ballot((n >> b) & 1);
         so += __popcll(bits & ((1ull << lane) - 1)) << b;
         wave_n += __popcll(bits) << b;
@@ -380,6 +352,300 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
         const bool s = selected(i);
         if (i < K) perm[s ? so : K_o + (i - so)] = i;
         so += s ? 1 : 0;
+    }
+    if (t == 0) sc->K_o = K_o;
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void detect_long_kernel(const float *__restrict__ v, int K, double c, double alpha, int align,
+                                                         const uint8_t *__restrict__ forced, DetectScalars *sc, int32_t *__restrict__ perm)
+{
+    detect_by_search<NT>(v, K, c, alpha, align, forced, sc, perm);
+}
+
+// ---- detection and permutation: one workgroup ------------------------------------------------
+// The norms are sorted first; then the median is read off.  The deviations from it fall towards the median and rise after it, so the
+// k + 1 smallest of them are k + 1 neighbours, and the k-th (from 0) is the smallest over all windows of k + 1 neighbours of the larger
+// of the two deviations at the window's ends: one pass and one reduction for the MAD (for an even K the next one too).  (Subtraction
+// and rounding are monotone, and infinities and NaNs have the largest patterns, so this holds for the rounded values.)
+//
+// The sort: bit patterns (which order as the norms do) are counted in 512 coarse bins over their range; a pattern's place within its
+// bin, times the number of patterns there, points to one of 2 K fine bins (K beyond 9216) that hold half a pattern on average whatever the distribution; the
+// fine counts summed up give every pattern its bin's first place, and within a bin (a few patterns) each counts the smaller
+// ones.  Equal norms share a bin: where one holds more than 48, the searches above take over.
+// One workgroup on an otherwise idle chip is bound by latency, a barrier and an LDS round trip per step; the coarse counters
+// are kept sixteen times, since nearly all norms fall into a few of those bins.
+// K = 1536 22 -> 9.5 us, K = 8960 30 -> 18 us against the three searches (about ten counts of all values each); all-pairs ranks
+// counted by the whole chip and summed up by one workgroup took 10 and 24.  Half of what is left at 8960 is LDS reads at random
+// places: counting within bins (5 us; with one fine bin a norm instead of two 6.2), scattering and sorting back.
+constexpr int COARSE = 512, COPIES = 16, BIN_MAX = 48;
+constexpr int fine_per_norm(int R) { return R <= 10 ? 2 : 1; }      // (what the LDS holds)
+
+template <int R, int NT>      // K <= R NT
+__global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v, int K, double c, double alpha, int align,
+                                                    const uint8_t *__restrict__ forced, DetectScalars *sc, int32_t *__restrict__ perm)
+{
+    constexpr int NW = NT / 64, E = R * NW, F = fine_per_norm(R);       // E: groups of 64 channels
+    static_assert(E <= 256, "four groups a lane");
+    typedef unsigned long long u64;
+    __shared__ u64 least[2][NW];
+    __shared__ int red[4][NW], before[E], coarse_first[COARSE + 1];
+    extern __shared__ __align__(16) unsigned lds[];        // sorted [K] (first the coarse counters) | fine [F K + 1]
+    unsigned *const sorted = lds;
+    int *const coarse = reinterpret_cast<int *>(lds);
+    int *const fine = reinterpret_cast<int *>(lds) + max(K, COARSE * COPIES);
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+
+    // running sums over the workgroup: what the threads before this one hold together; one barrier (slot: a buffer of its own)
+    auto sum_before = [&](int n, int slot) {
+        const int run = wave_scan(n);
+        if (lane == 63) red[slot][wave] = run;
+        __syncthreads();
+        int base = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) base += w < wave ? red[slot][w] : 0;
+        return base + run - n;
+    };
+    auto total = [&](int slot) {
+        int n = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) n += red[slot][w];
+        return n;
+    };
+
+    unsigned key[R];
+    int K_o = 0, cut = K - 1;
+    unsigned sel_min = ~0u;                    // selected: channels with a pattern above this one, and those equal to it up to `cut`
+    if (!forced) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) key[u] = __float_as_uint(v[min(u * NT + t, K - 1)]);
+        for (int i = t; i < COARSE * COPIES / 4; i += NT) reinterpret_cast<int4 *>(coarse)[i] = make_int4(0, 0, 0, 0);
+        for (int i = t; i <= F * K; i += NT) fine[i] = 0;
+        unsigned lo = ~0u, hi_inv = ~0u;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {          // (the last one again past the end)
+            lo = min(lo, key[u]);
+            hi_inv = min(hi_inv, ~key[u]);
+        }
+        lo = wave_min_all(lo);
+        hi_inv = wave_min_all(hi_inv);
+        if (lane == 0) {
+            red[0][wave] = (int)lo;
+            red[1][wave] = (int)hi_inv;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            lo = min(lo, (unsigned)red[0][w]);
+            hi_inv = min(hi_inv, (unsigned)red[1][w]);
+        }
+        const int bits = 32 - __clz((int)(~hi_inv - lo));              // (a range of 0 has 32 leading zeros)
+        const int shift = max(0, bits - 9);                            // range >> shift < 512
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * NT + t < K) atomicAdd(&coarse[((key[u] - lo) >> shift) * COPIES + (lane & (COPIES - 1))], 1);
+        __syncthreads();
+        {
+            constexpr int B = COARSE / NT > 0 ? COARSE / NT : 1;       // bins of a thread
+            int n[B], all = 0;
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                n[b] = 0;
+                if (t * B + b < COARSE) {
+#pragma unroll
+                    for (int q = 0; q < COPIES / 4; ++q) {
+                        const int4 o = reinterpret_cast<const int4 *>(coarse)[(t * B + b) * (COPIES / 4) + q];
+                        n[b] += (o.x + o.y) + (o.z + o.w);
+                    }
+                }
+                all += n[b];
+            }
+            int first = sum_before(all, 2);
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                if (t * B + b <= COARSE) coarse_first[t * B + b] = first;
+                first += n[b];
+            }
+            if (t == NT - 1 && NT * B == COARSE) coarse_first[COARSE] = first;
+        }
+        __syncthreads();
+        int place[R], slot[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const unsigned b = (key[u] - lo) >> shift, in_bin = (key[u] - lo) & ((1u << shift) - 1);
+            const int first = coarse_first[b], n = coarse_first[b + 1] - first;
+            place[u] = F * first + (int)(((u64)in_bin * (unsigned)(F * n)) >> shift);
+            slot[u] = u * NT + t < K ? atomicAdd(&fine[place[u]], 1) : 0;
+        }
+        __syncthreads();
+        {
+            constexpr int P = (F * R) | 1;                                   // neighbouring fine bins (odd: no bank conflicts)
+            const int i0 = t * P;
+            int n[P], all = 0, most = 0;
+#pragma unroll
+            for (int j = 0; j < P; ++j) n[j] = i0 + j < F * K ? fine[i0 + j] : 0;
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                all += n[j];
+                most = max(most, n[j]);
+            }
+            if (__ballot(most > BIN_MAX) && lane == 0) least[0][wave] = 1;
+            else if (lane == 0) least[0][wave] = 0;
+            int first = sum_before(all, 3);
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                if (i0 + j < F * K) fine[i0 + j] = first;
+                first += n[j];
+            }
+            if (t == 0) fine[F * K] = K;
+        }
+        u64 crowded = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) crowded |= least[0][w];
+        __syncthreads();
+        if (crowded) {                         // (the same for all threads)
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (u * NT + t < K) sorted[u * NT + t] = key[u];
+            __syncthreads();
+            detect_by_search<NT>(reinterpret_cast<const float *>(sorted), K, c, alpha, align, nullptr, sc, perm);
+            return;
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int first = fine[place[u]];
+            if (u * NT + t < K) sorted[first + slot[u]] = key[u];
+            slot[u] += first;
+        }
+        __syncthreads();
+        int at[R], end[R];
+        auto count_smaller = [&](int u, int s0) {                      // among four patterns of the bin from s0 on, read together
+            unsigned o[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) o[s] = sorted[min(place[u] + s0 + s, K - 1)];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int j = place[u] + s0 + s;
+                at[u] += j < end[u] && (o[s] < key[u] || (o[s] == key[u] && j < slot[u])) ? 1 : 0;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            end[u] = fine[place[u] + 1];
+            at[u] = place[u] = fine[place[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) count_smaller(u, 0);
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            for (int s0 = 4; __ballot(place[u] + s0 < end[u]); s0 += 4) count_smaller(u, s0);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+            if (u * NT + t < K) sorted[at[u]] = key[u];
+        __syncthreads();
+
+        const int k = (K - 1) / 2;
+        auto norm = [&](int i) { return (double)__uint_as_float(sorted[i]); };
+        // median: mean of the two middle order statistics (odd K: the middle one)
+        const double m0 = norm(k), m1 = norm(min(k + 1, K - 1));
+        const double med = (K & 1) ? m0 : (m1 + m0) / 2.0;
+        auto dev = [&](int i) { return (u64)__double_as_longlong(fabs(norm(i) - med)); };
+        u64 m[2] = {~0ull, ~0ull};
+        for (int i = t; i + k < K; i += NT) {
+            const u64 d = dev(i), e = dev(i + k);
+            m[0] = min(m[0], max(d, e));
+            if (i + k + 1 < K) m[1] = min(m[1], max(d, dev(i + k + 1)));
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const unsigned h = wave_min_all((unsigned)(m[r] >> 32));
+            const unsigned l = wave_min_all((unsigned)(m[r] >> 32) == h ? (unsigned)m[r] : ~0u);
+            if (lane == 0) least[r][wave] = (u64)h << 32 | l;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            m[r] = least[r][0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) m[r] = min(m[r], least[r][w]);
+        }
+        const double a = __longlong_as_double((long long)m[0]), b = __longlong_as_double((long long)m[1]);
+        const double mad = (K & 1) ? a : (b + a) / 2.0;
+        double T1 = c * mad;
+        T1 = med + T1;
+        const double T2 = alpha * med;
+        const double T = T1 > T2 ? T1 : T2;
+        int n_det = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) n_det += __popcll(__ballot(u * NT + t < K && (double)__uint_as_float(key[u]) > T));
+        if (lane == 0) red[0][wave] = n_det;
+        __syncthreads();
+        n_det = total(0);
+        if (t == 0) sc->n_det = n_det;
+        const long long up = ((long long)n_det + align - 1) / align * align;
+        K_o = up > K ? K : (int)up;
+        if (K_o > 0) {
+            sel_min = sorted[K - K_o];
+            // equal norms at the edge of the block: the smaller channels
+            const bool tie = K_o < K && sorted[K - K_o - 1] == sel_min;
+            if (tie) {
+                int above = 0;
+#pragma unroll
+                for (int u = 0; u < R; ++u) above += __popcll(__ballot(u * NT + t < K && key[u] > sel_min));
+                if (lane == 0) red[1][wave] = above;
+                __syncthreads();
+                const int need = K_o - total(1);
+                for (int first = 0; first < cut;) {
+                    const int mid = (first + cut) / 2;
+                    int n = 0;
+#pragma unroll
+                    for (int u = 0; u < R; ++u) n += __popcll(__ballot(u * NT + t <= mid && key[u] == sel_min));
+                    __syncthreads();
+                    if (lane == 0) red[1][wave] = n;
+                    __syncthreads();
+                    if (total(1) >= need) cut = mid;
+                    else first = mid + 1;
+                }
+            }
+        }
+    }
+    // Stable partition: perm = [selected ascending | rest ascending].  A group is 64 neighbouring channels; the selected ones before
+    // a channel are those of the groups before its own and those of the lanes below.
+    u64 mask[R];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = u * NT + t;
+        mask[u] = __ballot(i < K && (forced ? forced[i] != 0 : K_o > 0 && (key[u] > sel_min || (key[u] == sel_min && i <= cut))));
+        if (lane == 0) before[u * NW + wave] = __popcll(mask[u]);
+    }
+    __syncthreads();
+    if (wave == 0) {                            // running sums over the groups, four (or fewer) a lane
+        constexpr int G = (E + 63) / 64;
+        int n[G], all = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int e = lane * G + g;
+            n[g] = e < E ? before[e] : 0;
+            all += n[g];
+        }
+        int run = wave_scan(all);
+        if (lane == 63) red[2][0] = run;
+        run -= all;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int e = lane * G + g;
+            if (e < E) before[e] = run;
+            run += n[g];
+        }
+    }
+    __syncthreads();
+    if (forced) K_o = red[2][0];
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        const int i = u * NT + t;
+        const int so = before[u * NW + wave] + __popcll(mask[u] & ((1ull << lane) - 1));
+        if (i < K) perm[(mask[u] >> lane) & 1 ? so : K_o + (i - so)] = i;
     }
     if (t == 0) sc->K_o = K_o;
 }
@@ -904,23 +1170,29 @@ size_t carve(void *base, int32_t K, Workspace *ws)
     return off;
 }
 
+template <int R, int NT>
+qarvd_status launch_sorting_detect(const Workspace &ws, int32_t K, double f, const qarvd_detect_cfg &c, const uint8_t *forced, int32_t *perm, hipStream_t st)
+{
+    static unsigned long long raised = 0;      // one mask per kernel
+    if (qarvd_status s_a = qarvd_raise_lds_limit_once(detect_kernel<R, NT>, 132 * 1024, raised); s_a != QARVD_OK) return s_a;
+    // the sorted norms (or the coarse counters) and the fine bins: 36 KB and 72 KB at K = 9216, 64 KB and 64 KB at 16384
+    const size_t lds = ((size_t)(K > COARSE * COPIES ? K : COARSE * COPIES) + (size_t)K * fine_per_norm(R) + 1) * 4;
+    hipLaunchKernelGGL((detect_kernel<R, NT>), dim3(1), dim3(NT), lds, st, ws.v, K, f, c.alpha, c.align, forced, ws.sc, perm);
+    return qarvd_launch_status();
+}
+
 qarvd_status launch_detect(const Workspace &ws, int32_t K, const qarvd_detect_cfg &c, int32_t *perm, hipStream_t st)
 {
     const uint8_t *forced = c.forced_mask ? ws.forced : nullptr;
     const double f = c.tau / 0.6745;
-    auto go = [&](auto kern, int nt, bool keep) {
-        const size_t lds = keep ? (size_t)K * sizeof(float) : 0;
-        hipLaunchKernelGGL(kern, dim3(1), dim3(nt), lds, st, ws.v, K, f, c.alpha, c.align, forced, ws.sc, perm);
-    };
-    if (K <= 6 * 256) go(detect_kernel<6, 256>, 256, true);
-    else if (K <= 10 * 512) go(detect_kernel<10, 512>, 512, true);
-    else if (K <= 9 * 1024) go(detect_kernel<9, 1024>, 1024, true);
-    else if (K <= 16 * 1024) {
-        static unsigned long long raised = 0;  // K = 16384 takes 66 KB of LDS
-        if (qarvd_status s_a = qarvd_raise_lds_limit_once(detect_kernel<16, 1024>, 80 * 1024, raised); s_a != QARVD_OK) return s_a;
-        go(detect_kernel<16, 1024>, 1024, true);
-    } else go(detect_kernel<0, 1024>, 1024, false);
-    return qarvd_launch_status();
+    if (K > 16384) {
+        hipLaunchKernelGGL((detect_long_kernel<1024>), dim3(1), dim3(1024), 0, st, ws.v, K, f, c.alpha, c.align, forced, ws.sc, perm);
+        return qarvd_launch_status();
+    }
+    if (K <= 6 * 256) return launch_sorting_detect<6, 256>(ws, K, f, c, forced, perm, st);
+    if (K <= 10 * 512) return launch_sorting_detect<10, 512>(ws, K, f, c, forced, perm, st);
+    if (K <= 9 * 1024) return launch_sorting_detect<9, 1024>(ws, K, f, c, forced, perm, st);
+    return launch_sorting_detect<16, 1024>(ws, K, f, c, forced, perm, st);
 }
 
 template <int CH, int NT>
@@ -1027,7 +1299,7 @@ qarvd_status quantize_weight_impl(int bits, const float *W, int32_t N, int32_t K
     const dim3 ng((K + 255) / 256, chunks);
     if (vec) hipLaunchKernelGGL((norm_partial_kernel<true>), ng, dim3(256), 0, st, W, N, K, ldw, per_chunk, ws.partial);
     else hipLaunchKernelGGL((norm_partial_kernel<false>), ng, dim3(256), 0, st, W, N, K, ldw, per_chunk, ws.partial);
-    hipLaunchKernelGGL(norm_final_kernel, dim3((K + 63) / 64), dim3(256), 0, st, ws.partial, chunks, W, N, K, ldw, ws.v, v_out);
+    hipLaunchKernelGGL(norm_final_kernel, dim3((K + 63) / 64), dim3(1024), 0, st, ws.partial, chunks, W, N, K, ldw, ws.v, v_out);
     if (qarvd_status s_l = launch_detect(ws, K, c, perm, st); s_l != QARVD_OK) return s_l;
 
     RowsArgs a;

@@ -108,3 +108,17 @@ def test_ties_among_the_fillers_take_the_smaller_indices():
     W[:, 1234] = 40.0
     o = check(W)
     assert o["K_o"] == 32 and list(o["perm"][:31]) == list(range(31))
+
+
+@pytest.mark.parametrize("K", [2, 64, 65, 128, 1025, 1536, 2050, 8960, 16384])
+@pytest.mark.parametrize("levels", [1, 2, 5, 40])
+def test_detection_among_ties_and_infinite_norms(K, levels):
+    """Norms of a few distinct values: equal norms around both medians and at the edge of the outlier block; then a few infinite ones."""
+    rng = np.random.default_rng(K + levels)
+    W = np.zeros((3, K), np.float32)
+    W[0] = rng.choice(np.linspace(1.0, 1.5, levels), K)
+    W[1, rng.choice(K, max(1, K // 40), replace=False)] = 30.0
+    check(W)
+    W[2, rng.choice(K, max(1, K // 60), replace=False)] = np.float32(3e38)      # the sum of squares is beyond a float's range
+    W[1, W[2] > 0] = np.float32(3e38)
+    check(W)
