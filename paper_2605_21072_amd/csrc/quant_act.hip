@@ -68,6 +68,13 @@ struct ActArgs {
     int32_t store_wt;      // 1: Xq leaves through write-through stores (see store_q)
 };
 
+// An X of more than this is loaded with the non-temporal hint: it does not displace what the last-level cache (256 MB) holds, and
+// memory delivers 6.3 TB/s instead of 5.4 (a plain loop over 168 MB in, 42 MB out: 38.5 -> 33 us).  4680 x 8960 fp32, 168 MB: from
+// inputs that no cache holds 42.0 -> 37.8 us, right behind the kernel that wrote X 44.8 -> 37.5.  What fits there beside its
+// producer's inputs is level or better with plain loads: 129 MB 41.9 and 42.3 us behind a producer, read a second time 39.6 and 42.9.
+// (168 MB read a second time: 35.4 -> 38.0.)
+constexpr size_t STREAM_BYTES = (size_t)144 << 20;
+
 // Stores of the quantized rows.  A kernel ends with a write-back of what its XCDs' L2s still hold, and the
 // consumer (the GEMM, on any XCD) reads Xq from memory either way; for an Xq of a few MB that write-back is
 // 1-2 us at the end of a 9 us kernel.  Write-through stores (sc0 sc1) send the bytes on while the kernel still
@@ -136,7 +143,7 @@ template <typename T, int CH, int NT, Order ORD> constexpr int waves_per_simd()
 {
     return ORD != NATURAL || CH * NT > 4096 ? (CH > 6 ? 3 : 4) : sizeof(T) == 2 || CH <= 3 ? 8 : 6;
 }
-template <typename T, int CH, int NT, Order ORD, bool TAIL>
+template <typename T, int CH, int NT, Order ORD, bool TAIL, bool STREAM>
 __global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD>())) void quant_act_kernel(ActArgs a)
 {
     typedef typename Elem<T>::raw raw;
@@ -159,9 +166,12 @@ __global__ __launch_bounds__(NT == 64 ? 256 : NT, (waves_per_simd<T, CH, NT, ORD
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int k = 4 * (t + c * NT);
-            if (k < K)
-                v[c] = Elem<T>::of(*reinterpret_cast<const typename Elem<T>::raw_any *>(
-                    reinterpret_cast<const char *>(x) + (uint32_t)(TAIL ? min(k, K - 4) : k) * (uint32_t)sizeof(T)));
+            if (k < K) {
+                const typename Elem<T>::raw_any *p = reinterpret_cast<const typename Elem<T>::raw_any *>(
+                    reinterpret_cast<const char *>(x) + (uint32_t)(TAIL ? min(k, K - 4) : k) * (uint32_t)sizeof(T));
+                if constexpr (STREAM) v[c] = Elem<T>::of(__builtin_nontemporal_load(p));
+                else v[c] = Elem<T>::of(*p);
+            }
         }
     };
 
@@ -337,17 +347,27 @@ template <auto kern> int blocks_per_cu(int threads)
     return n;
 }
 
-template <typename T, int CH, int NT, Order ORD, bool TAIL>
-qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
+template <typename T, int CH, int NT, Order ORD, bool TAIL, bool STREAM>
+qarvd_status launch_rows_as(const ActArgs &a, hipStream_t st)
 {
     constexpr int RW = NT == 64 ? 4 : 1, TH = NT == 64 ? 256 : NT;
     // as many workgroups as the chip holds, trimmed so that all of them walk the same number of rows
     // (4680 rows on 1024 slots: 936 workgroups of exactly 5 rows instead of 1024 of 4 or 5)
-    const int slots = num_cu() * blocks_per_cu<quant_act_kernel<T, CH, NT, ORD, TAIL>>(TH);
+    const int slots = num_cu() * blocks_per_cu<quant_act_kernel<T, CH, NT, ORD, TAIL, STREAM>>(TH);
     const int groups = (a.M + RW - 1) / RW;
     const int rounds = (groups + slots - 1) / slots;
-    hipLaunchKernelGGL((quant_act_kernel<T, CH, NT, ORD, TAIL>), dim3((groups + rounds - 1) / rounds), dim3(TH), 0, st, a);
+    hipLaunchKernelGGL((quant_act_kernel<T, CH, NT, ORD, TAIL, STREAM>), dim3((groups + rounds - 1) / rounds), dim3(TH), 0, st, a);
     return qarvd_launch_status();
+}
+
+// The streaming form is built where a model's widths lead: whole dwords on either side.  (Chosen at run time inside one kernel it cost
+// the other inputs 5 to 12 %.)
+template <typename T, int CH, int NT, Order ORD, bool TAIL>
+qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
+{
+    if constexpr (!TAIL && ORD != ANY_ORDER)
+        if ((size_t)a.M * (size_t)a.K * sizeof(T) > STREAM_BYTES) return launch_rows_as<T, CH, NT, ORD, TAIL, true>(a, st);
+    return launch_rows_as<T, CH, NT, ORD, TAIL, false>(a, st);
 }
 
 // Threads and chunks for a row of `width` channels (ANY_ORDER) or packed bytes; no launch beyond the last width.  A row that

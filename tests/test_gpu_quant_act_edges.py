@@ -110,3 +110,21 @@ def test_scales_outside_the_exact_quotients_range(K, dtype):
         for scale in (np.float32(1e-45), np.float32(3e-39), np.float32(2e-31), np.float32(1e-30), np.float32(3e30), np.float32(3e38)):
             got = q.quant_act_static(Xd, pd, K_o, float(scale))
             assert np.array_equal(logical(got, K, K_o), oracle.quant_act_static(X, scale, p)), scale
+
+
+@pytest.mark.parametrize("K,dtype", [(256, torch.float32), (1536, torch.bfloat16), (5120, torch.bfloat16), (8960, torch.float32), (16384, torch.float32)])
+@pytest.mark.parametrize("K_o", [0, 32])
+def test_inputs_larger_than_the_cache_rule_loads_plainly(K, dtype, K_o):
+    """Inputs of more than 144 MB take kernels that load X with another cache hint; halves of them take the plain ones, which the tests
+    above check against the oracle."""
+    M = 160 * 2 ** 20 // (K * (4 if dtype == torch.float32 else 2)) + 3
+    gen = torch.Generator(device="cuda").manual_seed(K + K_o)
+    X = torch.randn((M, K), generator=gen, device="cuda").to(dtype)
+    perm = torch.cat([p.sort().values for p in torch.randperm(K, generator=gen, device="cuda").split([K_o, K - K_o])]).int() if K_o else None
+    Xq, s_x = q.quant_act(X, perm, K_o)
+    static = q.quant_act_static(X, perm, K_o, 0.03)
+    kp = q.packed_k(K, K_o)
+    for rows in (slice(0, M // 2), slice(M // 2, M)):
+        a, s = q.quant_act(X[rows], perm, K_o)
+        assert torch.equal(a[:, :kp], Xq[rows, :kp]) and torch.equal(s, s_x[rows])
+        assert torch.equal(q.quant_act_static(X[rows], perm, K_o, 0.03)[:, :kp], static[rows, :kp])
