@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI declared in ``include/qarvd.h``.
+"""Binding of the C ABI declared in ``include/qarvd.h``: ctypes, and for the online calls on the current stream ``_host.so``
+(``csrc/host.cpp``), which does the same marshalling in native code.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of ``libqarvd.so``.
 There is no CPU or PyTorch fallback; a missing library raises at first use.
@@ -15,6 +16,7 @@ import torch
 _PKG = Path(__file__).resolve().parent
 _LIB_PATH = _PKG / "libqarvd.so"
 _lib = None
+_host = None          # the native marshalling, on the same loaded library
 
 QARVD_F32, QARVD_BF16 = 0, 1
 _STATUS = {0: "QARVD_OK", -1: "QARVD_ERR_INVALID_ARG", -2: "QARVD_ERR_UNSUPPORTED",
@@ -100,8 +102,23 @@ def load_library():
     lib.qarvd_gemm_variant_name.restype = C.c_char_p
     lib.qarvd_probe_mfma_peak.argtypes = [i32, vp, C.c_size_t, C.POINTER(C.c_double), vp]
     lib.qarvd_probe_mfma_peak.restype = C.c_int
+    _load_host(lib)
     _lib = lib
     return lib
+
+
+def _load_host(lib):
+    global _host
+    from . import _host as host
+    host.init([C.cast(f, C.c_void_p).value for f in (
+        lib.qarvd_linear, lib.qarvd_linear_workspace, lib.qarvd_packed_ld, lib.qarvd_quant_act, lib.qarvd_quant_act_static,
+        lib.qarvd_w8a8_dual_gemm_variant, lib.qarvd_w4a8_dual_gemm, lib.qarvd_w8a8_dual_gemm_q8)])
+    _host = host
+
+
+def _native(lib, stream):
+    """The native marshalling, or None: it works for calls on the current stream through the library that it was given."""
+    return _host if stream is None and lib is _lib else None
 
 
 def _check(status: int, where: str):
@@ -296,6 +313,10 @@ def quant_act(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, Xq: Optio
               s_x: Optional[torch.Tensor] = None, stream=None):
     """qarvd_quant_act: X [M,K] f32/bf16 -> (Xq int8 [M, ld] packed for (K, K_o), s_x f32 [M])."""
     lib = load_library()
+    if host := _native(lib, stream):
+        st, Xq, s_x = host.quant_act(X, perm, K_o, Xq, s_x, None, _stream(None))
+        _check(st, "qarvd_quant_act")
+        return Xq, s_x
     _dev2d(X, "X")
     M, K = X.shape
     if Xq is None:
@@ -312,6 +333,10 @@ def quant_act_static(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, sc
                      Xq: Optional[torch.Tensor] = None, stream=None):
     """qarvd_quant_act_static: same packing with a given per-tensor scale."""
     lib = load_library()
+    if host := _native(lib, stream):
+        st, Xq, _ = host.quant_act(X, perm, K_o, Xq, None, scale, _stream(None))
+        _check(st, "qarvd_quant_act_static")
+        return Xq
     _dev2d(X, "X")
     M, K = X.shape
     if Xq is None:
@@ -328,6 +353,11 @@ def w8a8_dual_gemm(Xq: torch.Tensor, s_x: torch.Tensor, w: DualScaleWeight, bias
     """qarvd_w8a8_dual_gemm (or qarvd_w4a8_dual_gemm when `w` holds INT4 codes).  Returns Y, or
     (Y, acc_normal, acc_outlier) with debug_acc."""
     lib = load_library()
+    host = None if debug_acc else _native(lib, stream)
+    if host:
+        st, Y = host.gemm(Xq, s_x, w.bits, w.Wq, w.s_normal, w.s_outlier, bias, M, w.N, w.K, w.K_o, out_dtype, Y, variant, _stream(None))
+        _check(st, "qarvd_w4a8_dual_gemm" if w.bits == 4 else "qarvd_w8a8_dual_gemm")
+        return Y
     if Y is None:
         Y = _empty((M, w.N), out_dtype, Xq.device, stream)
     an = ao = None
@@ -362,6 +392,10 @@ def w8a8_dual_gemm_q8(Xq: torch.Tensor, s_x: torch.Tensor, w: DualScaleWeight, b
     lib = load_library()
     if w.bits != 8:
         raise ValueError("the chained epilogue takes INT8 weights")
+    if host := _native(lib, stream):
+        st, Y8 = host.gemm_q8(Xq, s_x, w.Wq, w.s_normal, w.s_outlier, bias, M, w.N, w.K, w.K_o, out_scale, int(act), Y8, variant, _stream(None))
+        _check(st, "qarvd_w8a8_dual_gemm_q8")
+        return Y8
     if Y8 is None:
         Y8 = _empty((M, w.N), torch.int8, Xq.device, stream)
     st = lib.qarvd_w8a8_dual_gemm_q8(_ptr(Xq), Xq.stride(0), _ptr(s_x), _ptr(w.Wq), w.Wq.stride(0), _ptr(w.s_normal),
@@ -385,6 +419,10 @@ def w8a8_linear(X: torch.Tensor, w: DualScaleWeight, bias: Optional[torch.Tensor
                 stream=None) -> torch.Tensor:
     """The online pair: quant_act followed by the dual GEMM (qarvd_linear: one call, one scratch buffer)."""
     lib = load_library()
+    if host := _native(lib, stream):
+        st, Y = host.linear(X, w.perm, w.bits, w.Wq, w.s_normal, w.s_outlier, bias, w.N, w.K, w.K_o, out_dtype, _stream(None))
+        _check(st, "qarvd_linear")
+        return Y
     _dev2d(X, "X")
     M, K = X.shape
     K_o, dev = w.K_o, X.device

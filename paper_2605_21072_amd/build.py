@@ -1,4 +1,5 @@
-"""Builds ``libqarvd.so`` (the gfx950 HIP library behind the C ABI) in-tree with hipcc."""
+"""Builds ``libqarvd.so`` (the gfx950 HIP library behind the C ABI) in-tree with hipcc, and ``_host.so`` (the binding's native
+marshalling, host code against torch's headers) with g++."""
 from __future__ import annotations
 
 import os
@@ -33,10 +34,31 @@ def _compile(src: str, verbose: bool) -> Path:
     return obj
 
 
+def _build_host(verbose: bool) -> None:
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    dirs = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
+    out = PKG / "_host.so"
+    tmp = out.with_suffix(".so.tmp%d" % os.getpid())
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, *(x for d in dirs for x in ("-isystem", d)),
+           str(CSRC / "host.cpp"), "-o", str(tmp), "-L" + cpp_extension.library_paths()[0], "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0 or verbose:
+        sys.stderr.write(r.stdout + r.stderr)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on host.cpp")
+    os.replace(tmp, out)
+
+
 def build(verbose: bool = False) -> Path:
-    """Compile every HIP source for gfx950 and link the shared library (always rebuilds)."""
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), 8)) as ex:
+    """Compile every HIP source for gfx950 and link the shared library, and the native marshalling (always rebuilds)."""
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, 8)) as ex:
+        host = ex.submit(_build_host, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        host.result()
     tmp = LIB.with_suffix(".so.tmp%d" % os.getpid())
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *map(str, objs), "-o", str(tmp)]
     r = subprocess.run(cmd, capture_output=True, text=True)
