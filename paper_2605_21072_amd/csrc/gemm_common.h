@@ -42,7 +42,7 @@ struct GemmArgs {
     int32_t act;
     float out_scale;
     int32_t vec_out;   // every row of Y is whole, 16-byte aligned chunks; set by the entry points
-    int32_t store_wt;  // output stores write through the L2 (small outputs); set by the launchers
+    int32_t store_wt;  // (kernels on 64-byte stages) output stores write through the L2; set by the launchers
 };
 
 // LDS image of an operand tile: row r at byte r*128, its eight 16-byte chunks XOR-swizzled by

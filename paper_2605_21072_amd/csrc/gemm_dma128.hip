@@ -434,7 +434,11 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
     const int y_bytes = (min(BM, g.M - m0) - 1) * ldy_b + g.N * ESZ;
     const int y_lane = (wm * G::WTM + prow) * ldy_b + (n0 + wn * G::WTN + pch * EPC) * ESZ;
     const int n_left = g.N - n0 - wn * G::WTN - pch * EPC;            // columns from this lane's chunk to the matrix edge
-    const bool wt = g.store_wt != 0;
+    // Output stores always write through: as whole lines they cost nothing extra, nothing is left to write back when the kernel ends,
+    // and the L2s keep the operands.  (Against write-through up to 40 MB only, chosen by a branch at every store: 4680 x 1536 -> 8960
+    // 73.7 -> 72.1 us, on 128x256 tiles 81.5 -> 77; 4680 x 5120 -> 13824 280 -> 276; with a kernel that reads the output next 95.6 -> 94.3
+    // and 330 -> 327.  The non-temporal hint instead: 72.8 and 272 alone, but 96.8 with the reader behind it.)
+    constexpr bool wt = true;
     const StaticQuant sq = make_static_quant(sizeof(OutT) == 1 ? g.out_scale : 1.0f);
 
     // Software pipeline over the 16 x 16 blocks, row blocks outermost: a patch is read back as soon as it is complete and
@@ -651,7 +655,6 @@ qarvd_status launch_dma128(const GemmArgs &g0, qarvd_dtype ydt, hipStream_t st)
     GemmArgs g = g0;
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    g.store_wt = store_write_through(g, ydt == QARVD_BF16 ? 2 : 4);
     const bool dbg = g.dbg_n != nullptr || g.dbg_o != nullptr;   // raw-accumulator dumps: separate, slower build
     if (ydt == QARVD_BF16)
         return !dbg ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, uint16_t, GEN, W4>(g, st)
@@ -666,7 +669,6 @@ qarvd_status launch_dma128_q8(const GemmArgs &g0, hipStream_t st)
     GemmArgs g = g0;
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    g.store_wt = store_write_through(g, 1);
     return g.act == 1 ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8GeluOut>(g, st)
                       : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8Out>(g, st);
 }

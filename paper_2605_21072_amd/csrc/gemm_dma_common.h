@@ -78,8 +78,8 @@ __device__ __forceinline__ void buffer_load_lds16(const void *base, int voffset,
 // output rows below a ragged last tile are masked (checked on MI355X).  base, bytes, soffset wave-uniform.
 // `write_through` (wave-uniform) sends the data on to memory at once instead of leaving dirty lines in the
 // L2: a kernel ends with a write-back of what its XCDs' L2s still hold, which for an output of a few MB is
-// most of it -- 1-2 us at the end of a 17 us GEMM; for outputs much larger than the L2s it only adds traffic
-// while the kernel computes (measured: 4680 x 1536 bf16 18.0 -> 16.2 us, 4680 x 8960 72 -> 75 us).
+// most of it -- 1-2 us at the end of a 17 us GEMM; where the stores are half lines it only adds traffic for outputs much larger
+// than the L2s (64-byte patches: 4680 x 1536 bf16 18.0 -> 16.2 us, 4680 x 8960 72 -> 75 us).
 __device__ __forceinline__ void buffer_store16(void *base, int bytes, int voffset, int soffset, v4i data, bool write_through = false)
 {
 #if defined(__HIP_DEVICE_COMPILE__) && QARVD_NO_STORE != 2
@@ -179,7 +179,7 @@ __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, h);
 }
 
-// Outputs up to 40 MB are stored write-through (see buffer_store16): 4680 x 1536 and 1560 x 8960 bf16 gain
+// The kernels on 64-byte stages store outputs of up to 40 MB write-through (see buffer_store16): 4680 x 1536 and 1560 x 8960 bf16 gain
 // 1-2 us, 4680 x 8960 (84 MB) loses 3.
 inline int32_t store_write_through(const GemmArgs &g, int elem_bytes)
 {
