@@ -14,6 +14,8 @@
 //
 // Because K_o is a multiple of 32 after padding, every 32-byte k-step lies wholly in one of the
 // two ranges: steps below the normal offset accumulate into acc_o, the rest into acc_n.
+// (gemm_dma128.hip and gemm_mfma16.hip run v_mfma_i32_16x16x64_i8: 16 rows x 64 bytes a step, which may hold the end of one range
+// and the start of the other; they say how they part it.)
 #pragma once
 #include "qarvd_common.h"
 
