@@ -314,7 +314,7 @@ def quant_act(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, Xq: Optio
     """qarvd_quant_act: X [M,K] f32/bf16 -> (Xq int8 [M, ld] packed for (K, K_o), s_x f32 [M])."""
     lib = load_library()
     if host := _native(lib, stream):
-        st, Xq, s_x = host.quant_act(X, perm, K_o, Xq, s_x, None, _stream(None))
+        st, Xq, s_x = host.quant_act(X, perm, K_o, Xq, s_x, _stream(None))
         _check(st, "qarvd_quant_act")
         return Xq, s_x
     _dev2d(X, "X")
@@ -334,7 +334,7 @@ def quant_act_static(X: torch.Tensor, perm: Optional[torch.Tensor], K_o: int, sc
     """qarvd_quant_act_static: same packing with a given per-tensor scale."""
     lib = load_library()
     if host := _native(lib, stream):
-        st, Xq, _ = host.quant_act(X, perm, K_o, Xq, None, scale, _stream(None))
+        st, Xq = host.quant_act_static(X, perm, K_o, scale, Xq, _stream(None))
         _check(st, "qarvd_quant_act_static")
         return Xq
     _dev2d(X, "X")

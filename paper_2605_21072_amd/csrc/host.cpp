@@ -83,21 +83,32 @@ py::tuple linear(const at::Tensor &X, const OptTensor &perm, int bits, const at:
     return py::make_tuple(st, std::move(Y));
 }
 
-py::tuple quant_act(const at::Tensor &X, const OptTensor &perm, int64_t K_o, OptTensor Xq, OptTensor s_x, std::optional<double> scale, uintptr_t stream)
+py::tuple quant_act(const at::Tensor &X, const OptTensor &perm, int64_t K_o, OptTensor Xq, OptTensor s_x, uintptr_t stream)
 {
     check_2d(X, "X");
     const int64_t M = X.size(0), K = X.size(1);
     if (!Xq) Xq = fresh({M, (int64_t)packed_ld_fn((int32_t)K, (int32_t)K_o)}, at::kChar, X);
-    if (!s_x && !scale) s_x = fresh({M}, at::kFloat, X);
+    if (!s_x) s_x = fresh({M}, at::kFloat, X);
     const qarvd_dtype xdt = dtype_of(X.scalar_type());
     const int st = run([&] {
-        if (scale)
-            return quant_act_static_fn(X.data_ptr(), xdt, (int32_t)M, (int32_t)K, X.stride(0), (const int32_t *)ptr(perm), (int32_t)K_o, (float)*scale,
-                                       (int8_t *)Xq->data_ptr(), Xq->stride(0), (void *)stream);
         return quant_act_fn(X.data_ptr(), xdt, (int32_t)M, (int32_t)K, X.stride(0), (const int32_t *)ptr(perm), (int32_t)K_o,
                             (int8_t *)Xq->data_ptr(), Xq->stride(0), (float *)s_x->data_ptr(), (void *)stream);
     });
     return py::make_tuple(st, std::move(Xq), std::move(s_x));
+}
+
+// The scale is required (None is a TypeError): a call without one must not become the per-token quantizer.
+py::tuple quant_act_static(const at::Tensor &X, const OptTensor &perm, int64_t K_o, double scale, OptTensor Xq, uintptr_t stream)
+{
+    check_2d(X, "X");
+    const int64_t M = X.size(0), K = X.size(1);
+    if (!Xq) Xq = fresh({M, (int64_t)packed_ld_fn((int32_t)K, (int32_t)K_o)}, at::kChar, X);
+    const qarvd_dtype xdt = dtype_of(X.scalar_type());
+    const int st = run([&] {
+        return quant_act_static_fn(X.data_ptr(), xdt, (int32_t)M, (int32_t)K, X.stride(0), (const int32_t *)ptr(perm), (int32_t)K_o, (float)scale,
+                                   (int8_t *)Xq->data_ptr(), Xq->stride(0), (void *)stream);
+    });
+    return py::make_tuple(st, std::move(Xq));
 }
 
 py::tuple gemm(const at::Tensor &Xq, const at::Tensor &s_x, int bits, const at::Tensor &Wq, const at::Tensor &sn, const at::Tensor &so,
@@ -136,6 +147,7 @@ PYBIND11_MODULE(_host, m)
     m.def("init", &init);
     m.def("linear", &linear);
     m.def("quant_act", &quant_act);
+    m.def("quant_act_static", &quant_act_static);
     m.def("gemm", &gemm);
     m.def("gemm_q8", &gemm_q8);
 }

@@ -46,6 +46,9 @@ def test_same_errors():
             q.quant_act(X.half(), None, 0, stream=st)
         with pytest.raises(TypeError):
             q.w8a8_linear(X, w, None, torch.float16, stream=st)
+        for scale in (None, "0.03"):
+            with pytest.raises(TypeError):
+                q.quant_act_static(X, None, 0, scale, stream=st)
         for call in (lambda: q.w8a8_linear(X[:0], w, None, stream=st), lambda: q.quant_act(X, None, 32, stream=st),
                      lambda: q.quant_act_static(X, None, 0, -1.0, stream=st), lambda: q.w8a8_dual_gemm(Xq, s_x, w, None, 4, variant=999, stream=st),
                      lambda: q.w8a8_dual_gemm_q8(Xq, s_x, w, None, 4, 0.0, stream=st)):
