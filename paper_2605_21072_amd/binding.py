@@ -355,7 +355,8 @@ def w8a8_dual_gemm(Xq: torch.Tensor, s_x: torch.Tensor, w: DualScaleWeight, bias
     lib = load_library()
     host = None if debug_acc else _native(lib, stream)
     if host:
-        st, Y = host.gemm(Xq, s_x, w.bits, w.Wq, w.s_normal, w.s_outlier, bias, M, w.N, w.K, w.K_o, out_dtype, Y, variant, _stream(None))
+        st, Y = host.gemm(Xq, s_x, w.bits, w.Wq, w.s_normal, w.s_outlier, bias, M, w.N, w.K, w.K_o, out_dtype if Y is None else None, Y, variant,
+                          _stream(None))
         _check(st, "qarvd_w4a8_dual_gemm" if w.bits == 4 else "qarvd_w8a8_dual_gemm")
         return Y
     if Y is None:

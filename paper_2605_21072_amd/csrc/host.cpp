@@ -65,9 +65,10 @@ template <typename F> int run(F f)
 }
 
 py::tuple linear(const at::Tensor &X, const OptTensor &perm, int bits, const at::Tensor &Wq, const at::Tensor &sn, const at::Tensor &so,
-                 const OptTensor &bias, int64_t N, int64_t K, int64_t K_o, at::ScalarType out, uintptr_t stream)
+                 const OptTensor &bias, int64_t N, int64_t K, int64_t K_o, std::optional<at::ScalarType> out_dtype, uintptr_t stream)
 {
     check_2d(X, "X");
+    const at::ScalarType out = c10::dtype_or_default(out_dtype);
     const int64_t M = X.size(0);
     if (X.size(1) != K)
         throw py::value_error("X has " + std::to_string(X.size(1)) + " channels, the layer " + std::to_string(K));
@@ -111,30 +112,32 @@ py::tuple quant_act_static(const at::Tensor &X, const OptTensor &perm, int64_t K
     return py::make_tuple(st, std::move(Xq));
 }
 
-py::tuple gemm(const at::Tensor &Xq, const at::Tensor &s_x, int bits, const at::Tensor &Wq, const at::Tensor &sn, const at::Tensor &so,
-               const OptTensor &bias, int64_t M, int64_t N, int64_t K, int64_t K_o, at::ScalarType out, OptTensor Y, int variant, uintptr_t stream)
+// A vector that is missing (None) is refused by the entry point, with its status.
+py::tuple gemm(const at::Tensor &Xq, const OptTensor &s_x, int bits, const at::Tensor &Wq, const OptTensor &sn, const OptTensor &so,
+               const OptTensor &bias, int64_t M, int64_t N, int64_t K, int64_t K_o, std::optional<at::ScalarType> out_dtype, OptTensor Y,
+               int variant, uintptr_t stream)
 {
-    if (!Y) Y = fresh({M, N}, out, Xq);
+    if (!Y) Y = fresh({M, N}, c10::dtype_or_default(out_dtype), Xq);
     const qarvd_dtype ydt = dtype_of(Y->scalar_type());
     const int st = run([&] {
         if (bits == 4)
-            return gemm_w4_fn((const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)s_x.data_ptr(), (const uint8_t *)Wq.data_ptr(), Wq.stride(0),
-                              (const float *)sn.data_ptr(), (const float *)so.data_ptr(), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
+            return gemm_w4_fn((const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)ptr(s_x), (const uint8_t *)Wq.data_ptr(), Wq.stride(0),
+                              (const float *)ptr(sn), (const float *)ptr(so), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
                               (int32_t)K_o, Y->data_ptr(), ydt, Y->stride(0), nullptr, nullptr, variant, (void *)stream);
-        return gemm_fn(variant, (const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)s_x.data_ptr(), (const int8_t *)Wq.data_ptr(), Wq.stride(0),
-                       (const float *)sn.data_ptr(), (const float *)so.data_ptr(), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
+        return gemm_fn(variant, (const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)ptr(s_x), (const int8_t *)Wq.data_ptr(), Wq.stride(0),
+                       (const float *)ptr(sn), (const float *)ptr(so), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
                        (int32_t)K_o, Y->data_ptr(), ydt, Y->stride(0), nullptr, nullptr, (void *)stream);
     });
     return py::make_tuple(st, std::move(Y));
 }
 
-py::tuple gemm_q8(const at::Tensor &Xq, const at::Tensor &s_x, const at::Tensor &Wq, const at::Tensor &sn, const at::Tensor &so, const OptTensor &bias,
+py::tuple gemm_q8(const at::Tensor &Xq, const OptTensor &s_x, const at::Tensor &Wq, const OptTensor &sn, const OptTensor &so, const OptTensor &bias,
                   int64_t M, int64_t N, int64_t K, int64_t K_o, double scale, int act, OptTensor Y8, int variant, uintptr_t stream)
 {
     if (!Y8) Y8 = fresh({M, N}, at::kChar, Xq);
     const int st = run([&] {
-        return gemm_q8_fn((const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)s_x.data_ptr(), (const int8_t *)Wq.data_ptr(), Wq.stride(0),
-                          (const float *)sn.data_ptr(), (const float *)so.data_ptr(), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
+        return gemm_q8_fn((const int8_t *)Xq.data_ptr(), Xq.stride(0), (const float *)ptr(s_x), (const int8_t *)Wq.data_ptr(), Wq.stride(0),
+                          (const float *)ptr(sn), (const float *)ptr(so), (const float *)ptr(bias), (int32_t)M, (int32_t)N, (int32_t)K,
                           (int32_t)K_o, (qarvd_act)act, (float)scale, (int8_t *)Y8->data_ptr(), Y8->stride(0), variant, (void *)stream);
     });
     return py::make_tuple(st, std::move(Y8));

@@ -46,6 +46,12 @@ def test_same_errors():
             q.quant_act(X.half(), None, 0, stream=st)
         with pytest.raises(TypeError):
             q.w8a8_linear(X, w, None, torch.float16, stream=st)
+        for y in (q.w8a8_linear(X, w, None, None, stream=st), q.w8a8_dual_gemm(Xq, s_x, w, None, 4, None, stream=st)):
+            assert y.dtype == torch.get_default_dtype() == torch.float32
+        Y = torch.empty((4, 16), dtype=torch.bfloat16, device="cuda")
+        assert q.w8a8_dual_gemm(Xq, s_x, w, None, 4, None, Y=Y, stream=st) is Y
+        with pytest.raises(q.QarvdError):
+            q.w8a8_dual_gemm(Xq, None, w, None, 4, stream=st)
         for scale in (None, "0.03"):
             with pytest.raises(TypeError):
                 q.quant_act_static(X, None, 0, scale, stream=st)
