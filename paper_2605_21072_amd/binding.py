@@ -1,4 +1,4 @@
-"""Binding of the C ABI declared in ``include/qarvd.h``: ctypes, and for the online calls on the current stream ``_host.so``
+"""Binding of the C ABI declared in ``include/qarvd.h``: ctypes, and for the online calls on the current stream ``_host``
 (``csrc/host.cpp``), which does the same marshalling in native code.
 
 Argument marshalling only: every step of the path runs in the HIP kernels of ``libqarvd.so``.
@@ -16,7 +16,7 @@ import torch
 _PKG = Path(__file__).resolve().parent
 _LIB_PATH = _PKG / "libqarvd.so"
 _lib = None
-_host = None          # the native marshalling, on the same loaded library
+_host = None          # the native marshalling on the same loaded library, from the first online call on
 
 QARVD_F32, QARVD_BF16 = 0, 1
 _STATUS = {0: "QARVD_OK", -1: "QARVD_ERR_INVALID_ARG", -2: "QARVD_ERR_UNSUPPORTED",
@@ -102,23 +102,30 @@ def load_library():
     lib.qarvd_gemm_variant_name.restype = C.c_char_p
     lib.qarvd_probe_mfma_peak.argtypes = [i32, vp, C.c_size_t, C.POINTER(C.c_double), vp]
     lib.qarvd_probe_mfma_peak.restype = C.c_int
-    _load_host(lib)
     _lib = lib
     return lib
 
 
 def _load_host(lib):
     global _host
-    from . import _host as host
+    rebuild = "run `python -m paper_2605_21072_amd.build` (or __graft_entry__.build())"
+    try:
+        from . import _host as host
+    except ImportError as e:
+        raise ImportError("the native marshalling of the online calls (_host) is missing or does not load: %s; %s first" % (e, rebuild)) from e
+    if getattr(host, "torch_version", None) != torch.__version__:
+        raise ImportError("%s was built against torch %s, this is %s: %s again" % (host.__file__, getattr(host, "torch_version", "of an unknown version"),
+                                                                                   torch.__version__, rebuild))
     host.init([C.cast(f, C.c_void_p).value for f in (
         lib.qarvd_linear, lib.qarvd_linear_workspace, lib.qarvd_packed_ld, lib.qarvd_quant_act, lib.qarvd_quant_act_static,
         lib.qarvd_w8a8_dual_gemm_variant, lib.qarvd_w4a8_dual_gemm, lib.qarvd_w8a8_dual_gemm_q8)])
     _host = host
+    return host
 
 
 def _native(lib, stream):
     """The native marshalling, or None: it works for calls on the current stream through the library that it was given."""
-    return _host if stream is None and lib is _lib else None
+    return (_host or _load_host(lib)) if stream is None and lib is _lib else None
 
 
 def _check(status: int, where: str):

@@ -1,5 +1,5 @@
-"""Builds ``libqarvd.so`` (the gfx950 HIP library behind the C ABI) in-tree with hipcc, and ``_host.so`` (the binding's native
-marshalling, host code against torch's headers) with g++."""
+"""Builds ``libqarvd.so`` (the gfx950 HIP library behind the C ABI) in-tree with hipcc, and ``_host`` (the binding's native
+marshalling, an extension module against torch's headers) with g++."""
 from __future__ import annotations
 
 import os
@@ -40,10 +40,10 @@ def _build_host(verbose: bool) -> None:
     import torch
     from torch.utils import cpp_extension
     dirs = cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]
-    out = PKG / "_host.so"
+    out = PKG / ("_host" + sysconfig.get_config_var("EXT_SUFFIX"))       # no other Python takes it for its own
     tmp = out.with_suffix(".so.tmp%d" % os.getpid())
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, *(x for d in dirs for x in ("-isystem", d)),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DQARVD_TORCH_VERSION="%s"' % torch.__version__, *(x for d in dirs for x in ("-isystem", d)),
            str(CSRC / "host.cpp"), "-o", str(tmp), "-L" + cpp_extension.library_paths()[0], "-lc10", "-ltorch_cpu", "-ltorch_python"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0 or verbose:

@@ -147,6 +147,7 @@ py::tuple gemm_q8(const at::Tensor &Xq, const OptTensor &s_x, const at::Tensor &
 
 PYBIND11_MODULE(_host, m)
 {
+    m.attr("torch_version") = QARVD_TORCH_VERSION;      // whose headers this was compiled against
     m.def("init", &init);
     m.def("linear", &linear);
     m.def("quant_act", &quant_act);

@@ -2,6 +2,8 @@
 functions that record their arguments and return the library's status for a missing buffer."""
 import ctypes as C
 import dataclasses
+import sys
+import types
 
 import pytest
 import torch
@@ -19,7 +21,7 @@ def no_stream(monkeypatch):
     if not q.lib_path().exists():
         from paper_2605_21072_amd import build
         build.build()
-    q.load_library()
+    binding._load_host(q.load_library())
     monkeypatch.setattr(binding, "_stream", lambda stream: 0)
 
 
@@ -80,3 +82,16 @@ def test_a_missing_vector_is_refused_by_the_entry_point(gemm_calls):
                 call()
             assert e.value.status == -1
     assert q.w8a8_dual_gemm_q8(Xq, s_x, w, None, 4, 0.1, Y8=Y8) is Y8 and gemm_calls[-1][15] == Y8.data_ptr()
+
+
+def test_only_the_online_calls_need_the_module_and_say_how_to_get_it(no_stream, monkeypatch):
+    w, Xq, s_x = _layer()
+    for other in (None, types.SimpleNamespace(__file__="_host.so", torch_version="1.0")):        # absent; built for another torch
+        monkeypatch.setattr(binding, "_lib", None)
+        monkeypatch.setattr(binding, "_host", None)
+        monkeypatch.delattr(q, "_host", raising=False)          # (`from . import` looks for the attribute first)
+        monkeypatch.setitem(sys.modules, q.__name__ + "._host", other)
+        assert q.packed_k(1536, 0) == 1536 and q.quantize_weight_workspace(16, 1536) > 0
+        for call in (lambda: q.w8a8_linear(s_x, w, None), lambda: q.quant_act(s_x, None, 0), lambda: q.w8a8_dual_gemm(Xq, s_x, w, None, 4)):
+            with pytest.raises(ImportError, match="paper_2605_21072_amd.build"):
+                call()
