@@ -10,7 +10,7 @@
 // 3 columns in 10^5 at 8960 rows) are redone in order.  W is streamed twice: once for the norms, once by
 // the row quantizer; detection between them is one workgroup that sorts the norms.
 //   kernel times, us        norms       detection    scales and codes
-//   8960 x 1536, INT8       15 (397)    9.5 (258)    19 (32)
+//   8960 x 1536, INT8       15 (397)    10.5 (258)   19 (32)
 //   1536 x 8960, INT4, clip 14 (70)     18 (1316)    50 (4697: search, codes, packing)
 // In brackets one thread per column, O(K^2) rankings, one thread per (row, block) for the search and byte stores.
 #include "qarvd_common.h"
@@ -149,15 +149,17 @@ __global__ __launch_bounds__(1024) void norm_final_kernel(const double *__restri
 
 // ---- detection by searches --------------------------------------------------------------------
 // For more than 16384 channels, and for norms that the sort below gives up on.  Norms are non-negative floats, so their
-// bit patterns order as they do, and any order statistic is found by
-// bisecting the pattern range with counts, and once at most 64
+// bit patterns order as they do, and any order statistic is found by bisecting the pattern range with counts, and once at most 64
 // values are left in the range they are ranked directly: three selections (median, MAD, the K_o-th largest norm) of
-// about ten counts each.  The MAD's doubles are bisected by their upper 32 bits first.  Keys are recomputed from memory.
-template <int NT>
+// about ten counts each.  The MAD's doubles are bisected by their upper 32 bits first.
+// KPT: keys per thread, kept in registers through a selection's counts, the norms in LDS; 0 (K > 16384): keys are recomputed from
+// memory.  Code that runs once is fetched from memory at about a microsecond per kilobyte, so every loop but the count itself is
+// rolled.
+template <int KPT, int NT>
 __device__ __forceinline__ void detect_by_search(const float *v, int K, double c, double alpha, int align, const uint8_t *__restrict__ forced,
                                                  DetectScalars *sc, int32_t *__restrict__ perm)
 {
-    constexpr int NW = NT / 64;
+    constexpr int R = KPT > 0 ? KPT : 1, NW = NT / 64;
     __shared__ int red[2][NW];
     __shared__ __align__(16) unsigned long long cand[64];
     __shared__ int n_cand, rank[64];
@@ -169,6 +171,7 @@ __device__ __forceinline__ void detect_by_search(const float *v, int K, double c
     auto value = [&](int i) { return v[i]; };
     auto dev = [&](float f) { return (unsigned long long)__double_as_longlong(fabs((double)f - med)); };
     auto key_of = [&](float f) { return devs ? (unsigned)(dev(f) >> 32) : __float_as_uint(f); };
+    unsigned key[R];                           // keys of the selection at hand, ~0 past the end
     // workgroup sum / minimum: one barrier each, two alternating LDS buffers
     auto all_sum = [&](int n) {
         n = wave_sum_all(n);
@@ -204,10 +207,20 @@ __device__ __forceinline__ void detect_by_search(const float *v, int K, double c
     for (int stage = forced ? 3 : 0; stage < 3; ++stage) {
         devs = stage == 1;
         unsigned min_key = ~0u, max_inv = ~0u;
-        for (int i = t; i < K; i += NT) {
-            const unsigned q = key_of(v[i]);
-            min_key = min(min_key, q);
-            max_inv = min(max_inv, ~q);
+        if constexpr (KPT > 0) {
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int i = u * NT + t;
+                key[u] = i < K ? key_of(v[i]) : ~0u;
+                min_key = min(min_key, key[u]);
+                max_inv = i < K ? min(max_inv, ~key[u]) : max_inv;
+            }
+        } else {
+            for (int i = t; i < K; i += NT) {
+                const unsigned q = key_of(v[i]);
+                min_key = min(min_key, q);
+                max_inv = min(max_inv, ~q);
+            }
         }
         min_key = all_min(min_key);
         const unsigned max_key = ~all_min(max_inv);
@@ -219,9 +232,14 @@ __device__ __forceinline__ void detect_by_search(const float *v, int K, double c
             unsigned lo = min_key, hi = max_key;
             int below = 0, upto = K;           // values below the range, and up to its end
             while (lo < hi && upto - below > 64) {
-                const unsigned mid = lo + ((hi - lo) >> 1);
+                const unsigned mid = lo + ((hi - lo) >> 1);       // < hi: never the key past the end
                 int n = 0;
-                for (int i = t; i < K; i += NT) n += key_of(v[i]) <= mid ? 1 : 0;
+                if constexpr (KPT > 0) {
+#pragma unroll
+                    for (int u = 0; u < R; ++u) n += key[u] <= mid ? 1 : 0;
+                } else {
+                    for (int i = t; i < K; i += NT) n += key_of(v[i]) <= mid ? 1 : 0;
+                }
                 n = all_sum(n);
                 if (n > k) {
                     hi = mid;
@@ -332,7 +350,7 @@ __device__ __forceinline__ void detect_by_search(const float *v, int K, double c
     for (int j = 0; j < P; ++j) n += selected(i0 + j) ? 1 : 0;
     int so = 0, wave_n = 0;
 #pragma unroll
-    for (int b = 0; b < 9; ++b) {              // P <= 131 (K <= QARVD_MAX_K)
+    for (int b = 0; b < (KPT > 0 ? 6 : 9); ++b) {        // P <= 33 (K <= 16384), 131 (K <= QARVD_MAX_K)
         const unsigned long long bits = __ballot((n >> b) & 1);
         so += __popcll(bits & ((1ull << lane) - 1)) << b;
         wave_n += __popcll(bits) << b;
@@ -360,7 +378,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void detect_long_kernel(const float *__restrict__ v, int K, double c, double alpha, int align,
                                                          const uint8_t *__restrict__ forced, DetectScalars *sc, int32_t *__restrict__ perm)
 {
-    detect_by_search<NT>(v, K, c, alpha, align, forced, sc, perm);
+    detect_by_search<0, NT>(v, K, c, alpha, align, forced, sc, perm);
 }
 
 // ---- detection and permutation: one workgroup ------------------------------------------------
@@ -369,16 +387,23 @@ __global__ __launch_bounds__(NT) void detect_long_kernel(const float *__restrict
 // of the two deviations at the window's ends: one pass and one reduction for the MAD (for an even K the next one too).  (Subtraction
 // and rounding are monotone, and infinities and NaNs have the largest patterns, so this holds for the rounded values.)
 //
-// The sort: bit patterns (which order as the norms do) are counted in 512 coarse bins over their range; a pattern's place within its
-// bin, times the number of patterns there, points to one of 2 K fine bins (K beyond 9216) that hold half a pattern on average whatever the distribution; the
-// fine counts summed up give every pattern its bin's first place, and within a bin (a few patterns) each counts the smaller
-// ones.  Equal norms share a bin: where one holds more than 48, the searches above take over.
+// The sort: bit patterns (which order as the norms do) are counted in 511 coarse bins over their range, zeros in one of their own (they
+// would make a bin a quarter of an octave wide, and nearly all others would fall into one or two); a pattern's place within its
+// bin, times the number of patterns there, points to one of 2 K fine bins (K beyond 9216, where the LDS holds no more); the
+// fine counts summed up give every pattern its bin's first place, and within a bin (5 to 8 patterns at most in ordinary layers) each
+// counts the smaller ones.
+// A bin of more than 48 patterns is not counted through.  It is nearly always one of equal norms (channels that are dead, padding or
+// copies), whose order is of no matter; up to 32 patterns that differ from their crowded bins' first ones are placed among
+// them one by one.  More, thousands of norms within bits of each other but not equal, take the searches above.
 // One workgroup on an otherwise idle chip is bound by latency, a barrier and an LDS round trip per step; the coarse counters
 // are kept sixteen times, since nearly all norms fall into a few of those bins.
-// K = 1536 22 -> 9.5 us, K = 8960 30 -> 18 us against the three searches (about ten counts of all values each); all-pairs ranks
+// Against the three searches alone (about ten counts of all values each), us at K = 1536, 5120 and 8960: ordinary norms 22.7 -> 10.9, 28.8
+// -> 16.0, 33.8 -> 18.3; 64 channels zero 24.1 -> 11.9, 31.9 -> 17.7, 36.8 -> 20.4 (by the searches behind the sort's first half, from
+// LDS, 39, 55 and 63); half of them zero 46 -> 12, 62 -> 20, 74 -> 23; 300 equal ones among the others 21.5 -> 11.1, 28.5 -> 18.3,
+// 34.9 -> 21.7; half of them within 20 bits of 1 (the searches take over) 31 -> 36, 40 -> 45, 87 -> 96.  All-pairs ranks
 // counted by the whole chip and summed up by one workgroup took 10 and 24.  Half of what is left at 8960 is LDS reads at random
 // places: counting within bins (5 us; with one fine bin a norm instead of two 6.2), scattering and sorting back.
-constexpr int COARSE = 512, COPIES = 16, BIN_MAX = 48;
+constexpr int COARSE = 512, COPIES = 16, BIN_MAX = 48, ODD_MAX = 32;
 constexpr int fine_per_norm(int R) { return R <= 10 ? 2 : 1; }      // (what the LDS holds)
 
 template <int R, int NT>      // K <= R NT
@@ -389,7 +414,8 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
     static_assert(E <= 256, "four groups a lane");
     typedef unsigned long long u64;
     __shared__ u64 least[2][NW];
-    __shared__ int red[4][NW], before[E], coarse_first[COARSE + 1];
+    __shared__ int red[4][NW], before[E], coarse_first[COARSE + 1], n_odd;
+    __shared__ int2 odd[ODD_MAX];
     extern __shared__ __align__(16) unsigned lds[];        // sorted [K] (first the coarse counters) | fine [F K + 1]
     unsigned *const sorted = lds;
     int *const coarse = reinterpret_cast<int *>(lds);
@@ -421,10 +447,11 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
         for (int u = 0; u < R; ++u) key[u] = __float_as_uint(v[min(u * NT + t, K - 1)]);
         for (int i = t; i < COARSE * COPIES / 4; i += NT) reinterpret_cast<int4 *>(coarse)[i] = make_int4(0, 0, 0, 0);
         for (int i = t; i <= F * K; i += NT) fine[i] = 0;
+        if (t == 0) n_odd = 0;
         unsigned lo = ~0u, hi_inv = ~0u;
 #pragma unroll
         for (int u = 0; u < R; ++u) {          // (the last one again past the end)
-            lo = min(lo, key[u]);
+            lo = min(lo, key[u] ? key[u] : ~0u);
             hi_inv = min(hi_inv, ~key[u]);
         }
         lo = wave_min_all(lo);
@@ -439,11 +466,13 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
             lo = min(lo, (unsigned)red[0][w]);
             hi_inv = min(hi_inv, (unsigned)red[1][w]);
         }
-        const int bits = 32 - __clz((int)(~hi_inv - lo));              // (a range of 0 has 32 leading zeros)
-        const int shift = max(0, bits - 9);                            // range >> shift < 512
+        const unsigned range = ~hi_inv - lo;                           // (all zero: 1)
+        int shift = max(0, 32 - 9 - __clz((int)range));                // (a range of 0 has 32 leading zeros)
+        if (range >> shift > COARSE - 2) ++shift;                      // bin 0 holds the zeros
+        auto coarse_bin = [&](unsigned q) { return q ? 1 + ((q - lo) >> shift) : 0; };
 #pragma unroll
         for (int u = 0; u < R; ++u)
-            if (u * NT + t < K) atomicAdd(&coarse[((key[u] - lo) >> shift) * COPIES + (lane & (COPIES - 1))], 1);
+            if (u * NT + t < K) atomicAdd(&coarse[coarse_bin(key[u]) * COPIES + (lane & (COPIES - 1))], 1);
         __syncthreads();
         {
             constexpr int B = COARSE / NT > 0 ? COARSE / NT : 1;       // bins of a thread
@@ -472,7 +501,7 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
         int place[R], slot[R];
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            const unsigned b = (key[u] - lo) >> shift, in_bin = (key[u] - lo) & ((1u << shift) - 1);
+            const unsigned b = coarse_bin(key[u]), in_bin = key[u] ? (key[u] - lo) & ((1u << shift) - 1) : 0;
             const int first = coarse_first[b], n = coarse_first[b + 1] - first;
             place[u] = F * first + (int)(((u64)in_bin * (unsigned)(F * n)) >> shift);
             slot[u] = u * NT + t < K ? atomicAdd(&fine[place[u]], 1) : 0;
@@ -503,14 +532,6 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
 #pragma unroll
         for (int w = 0; w < NW; ++w) crowded |= least[0][w];
         __syncthreads();
-        if (crowded) {                         // (the same for all threads)
-#pragma unroll
-            for (int u = 0; u < R; ++u)
-                if (u * NT + t < K) sorted[u * NT + t] = key[u];
-            __syncthreads();
-            detect_by_search<NT>(reinterpret_cast<const float *>(sorted), K, c, alpha, align, nullptr, sc, perm);
-            return;
-        }
 #pragma unroll
         for (int u = 0; u < R; ++u) {
             const int first = fine[place[u]];
@@ -519,6 +540,46 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
         }
         __syncthreads();
         int at[R], end[R];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            end[u] = fine[place[u] + 1];
+            at[u] = place[u] = fine[place[u]];
+        }
+        if (crowded) {                         // (the same for all threads)
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (u * NT + t < K && end[u] - place[u] > BIN_MAX && sorted[place[u]] != key[u]) {
+                    const int n = atomicAdd(&n_odd, 1);
+                    if (n < ODD_MAX) odd[n] = make_int2(slot[u], (int)key[u]);
+                }
+            __syncthreads();
+            const int n = n_odd;
+            if (n > ODD_MAX) {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (u * NT + t < K) sorted[u * NT + t] = key[u];
+                __syncthreads();
+                detect_by_search<R, NT>(reinterpret_cast<const float *>(sorted), K, c, alpha, align, nullptr, sc, perm);
+                return;
+            }
+            // In a crowded bin `most` is the pattern in its first place.  Places of equal patterns follow their slots, less the odd ones
+            // before them, plus the smaller odd ones; an odd one counts the smaller odd ones, and all others if it is above them.
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                if (end[u] - place[u] <= BIN_MAX) continue;
+                const unsigned most = sorted[place[u]];
+                int smaller = 0, ahead = 0, here = 0;          // odd ones of this bin
+                for (int j = 0; j < n; ++j) {
+                    const int2 o = odd[j];
+                    if (o.x < place[u] || o.x >= end[u]) continue;
+                    smaller += (unsigned)o.y < key[u] || ((unsigned)o.y == key[u] && o.x < slot[u]) ? 1 : 0;
+                    ahead += o.x < slot[u] ? 1 : 0;
+                    ++here;
+                }
+                at[u] = key[u] == most ? slot[u] + smaller - ahead : place[u] + smaller + (key[u] > most ? end[u] - place[u] - here : 0);
+                end[u] = place[u];             // nothing left to count below
+            }
+        }
         auto count_smaller = [&](int u, int s0) {                      // among four patterns of the bin from s0 on, read together
             unsigned o[4];
 #pragma unroll
@@ -529,11 +590,6 @@ __global__ __launch_bounds__(NT) void detect_kernel(const float *__restrict__ v,
                 at[u] += j < end[u] && (o[s] < key[u] || (o[s] == key[u] && j < slot[u])) ? 1 : 0;
             }
         };
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-            end[u] = fine[place[u] + 1];
-            at[u] = place[u] = fine[place[u]];
-        }
 #pragma unroll
         for (int u = 0; u < R; ++u) count_smaller(u, 0);
 #pragma unroll

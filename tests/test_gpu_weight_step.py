@@ -122,3 +122,39 @@ def test_detection_among_ties_and_infinite_norms(K, levels):
     W[2, rng.choice(K, max(1, K // 60), replace=False)] = np.float32(3e38)      # the sum of squares is beyond a float's range
     W[1, W[2] > 0] = np.float32(3e38)
     check(W)
+
+
+def _ulps(x, n):
+    return (np.float32(x).view(np.uint32) + n).astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("K", [257, 1536, 5120, 8960, 16384])
+@pytest.mark.parametrize("kind", ["dead", "levels", "equal and a few near", "equal and many near", "two equal", "all"])
+def test_detection_where_many_norms_are_equal(K, kind):
+    """More equal norms than the sort counts through: alone in their bin, among a few neighbours within bits of them, among so many that
+    the searches take over; as many as the sort still counts through, at the medians and at the edge of the outlier block.  A column with one
+    nonzero weight has that weight for its norm."""
+    rng = np.random.default_rng(K)
+    v = rng.lognormal(0.0, 0.02, K).astype(np.float32)
+    idx = rng.permutation(K)
+    half = idx[:K // 2]
+    if kind == "dead":
+        v[half] = 0.0
+    elif kind == "levels":
+        v = rng.choice(np.linspace(0.5, 1.5, max(2, K // 20)).astype(np.float32), K)
+    elif kind == "equal and a few near":
+        v[half] = 1.0
+        v[half[:12]] = _ulps(1.0, rng.integers(-6, 7, 12))
+    elif kind == "equal and many near":
+        v[half] = _ulps(1.0, rng.integers(-20, 21, half.size))
+    elif kind == "two equal":
+        v[half[::2]], v[half[1::2]] = 1.0, 2.0
+        v[half[:5]], v[half[5:9]] = _ulps(1.0, np.arange(1, 6)), _ulps(2.0, -np.arange(1, 5))
+    else:
+        v[:] = 0.25
+    for outliers in (0, 40):                      # 40: the block of 64 ends among the others
+        o = v.copy()
+        o[idx[-outliers:] if outliers else []] = 30.0
+        W = np.zeros((3, K), np.float32)
+        W[rng.integers(0, 3, K), np.arange(K)] = o
+        check(W)
