@@ -21,7 +21,8 @@
 //   * the outlier range (at most 128 packed bytes, in units of 32) is exactly the first K tile: one head tile, H <= 1.  Where it
 //     ends in the middle of a k-step, that step is multiplied twice, with the other half's lanes zeroed;
 //   * a lane owns 4 consecutive columns of every 16x16 block and the same columns in every row block, so the epilogue reads
-//     its scales and biases once a tile, and an output patch is whole 128-byte lines;
+//     its scales and biases once a tile, and an output patch is whole 128-byte lines (whole 64-byte sectors for bf16 outputs of
+//     tiles up to 128 x 128 and for INT8 outputs);
 //   * a stage is refilled by the iteration that consumed it (its last fragments are in registers before the
 //     iteration's barrier, and each wave waits for its own LDS reads before arriving), so all NSTAGE stages are
 //     in use and a load has NSTAGE - 1 iterations to land; 256 x 256 tiles run with two 64 KB stages;
@@ -97,7 +98,8 @@ struct Geo2 {
 
 typedef v4i v4i_unaligned __attribute__((aligned(2)));   // 16 bytes at an address that is aligned to an output element only
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN, bool W4>
+// WT: output stores write through the L2 (see output_writes_through).
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN, bool W4, bool WT>
 __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WAVES_PER_SIMD)) void gemm_dma128_kernel(GemmArgs g)
 {
     using G = Geo2<BM, BN, WM, WN, NSTAGE, W4>;
@@ -434,11 +436,6 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
     const int y_bytes = (min(BM, g.M - m0) - 1) * ldy_b + g.N * ESZ;
     const int y_lane = (wm * G::WTM + prow) * ldy_b + (n0 + wn * G::WTN + pch * EPC) * ESZ;
     const int n_left = g.N - n0 - wn * G::WTN - pch * EPC;            // columns from this lane's chunk to the matrix edge
-    // Output stores always write through: as whole lines they cost nothing extra, nothing is left to write back when the kernel ends,
-    // and the L2s keep the operands.  (Against write-through up to 40 MB only, chosen by a branch at every store: 4680 x 1536 -> 8960
-    // 73.7 -> 72.1 us, on 128x256 tiles 81.5 -> 77; 4680 x 5120 -> 13824 280 -> 276; with a kernel that reads the output next 95.6 -> 94.3
-    // and 330 -> 327.  The non-temporal hint instead: 72.8 and 272 alone, but 96.8 with the reader behind it.)
-    constexpr bool wt = true;
     const StaticQuant sq = make_static_quant(sizeof(OutT) == 1 ? g.out_scale : 1.0f);
 
     // Software pipeline over the 16 x 16 blocks, row blocks outermost: a patch is read back as soon as it is complete and
@@ -489,7 +486,7 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
             }
             if (!GEN || g.vec_out) {
 #pragma unroll
-                for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * (PROWS / 2) * ldy_b, pend[p], wt);
+                for (int p = 0; p < 2; ++p) buffer_store16(y_tile, y_bytes, pend_voff, pend_soff + p * (PROWS / 2) * ldy_b, pend[p], WT);
             }
             pending = false;
         };
@@ -634,11 +631,28 @@ __global__ __launch_bounds__(64 * WM * WN, (Geo2<BM, BN, WM, WN, NSTAGE, W4>::WA
 #endif
 }
 
-template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN = false, bool W4 = false>
+// Output stores write through the L2 where they are whole 64-byte sectors: nothing is left to write back when the kernel ends, and the
+// L2s keep the operands.  Against plain stores of more than 40 MB, us, GEMM alone: 4680 x 1536 -> 8960 bf16 69.6 -> 65.2, INT8
+// out 76.1 -> 73.4; 4680 x 5120 -> 13824 INT8 out 285 -> 276 (with a kernel that reads the output next 93.6 -> 90.6, 89.6 -> 88.1, 306
+// -> 297).  Rows that begin inside a sector share theirs with the next tile's stores, in another XCD's L2: there it costs more than it
+// saves beyond 40 MB, for outputs up to that size it is level (1536 -> 4616 bf16, 41 MB: 41.4 plain, 42.5 written through).
+// Plain and written through: 1536 -> 8968 bf16 65.3 and 77.3 (with a reader 91.2 and 109), 1536 -> 8976 64.8 and 70.5, 1536 -> 8968 fp32 84.4
+// and 125, 5120 -> 13832 bf16 270 and 305, general tile with 200 outliers 1536 -> 8968 bf16 85.8 and 99.7; rows at 64 bytes,
+// 1536 -> 8992 bf16, 67.8 and 65.1; INT8 outputs, whose rows are whole 16-byte chunks, level (1536 -> 13840 125 both, with a reader 146.5
+// and 149.5).  The choice is a kernel's, not a branch's: at every store it cost 2 to 4 % of the GEMM.
+bool output_writes_through(const GemmArgs &g, size_t elem)
+{
+    return (size_t)g.M * (size_t)g.N * elem <= ((size_t)40 << 20) || ((g.ldy * (int64_t)elem | (int64_t)reinterpret_cast<uintptr_t>(g.Y)) & 63) == 0;
+}
+
+template <int BM, int BN, int WM, int WN, int NSTAGE, bool DUAL, bool DBG, typename OutT, bool GEN, bool W4, bool WT = true>
 qarvd_status launch128_one(const GemmArgs &g, hipStream_t st)
 {
     using G = Geo2<BM, BN, WM, WN, NSTAGE, W4>;
-    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN, W4>;
+    // (the smaller tiles are not chosen for outputs that large, and a dump of the accumulators is not timed)
+    if constexpr (WT && BM >= 128 && !DBG && sizeof(OutT) > 1)
+        if (!output_writes_through(g, sizeof(OutT))) return launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN, W4, false>(g, st);
+    auto k = gemm_dma128_kernel<BM, BN, WM, WN, NSTAGE, DUAL, DBG, OutT, GEN, W4, WT>;
     static unsigned long long lds_limit_raised = 0;      // one mask per instantiation, i.e. per kernel symbol
     if (qarvd_status st_a = qarvd_raise_lds_limit_once(k, G::LDS_BYTES, lds_limit_raised); st_a != QARVD_OK) return st_a;
     int grid = 0;
@@ -669,8 +683,8 @@ qarvd_status launch_dma128_q8(const GemmArgs &g0, hipStream_t st)
     GemmArgs g = g0;
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_n = (g.N + BN - 1) / BN;
-    return g.act == 1 ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8GeluOut>(g, st)
-                      : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8Out>(g, st);
+    return g.act == 1 ? launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8GeluOut, false, false>(g, st)
+                      : launch128_one<BM, BN, WM, WN, NSTAGE, DUAL, false, Int8Out, false, false>(g, st);
 }
 
 #define QARVD_INST128_Q8(BM, BN, WM, WN, NS)                                                         \

@@ -58,3 +58,36 @@ def test_aligned_tiles_against_the_general_one(M, N, K, K_o):
         want = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=general[0])
         for v in general[1:] + tiles:
             assert torch.equal(q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=v), want), names[v]
+
+
+@pytest.mark.parametrize("dt,M,N", [(torch.bfloat16, 2709, 8008), (torch.float32, 1420, 7688), (torch.bfloat16, 2709, 8000)])
+@pytest.mark.parametrize("K,K_o,bits", [(256, 0, 8), (384, 33, 8), (300, 130, 8), (384, 33, 4)])
+def test_large_outputs_with_rows_inside_a_sector(dt, M, N, K, K_o, bits):
+    """Outputs of more than 40 MB: rows that begin inside a 64-byte sector (8008 bf16 and 7688 fp32 columns, padded and shifted views) leave through
+    plain stores, whole ones (8000 bf16) through write-through ones.  Every tile against the register-staged kernel, nothing outside."""
+    gen = torch.Generator(device="cuda").manual_seed(K + N)
+    kp = q.packed_k(K, K_o)
+    Xq = torch.randint(-127, 128, (M, kp), generator=gen, device="cuda", dtype=torch.int8)
+    Wq = torch.randint(-128, 128, (N, kp * bits // 8), generator=gen, device="cuda", dtype=torch.int8).clamp_(min=-127 if bits == 8 else -128)
+    sx, sn, so, b = (torch.rand(n, generator=gen, device="cuda") * 0.1 for n in (M, N, N, N))
+    w = q.DualScaleWeight(Wq if bits == 8 else Wq.view(torch.uint8), sn, so, None, K_o, N, K, bits=bits)
+    want = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=2 if bits == 8 else 3)
+    if bits == 8:
+        names = {v: q.gemm_variant_name(v) for v in range(1, q.gemm_num_variants() + 1)}
+        tiles = [v for v in names if "128-byte stages" in names[v] and ("single" not in names[v] or not K_o)]
+    else:
+        tiles = range(4, q.load_library().qarvd_w4_gemm_num_variants() + 1)
+    ran = 0
+    for v in (0, *tiles):
+        for pad, shift in ((0, 0), (16, 8)):
+            big = torch.full((M + 1, N + pad), 7.0, dtype=dt, device="cuda")
+            Y = big[:M, shift:shift + N]
+            try:
+                q.w8a8_dual_gemm(Xq, sx, w, b, M, Y=Y, variant=v)
+            except q.QarvdError as e:
+                assert e.status == -2 and K_o > 128
+                continue
+            assert torch.equal(Y, want), (v, pad)
+            assert (big[M] == 7).all() and (big[:, :shift] == 7).all() and (big[:, shift + N:] == 7).all(), (v, pad)
+            ran += 1
+    assert ran >= 4
