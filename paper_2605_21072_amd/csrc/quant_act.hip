@@ -68,12 +68,17 @@ struct ActArgs {
     int32_t store_wt;      // 1: Xq leaves through write-through stores (see store_q)
 };
 
-// An X of more than this is loaded with the non-temporal hint: it does not displace what the last-level cache (256 MB) holds, and
-// memory delivers 6.3 TB/s instead of 5.4 (a plain loop over 168 MB in, 42 MB out: 38.5 -> 33 us).  4680 x 8960 fp32, 168 MB: from
-// inputs that no cache holds 42.0 -> 37.8 us, right behind the kernel that wrote X 44.8 -> 37.5.  What fits there beside its
-// producer's inputs is level or better with plain loads: 129 MB 41.9 and 42.3 us behind a producer, read a second time 39.6 and 42.9.
-// (168 MB read a second time: 35.4 -> 38.0.)
-constexpr size_t STREAM_BYTES = (size_t)144 << 20;
+// Where X and its codes are more than this, X is loaded with the non-temporal hint: it does not displace what the last-level cache
+// (256 MB) holds, and memory delivers more (a plain loop over 168 MB in, 42 MB out: 6.3 TB/s instead of 5.4).  The line lies where
+// no use of X loses by it.  While X and the codes fit that cache a second linear on the same X finds it there, a tenth beyond still in part.  Plain
+// -> non-temporal, us behind the kernel that wrote X, quantized once | twice | four times, rows of 5120 with a permutation:
+//   fp32 168 MB (210 with codes)  32 -> 30 | 73 -> 75 | 143 -> 149      bf16 146 MB (219)  43 -> 47 | 89 -> 100 | 178 -> 194
+//   fp32 192 MB (240)             42 -> 35 | 75 -> 80 | 158 -> 167      bf16 168 MB (252)  52 -> 54 | 110 -> 112 | 209 -> 215
+//   fp32 208 MB (260)             52 -> 37 | 89 -> 88 | 175 -> 182      bf16 180 MB (270)  57 -> 56 | 113 -> 115 | 230 -> 227
+//   fp32 224 MB (280)             54 -> 40 | 100 -> 92 | 188 -> 191     bf16 192 MB (288)  63 -> 58 | 122 -> 120 | 243 -> 236
+//   fp32 240 MB (300)             61 -> 43 | 119 -> 100 | 230 -> 208    bf16 256 MB (384)  89 -> 79 | 178 -> 167 | 355 -> 325
+// (X that no cache holds is read faster at any of these sizes: fp32 168 MB 60 -> 41.)
+constexpr size_t STREAM_BYTES = (size_t)280 << 20;
 
 // Stores of the quantized rows.  A kernel ends with a write-back of what its XCDs' L2s still hold, and the
 // consumer (the GEMM, on any XCD) reads Xq from memory either way; for an Xq of a few MB that write-back is
@@ -366,7 +371,7 @@ template <typename T, int CH, int NT, Order ORD, bool TAIL>
 qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
 {
     if constexpr (!TAIL && ORD != ANY_ORDER)
-        if ((size_t)a.M * (size_t)a.K * sizeof(T) > STREAM_BYTES) return launch_rows_as<T, CH, NT, ORD, TAIL, true>(a, st);
+        if ((size_t)a.M * ((size_t)a.K * sizeof(T) + (size_t)a.kp) > STREAM_BYTES) return launch_rows_as<T, CH, NT, ORD, TAIL, true>(a, st);
     return launch_rows_as<T, CH, NT, ORD, TAIL, false>(a, st);
 }
 
