@@ -23,10 +23,12 @@ def _pack(a, K, K_o):
 
 
 # one element; tails of one column beside whole tiles; an outlier range that ends inside, at the end of and past the
-# first stage, in the last stage and with the whole K; fewer K tiles than LDS stages; more tiles than workgroups
-@pytest.mark.parametrize("which", ["heuristic", "128x128", "64x64"])
+# first stage, in the last stage and with the whole K; fewer K tiles than LDS stages; more tiles than workgroups; two shapes for which
+# the cost model takes the 64x128 tile, odd columns and an outlier range beyond the first stage among them
+@pytest.mark.parametrize("which", ["heuristic", "128x128", "64x128", "64x64"])
 @pytest.mark.parametrize("M,N,K,K_o", [(1, 1, 1, 0), (1, 3, 1, 1), (16, 7, 77, 77), (65, 129, 130, 1), (127, 255, 640, 161), (128, 128, 512, 512),
-                                       (129, 257, 700, 96), (64, 65, 1003, 128), (300, 1003, 1000, 129), (40, 64, 2048, 1900), (2300, 2305, 200, 33)])
+                                       (129, 257, 700, 96), (64, 65, 1003, 128), (300, 1003, 1000, 129), (40, 64, 2048, 1900), (2300, 2305, 200, 33),
+                                       (300, 3331, 200, 33), (600, 1603, 250, 140)])
 def test_any_width(which, M, N, K, K_o):
     variant = 0 if which == "heuristic" else [v for v in _named("any width") if which in q.gemm_variant_name(v)][0]
     rng = np.random.default_rng(M * 7 + N * 5 + K * 3 + K_o)
@@ -55,16 +57,18 @@ def test_any_width(which, M, N, K, K_o):
 
 @pytest.mark.parametrize("M,N,K,K_o", [(1, 8, 100, 0), (65, 72, 640, 128), (129, 136, 1280, 96), (200, 392, 384, 0), (520, 1536, 8960, 32), (1560, 1536, 2048, 64)])
 def test_small_tiles_on_whole_lines(M, N, K, K_o):
-    """The aligned 128x128 and 64x64 tiles against the general ones (which the oracle checks above)."""
+    """The aligned 128x128, 64x128 and 64x64 tiles against the general ones (which the oracle checks above)."""
     gen = torch.Generator(device="cuda").manual_seed(M + N)
     Xq = torch.randint(-127, 128, (M, q.packed_k(K, K_o)), generator=gen, device="cuda", dtype=torch.int8)
     Wq = torch.randint(-127, 128, (N, q.packed_k(K, K_o)), generator=gen, device="cuda", dtype=torch.int8)
     sx, sn, so, b = (torch.rand(n, generator=gen, device="cuda") * 0.1 for n in (M, N, N, N))
     w = q.DualScaleWeight(Wq, sn, so, None, K_o, N, K)
     kind = "dual" if K_o else "single"
+    tiles = [[v for v in _named("128-byte stages %s " % size) if kind in q.gemm_variant_name(v)] for size in ("128x128", "64x128", "64x64")]
+    assert [len(t) for t in tiles] == [1, 1, 1]
     for dt in (torch.float32, torch.bfloat16):
         want = q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=_named("any width")[0])
-        for v in _named("128-byte stages 128x128 (8 waves, 4 stages) " + kind) + _named("128-byte stages 64x64 (4 waves, 4 stages) " + kind):
+        for v, in tiles:
             assert torch.equal(q.w8a8_dual_gemm(Xq, sx, w, b, M, dt, variant=v), want), q.gemm_variant_name(v)
 
 
