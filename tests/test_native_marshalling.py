@@ -7,7 +7,7 @@ q = pytest.importorskip("paper_2605_21072_amd")
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("M,K,N,c,bits,dtype", [(1, 256, 8, 0, 8, torch.float32), (33, 512, 264, 7, 8, torch.bfloat16), (70, 1001, 130, 40, 4, torch.float32)])
+@pytest.mark.parametrize("M,K,N,c,bits,dtype", [(1, 256, 8, 0, 8, torch.float32), (33, 512, 264, 7, 8, torch.bfloat16), (50, 512, 272, 7, 8, torch.bfloat16), (70, 1001, 130, 40, 4, torch.float32)])
 def test_same_results_and_buffers(M, K, N, c, bits, dtype):
     gen = torch.Generator(device="cuda").manual_seed(M + K)
     W = torch.randn((N, K), generator=gen, device="cuda") * 0.02
@@ -23,12 +23,15 @@ def test_same_results_and_buffers(M, K, N, c, bits, dtype):
                 Xq, s_x = q.quant_act(X, perm, w.K_o, stream=st)
                 static = q.quant_act_static(X, perm, w.K_o, 0.02, stream=st)
                 Y = torch.empty((M, N), dtype=out, device="cuda")
-                assert q.w8a8_dual_gemm(Xq, s_x, w, bias, M, Y=Y, stream=st) is Y or st is None
+                assert q.w8a8_dual_gemm(Xq, s_x, w, bias, M, Y=Y, stream=st) is Y
                 given = q.quant_act(X, perm, w.K_o, Xq=Xq, s_x=s_x, stream=st)
-                assert given[0].data_ptr() == Xq.data_ptr() and given[1].data_ptr() == s_x.data_ptr()
+                assert given[0] is Xq and given[1] is s_x and q.quant_act_static(X, perm, w.K_o, 0.02, Xq=static, stream=st) is static
                 got.append([Xq[:, :kp], s_x, static[:, :kp], Y, q.w8a8_dual_gemm(Xq, s_x, w, bias, M, out, stream=st), q.w8a8_linear(X, w, bias, out, stream=st)])
                 if bits == 8 and N % 16 == 0:
-                    got[-1].append(q.w8a8_dual_gemm_q8(Xq, s_x, w, bias, M, 0.05, q.ACT_GELU_TANH, stream=st))
+                    Y8 = torch.full((M, N + 16), 7, dtype=torch.int8, device="cuda")
+                    assert q.w8a8_dual_gemm_q8(Xq, s_x, w, bias, M, 0.05, Y8=Y8, stream=st) is Y8
+                    got[-1] += [Y8, q.w8a8_dual_gemm_q8(Xq, s_x, w, bias, M, 0.05, q.ACT_GELU_TANH, stream=st)]
+            assert len(got[0]) == (8 if N == 272 else 6)
             for a, b in zip(*got):
                 assert a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride() and torch.equal(a, b)
 
