@@ -221,7 +221,7 @@ def _pack(a, K, K_o):
 
 
 def _variants():
-    return list(range(0, 34))
+    return list(range(0, 42))
 
 
 @pytest.mark.parametrize("variant", _variants())
@@ -446,7 +446,7 @@ def test_more_tiles_than_slots_every_variant(M, N, K, K_o):
     assert ran >= 8
 
 
-@pytest.mark.parametrize("variant", [0, 1, 5, 9, 11, 13, 15, 17, 19, 21])
+@pytest.mark.parametrize("variant", [0, 1, 5, 9, 11, 13, 15, 17, 19, 21, 27, 29, 31, 33, 35, 37, 38, 39, 41])
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
 def test_rows_below_a_ragged_last_tile_are_not_written(variant, out_dtype):
     """Y is a view of the first M rows of a larger sentinel-filled buffer: the rows of the last row of
