@@ -332,7 +332,7 @@ def main():
         issue_peak = q.probe_mfma_peak(20000)
         out["mfma_issue_peak"] = dict(tops=round(issue_peak, 1), frac_of_datasheet=round(issue_peak / PEAK_INT8_TOPS, 4),
                                       gemm_frac_of_issue_peak=round(achieved / issue_peak, 4),
-                                      note="register-resident v_mfma_i32_32x32x32_i8 loop on every CU, measured in this run: "
+                                      note="register-resident v_mfma_i32_16x16x64_i8 loop on every CU, measured in this run: "
                                            "what the MFMA pipes sustain on non-zero operands before the clock is pulled down")
     except Exception as e:  # diagnostic only
         out["mfma_issue_peak"] = dict(error=str(e))

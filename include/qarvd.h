@@ -308,8 +308,8 @@ const char *qarvd_gemm_variant_name(int32_t variant);
 
 /*
  * Diagnostic for reports (not part of the layer): the measured issue-bound INT8 MFMA rate of the
- * current device, in TOPS.  Runs a register-resident loop of `iters` x 8 v_mfma_i32_32x32x32_i8
- * per wavefront on every CU (two wavefronts per SIMD) and times it with HIP events on `stream`.
+ * current device, in TOPS.  Runs a register-resident loop of `iters` x 16 v_mfma_i32_16x16x64_i8
+ * (the GEMM kernels' instruction) per wavefront on every CU (two wavefronts per SIMD) and times it with HIP events on `stream`.
  *   workspace  device, >= 4160 bytes, 4-byte aligned (operand seeds)
  *   tops_host  HOST out
  * Synchronises `stream`.  The result is below the datasheet figure when the MFMA clock is
