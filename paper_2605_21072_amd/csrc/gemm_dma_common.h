@@ -56,8 +56,9 @@ template <int MAXS, int NLOAD> __device__ __forceinline__ void wait_stages_in_fl
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14)); }
 
 // One LDS-direct load: lane l moves the 16 bytes at base + voffset(l) + soffset to lds + 16*l (lds and
-// soffset wave-uniform).  The buffer descriptor (raw, no stride, no bounds) is rebuilt from `base` at
-// each call; it is wave-uniform, so the compiler keeps it in four SGPRs across the K loop.  The body
+// soffset wave-uniform).  The buffer descriptor (raw, no stride) covers [base, base + bytes): lanes whose offset
+// voffset + soffset falls at or past `bytes`, also where soffset alone does, write zeros and fetch nothing (checked on
+// MI355X).  It is rebuilt at each call; it is wave-uniform, so the compiler keeps it in four SGPRs across the K loop.  The body
 // exists in the device pass only: the host pass has neither the descriptor type nor the builtin.
 __device__ __forceinline__ void buffer_load_lds16(const void *base, int bytes, int voffset, int soffset, unsigned char *lds)
 {
@@ -68,6 +69,7 @@ __device__ __forceinline__ void buffer_load_lds16(const void *base, int bytes, i
     (void)base; (void)bytes; (void)voffset; (void)soffset; (void)lds;
 #endif
 }
+// The same without a bound (tiles whose rows are clamped to the matrix).
 __device__ __forceinline__ void buffer_load_lds16(const void *base, int voffset, int soffset, unsigned char *lds)
 {
     buffer_load_lds16(base, 0x7fffffff, voffset, soffset, lds);
@@ -78,8 +80,9 @@ __device__ __forceinline__ void buffer_load_lds16(const void *base, int voffset,
 // output rows below a ragged last tile are masked (checked on MI355X).  base, bytes, soffset wave-uniform.
 // `write_through` (wave-uniform) sends the data on to memory at once instead of leaving dirty lines in the
 // L2: a kernel ends with a write-back of what its XCDs' L2s still hold, which for an output of a few MB is
-// most of it -- 1-2 us at the end of a 17 us GEMM; where the stores are half lines it only adds traffic for outputs much larger
-// than the L2s (64-byte patches: 4680 x 1536 bf16 18.0 -> 16.2 us, 4680 x 8960 72 -> 75 us).
+// most of it -- 1-2 us at the end of a 17 us GEMM.  For outputs much larger than the L2s it depends on the stores: in the kernels on
+// 64-byte stages, whose patches are half lines, it only adds traffic (4680 x 1536 bf16 18.0 -> 16.2 us, 4680 x 8960 72 -> 75); in
+// gemm_dma128.hip on whether rows begin at whole sectors (output_writes_through).
 __device__ __forceinline__ void buffer_store16(void *base, int bytes, int voffset, int soffset, v4i data, bool write_through = false)
 {
 #if defined(__HIP_DEVICE_COMPILE__) && QARVD_NO_STORE != 2
