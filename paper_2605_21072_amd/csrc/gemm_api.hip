@@ -351,7 +351,9 @@ extern "C" qarvd_status qarvd_linear(const void *X, qarvd_dtype xdt, int64_t ldx
                                           nullptr, &g);
         s_c != QARVD_OK)
         return s_c;
-    if (qarvd_status st = qarvd_quant_act(X, xdt, M, K, ldx, K_o > 0 ? perm : nullptr, K_o, Xq, ld, s_x, stream); st != QARVD_OK) return st;
+    const size_t gemm_bytes = (size_t)N * ((size_t)g.kp * w_bits / 8 + (size_t)M * (ydt == QARVD_F32 ? 4 : 2));
+    if (qarvd_status st = qarvd_quant_act_before_gemm(X, xdt, M, K, ldx, K_o > 0 ? perm : nullptr, K_o, Xq, ld, s_x, gemm_bytes, stream); st != QARVD_OK)
+        return st;
     if (w_bits == 4)
         return qarvd_w4a8_dual_gemm(Xq, ld, s_x, reinterpret_cast<const uint8_t *>(Wq), ldwq, s_normal, s_outlier, bias, M, N, K, K_o,
                                     Y, ydt, ldy, nullptr, nullptr, 0, stream);

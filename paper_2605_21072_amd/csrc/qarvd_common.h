@@ -14,6 +14,11 @@
         }                                        \
     } while (0)
 
+// qarvd_quant_act with a GEMM right behind it that moves `gemm_bytes` of weights and output (quant_act.hip).
+__attribute__((visibility("hidden")))
+qarvd_status qarvd_quant_act_before_gemm(const void *X, qarvd_dtype xdt, int32_t M, int32_t K, int64_t ldx, const int32_t *perm, int32_t K_o,
+                                         int8_t *Xq, int64_t ldxq, float *s_x, size_t gemm_bytes, void *stream);
+
 static inline qarvd_status qarvd_launch_status()
 {
     hipError_t e = hipGetLastError();

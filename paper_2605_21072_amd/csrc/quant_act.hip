@@ -66,19 +66,24 @@ struct ActArgs {
     int32_t M, K, K_o, n_off, kp;
     int32_t is_static;     // 1: static_scale for every row, no absmax
     int32_t store_wt;      // 1: Xq leaves through write-through stores (see store_q)
+    int32_t stream;        // 1: X is loaded with the non-temporal hint where that form is built
 };
 
-// Where X and its codes are more than this, X is loaded with the non-temporal hint: it does not displace what the last-level cache
-// (256 MB) holds, and memory delivers more (a plain loop over 168 MB in, 42 MB out: 6.3 TB/s instead of 5.4).  The line lies where
-// no use of X loses by it.  While X and the codes fit that cache a second linear on the same X finds it there, a tenth beyond still in part.  Plain
-// -> non-temporal, us behind the kernel that wrote X, quantized once | twice | four times, rows of 5120 with a permutation:
-//   fp32 168 MB (210 with codes)  32 -> 30 | 73 -> 75 | 143 -> 149      bf16 146 MB (219)  43 -> 47 | 89 -> 100 | 178 -> 194
-//   fp32 192 MB (240)             42 -> 35 | 75 -> 80 | 158 -> 167      bf16 168 MB (252)  52 -> 54 | 110 -> 112 | 209 -> 215
-//   fp32 208 MB (260)             52 -> 37 | 89 -> 88 | 175 -> 182      bf16 180 MB (270)  57 -> 56 | 113 -> 115 | 230 -> 227
-//   fp32 224 MB (280)             54 -> 40 | 100 -> 92 | 188 -> 191     bf16 192 MB (288)  63 -> 58 | 122 -> 120 | 243 -> 236
-//   fp32 240 MB (300)             61 -> 43 | 119 -> 100 | 230 -> 208    bf16 256 MB (384)  89 -> 79 | 178 -> 167 | 355 -> 325
-// (X that no cache holds is read faster at any of these sizes: fp32 168 MB 60 -> 41.)
-constexpr size_t STREAM_BYTES = (size_t)280 << 20;
+// Loads of X with the non-temporal hint: X does not displace what the last-level cache (256 MB) holds, and memory delivers more (a plain
+// loop over 168 MB in, 42 MB out: 6.3 TB/s instead of 5.4).  But a second linear on the same X then finds none of it in the cache.  So the line
+// lies where it would not find it anyway: X and its codes, and where a GEMM follows in the same call its weights and output, are more than
+// the cache holds.  us behind the kernel that wrote X, plain -> non-temporal, for one, two and three linears on it:
+//   total below the line, plain:     fp32 168 MB, 8960 -> 1536 (239 in all) 150 -> 144 | 232 -> 238 | 320 -> 332
+//                                    fp32 168 MB, 5120 -> 1536 (243)        161 -> 152 | 237 -> 245 | 323 -> 338
+//   above it, non-temporal:          fp32 192 MB, 8960 -> 1536 (270)        221 -> 208 | 335 -> 332 | 455 -> 455
+//                                    fp32 168 MB, 5120 -> 5120 (319)        286 -> 273 | 502 -> 474 | 718 -> 681
+//                                    fp32 192 MB, 1536 -> 1536 (338)        192 -> 175 | 313 -> 286 | 434 -> 397
+//                                    bf16 146 MB, 5120 -> 5120 (391)        406 -> 385 | 760 -> 719 | 1109 -> 1046
+// and quantized one, two and three times in a row with nothing between:
+//   below:  fp32 192 MB (240 with its codes) 42 -> 35 | 76 -> 80 | 117 -> 122      bf16 146 MB (219) 43 -> 48 | 90 -> 98 | 135 -> 145
+//   above:  fp32 216 MB (270)                52 -> 39 | 93 -> 90 | 137 -> 138      bf16 192 MB (288) 63 -> 58 | 122 -> 119 | 183 -> 177
+// An X of up to 144 MB is level at best (129 MB behind its producer 41.9 and 42.3).
+constexpr size_t STREAM_X_BYTES = (size_t)144 << 20, STREAM_CALL_BYTES = (size_t)265 << 20;
 
 // Stores of the quantized rows.  A kernel ends with a write-back of what its XCDs' L2s still hold, and the
 // consumer (the GEMM, on any XCD) reads Xq from memory either way; for an Xq of a few MB that write-back is
@@ -371,7 +376,7 @@ template <typename T, int CH, int NT, Order ORD, bool TAIL>
 qarvd_status launch_rows(const ActArgs &a, hipStream_t st)
 {
     if constexpr (!TAIL && ORD != ANY_ORDER)
-        if ((size_t)a.M * ((size_t)a.K * sizeof(T) + (size_t)a.kp) > STREAM_BYTES) return launch_rows_as<T, CH, NT, ORD, TAIL, true>(a, st);
+        if (a.stream) return launch_rows_as<T, CH, NT, ORD, TAIL, true>(a, st);
     return launch_rows_as<T, CH, NT, ORD, TAIL, false>(a, st);
 }
 
@@ -443,7 +448,7 @@ qarvd_status dispatch(const ActArgs &a, bool whole_words, hipStream_t st)
 
 qarvd_status quant_act_common(const void *X, qarvd_dtype xdt, int32_t M, int32_t K, int64_t ldx,
                               const int32_t *perm, int32_t K_o, int8_t *Xq, int64_t ldxq, float *s_x,
-                              bool is_static, float scale, void *stream)
+                              bool is_static, float scale, size_t gemm_bytes, void *stream)
 {
     if (!X || !Xq || (!is_static && !s_x)) return QARVD_ERR_INVALID_ARG;
     if (M <= 0 || K <= 0 || K > QARVD_MAX_K || K_o < 0 || K_o > K || ldx < K) return QARVD_ERR_INVALID_ARG;
@@ -460,6 +465,8 @@ qarvd_status quant_act_common(const void *X, qarvd_dtype xdt, int32_t M, int32_t
     a.M = M; a.K = K; a.K_o = K_o; a.n_off = g.n_off; a.kp = g.kp;
     a.store_wt = ((size_t)M * (size_t)g.kp <= ((size_t)40 << 20) && (size_t)M * (size_t)ldxq < ((size_t)1 << 31)) ? 1 : 0;
     a.is_static = is_static ? 1 : 0;
+    const size_t x_bytes = (size_t)M * (size_t)K * esz;
+    a.stream = x_bytes > STREAM_X_BYTES && x_bytes + (size_t)M * (size_t)g.kp + gemm_bytes > STREAM_CALL_BYTES ? 1 : 0;
     const bool whole_words = K % 4 == 0 && g.n_off == K_o && qarvd_aligned16(perm);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     return xdt == QARVD_F32 ? dispatch<float>(a, whole_words, st) : dispatch<uint16_t>(a, whole_words, st);
@@ -467,16 +474,22 @@ qarvd_status quant_act_common(const void *X, qarvd_dtype xdt, int32_t M, int32_t
 
 }  // namespace
 
+qarvd_status qarvd_quant_act_before_gemm(const void *X, qarvd_dtype xdt, int32_t M, int32_t K, int64_t ldx, const int32_t *perm, int32_t K_o,
+                                         int8_t *Xq, int64_t ldxq, float *s_x, size_t gemm_bytes, void *stream)
+{
+    return quant_act_common(X, xdt, M, K, ldx, perm, K_o, Xq, ldxq, s_x, false, 0.0f, gemm_bytes, stream);
+}
+
 extern "C" qarvd_status qarvd_quant_act(const void *X, qarvd_dtype xdt, int32_t M, int32_t K, int64_t ldx,
                                         const int32_t *perm, int32_t K_o, int8_t *Xq, int64_t ldxq,
                                         float *s_x, void *stream)
 {
-    return quant_act_common(X, xdt, M, K, ldx, perm, K_o, Xq, ldxq, s_x, false, 0.0f, stream);
+    return quant_act_common(X, xdt, M, K, ldx, perm, K_o, Xq, ldxq, s_x, false, 0.0f, 0, stream);
 }
 
 extern "C" qarvd_status qarvd_quant_act_static(const void *X, qarvd_dtype xdt, int32_t M, int32_t K,
                                                int64_t ldx, const int32_t *perm, int32_t K_o, float scale,
                                                int8_t *Xq, int64_t ldxq, void *stream)
 {
-    return quant_act_common(X, xdt, M, K, ldx, perm, K_o, Xq, ldxq, nullptr, true, scale, stream);
+    return quant_act_common(X, xdt, M, K, ldx, perm, K_o, Xq, ldxq, nullptr, true, scale, 0, stream);
 }

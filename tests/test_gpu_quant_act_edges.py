@@ -115,7 +115,7 @@ def test_scales_outside_the_exact_quotients_range(K, dtype):
 @pytest.mark.parametrize("K,dtype", [(256, torch.float32), (1536, torch.bfloat16), (5120, torch.bfloat16), (8960, torch.float32), (16384, torch.float32)])
 @pytest.mark.parametrize("K_o", [0, 32])
 def test_inputs_larger_than_the_cache_rule_loads_plainly(K, dtype, K_o):
-    """Inputs that are more than 280 MB together with their codes take kernels that load X with another cache hint; halves of them take the
+    """Inputs that are more than 265 MB together with their codes take kernels that load X with another cache hint; halves of them take the
     plain ones, which the tests above check against the oracle."""
     M = 240 * 2 ** 20 // (K * (4 if dtype == torch.float32 else 2)) + 3
     gen = torch.Generator(device="cuda").manual_seed(K + K_o)

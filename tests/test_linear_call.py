@@ -110,3 +110,19 @@ def test_equals_the_pair(bits, M, N, K, c):
         Y = q.w8a8_linear(X, w, b)
     stream.synchronize()
     assert torch.equal(Y, q.w8a8_linear(X, w, b))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,c,dtype", [(7500, 5120, 5120, 20, torch.float32), (4700, 8960, 256, 0, torch.float32), (25000, 1536, 4608, 9, torch.float32),
+                                           (15100, 5120, 1536, 0, torch.bfloat16)])
+def test_large_inputs_by_either_loads(M, K, N, c, dtype):
+    """X of more than 144 MB: how it is loaded depends on what the call moves in all, so the linear and quant_act by itself may differ in that;
+    the results do not."""
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    W = torch.randn((N, K), generator=gen, device="cuda") * 0.02
+    W[:, :c] *= 30
+    w = q.quantize_weight(W)
+    X = torch.randn((M, K), generator=gen, device="cuda").to(dtype)
+    b = torch.randn(N, generator=gen, device="cuda")
+    Xq, s_x = q.quant_act(X, w.perm if w.K_o else None, w.K_o)
+    assert torch.equal(q.w8a8_linear(X, w, b), q.w8a8_dual_gemm(Xq, s_x, w, b, M))
